@@ -34,25 +34,40 @@ namespace memo {
 namespace {
 
 // ============================================================================ forward
-// Workgroup: kFwdWaves waves, 32 query rows per wave; keys/values streamed in tiles of 64 through
-// a double-buffered LDS ring filled asynchronously (one barrier per tile).  The more query rows
-// share a K/V tile, the less fill traffic (L2 -> LDS) each MFMA has to pay for.
+// Workgroup: kFwdWaves waves as QG query groups (32 rows each) x KS = 8 / QG key groups; key group g
+// takes the key tiles g, g + KS, ... of T rows through its own double-buffered LDS ring, filled
+// asynchronously (one barrier per step), and the groups of a row are combined at the end.
+//   QG = 8: 256 rows, no split.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
+//           each MFMA pays for: the best rate on a full chip (1205 TFLOP/s at S = 128K, H = 4).
+//   QG = 4: 128 rows, keys in two (1097); QG = 2: 64 rows, keys in four (885).
+//   QG = 1: 32 rows, keys in eight (752); every wave has a tile of its own, so there is no barrier: one
+//           buffer, whose K half is refilled while V is worked and the other way round.
+// A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
+// last row: what bounds it is the longest workgroup, which QG = 1 makes 64 times shorter.  The launcher
+// takes the cheapest by estimate (kFwdChoices).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 8.7,
+// B = 2 S = 2000 H = 3 67.8 -> 19.5, S = 8192 H = 4 250 -> 93, S = 16461 H = 4 482 -> 285, S = 40000 H = 4 2202 -> 1516.
 constexpr int kFwdWaves = 8;                 // waves per workgroup
-constexpr int kFwdBq = 32 * kFwdWaves, kBk = 64;
 // A lane's 32 exponentials of a tile may sum to this much before the running maximum is brought up to
 // date: 2^40 per tile leaves the row sum over 2^20 keys and the output accumulators far inside fp32.
 constexpr float kRescaleAbove = 1099511627776.f;
 
-__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a)
+template <int QG, int T>
+__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int order)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * kTileBytes];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [buf][K|V] tiles
+    constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = T, JB = T / 32;
+    constexpr int kTile = T * 256;              // bytes of one K or V tile
+    constexpr int kStage = 2 * kTile, kGroup = (QG == 1 ? 1 : 2) * kStage, kRing = KS * kGroup;
+    constexpr int kMerge = KS > 1 ? 8 * 32 * 8 : 0;             // (maximum, sum) of every row of every wave
+    static_assert(KS == 1 || kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kRing + kMerge];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [key group][buf][K|V] tiles
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: lives in a scalar register
     const LaneAddr la = make_lane_addr(lane);
-    const int64_t nqt = (a.S + kFwdBq - 1) / kFwdBq;
-    const PairId t = decode_block_folded(a, nqt);
+    const int wq = wave % QG, grp = wave / QG;  // query group, key group
+    const int64_t nqt = (a.S + kBq - 1) / kBq;
+    const PairId t = decode_block(a, nqt, order, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -60,7 +75,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
     const float c = a.scale * kLog2e;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const LdsAddr ad = make_lds_addr(lds, la);
+    const LdsAddr ad = make_lds_addr(lds + grp * kGroup, la);
     const uint32_t (&row_addr)[8] = ad.row;
     const uint32_t (&tr_addr)[4][2] = ad.tr;
 
@@ -69,15 +84,24 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     for (int pass = 0; pass < 2; ++pass) {
     const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
     if (tile < 0) break;
-    const int64_t row0 = tile * kFwdBq, i0w = row0 + 32 * wave, i = i0w + l32;
-    const int64_t last_row = min(row0 + kFwdBq, a.S) - 1;
-    const int ntiles = (int)(last_row / kBk) + 1;
-    const int jfirst = pass ? ntiles - 1 : 0, jstep = pass ? -1 : 1;
+    const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq, i = i0w + l32;
+    const int64_t last_row = min(row0 + kBq, a.S) - 1;
+    const int ntiles = (int)(last_row / kBk) + 1, nsteps = (ntiles + KS - 1) / KS;
+    // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
+    const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
     if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
-    TileStream<kFwdWaves> ks = make_tile_stream<kFwdWaves>(k, a.ss, (int64_t)jfirst * kBk, wave, lane);
-    TileStream<kFwdWaves> vs = make_tile_stream<kFwdWaves>(v, a.ss, (int64_t)jfirst * kBk, wave, lane);
-    fill_tile_async(lds, ks, k, a.ss, (int64_t)jfirst * kBk, a.S, wave, lane, jstep);
-    fill_tile_async(lds + kTileBytes, vs, v, a.ss, (int64_t)jfirst * kBk, a.S, wave, lane, jstep);
+    auto ks = make_tile_stream<QG, SwzA, T>(k, a.ss, (int64_t)jfirst * kBk, wq, lane);
+    auto vs = make_tile_stream<QG, SwzA, T>(v, a.ss, (int64_t)jfirst * kBk, wq, lane);
+    auto fill_k = [&](int off, int jt) {
+        fill_tile_async<QG, SwzA, T>(lds + grp * kGroup + off, ks, k, a.ss, (int64_t)jt * kBk, a.S, wq, lane, jstep);
+    };
+    auto fill_v = [&](int off, int jt) {
+        fill_tile_async<QG, SwzA, T>(lds + grp * kGroup + off + kTile, vs, v, a.ss, (int64_t)jt * kBk, a.S, wq, lane, jstep);
+    };
+    if (QG > 1 && jfirst < ntiles) {
+        fill_k(0, jfirst);
+        fill_v(0, jfirst);
+    }
 
     // Q^T as B operand: lane = query row i, 8 head-dim values per 16-wide chunk
     bf16x8 qB[8];
@@ -88,45 +112,66 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
             qB[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq * a.ss + 16 * kc + 8 * half));
     }
 
+    if (QG == 1) {                // the loads of Q come first: the loop counts the fills queued after them
+        wait_fills();
+        if (jfirst < ntiles) {
+            fill_k(0, jfirst);
+            fill_v(0, jfirst);
+        }
+    }
     f32x16 accO[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) accO[cb][e] = 0.f;
     float m = -INFINITY, mc = -INFINITY, lsum = 0.f;   // running max of raw dots (and times c), running sum
-    const int wave_first_tile_masked = (int)((i0w + 31) / kBk) + 1;   // tiles >= this are fully masked
+    const int wave_first_tile_masked = min((int)((i0w + 31) / kBk) + 1, ntiles);   // tiles >= this are fully masked
     const int wave_first_diag = (int)(i0w / kBk);                     // tiles >= this need the mask
 
     // One key/value tile.  BUF is a compile-time buffer index, so every LDS address below is
     // a per-lane register plus an immediate offset.
     auto tile_step = [&](auto bufc, int jt) {
         constexpr int BUF = decltype(bufc)::value;
-        constexpr int kOff = BUF * 2 * kTileBytes, vOff = kOff + kTileBytes;
-        constexpr int nOff = (BUF ^ 1) * 2 * kTileBytes;
-        wait_fills();
-        __syncthreads();          // tile jt is complete; nobody still reads the other buffer
+        constexpr int kOff = BUF * kStage, vOff = kOff + kTile;
+        constexpr int nOff = (BUF ^ 1) * kStage;
         const int jn = jt + jstep;
-        if (jn >= 0 && jn < ntiles) {
-            fill_tile_async(lds + nOff, ks, k, a.ss, (int64_t)jn * kBk, a.S, wave, lane, jstep);
-            fill_tile_async(lds + nOff + kTileBytes, vs, v, a.ss, (int64_t)jn * kBk, a.S, wave, lane, jstep);
+        if constexpr (QG > 1) {
+            wait_fills();
+            __syncthreads();      // tile jt is complete; nobody still reads the other buffer
+            if (jn >= 0 && jn < ntiles) {
+                fill_k(nOff, jn);
+                fill_v(nOff, jn);
+            }
+            if (jt >= wave_first_tile_masked) return;     // every key of this tile is masked for this wave
+        } else {
+            // the tiles are this wave's own: no barrier.  K has landed; V (queued behind it) may still be on its way
+            if (jt >= ntiles) return;
+            wait_fills_but<T / 4>();
         }
-        if (jt >= wave_first_tile_masked) return;     // every key of this tile is masked for this wave
 
-        // S^T tile: rows = 64 keys (2 blocks of 32), cols = this wave's 32 queries.
-        // item n = (jb = n%2, kc = n/2): one row operand of K, read 2 MFMAs ahead; the two key blocks
+        // S^T tile: rows = T keys (JB blocks of 32), cols = this wave's 32 queries.
+        // item n = (jb = n%JB, kc = n/JB): one row operand of K, read 2 MFMAs ahead; two key blocks
         // alternate, so that no MFMA accumulates onto the result of the one issued right before it
-        f32x16 s[2];
+        f32x16 s[JB];
         {
             bf16x8 ring[3];
             auto issue = [&](auto n, bf16x8 &slot) {
-                constexpr int jb = decltype(n)::value % 2, kc = decltype(n)::value / 2;
+                constexpr int jb = decltype(n)::value % JB, kc = decltype(n)::value / JB;
                 lds_issue_b128<jb * 8192 + kOff>(slot, row_addr[kc]);
             };
-            lds_pipeline_prologue<16, 2, 1>(ring, issue);
-            lds_pipeline_body<16, 2, 1>(ring, issue, [&](auto n, bf16x8 &slot) {
-                constexpr int jb = decltype(n)::value % 2, kc = decltype(n)::value / 2;
+            lds_pipeline_prologue<8 * JB, 2, 1>(ring, issue);
+            lds_pipeline_body<8 * JB, 2, 1>(ring, issue, [&](auto n, bf16x8 &slot) {
+                constexpr int jb = decltype(n)::value % JB, kc = decltype(n)::value / JB;
                 s[jb] = mfma32(slot, qB[kc], kc == 0 ? zero : s[jb]);
             });
+        }
+        if constexpr (QG == 1) {  // K is used up: the next K tile overwrites it while V is worked, and the next V tile while K is
+            if (jn < ntiles) {
+                fill_k(0, jn);
+                wait_fills_but<T / 4>();
+            } else {
+                wait_fills();
+            }
         }
         // the first V^T operands are requested now: their latency hides behind the softmax
         TrSlot vring[3];
@@ -134,11 +179,11 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
             constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
             lds_issue_tr<kj * 4096 + vOff>(slot, tr_addr[cb][0], tr_addr[cb][1]);
         };
-        lds_pipeline_prologue<16, 2, 2>(vring, v_issue);
+        lds_pipeline_prologue<8 * JB, 2, 2>(vring, v_issue);
         if (jt >= wave_first_diag) {                  // diagonal tile: mask keys j > i
             const int thr = (int)(i - (int64_t)jt * kBk) - 4 * half;    // key offset e' is visible iff e' <= thr
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb)
+            for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     if (32 * jb + 8 * (e >> 2) + (e & 3) > thr) s[jb][e] = -INFINITY;
@@ -150,12 +195,12 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
         // formed at all (16 three-input maxima, an exchange between the half-waves, and the exponentials
         // waiting for both) unless some row sum shows a score far above m, which also covers the first
         // tile, where m = -inf gives +inf or NaN here.
-        bf16x8 pB[4];
+        bf16x8 pB[2 * JB];
         float psum0, psum1;
         auto exponentials = [&]() __attribute__((always_inline)) {
             psum0 = psum1 = 0.f;
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb)
+            for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
                 for (int e = 0; e < 16; e += 2) {
                     const f32x2 two = {__builtin_amdgcn_exp2f(fmaf(s[jb][e], c, -mc)), __builtin_amdgcn_exp2f(fmaf(s[jb][e + 1], c, -mc))};
@@ -169,15 +214,16 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
         exponentials();
         // not (sum <= bound) rather than sum > bound: a NaN sum takes the careful path too
         if (__builtin_amdgcn_ballot_w64(!(psum0 + psum1 <= kRescaleAbove)) != 0) {
-            // 32 values in 16 three-input maxima (two chains)
-            float mt = fmaxf(fmaxf(s[0][0], s[0][1]), s[0][2]), mu = fmaxf(fmaxf(s[1][0], s[1][1]), s[1][2]);
+            // three-input maxima, one chain per key block
+            float mb[JB];
 #pragma unroll
-            for (int e = 3; e < 15; e += 2) {
-                mt = fmaxf(fmaxf(mt, s[0][e]), s[0][e + 1]);
-                mu = fmaxf(fmaxf(mu, s[1][e]), s[1][e + 1]);
+            for (int jb = 0; jb < JB; ++jb) {
+                mb[jb] = fmaxf(fmaxf(s[jb][0], s[jb][1]), s[jb][2]);
+#pragma unroll
+                for (int e = 3; e < 15; e += 2) mb[jb] = fmaxf(fmaxf(mb[jb], s[jb][e]), s[jb][e + 1]);
+                mb[jb] = fmaxf(mb[jb], s[jb][15]);
             }
-            mt = fmaxf(fmaxf(mt, s[0][15]), fmaxf(mu, s[1][15]));
-            mt = max_across_halves(mt);
+            const float mt = max_across_halves(JB == 2 ? fmaxf(mb[0], mb[JB - 1]) : mb[0]);
             // Every processed tile has key j0 visible to all 32 rows, so the maximum is finite.
             const float m_new = fmaxf(m, mt);
             const float corr = __builtin_amdgcn_exp2f((m - m_new) * c);
@@ -194,36 +240,100 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
 
         // O^T += V^T P^T : A = V^T (transposed LDS read), B = P^T straight from the score registers.
         // item n = (kj = n/4, cb = n%4)
-        lds_pipeline_body<16, 2, 2>(vring, v_issue, [&](auto n, TrSlot &slot) {
+        lds_pipeline_body<8 * JB, 2, 2>(vring, v_issue, [&](auto n, TrSlot &slot) {
             constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
             accO[cb] = mfma32(tr_operand(slot), pB[kj], accO[cb]);
         });
+        if constexpr (QG == 1)
+            if (jn < ntiles) fill_v(0, jn);
     };
 
-    for (int n = 0; n < ntiles; n += 2) {
+    for (int n = 0; n < nsteps; n += 2) {
         tile_step(IntC<0>{}, jfirst + jstep * n);
-        if (n + 1 < ntiles) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
+        if (n + 1 < nsteps) tile_step(IntC<(QG > 1 ? 1 : 0)>{}, jfirst + jstep * (n + 1));
     }
 
     const float ltot = add_across_halves(lsum);
-    if (i < a.S) {
-        __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
-        store_acc_T(o, accO, 1.f / ltot, half);
-        if (half == 0)
-            a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = (mc + __builtin_amdgcn_logf(ltot)) * kLn2;
+    __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
+    float *lse = a.lse + ((int64_t)t.b * a.H + t.h) * a.S + i;
+    if constexpr (KS == 1) {
+        if (i < a.S) {
+            store_acc_T(o, accO, 1.f / ltot, half);
+            if (half == 0) *lse = (mc + __builtin_amdgcn_logf(ltot)) * kLn2;
+        }
+    } else {
+        // The key groups of a row meet in LDS: every wave leaves its accumulators, (c m) and row sums; each
+        // then combines 16/KS of the sixteen 4-value pieces of its rows over the groups.  A group that had
+        // no tile has m = -inf and weighs exactly zero.
+        LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+        LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kRing);
+        __syncthreads();          // every wave has left the last LDS buffer
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
+                                                        accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
+        if (half == 0) stats[wave * 32 + l32] = f32x2{mc, ltot};
+        __syncthreads();
+        float top = -INFINITY, total = 0.f, weight[KS];
+        f32x2 st[KS];
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            st[g] = stats[(g * QG + wq) * 32 + l32];
+            top = fmaxf(top, st[g][0]);
+        }
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
+            total += weight[g] * st[g][1];
+        }
+        if (i < a.S) {
+            const float inv = 1.f / total;
+#pragma unroll
+            for (int n = 0; n < 16 / KS; ++n) {
+                const int e = grp * (16 / KS) + n;
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int g = 0; g < KS; ++g) {
+                    const f32x4 x = pieces[((g * QG + wq) * 16 + e) * 64 + lane];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
+                }
+                store4(o + 8 * e + 4 * half, sum, inv);
+            }
+            if (grp == 0 && half == 0) *lse = (top + __builtin_amdgcn_logf(total)) * kLn2;
+        }
     }
     }   // pass
 }
 
 }  // namespace
 
+template <int QG, int T>
+hipError_t launch_fwd(const AttnArgs &a, int order, hipStream_t st)
+{
+    const int64_t nqt = (a.S + 32 * QG - 1) / (32 * QG);
+    const int64_t blocks = order_grid(nqt, (int64_t)a.H * a.B, order);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    attn_fwd_bf16_kernel<QG, T><<<dim3((unsigned)blocks), 64 * kFwdWaves, 0, st>>>(a, order);
+    return hipGetLastError();
+}
+
+// Costs fitted to launches of every variant (N(0,1) inputs, S = 200 .. 200K, 1 to 10 heads): over 40 random
+// (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst.
+constexpr TileChoice kFwdChoices[] = {
+    {256, kFolded, 115.5, 4.0}, {256, kLongestFirst, 117.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
+    {64, kLongestFirst, 155.0, 6.5}, {32, kLongestFirst, 185.0, 4.5},
+};
+
 hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
 {
-    const int64_t nqt = (a.S + kFwdBq - 1) / kFwdBq;
-    const int64_t blocks = folded_grid(nqt, (int64_t)a.H * a.B);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    attn_fwd_bf16_kernel<<<dim3((unsigned)blocks), 64 * kFwdWaves, 0, st>>>(a);
-    return hipGetLastError();
+    const TileChoice &c = kFwdChoices[cheapest_tiles(kFwdChoices, a.S, (int64_t)a.H * a.B)];
+    switch (c.rows) {
+    case 32: return launch_fwd<1, 32>(a, c.order, st);
+    case 64: return launch_fwd<2, 32>(a, c.order, st);
+    case 128: return launch_fwd<4, 64>(a, c.order, st);
+    default: return launch_fwd<8, 64>(a, c.order, st);
+    }
 }
 
 }  // namespace memo

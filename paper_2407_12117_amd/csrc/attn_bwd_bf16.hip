@@ -51,7 +51,7 @@ __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArg
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t nqt = (a.S + kDqBq - 1) / kDqBq;
-    const PairId t = decode_block_folded(a, nqt);
+    const PairId t = decode_block(a, nqt, kFolded, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t nkt = (a.S + kBwdBk - 1) / kBwdBk;
-    const PairId t = decode_block_folded(a, nkt);     // key tile p (long) and key tile nkt-1-p (short)
+    const PairId t = decode_block(a, nkt, kFolded, false);     // key tile p (long) and key tile nkt-1-p (short)
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -455,8 +455,8 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
 {
     const int64_t hb = (int64_t)a.H * a.B;
     const int64_t nkt = (a.S + kBwdBk - 1) / kBwdBk, nqt = (a.S + kDqBq - 1) / kDqBq;
-    const int64_t dq_blocks = folded_grid(nqt, hb);
-    const int64_t dkdv_blocks = folded_grid(nkt, hb);
+    const int64_t dq_blocks = order_grid(nqt, hb, kFolded);
+    const int64_t dkdv_blocks = order_grid(nkt, hb, kFolded);
     if (dkdv_blocks > 0x7fffffffLL || dq_blocks > 0x7fffffffLL) return hipErrorInvalidValue;   // the front end checks too
     hipError_t e = record_stage(a, 0, st);
     if (e != hipSuccess) return e;

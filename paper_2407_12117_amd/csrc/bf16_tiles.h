@@ -6,6 +6,8 @@
 #include "memo_kernels.h"
 #include <hip/hip_bf16.h>
 
+#include <cmath>
+
 namespace memo {
 namespace {
 
@@ -166,14 +168,14 @@ __device__ __forceinline__ void store_acc_T(__bf16 *out_row, const f32x16 (&acc)
 
 constexpr int kXcds = 8, kChunk = 32;   // XCDs per device; compute units (one workgroup each) per XCD
 
-// Folded order of all three attention kernels.  Every workgroup of a head streams that head's K/V
-// rows (forward, dQ) or Q/dO rows (dK/dV), and a tile's sweep is as long as its distance from the
-// end of the causal triangle.  A workgroup works a PAIR of tiles of one head, the p-th longest and
-// the p-th shortest, so every workgroup of a launch has the same length (ntiles + 1 tile units): a
-// launch is a whole number of equal rounds and no compute unit waits for a straggler, whatever S
-// is.  Chunks of kChunk consecutive pairs go to one XCD (the dispatcher deals consecutive workgroup
+// Two orders of work.  Every workgroup of a head streams that head's K/V rows (forward, dQ) or Q/dO
+// rows (dK/dV), and a tile's sweep is as long as its distance from the end of the causal triangle.
+//
+// Folded (launches of many whole rounds): a workgroup works a PAIR of tiles of one head, the p-th longest
+// and the p-th shortest, so every workgroup of a launch has the same length (ntiles + 1 tile units).
+// Chunks of kChunk consecutive pairs go to one XCD (the dispatcher deals consecutive workgroup
 // ids round-robin to the 8 XCDs; an XCD has 32 compute units and these kernels run one workgroup
-// per unit), chunks of one head to the 8 XCDs of a round.  The long tile is swept from the end all
+// per unit), consecutive chunks to the 8 XCDs of a round.  The long tile is swept from the end all
 // tiles share towards its own end, the short tile the other way round (forward and dQ: keys upwards
 // from row 0, then downwards to row 0; dK/dV: queries downwards from row S-1, then upwards to it).
 // Workgroup s of a chunk ends its first sweep a fixed number of steps per s before workgroup 0 and
@@ -182,27 +184,85 @@ constexpr int kXcds = 8, kChunk = 32;   // XCDs per device; compute units (one w
 // lets that XCD's L2 serve most of those reads (measured: 32 workgroups, one fetch from the fabric,
 // up to S = 256K; at S = 1M the forward keeps that, the two backward kernels drift apart over their
 // 16384 steps and fetch about half of what they stream).
+//
+// Longest first (everything else): one tile per workgroup, in order of falling length, heads fastest, each
+// unit taking the next tile when it is done.  A launch of 1.2 rounds of pairs costs two rounds, in
+// this order 1.2 to 1.3 (S = 40000, H = 4: forward 2202 -> 1516 us); on whole rounds it is 2 % slower
+// than folded (S = 128K: 14.84 against 14.59 ms), because the units of an XCD no longer sweep together.
 struct PairId { int64_t first, second; int h, b; };   // first < 0: nothing to do; second < 0: one tile only
 
-__host__ __device__ inline int64_t folded_grid(int64_t ntiles, int64_t heads)
+enum BlockOrder { kFolded = 0, kLongestFirst = 1 };
+
+inline int64_t order_grid(int64_t ntiles, int64_t heads, int order)
 {
-    const int64_t cph = ((ntiles + 1) / 2 + kChunk - 1) / kChunk;      // chunks per head
-    return (cph * heads + kXcds - 1) / kXcds * kXcds * kChunk;
+    if (order == kLongestFirst) return ntiles * heads;
+    const int64_t round = kXcds * kChunk;
+    return ((ntiles + 1) / 2 * heads + round - 1) / round * round;
 }
 
-__device__ __forceinline__ PairId decode_block_folded(const AttnArgs &a, int64_t ntiles)
+// One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
+// 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
+// and after its sweep.
+struct TileChoice { int rows, order; double us_per_mpair, us_per_item; };
+
+// Estimated time of a launch, us.  Folded: rounds of 256 equal pairs of tiles.  Longest first: the n
+// tiles an XCD gets have lengths n, n-1, .. 1 (in units of ntiles / n tiles); the first 32 start
+// together, the next 32 go to the units that end first, so that two layers add up to equal sums, and
+// what remains after whole double layers ends with the longest remaining tile.
+inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads)
 {
-    const int64_t npairs = (ntiles + 1) / 2, cph = (npairs + kChunk - 1) / kChunk;
-    const int64_t id = blockIdx.x;
-    const int64_t chunk = id / (kXcds * kChunk) * kXcds + id % kXcds;  // round * 8 + xcd
-    const int64_t p = (chunk % cph) * kChunk + (id / kXcds) % kChunk;
-    const int64_t hbi = chunk / cph;
-    const bool live = hbi < (int64_t)a.H * a.B && p < npairs;
+    const int64_t ntiles = (S + c.rows - 1) / c.rows;
+    const double mpairs = (double)c.rows * c.rows / (1 << 20);            // a tile unit: rows x rows
+    if (c.order == kFolded) {
+        const int64_t round = kXcds * kChunk, rounds = ((ntiles + 1) / 2 * heads + round - 1) / round;
+        return rounds * ((ntiles + 1) * mpairs * c.us_per_mpair + 2 * c.us_per_item);
+    }
+    const double n = (double)(ntiles * heads) / kXcds, P = kChunk, j = std::floor(n / (2 * P));
+    double makespan = 2 * n * j - 2 * P * j * j + j + n - 2 * P * j;
+    if (n < 1) makespan = 1;                                              // fewer tiles than XCDs
+    const double busy = n < P ? n / P : 1.0;                              // a partly idle chip clocks higher
+    return makespan * (ntiles / (n < 1 ? 1 : n)) * mpairs * c.us_per_mpair * (0.8 + 0.2 * busy) +
+           std::ceil(n / P) * c.us_per_item;
+}
+
+template <int N>
+inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t heads)
+{
+    int best = 0;
+    double best_us = tile_choice_us(choices[0], S, heads);
+    for (int i = 1; i < N; ++i) {
+        const double us = tile_choice_us(choices[i], S, heads);
+        if (us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+__device__ __forceinline__ PairId decode_block(const AttnArgs &a, int64_t ntiles, int order, bool last_is_longest)
+{
+    // a grid is below 2^31 workgroups: 32-bit divisions (a 64-bit one is a hundred instructions of start-up)
+    const uint32_t id = blockIdx.x, heads = (uint32_t)a.H * (uint32_t)a.B;
     PairId t;
-    t.first = live ? p : -1;                                           // tile p and tile ntiles-1-p
-    t.second = (live && p != ntiles - 1 - p) ? ntiles - 1 - p : -1;
-    t.h = (int)(hbi % a.H);
-    t.b = (int)(hbi / a.H);
+    uint32_t hbi;
+    if (order == kLongestFirst) {
+        const uint32_t rank = id / heads;
+        hbi = id % heads;
+        t.first = last_is_longest ? ntiles - 1 - rank : rank;
+        t.second = -1;
+    } else {
+        const uint32_t npairs = (uint32_t)((ntiles + 1) / 2);
+        const uint32_t chunk = id / (kXcds * kChunk) * kXcds + id % kXcds; // round * 8 + xcd
+        const uint32_t flat = chunk * kChunk + (id / kXcds) % kChunk;
+        hbi = flat / npairs;
+        const int64_t p = flat % npairs;
+        const bool live = hbi < heads;
+        t.first = live ? p : -1;                                           // tile p and tile ntiles-1-p
+        t.second = (live && p != ntiles - 1 - p) ? ntiles - 1 - p : -1;
+    }
+    t.h = (int)(hbi % (uint32_t)a.H);
+    t.b = (int)(hbi / (uint32_t)a.H);
     return t;
 }
 
@@ -213,36 +273,36 @@ __device__ __forceinline__ PairId decode_block_folded(const AttnArgs &a, int64_t
 // logical chunk p ^ swz(row), so the swizzle is applied on the global side.  Each lane keeps
 // the global address of its piece per instruction and steps it by one tile (a wave-uniform
 // stride) after every fill: one 64-bit add per instruction and tile, nothing else.
-template <int NW>
+template <int NW, int ROWS = 64>
 struct TileStream {
-    static constexpr int kInstr = 16 / NW;
-    const char *p[16 / NW];
+    static constexpr int kInstr = ROWS / 4 / NW;
+    const char *p[kInstr];
 };
 
-template <int NW, typename SW = SwzA>
-__device__ __forceinline__ TileStream<NW> make_tile_stream(const __bf16 *src, int64_t ss, int64_t r0,
-                                                           int wave, int lane)
+template <int NW, typename SW = SwzA, int ROWS = 64>
+__device__ __forceinline__ TileStream<NW, ROWS> make_tile_stream(const __bf16 *src, int64_t ss, int64_t r0,
+                                                                 int wave, int lane)
 {
-    TileStream<NW> f;
+    TileStream<NW, ROWS> f;
 #pragma unroll
-    for (int n = 0; n < TileStream<NW>::kInstr; ++n) {
-        const int row = 4 * (TileStream<NW>::kInstr * wave + n) + (lane >> 4);
+    for (int n = 0; n < TileStream<NW, ROWS>::kInstr; ++n) {
+        const int row = 4 * (TileStream<NW, ROWS>::kInstr * wave + n) + (lane >> 4);
         const int chunk = (lane & 15) ^ SW::f(row);
         f.p[n] = reinterpret_cast<const char *>(src + (r0 + row) * ss + chunk * 8);
     }
     return f;
 }
 
-// Queues the fill of the 64-row tile the stream points at (rows r0..r0+63 of the head view
-// `src`) and steps the stream to the next tile (the previous one with dir = -1).  A tile that reaches past row S-1 takes the
+// Queues the fill of the ROWS-row tile the stream points at (rows r0.. of the head view `src`) and
+// steps the stream `dir` tiles on (dir = -1: to the previous one).  A tile that reaches past row S-1 takes the
 // slow path: rows past S re-read row S-1 (finite values; every consumer masks them).
-template <int NW, typename SW = SwzA>
-__device__ __forceinline__ void fill_tile_async(LDS_AS unsigned char *tile, TileStream<NW> &f,
+template <int NW, typename SW = SwzA, int ROWS = 64>
+__device__ __forceinline__ void fill_tile_async(LDS_AS unsigned char *tile, TileStream<NW, ROWS> &f,
                                                 const __bf16 *src, int64_t ss, int64_t r0, int64_t S,
                                                 int wave, int lane, int dir = 1)
 {
-    constexpr int NI = TileStream<NW>::kInstr;
-    if (__builtin_expect(r0 + 64 <= S, 1)) {
+    constexpr int NI = TileStream<NW, ROWS>::kInstr;
+    if (__builtin_expect(r0 + ROWS <= S, 1)) {
 #pragma unroll
         for (int n = 0; n < NI; ++n)
             __builtin_amdgcn_global_load_lds((const GLB_AS void *)f.p[n],
@@ -258,7 +318,7 @@ __device__ __forceinline__ void fill_tile_async(LDS_AS unsigned char *tile, Tile
                                              (LDS_AS void *)(tile + (NI * wave + n) * 1024), 16, 0, 0);
         }
     }
-    const int64_t step = dir * 64 * ss * 2;       // dir = -1: the stream walks towards row 0
+    const int64_t step = dir * ROWS * ss * 2;     // dir = -1: the stream walks towards row 0
 #pragma unroll
     for (int n = 0; n < NI; ++n) f.p[n] += step;
 }
@@ -400,8 +460,10 @@ __device__ __forceinline__ void lds_pipeline_body(Slot (&ring)[DEPTH + 1], Issue
     });
 }
 
-// All of this wave's queued fills have landed in LDS.
+// All of this wave's queued fills have landed in LDS; or all but the N queued last.
 __device__ __forceinline__ void wait_fills() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <int N>
+__device__ __forceinline__ void wait_fills_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // v_permlane32_swap exchanges lanes 32..63 of its first operand with lanes 0..31 of its second:
 // fed two copies of x it leaves {x.lo, x.lo} and {x.hi, x.hi}.  The two results are copied to

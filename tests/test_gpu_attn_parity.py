@@ -57,6 +57,17 @@ def test_bf16_many_query_tiles_dense(oracle):
     _dense_case(oracle, 1, 16461, 1, 128, "bf16", 333)
 
 
+@pytest.mark.parametrize("S", [289, 513, 700])
+@pytest.mark.parametrize("heads", [2, 24, 32, 48, 64, 100, 160])
+def test_bf16_every_workgroup_shape(oracle, S, heads):
+    # how a launch is cut into workgroups (32 to 256 rows each, keys or queries split over up to eight
+    # wave groups, single tiles or pairs) depends on the length and the number of heads: few heads take the
+    # small tiles, many the large ones.  Scaled bar: among this many heads some |dV| exceeds 4 (dV of the
+    # first keys sums dO over rows that see little else), where half a bf16 ulp is 2^-6 = 1.6e-2 of the
+    # unscaled bar's 2e-2; the relative bar is the plain one
+    _dense_case(oracle, 1, S, heads, 128, "bf16", 7000 + S + heads, scaled=True)
+
+
 def test_bf16_scale_below_the_usual_one(oracle):
     _dense_case(oracle, 1, 500, 2, 128, "bf16", 41, scale=0.06)
 
