@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const LaneAddr la = make_lane_addr(lane);
     const int wq = wave % QG, grp = wave / QG;  // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const PairId t = decode_block(a, nqt, order, true);
+    const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;

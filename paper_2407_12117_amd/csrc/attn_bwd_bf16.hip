@@ -29,11 +29,27 @@
 // (bf16_tiles.h); all operand reads are issued by hand ahead of their MFMAs.
 #include "bf16_tiles.h"
 
+#include <algorithm>
+
 namespace memo {
 namespace {
 
-constexpr int kDqWaves = 8, kDqBq = 32 * kDqWaves, kBk = 64;
+constexpr int kDqWaves = 8;
 constexpr f32x4 kZero4 = {0.f, 0.f, 0.f, 0.f};
+
+// sum over the G groups of piece e of group member m (wave g * M + m), pieces as [wave][16][lane]
+template <int G, int M>
+__device__ __forceinline__ f32x4 sum_pieces(const LDS_AS f32x4 *pieces, int m, int e, int lane)
+{
+    f32x4 sum = pieces[(m * 16 + e) * 64 + lane];
+#pragma unroll
+    for (int g = 1; g < G; ++g) {
+        const f32x4 x = pieces[((g * M + m) * 16 + e) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[r] += x[r];
+    }
+    return sum;
+}
 
 // ============================================================================ backward: dQ
 // Workgroup: 8 waves, 32 query rows per wave (two blocks of 16); keys/values streamed in tiles
@@ -41,17 +57,33 @@ constexpr f32x4 kZero4 = {0.f, 0.f, 0.f, 0.f};
 //   S^T = K Q^T, dP^T = V dO^T - D   (A = K / V rows from LDS, B = Q^T / dO^T from registers)
 //   dS^T = exp(S^T - LSE) dP^T        (lane = query, registers = keys)
 //   dQ^T += K^T dS^T                  (A = K^T, transposed LDS read; B = dS^T from registers)
-// A tile is worked in two halves of 32 keys so that the element-wise work of one half can run
+// A tile is worked in halves of 32 keys so that the element-wise work of one half can run
 // under the MFMAs of the other wave of the SIMD.
-__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a)
+// Smaller workgroups for short sequences, as in the forward (attn_bf16.hip): QG query groups of 32 rows and
+// 8 / QG key groups, each with its own ring of T-row tiles, their dQ added up at the end.  Rates of 256 / 128 / 64
+// rows on a full chip (S = 128K, H = 4): 1383 / 1319 / 1138 TFLOP/s of its three contractions.  (32 rows with the
+// keys in eight, V in registers and Q in LDS: 704, ahead of 64 rows only below S = 2000 and never in
+// the joint launch below; not kept.)
+template <int QG, int T>
+struct DqShape {
+    static constexpr int KS = kDqWaves / QG, kTile = T * 256;     // bytes of one K or V tile
+    static constexpr int kStage = 2 * kTile, kGroup = 2 * kStage, kLds = KS * kGroup;
+    static_assert(KS == 1 || kLds == 8 * 16384, "the sum over the key groups lays eight accumulator sets over the ring");
+};
+
+template <int QG, int T>
+__device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, int order)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * kTileBytes];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [buf][K|V] tiles
+    using Shape = DqShape<QG, T>;
+    constexpr int KS = Shape::KS, kTile = Shape::kTile, kStage = Shape::kStage, kGroup = Shape::kGroup;
+    constexpr int kBq = 32 * QG, kBk = T;
+    // lds: [key group][buf][K|V] tiles
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t nqt = (a.S + kDqBq - 1) / kDqBq;
-    const PairId t = decode_block(a, nqt, kFolded, true);
+    const int wq = wave % QG, grp = wave / QG;        // query group, key group
+    const int64_t nqt = (a.S + kBq - 1) / kBq;
+    const PairId t = decode_block(a, id, nqt, order, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -59,23 +91,27 @@ __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArg
     const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
     const __bf16 *g = static_cast<const __bf16 *>(a.d_o) + base;
     const int64_t stat = ((int64_t)t.b * a.H + t.h) * a.S;
-    const LdsAddr16 ad = make_lds_addr16(lds, lane);
+    const LdsAddr16 ad = make_lds_addr16(lds + grp * kGroup, lane);
     const float c = a.scale * kLog2e;
 
     // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
     for (int pass = 0; pass < 2; ++pass) {
     const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
     if (tile < 0) break;
-    const bool down = pass == 1;
-    const int64_t row0 = tile * kDqBq, i0w = row0 + 32 * wave;
-    const int64_t last_row = min(row0 + kDqBq, a.S) - 1;
-    const int ntiles = (int)(last_row / kBk) + 1;
-    const int jfirst = down ? ntiles - 1 : 0, jstep = down ? -1 : 1;
+    const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq;
+    const int64_t last_row = min(row0 + kBq, a.S) - 1;
+    const int ntiles = (int)(last_row / kBk) + 1, nsteps = (ntiles + KS - 1) / KS;
+    // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
+    const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
     if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
-    TileStream<kDqWaves> ks = make_tile_stream<kDqWaves, SwzB>(k, a.ss, (int64_t)jfirst * kBk, wave, lane);
-    TileStream<kDqWaves> vs = make_tile_stream<kDqWaves, SwzB>(v, a.ss, (int64_t)jfirst * kBk, wave, lane);
-    fill_tile_async<kDqWaves, SwzB>(lds, ks, k, a.ss, (int64_t)jfirst * kBk, a.S, wave, lane, jstep);
-    fill_tile_async<kDqWaves, SwzB>(lds + kTileBytes, vs, v, a.ss, (int64_t)jfirst * kBk, a.S, wave, lane, jstep);
+    // K and V rows have the same strides: one set of per-lane offsets serves both fills
+    const TileOffsets<QG, T> toff = make_tile_offsets<QG, SwzB, T>(a.ss, wq, lane);
+    auto fill = [&](int off, int jt) {
+        LDS_AS unsigned char *dst = lds + grp * kGroup + off;
+        fill_tile_at<SwzB>(dst, toff, k, a.ss, (int64_t)jt * kBk, a.S, wq, lane);
+        fill_tile_at<SwzB>(dst + kTile, toff, v, a.ss, (int64_t)jt * kBk, a.S, wq, lane);
+    };
+    if (jfirst < ntiles) fill(0, jfirst);
 
     // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
     bf16x8 qB[2][4], gB[2][4];
@@ -100,23 +136,20 @@ __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArg
     for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) accQ[dt][qt] = kZero4;
-    const int wave_first_tile_masked = (int)((i0w + 31) / kBk) + 1;   // tiles >= this are fully masked
+    const int wave_first_tile_masked = min((int)((i0w + 31) / kBk) + 1, ntiles);   // tiles >= this are fully masked
     const int wave_first_diag = (int)(i0w / kBk);                     // tiles >= this need the mask
 
     auto tile_step = [&](auto bufc, int jt) {
         constexpr int BUF = decltype(bufc)::value;
-        constexpr int kOff = BUF * 2 * kTileBytes, vOff = kOff + kTileBytes;
-        constexpr int nOff = (BUF ^ 1) * 2 * kTileBytes;
+        constexpr int kOff = BUF * kStage, vOff = kOff + kTile;
+        constexpr int nOff = (BUF ^ 1) * kStage;
         wait_fills();
         __syncthreads();          // tile jt is complete; nobody still reads the other buffer
         const int jn = jt + jstep;
-        if (jn >= 0 && jn < ntiles) {
-            fill_tile_async<kDqWaves, SwzB>(lds + nOff, ks, k, a.ss, (int64_t)jn * kBk, a.S, wave, lane, jstep);
-            fill_tile_async<kDqWaves, SwzB>(lds + nOff + kTileBytes, vs, v, a.ss, (int64_t)jn * kBk, a.S, wave, lane, jstep);
-        }
+        if (jn >= 0 && jn < ntiles) fill(nOff, jn);
         if (jt >= wave_first_tile_masked) return;
         const bool diag = jt >= wave_first_diag;
-        static_for<0, 2>([&](auto hc) {
+        static_for<0, T / 32>([&](auto hc) {
             constexpr int h = decltype(hc)::value;    // keys 32*h .. 32*h+31 of the tile: key blocks 2h, 2h+1
             f32x4 s[2][2], dp[2][2];                  // [key block of the half][query block]
             {
@@ -175,25 +208,46 @@ __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArg
             });
         });
     };
-    for (int n = 0; n < ntiles; n += 2) {
+    for (int n = 0; n < nsteps; n += 2) {
         tile_step(IntC<0>{}, jfirst + jstep * n);
-        if (n + 1 < ntiles) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
+        if (n + 1 < nsteps) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
     }
+    __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + (i0w + l16) * a.ss + 4 * g4;
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-        const int64_t i = i0w + 16 * qt + l16;
-        if (i < a.S) {
-            __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + i * a.ss + 4 * g4;
+        for (int qt = 0; qt < 2; ++qt)
+            if (i0w + 16 * qt + l16 < a.S) {
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) store4(dq + 16 * dt, accQ[dt][qt], a.scale);
+                for (int dt = 0; dt < 8; ++dt) store4(dq + 16 * qt * a.ss + 16 * dt, accQ[dt][qt], a.scale);
+            }
+    } else {
+        // piece 8 qt + dt of every wave goes through LDS; each wave adds up 16/KS pieces of its rows over the key groups
+        LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+        __syncthreads();          // every wave has left the last LDS buffer
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) pieces[(wave * 16 + 8 * qt + dt) * 64 + lane] = accQ[dt][qt];
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16 / KS; ++n) {
+            const int e = grp * (16 / KS) + n, qt = e >> 3, dt = e & 7;
+            const f32x4 sum = sum_pieces<KS, QG>(pieces, wq, e, lane);
+            if (i0w + 16 * qt + l16 < a.S) store4(dq + 16 * qt * a.ss + 16 * dt, sum, a.scale);
         }
     }
     }   // pass
 }
 
+template <int QG, int T>
+__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<QG, T>::kLds];
+    dq_rows<QG, T>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+}
 
 // ============================================================================ backward: dK, dV
-// Workgroup: 8 waves, 256 key rows whose K and V stay in LDS for the workgroup's lifetime (128 KB);
+// Workgroup (KG = 8): 8 waves, 256 key rows whose K and V stay in LDS for the workgroup's lifetime (128 KB);
 // queries streamed in tiles of 32 through a double-buffered ring (Q and dO rows, 16 KB per stage,
 // one barrier per tile): LDS is full to the byte (160 KB).  The bytes streamed per (query, key) pair
 // are (Q + dO bytes per query) / (keys per workgroup): 256 resident keys halve the L2 -> LDS and the
@@ -206,8 +260,11 @@ __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArg
 //   dV^T += dO^T P,  dK^T += Q^T dS  (A = transposed LDS reads over the tile's 32 queries,
 //                                     B = P / dS from registers; lane = key, rows = head dim)
 // No atomics, no reduction across waves: every wave writes the dK and dV rows of its own keys.
+// Smaller workgroups for short sequences: KG = 4 or 2 key blocks, and 8 / KG query groups that take every
+// 8 / KG-th query tile through rings of their own; their dV, then their dK, are added up through LDS at the end.
+// Rates of 256 / 128 / 64 keys on a full chip (S = 128K, H = 4): 1264 / 1237 / 1186 TFLOP/s of its four contractions.
 // The row statistics do not pass through LDS (there is no room left): see "Row statistics" below.
-constexpr int kBwdBk = 256, kBq = 32;
+constexpr int kBq = 32;
 constexpr int kStageBytes = 2 * kBq * 256;            // Q rows, then dO rows
 constexpr int kKvBlockBytes = 2 * 32 * 256;           // per wave: its 32 K rows, then its 32 V rows
 
@@ -220,16 +277,26 @@ __device__ __forceinline__ void lds_wait(QuadSlot &x)
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(x.a0), "+v"(x.a1), "+v"(x.b0), "+v"(x.b1) : "n"(N));
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
+template <int KG>
+struct DkdvShape {
+    static constexpr int QS = 8 / KG;
+    static constexpr int kGroup = 2 * kStageBytes, kKvOff = QS * kGroup;
+    static constexpr int kLds = kKvOff + KG * kKvBlockBytes;      // 160, 128, 160 KB for KG = 8, 4, 2
+    static_assert(QS == 1 || kLds >= 8 * 16384, "the sum over the query groups lays eight accumulator sets over it");
+};
+
+template <int KG>
+__device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, int order)
 {
-    constexpr int kKvOff = 2 * kStageBytes;
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[kKvOff + 8 * kKvBlockBytes];   // 160 KB
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    using Shape = DkdvShape<KG>;
+    constexpr int QS = Shape::QS, kKvOff = Shape::kKvOff, kBwdBk = 32 * KG;
+    // lds: [query group][stage][Q|dO] tiles, then [key block][K|V] rows
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave % KG, grp = wave / KG;        // key block, query group
     const int64_t nkt = (a.S + kBwdBk - 1) / kBwdBk;
-    const PairId t = decode_block(a, nkt, kFolded, false);     // key tile p (long) and key tile nkt-1-p (short)
+    const PairId t = decode_block(a, id, nkt, order, false);      // key tile p (long) and key tile nkt-1-p (short)
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -238,9 +305,12 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
     const float *dlt = a.delta + ((int64_t)t.b * a.H + t.h) * a.S;
     const int nit = (int)((a.S + kBq - 1) / kBq);
     const float c = a.scale * kLog2e, neg_inv_scale = -1.f / a.scale;
-    const TileOffsets<16> toff = make_tile_offsets<16, SwzB>(a.ss, wave, lane);   // a 32-row ring tile is one fill instruction per wave
+    // a 32-row ring tile is eight fill instructions, 8 / KG per wave of the query group
+    constexpr int NF = 8 / KG;
+    const TileOffsets<KG, kBq> toff = make_tile_offsets<KG, SwzB, kBq>(a.ss, wk, lane);
     const int64_t tile_step_bytes = kBq * a.ss * 2;
-    const LdsAddr16 ad = make_lds_addr16(lds, lane);
+    LDS_AS unsigned char *ring_base = lds + grp * Shape::kGroup;
+    const LdsAddr16 ad = make_lds_addr16(ring_base, lane);
 
     // The long tile walks the query tiles downwards from the last one to its diagonal, the short tile
     // upwards from its diagonal to the last one (the sums take the query tiles in any order): the
@@ -250,9 +320,10 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
     const int64_t tile = pass == 0 ? t.first : t.second;
     if (tile < 0) break;
     const int dir = pass == 0 ? -1 : 1;
-    const int64_t col0 = tile * kBwdBk, j0w = col0 + 32 * wave;
+    const int64_t col0 = tile * kBwdBk, j0w = col0 + 32 * wk;
     const int it0 = (int)(col0 / kBq);                // the tile's first query tile (its diagonal)
-    const int it_first = dir > 0 ? it0 : nit - 1, nsteps = nit - it0;
+    // the sweep's query tiles it_first, it_first + dir, ...: query group grp takes the positions grp, grp + QS, ...
+    const int it_first = dir > 0 ? it0 : nit - 1, npos = nit - it0, nsteps = (npos + QS - 1) / QS;
     if (pass) __syncthreads();    // every wave has left the first tile's K, V and ring
     {   // resident K and V rows (rows past S repeat row S-1, never stored): 32-row pieces, 8 waves x 4 rows
         const __bf16 *kp = static_cast<const __bf16 *>(a.k) + base;
@@ -260,22 +331,18 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
         int ln = lane;            // opaque copy: these addresses are formed here, once per sweep, not kept in registers
         asm volatile("" : "+v"(ln));
 #pragma unroll
-        for (int blk = 0; blk < 8; ++blk) {
-            fill_ragged_tile<16, SwzB>(lds + kKvOff + blk * kKvBlockBytes, kp, a.ss, col0 + 32 * blk, a.S, wave, ln);
-            fill_ragged_tile<16, SwzB>(lds + kKvOff + blk * kKvBlockBytes + 8192, vp, a.ss, col0 + 32 * blk, a.S, wave, ln);
+        for (int blk = 0; blk < KG; ++blk) {
+            fill_ragged_tile<8, SwzB, 32>(lds + kKvOff + blk * kKvBlockBytes, kp, a.ss, col0 + 32 * blk, a.S, wave, ln);
+            fill_ragged_tile<8, SwzB, 32>(lds + kKvOff + blk * kKvBlockBytes + 8192, vp, a.ss, col0 + 32 * blk, a.S, wave, ln);
         }
     }
     auto fill_tile = [&](LDS_AS unsigned char *dst, const __bf16 *src, int64_t r0) {
-        if (r0 + kBq <= a.S) {
-            fill_full_tile_part(dst, toff, 0, reinterpret_cast<const char *>(src) + (r0 / kBq) * tile_step_bytes, wave);
-        } else {
-            int ln = lane;        // opaque copy: the addresses of this rare path are formed here, not kept in registers
-            asm volatile("" : "+v"(ln));
-            fill_ragged_tile<16, SwzB>(dst, src, a.ss, r0, a.S, wave, ln);
-        }
+        fill_tile_at<SwzB>(dst, toff, src, a.ss, r0, a.S, wk, lane);
     };
-    fill_tile(lds, q, (int64_t)it_first * kBq);
-    fill_tile(lds + kBq * 256, g, (int64_t)it_first * kBq);
+    if (grp < npos) {
+        fill_tile(ring_base, q, (int64_t)(it_first + dir * grp) * kBq);
+        fill_tile(ring_base + kBq * 256, g, (int64_t)(it_first + dir * grp) * kBq);
+    }
 
     f32x4 accV[8][2], accK[8][2];                     // dV^T, dK^T: [head-dim block][key block]; lane = key
 #pragma unroll
@@ -312,38 +379,41 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
             nd[qt] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.d[qt], -1.f, kZero4, 0, 0, 0);
         }
     };
-    RawStats raw = load_stats(it_first);
+    RawStats raw = load_stats(it_first + dir * min(grp, npos - 1));
 
     uint32_t kv_row[4];                               // this wave's K rows; its V rows are 8192 bytes further
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) kv_row[kk] = ad.row16[kk] + (uint32_t)(kKvOff + wave * kKvBlockBytes);
+    for (int kk = 0; kk < 4; ++kk) kv_row[kk] = ad.row16[kk] + (uint32_t)(kKvOff - grp * Shape::kGroup + wk * kKvBlockBytes);
     const uint32_t (&q_row)[4] = ad.row16;            // query rows of ring stage 0 (Q part)
     const uint32_t (&q_tr)[8] = ad.tr16;
 
-    auto tile_step = [&](auto bufc, int it, bool more) {
+    auto tile_step = [&](auto bufc, int pos) {
         constexpr int BUF = decltype(bufc)::value;
         constexpr int qOff = BUF * kStageBytes, gOff = qOff + kBq * 256;
         constexpr int nOff = (BUF ^ 1) * kStageBytes;
         wait_fills();
         __syncthreads();          // tile `it` is complete; the other stage is free
-        const int64_t rn = (int64_t)(it + dir) * kBq;   // first query of the next tile (if there is one)
+        const int it = it_first + dir * pos, itn = it + dir * QS;
+        const bool more = pos + QS < npos;
+        const int64_t rn = (int64_t)itn * kBq;        // first query of the group's next tile (if there is one)
         const int64_t i0 = (int64_t)it * kBq;         // first query of the tile
         const RawStats raw_now = raw;
-        if (more) raw = load_stats(it + dir);         // four registers, used a whole step from now
-        const bool active = i0 + 31 >= j0w;           // else all 32 queries precede this wave's keys
-        // A full next tile is fetched by two fill instructions queued one at a time between the
+        if (more) raw = load_stats(itn);              // four registers, used a whole step from now
+        // else there is no tile for this group, or all 32 queries precede this wave's keys
+        const bool active = pos < npos && i0 + 31 >= j0w;
+        // A full next tile is fetched by fill instructions queued one at a time between the
         // MFMAs below; the ragged last tile (and a wave with nothing to compute) queues them here.
         const bool spread = more && active && rn + kBq <= a.S;
         if (more && !spread) {
-            fill_tile(lds + nOff, q, rn);
-            fill_tile(lds + nOff + kBq * 256, g, rn);
+            fill_tile(ring_base + nOff, q, rn);
+            fill_tile(ring_base + nOff + kBq * 256, g, rn);
         }
-        const char *nq = reinterpret_cast<const char *>(q) + (int64_t)(it + dir) * tile_step_bytes;
-        const char *ng = reinterpret_cast<const char *>(g) + (int64_t)(it + dir) * tile_step_bytes;
+        const char *nq = reinterpret_cast<const char *>(q) + (int64_t)itn * tile_step_bytes;
+        const char *ng = reinterpret_cast<const char *>(g) + (int64_t)itn * tile_step_bytes;
         auto fill_part = [&](auto pc) {
             constexpr int part = decltype(pc)::value;
             if (!spread) return;
-            fill_full_tile_part(lds + nOff + part * kBq * 256, toff, 0, part == 0 ? nq : ng, wave);
+            fill_full_tile_part(ring_base + nOff + (part / NF) * kBq * 256, toff, part % NF, part < NF ? nq : ng, wk);
         };
         if (active) {
             spread_stats(raw_now);
@@ -374,8 +444,9 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
                         dp[1][0] = mfma16(slot.a1, slot.b0, kk == 0 ? nd[1] : dp[1][0]);
                         dp[1][1] = mfma16(slot.a1, slot.b1, kk == 0 ? nd[1] : dp[1][1]);
                     }
-                    if constexpr (decltype(n)::value == 3) fill_part(IntC<0>{});
-                    if constexpr (decltype(n)::value == 7) fill_part(IntC<1>{});
+                    // 2 NF fills spread over the eight items
+                    constexpr int done = decltype(n)::value + 1;
+                    if constexpr (done * 2 * NF % 8 == 0) fill_part(IntC<done * 2 * NF / 8 - 1>{});
                 });
             }
             // item n < 8: dV^T head-dim block n, A = dO^T; n >= 8: dK^T block n - 8, A = Q^T
@@ -425,48 +496,163 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a)
         }
     };
     for (int n = 0; n < nsteps; n += 2) {
-        tile_step(IntC<0>{}, it_first + dir * n, n + 1 < nsteps);
-        if (n + 1 < nsteps) tile_step(IntC<1>{}, it_first + dir * (n + 1), n + 2 < nsteps);
+        tile_step(IntC<0>{}, QS * n + grp);
+        if (n + 1 < nsteps) tile_step(IntC<1>{}, QS * (n + 1) + grp);
     }
 
     int g4e = g4;                 // opaque copy: the output addresses are formed here, once per sweep, not kept in registers
     asm volatile("" : "+v"(g4e));
+    __bf16 *dv = static_cast<__bf16 *>(a.dv) + base + (j0w + l16) * a.ss + 4 * g4e;
+    __bf16 *dk = static_cast<__bf16 *>(a.dk) + base + (j0w + l16) * a.ss + 4 * g4e;
+    if constexpr (QS == 1) {
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-        const int64_t j = j0w + 16 * kt + l16;
-        if (j < a.S) {
-            __bf16 *dv = static_cast<__bf16 *>(a.dv) + base + j * a.ss + 4 * g4e;
-            __bf16 *dk = static_cast<__bf16 *>(a.dk) + base + j * a.ss + 4 * g4e;
+        for (int kt = 0; kt < 2; ++kt)
+            if (j0w + 16 * kt + l16 < a.S) {
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-                store4(dv + 16 * dt, accV[dt][kt], 1.f);
-                store4(dk + 16 * dt, accK[dt][kt], a.scale);
+                for (int dt = 0; dt < 8; ++dt) {
+                    store4(dv + 16 * kt * a.ss + 16 * dt, accV[dt][kt], 1.f);
+                    store4(dk + 16 * kt * a.ss + 16 * dt, accK[dt][kt], a.scale);
+                }
             }
-        }
+    } else {
+        // first dV, then dK: piece 8 kt + dt of every wave goes through LDS and each wave adds up 16/QS
+        // pieces of its key block over the query groups
+        LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+        auto combine = [&](f32x4 (&acc)[8][2], __bf16 *out, float mul) {
+            __syncthreads();      // every wave has left what lies there
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int dt = 0; dt < 8; ++dt) pieces[(wave * 16 + 8 * kt + dt) * 64 + lane] = acc[dt][kt];
+            __syncthreads();
+#pragma unroll
+            for (int n = 0; n < 16 / QS; ++n) {
+                const int e = grp * (16 / QS) + n, kt = e >> 3, dt = e & 7;
+                const f32x4 sum = sum_pieces<QS, KG>(pieces, wk, e, lane);
+                if (j0w + 16 * kt + l16 < a.S) store4(out + 16 * kt * a.ss + 16 * dt, sum, mul);
+            }
+        };
+        combine(accV, dv, 1.f);
+        combine(accK, dk, a.scale);
     }
     }   // pass
 }
 
+template <int KG>
+__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<KG>::kLds];
+    dkdv_rows<KG>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+}
+
+// both gradients in one launch, longest tiles first: the first `dkdv_blocks` workgroups are the key-stationary
+// ones, the others the query-stationary ones
+template <int KG, int QG, int T>
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+{
+    constexpr int kLds = DkdvShape<KG>::kLds > DqShape<QG, T>::kLds ? DkdvShape<KG>::kLds : DqShape<QG, T>::kLds;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    if (blockIdx.x < dkdv_blocks) dkdv_rows<KG>(a, lds, blockIdx.x, kLongestFirst);
+    else dq_rows<QG, T>(a, lds, blockIdx.x - dkdv_blocks, kLongestFirst);
+}
+
+template <int KG>
+hipError_t launch_dkdv(const AttnArgs &a, int order, hipStream_t st)
+{
+    const int64_t blocks = order_grid((a.S + 32 * KG - 1) / (32 * KG), (int64_t)a.H * a.B, order);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;       // the front end checks too
+    attn_bwd_dkdv_bf16_kernel<KG><<<dim3((unsigned)blocks), 512, 0, st>>>(a, order);
+    return hipGetLastError();
+}
+
+template <int QG, int T>
+hipError_t launch_dq(const AttnArgs &a, int order, hipStream_t st)
+{
+    const int64_t blocks = order_grid((a.S + 32 * QG - 1) / (32 * QG), (int64_t)a.H * a.B, order);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    attn_bwd_dq_bf16_kernel<QG, T><<<dim3((unsigned)blocks), 64 * kDqWaves, 0, st>>>(a, order);
+    return hipGetLastError();
+}
+
+template <int KG, int QG, int T>
+hipError_t launch_both(const AttnArgs &a, hipStream_t st)
+{
+    const int64_t hb = (int64_t)a.H * a.B;
+    const int64_t nk = order_grid((a.S + 32 * KG - 1) / (32 * KG), hb, kLongestFirst);
+    const int64_t nq = order_grid((a.S + 32 * QG - 1) / (32 * QG), hb, kLongestFirst);
+    if (nk + nq > 0x7fffffffLL) return hipErrorInvalidValue;
+    attn_bwd_both_bf16_kernel<KG, QG, T><<<dim3((unsigned)(nk + nq)), 512, 0, st>>>(a, (uint32_t)nk);
+    return hipGetLastError();
+}
+
 }  // namespace
 
-// D_i preprocess, then the key-stationary kernel (dK, dV), then the query-stationary one (dQ); events
-// between the stages when the caller asked for them.
+// Costs of the workgroup shapes alone (see tile_choice_us), fitted as the forward's.  64-row workgroups pay
+// 5 to 20 % more per pair than 256-row ones for their four times larger fill traffic.
+constexpr TileChoice kDkdvChoices[] = {
+    {256, kFolded, 216.0, 4.0}, {256, kLongestFirst, 218.0, 8.0}, {128, kLongestFirst, 222.0, 8.0}, {64, kLongestFirst, 232.0, 6.5},
+};
+constexpr TileChoice kDqChoices[] = {
+    {256, kFolded, 146.0, 4.0}, {256, kLongestFirst, 149.0, 8.0}, {128, kLongestFirst, 156.0, 8.0}, {64, kLongestFirst, 181.0, 6.5},
+};
+
+// One launch for both gradients: all work there is, spread over the chip, but no shorter than the longest
+// key tile; the last dQ tiles leave a tenth of the longest one uneven.
+inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
+{
+    const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
+    const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
+    const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
+    return std::max(longest, spread) + 10.0;
+}
+
+// D_i preprocess, then dK, dV and dQ: in one launch of 64-, 128- or 256-row workgroups, or, where whole rounds
+// of folded pairs are cheaper (or events between the stages are asked for), the key-stationary kernel and
+// then the query-stationary one.  The single launch fills the chip where neither kernel does alone (S = 2000, 6
+// heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups, 207 as two launches of 256-row pairs) and lets the dQ
+// tiles run in the tail of the dK/dV ones (S = 16461, H = 4: 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us);
+// two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 27.8 + 18.8 against 47.3 ms).
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
 {
     const int64_t hb = (int64_t)a.H * a.B;
-    const int64_t nkt = (a.S + kBwdBk - 1) / kBwdBk, nqt = (a.S + kDqBq - 1) / kDqBq;
-    const int64_t dq_blocks = order_grid(nqt, hb, kFolded);
-    const int64_t dkdv_blocks = order_grid(nkt, hb, kFolded);
-    if (dkdv_blocks > 0x7fffffffLL || dq_blocks > 0x7fffffffLL) return hipErrorInvalidValue;   // the front end checks too
+    const TileChoice &kc = kDkdvChoices[cheapest_tiles(kDkdvChoices, a.S, hb)];
+    const TileChoice &qc = kDqChoices[cheapest_tiles(kDqChoices, a.S, hb)];
     hipError_t e = record_stage(a, 0, st);
     if (e != hipSuccess) return e;
     if ((e = launch_attn_delta(a, true, st)) != hipSuccess) return e;
     if ((e = record_stage(a, 1, st)) != hipSuccess) return e;
-    attn_bwd_dkdv_bf16_kernel<<<dim3((unsigned)dkdv_blocks), 512, 0, st>>>(a);
+    if (!a.stage_events) {
+        double best = tile_choice_us(kc, a.S, hb) + tile_choice_us(qc, a.S, hb);
+        int rows = 0;
+        for (int n = 1; n < 4; ++n) {
+            const double us = both_us(kDkdvChoices[n], kDqChoices[n], a.S, hb);
+            if (us < best) {
+                best = us;
+                rows = kDkdvChoices[n].rows;
+            }
+        }
+        switch (rows) {
+        case 64: return launch_both<2, 2, 32>(a, st);
+        case 128: return launch_both<4, 4, 64>(a, st);
+        case 256: return launch_both<8, 8, 64>(a, st);
+        }
+    }
+    switch (kc.rows) {
+    case 64: e = launch_dkdv<2>(a, kc.order, st); break;
+    case 128: e = launch_dkdv<4>(a, kc.order, st); break;
+    default: e = launch_dkdv<8>(a, kc.order, st); break;
+    }
+    if (e != hipSuccess) return e;
     if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
-    attn_bwd_dq_bf16_kernel<<<dim3((unsigned)dq_blocks), 64 * kDqWaves, 0, st>>>(a);
-    if ((e = record_stage(a, 3, st)) != hipSuccess) return e;
-    return hipGetLastError();
+    switch (qc.rows) {
+    case 64: e = launch_dq<2, 32>(a, qc.order, st); break;
+    case 128: e = launch_dq<4, 64>(a, qc.order, st); break;
+    default: e = launch_dq<8, 64>(a, qc.order, st); break;
+    }
+    if (e != hipSuccess) return e;
+    return record_stage(a, 3, st);
 }
 
 }  // namespace memo

@@ -240,10 +240,10 @@ inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t hea
     return best;
 }
 
-__device__ __forceinline__ PairId decode_block(const AttnArgs &a, int64_t ntiles, int order, bool last_is_longest)
+__device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, int64_t ntiles, int order, bool last_is_longest)
 {
     // a grid is below 2^31 workgroups: 32-bit divisions (a 64-bit one is a hundred instructions of start-up)
-    const uint32_t id = blockIdx.x, heads = (uint32_t)a.H * (uint32_t)a.B;
+    const uint32_t heads = (uint32_t)a.H * (uint32_t)a.B;
     PairId t;
     uint32_t hbi;
     if (order == kLongestFirst) {
@@ -326,19 +326,19 @@ __device__ __forceinline__ void fill_tile_async(LDS_AS unsigned char *tile, Tile
 // The same fill addressed as a wave-uniform tile base (scalar registers, stepped once per tile)
 // plus a per-lane 32-bit byte offset that never changes: half the address registers of
 // TileStream and no per-tile vector adds.  Needs 64 rows of the view to span < 4 GiB.
-template <int NW>
+template <int NW, int ROWS = 64>
 struct TileOffsets {
-    static constexpr int kInstr = 16 / NW;
-    uint32_t off[16 / NW];
+    static constexpr int kInstr = ROWS / 4 / NW;
+    uint32_t off[kInstr];
 };
 
-template <int NW, typename SW = SwzA>
-__device__ __forceinline__ TileOffsets<NW> make_tile_offsets(int64_t ss, int wave, int lane)
+template <int NW, typename SW = SwzA, int ROWS = 64>
+__device__ __forceinline__ TileOffsets<NW, ROWS> make_tile_offsets(int64_t ss, int wave, int lane)
 {
-    TileOffsets<NW> f;
+    TileOffsets<NW, ROWS> f;
 #pragma unroll
-    for (int n = 0; n < TileOffsets<NW>::kInstr; ++n) {
-        const int row = 4 * (TileOffsets<NW>::kInstr * wave + n) + (lane >> 4);
+    for (int n = 0; n < TileOffsets<NW, ROWS>::kInstr; ++n) {
+        const int row = 4 * (TileOffsets<NW, ROWS>::kInstr * wave + n) + (lane >> 4);
         const int chunk = (lane & 15) ^ SW::f(row);
         f.off[n] = (uint32_t)(row * ss * 2 + chunk * 16);
     }
@@ -346,20 +346,20 @@ __device__ __forceinline__ TileOffsets<NW> make_tile_offsets(int64_t ss, int wav
 }
 
 // instruction n of the fill of the full tile whose first row is at `tile_base`
-template <int NW>
-__device__ __forceinline__ void fill_full_tile_part(LDS_AS unsigned char *tile, const TileOffsets<NW> &f, int n,
+template <int NW, int ROWS>
+__device__ __forceinline__ void fill_full_tile_part(LDS_AS unsigned char *tile, const TileOffsets<NW, ROWS> &f, int n,
                                                     const char *tile_base, int wave)
 {
     __builtin_amdgcn_global_load_lds((const GLB_AS void *)(tile_base + f.off[n]),
-                                     (LDS_AS void *)(tile + (TileOffsets<NW>::kInstr * wave + n) * 1024), 16, 0, 0);
+                                     (LDS_AS void *)(tile + (TileOffsets<NW, ROWS>::kInstr * wave + n) * 1024), 16, 0, 0);
 }
 
 // the ragged last tile: rows past S re-read row S-1 (finite values; every consumer masks them)
-template <int NW, typename SW = SwzA>
+template <int NW, typename SW = SwzA, int ROWS = 64>
 __device__ __forceinline__ void fill_ragged_tile(LDS_AS unsigned char *tile, const __bf16 *src, int64_t ss,
                                                  int64_t r0, int64_t S, int wave, int lane)
 {
-    constexpr int NI = 16 / NW;
+    constexpr int NI = ROWS / 4 / NW;
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
         const int row = 4 * (NI * wave + n) + (lane >> 4);
@@ -368,6 +368,22 @@ __device__ __forceinline__ void fill_ragged_tile(LDS_AS unsigned char *tile, con
         rg = rg < S ? rg : S - 1;
         __builtin_amdgcn_global_load_lds((const GLB_AS void *)(src + rg * ss + chunk * 8),
                                          (LDS_AS void *)(tile + (NI * wave + n) * 1024), 16, 0, 0);
+    }
+}
+
+// the whole fill of the tile at rows r0.., full or ragged
+template <typename SW, int NW, int ROWS>
+__device__ __forceinline__ void fill_tile_at(LDS_AS unsigned char *tile, const TileOffsets<NW, ROWS> &f, const __bf16 *src,
+                                             int64_t ss, int64_t r0, int64_t S, int wave, int lane)
+{
+    if (__builtin_expect(r0 + ROWS <= S, 1)) {
+#pragma unroll
+        for (int n = 0; n < TileOffsets<NW, ROWS>::kInstr; ++n)
+            fill_full_tile_part(tile, f, n, reinterpret_cast<const char *>(src) + r0 * ss * 2, wave);
+    } else {
+        int ln = lane;            // opaque copy: the addresses of this rare path are formed here, not kept in registers
+        asm volatile("" : "+v"(ln));
+        fill_ragged_tile<NW, SW, ROWS>(tile, src, ss, r0, S, wave, ln);
     }
 }
 
