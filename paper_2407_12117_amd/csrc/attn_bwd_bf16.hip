@@ -29,8 +29,6 @@
 // (bf16_tiles.h); all operand reads are issued by hand ahead of their MFMAs.
 #include "bf16_tiles.h"
 
-#include <algorithm>
-
 namespace memo {
 namespace {
 
@@ -596,17 +594,6 @@ constexpr TileChoice kDkdvChoices[] = {
 constexpr TileChoice kDqChoices[] = {
     {256, kFolded, 146.0, 4.0}, {256, kLongestFirst, 149.0, 8.0}, {128, kLongestFirst, 156.0, 8.0}, {64, kLongestFirst, 181.0, 6.5},
 };
-
-// One launch for both gradients: all work there is, spread over the chip, but no shorter than the longest
-// key tile; the last dQ tiles leave a tenth of the longest one uneven.
-inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
-{
-    const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
-    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
-    const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
-    const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
-    return std::max(longest, spread) + 10.0;
-}
 
 // D_i preprocess, then dK, dV and dQ: in one launch of 64-, 128- or 256-row workgroups, or, where whole rounds
 // of folded pairs are cheaper (or events between the stages are asked for), the key-stationary kernel and

@@ -6,6 +6,7 @@
 #include "memo_kernels.h"
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
 #include <cmath>
 
 namespace memo {
@@ -240,6 +241,18 @@ inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t hea
     return best;
 }
 
+// Estimated time of one launch that works the key tiles k and then the query tiles q, each longest first: all
+// work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
+// tenth of the longest one uneven.
+inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
+{
+    const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
+    const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
+    const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
+    return std::max(longest, spread) + 10.0;
+}
+
 __device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, int64_t ntiles, int order, bool last_is_longest)
 {
     // a grid is below 2^31 workgroups: 32-bit divisions (a 64-bit one is a hundred instructions of start-up)
@@ -410,8 +423,8 @@ __device__ __forceinline__ void static_for(F &&f)
 
 struct TrSlot { s16x4 lo, hi; };      // the two halves of a transposed operand
 
-template <int OFF>
-__device__ __forceinline__ void lds_issue_b128(bf16x8 &dst, uint32_t addr)
+template <int OFF, typename V16>       // V16: any 16-byte vector
+__device__ __forceinline__ void lds_issue_b128(V16 &dst, uint32_t addr)
 {
     static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
@@ -436,6 +449,13 @@ __device__ __forceinline__ void lds_issue_tr_pair(TrSlot &dst, uint32_t addr)
 
 template <int N>
 __device__ __forceinline__ void lds_wait(bf16x8 &x)
+{
+    static_assert(N >= 0 && N <= 15, "lgkmcnt range");
+    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));
+}
+
+template <int N>
+__device__ __forceinline__ void lds_wait(f32x4 &x)
 {
     static_assert(N >= 0 && N <= 15, "lgkmcnt range");
     asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));

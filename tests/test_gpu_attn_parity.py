@@ -41,6 +41,37 @@ def test_fp32_ragged_and_small(oracle, B, S, H, d):
     _dense_case(oracle, B, S, H, d, "f32", 7 + S)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S,heads", [(15, 2), (17, 70), (128, 3), (289, 24), (289, 64), (500, 100), (1025, 2)])
+def test_fp32_every_workgroup_shape(oracle, S, heads, d):
+    # 16- and 32-row workgroups (few and many heads), lengths on and off the 16-row tiles, fewer tiles than
+    # the wave groups that share them out
+    _dense_case(oracle, 1, S, heads, d, "f32", 900 + S + heads)
+
+
+def test_fp32_padded_rows(oracle):
+    B, S, H, d = 2, 150, 3, 64
+    print("[case] fp32 padded rows", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = synth.attn_inputs(B, S, H, d, "f32", 21)
+
+    def padded(values=None):
+        buf = torch.zeros(B, S, H, d + 12, device="cuda")[..., :d]
+        if values is not None:
+            buf.copy_(values)
+        return buf
+
+    qd, kd, vd, gd = (padded(x) for x in (q, k, v, g))
+    o, lse = mb.memo_attn_fwd(qd, kd, vd, scale, o=padded())
+    dq, dk, dv = mb.memo_attn_bwd(qd, kd, vd, o, lse, gd, scale, dq=padded(), dk=padded(), dv=padded())
+    torch.cuda.synchronize()
+    qf, kf, vf, gf = (to_f64(x) for x in (q, k, v, g))
+    ro, rlse = oracle.attn_fwd(qf, kf, vf, scale)
+    for name, got, ref in zip(("O", "LSE", "dQ", "dK", "dV"), (o, lse, dq, dk, dv),
+                              (ro, rlse) + tuple(oracle.attn_bwd(qf, kf, vf, gf, scale))):
+        assert_close(name, to_f64(got), ref, "f32")
+
+
 @pytest.mark.parametrize("S", [1, 2, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 200, 255, 256, 257, 287, 289, 383, 385, 511, 513, 777])
 def test_bf16_small_and_ragged(oracle, S):
     _dense_case(oracle, 2, S, 2, 128, "bf16", 100 + S)
