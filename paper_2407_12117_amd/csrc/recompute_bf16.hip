@@ -74,160 +74,285 @@ __global__ __launch_bounds__(256) void layernorm_rows_bf16_kernel(const __bf16 *
 
 // ---------------------------------------------------------------------------- projection
 // out[token, feature] = sum_c a[token, c] * w[feature, c] + bias[feature]   (w as [N, K], K contiguous)
-// Workgroup: 8 waves, 256 tokens x 256 features; K streamed in chunks of 64 through a double-buffered
-// LDS ring (32 KB of token rows + 32 KB of weight rows per stage).  The fills are what bounds this
-// kernel (bytes into LDS per MFMA), hence the large tile.  Wave w owns tokens 64*(w%4).. (4 blocks
-// of 16) and features 128*(w/4).. (8 blocks of 16): D[feature, token] = W_rows * A_rows^T on
-// v_mfma_f32_16x16x32_bf16, so a lane holds one token and 4 consecutive features per accumulator
-// (8-byte stores); per 32-wide k-step a wave reads 4 + 8 operands for 32 MFMAs.  The 16x16x32
-// shape is chosen over 32x32x16 because the chip is power-limited on random data and sustains
-// about an eighth more flops per second with it; the operand traffic from LDS is the same for
-// the same wave tile.
+// Workgroup: 8 waves as WM x WN, a wave's tile TB x FB blocks of 16 tokens x 16 features:
+// D[feature, token] = W_rows * A_rows^T on v_mfma_f32_16x16x32_bf16, so a lane holds one token and 4
+// consecutive features per accumulator.  K is streamed in chunks of 64 through LDS, token rows and weight
+// rows in rings of their own (ST and SW chunks deep).  A workgroup works several tiles, one after the other, and
+// the stream of chunks does not stop between them: the next tile's first chunks arrive under the last MFMAs and the
+// stores of the one before.
+//
+// What bounds it: a 256 x 256 tile is worked at the rate the MFMAs sustain under the power limit, within a tenth; short
+// launches are bound by how few tiles there are, so that the tile shrinks with the work (kLinChoices), and the smallest
+// by the latency of a chunk: barrier, operand reads, MFMAs.  Steps of the 256 x 256 shape at 138937 x 4096 -> 1536:
+// one barrier, the fills and the wait for the operands in front of every chunk's MFMAs 1531 us; operands and fills a
+// chunk ahead as described at `phase` 1370; stream not stopped between tiles, 16-byte stores 1309.
 //
 // Operand conventions of the 16x16x32 MFMA, D = A(16xK32) * B(K32x16), lane = 16*g4 + l16:
 //   A : lane holds row l16, k = 8*g4 .. 8*g4+7;  B : lane holds col l16, k = 8*g4 .. 8*g4+7;
 //   D : lane holds col l16, rows 4*g4 + r for register r (4 fp32).
+// Row 4*g + r of feature block 2p + j is feature 32p + 8g + 4j + r, so that a lane's accumulators of two blocks are 8
+// consecutive features: one 16-byte store.
+// Every shape adds up K in the same order with the same instruction, so a row's result does not depend on
+// the shape that computed it.
 //
-// LDS rows here are 128 bytes (64 bf16): chunk c (16 bytes) of row r sits at position
-// c ^ ((r >> 1) & 7), which keeps 16 lanes reading one chunk column of 16 consecutive rows on
-// distinct banks.  One global_load_lds_dwordx4 moves 8 rows.
-constexpr int kLinBm = 256, kLinBn = 256, kLinBk = 64;
-constexpr int kLinTile = 256 * 128;          // bytes of one operand's stage
-
-struct TwelveSlot { bf16x8 b[4], a[8]; };
-
-template <int N>
-__device__ __forceinline__ void lds_wait(TwelveSlot &x)
+// An LDS row is one chunk of one matrix row, 128 or 256 bytes; its 16-byte piece c sits at position c ^ tok_swz(r)
+// (token rows) or c ^ wgt_swz(r) (weight rows, read in the order above).  Both keep the reads on distinct banks.
+template <int RB> __device__ __forceinline__ int tok_swz(int r) { return RB == 128 ? (r >> 1) & 7 : r & 15; }
+template <int RB> __device__ __forceinline__ int wgt_swz(int r)
 {
-    static_assert(N >= 0 && N <= 15, "lgkmcnt range");
-    asm volatile("s_waitcnt lgkmcnt(%12)"
-                 : "+v"(x.b[0]), "+v"(x.b[1]), "+v"(x.b[2]), "+v"(x.b[3]), "+v"(x.a[0]), "+v"(x.a[1]), "+v"(x.a[2]),
-                   "+v"(x.a[3]), "+v"(x.a[4]), "+v"(x.a[5]), "+v"(x.a[6]), "+v"(x.a[7])
-                 : "n"(N));
+    return RB == 128 ? ((r >> 2) & 6) | ((r >> 1) & 1) : ((r >> 1) & 12) | (r & 3);
 }
 
+template <int WM_, int WN_, int TB_, int FB_, int ST_, int SW_, int KPH_>
+struct LinShape {
+    static constexpr int WM = WM_, WN = WN_, TB = TB_, FB = FB_;   // waves and 16-blocks per wave along tokens, features
+    static constexpr int ST = ST_, SW = SW_;                       // ring depths in chunks
+    static constexpr int KPH = KPH_, RB = 128 * KPH;               // 32-wide k steps of half a chunk; bytes of a chunk's row
+    static constexpr int BM = 16 * WM * TB, BN = 16 * WN * FB;
+    static constexpr int kTokTile = BM * RB, kWgtTile = BN * RB, kWgtOff = ST * kTokTile;
+    static constexpr int kLds = ST * kTokTile + SW * kWgtTile;
+    static constexpr int NT = kTokTile / 8192, NW = kWgtTile / 8192;   // fill instructions per wave and chunk
+    static_assert(WM * WN == 8 && BM % 64 == 0 && BN % 64 == 0 && FB % 2 == 0 && kLds <= 160 * 1024, "workgroup shape");
+    // the waits count fills in issue order: tokens run at most one chunk ahead of the weights, and what the first chunk
+    // of a tile needs was queued before the stores of the tile before it
+    static_assert(SW >= 2 && ST >= 3 && (ST == SW || ST == SW + 1), "ring depths");
+};
+
+// One operand's sequence of chunks over the tiles of a workgroup, as a buffer whose base is the tile's first row:
+// rows past the end of the matrix are out of the buffer's range and read as zero (their results are never stored).
+// Behind the last chunk the buffer is empty: the fills are still issued, so that every wait counts the same.
+struct ChunkStream {
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t tile;                // the tile that is being fetched
+    int chunk;                    // its next chunk
+};
+
+template <typename Sh>
 __global__ __launch_bounds__(512, 2) void linear_rows_bf16_kernel(const __bf16 *a, const __bf16 *w, const __bf16 *bias,
-                                                                    __bf16 *out, int64_t row_begin, int64_t row_end,
-                                                                    int K, int N)
+                                                                            __bf16 *out, int64_t row_begin, int64_t row_end,
+                                                                            int K, int N, uint32_t ntiles)
 {
-    // token rows [buf] in the first 64 KB, weight rows [buf] in the second: each operand's two buffers
-    // lie within the 64 KB an LDS immediate offset can reach from one address register
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * kLinTile];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    constexpr int TB = Sh::TB, FB = Sh::FB, KPH = Sh::KPH, RB = Sh::RB, NT = Sh::NT, NW = Sh::NW, ST = Sh::ST, SW = Sh::SW;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[Sh::kLds];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [token ring][weight ring]
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tb = wave & 3, fh = wave >> 2;
-    const int ntn = (N + kLinBn - 1) / kLinBn;
-    // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  The ids are remapped so
-    // that every XCD works through a contiguous range of (token tile, feature tile) pairs with the
-    // feature tile running fastest: the workgroups that share a token tile then run on one XCD close
+    const int wm = wave % Sh::WM, wn = wave / Sh::WM;
+    const uint32_t ntn = (uint32_t)(N + Sh::BN - 1) / Sh::BN;
+    // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  Every XCD works through a
+    // contiguous range of (token tile, feature tile) pairs, its workgroups side by side, with the feature tile
+    // running fastest: the workgroups that share a token tile then run on one XCD close
     // in time, and the token rows are fetched from HBM once instead of once per feature tile.
-    const int64_t nblk = gridDim.x, per = nblk / 8, rem = nblk % 8;
-    const int64_t xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
-    const int64_t logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-    const int64_t mt = logical / ntn;
-    const int nt = (int)(logical % ntn);
-    const int64_t m0 = row_begin + mt * kLinBm;
-    const int n0 = nt * kLinBn;
+    const uint32_t xcd = blockIdx.x % 8, per = ntiles / 8, rem = ntiles % 8;
+    const uint32_t stride = gridDim.x / 8 + (xcd < gridDim.x % 8 ? 1 : 0);      // workgroups of this XCD
+    const uint32_t tile0 = xcd * per + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
+    const uint32_t tile_end = (xcd + 1) * per + (xcd + 1 < rem ? xcd + 1 : rem);
+    if (tile0 >= tile_end) return;
+    const int nchunks = K / (RB / 2);                 // K is a multiple of 128
 
-    // operand read addresses: row l16 of a 16-row block, chunk 4*ks + g4, ks = 0..1
-    uint32_t tok_addr[2], wgt_addr[2];
+    // operand read addresses: piece 4*ks + g4 of this lane's row
+    uint32_t tok_addr[2 * KPH], wgt_addr[2 * KPH];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        const uint32_t in_block = (uint32_t)(l16 * 128 + ((((4 * ks + g4) ^ ((l16 >> 1) & 7))) << 4));
-        tok_addr[ks] = (uint32_t)(uintptr_t)lds + in_block + (uint32_t)(tb * 64 * 128);
-        wgt_addr[ks] = (uint32_t)(uintptr_t)lds + in_block + (uint32_t)(2 * kLinTile + fh * 128 * 128);
+    for (int ks = 0; ks < 2 * KPH; ++ks) {
+        const int wrow = 8 * (l16 >> 2) + (l16 & 3);
+        tok_addr[ks] = (uint32_t)(uintptr_t)lds + (uint32_t)((16 * TB * wm + l16) * RB + (((4 * ks + g4) ^ tok_swz<RB>(l16)) << 4));
+        wgt_addr[ks] = (uint32_t)(uintptr_t)lds + (uint32_t)(Sh::kWgtOff + (16 * FB * wn + wrow) * RB + (((4 * ks + g4) ^ wgt_swz<RB>(wrow)) << 4));
     }
-    // fills: instruction n of this wave covers stage rows 8*(4*wave + n) + lane/8, position lane%8
-    uint32_t tok_off[4], wgt_off[4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-        const int row = 8 * (4 * wave + n) + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-        int64_t tr = m0 + row, wr = n0 + row;
-        tr = tr < row_end ? tr : row_end - 1;         // rows past the range repeat the last one, never stored
-        wr = wr < N ? wr : N - 1;
-        tok_off[n] = (uint32_t)((tr - m0) * K * 2 + chunk * 16);
-        wgt_off[n] = (uint32_t)((wr - n0) * K * 2 + chunk * 16);
-    }
-    const char *abase = reinterpret_cast<const char *>(a + m0 * K);
-    const char *wbase = reinterpret_cast<const char *>(w + (int64_t)n0 * K);
-    const int nchunks = K / kLinBk;
+    // fills: instruction n of this wave covers the 1024 / RB tile rows from (wave + 8 n) * 1024 / RB on; the swizzles do
+    // not depend on n, so one offset register per operand serves them all
+    constexpr int kPieces = RB / 16;
+    const int frow = (64 / kPieces) * wave + lane / kPieces, fpiece = lane % kPieces;
+    const uint32_t tok_off = (uint32_t)frow * (uint32_t)K * 2 + (uint32_t)(fpiece ^ tok_swz<RB>(frow)) * 16;
+    const uint32_t wgt_off = (uint32_t)frow * (uint32_t)K * 2 + (uint32_t)(fpiece ^ wgt_swz<RB>(frow)) * 16;
+    uint32_t fill_step = (uint32_t)K * (2 * 8192 / RB);         // bytes between the rows of instructions n and n + 1
+    const uint32_t row_bytes = (uint32_t)K * 2;
+    auto tok_tile = [&](ChunkStream &s, uint32_t tile) {
+        const int64_t m0 = row_begin + (int64_t)(tile / ntn) * Sh::BM;
+        const int64_t left = tile < tile_end ? row_end - m0 : 0, rows = left < Sh::BM ? left : Sh::BM;
+        s.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(a + m0 * K), 0, (uint32_t)rows * row_bytes, 0x00020000);
+        s.tile = tile;
+        s.chunk = 0;
+    };
+    auto wgt_tile = [&](ChunkStream &s, uint32_t tile) {
+        const int n0 = (int)(tile % ntn) * Sh::BN, left = tile < tile_end ? N - n0 : 0, rows = left < Sh::BN ? left : Sh::BN;
+        s.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(w + (int64_t)n0 * K), 0, (uint32_t)rows * row_bytes, 0x00020000);
+        s.tile = tile;
+        s.chunk = 0;
+    };
+    ChunkStream ts, ws;
+    tok_tile(ts, tile0);
+    wgt_tile(ws, tile0);
+    int tslot = 0, wslot = 0;                         // ring slots the next chunks go to
+    auto next = [](int slot, int depth) { return slot + 1 == depth ? 0 : slot + 1; };
+    auto fill_tok = [&](int n) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ts.rsrc, (LDS_AS void *)(lds + tslot * Sh::kTokTile + (wave + 8 * n) * 1024), 16,
+                                                 tok_off + n * fill_step, ts.chunk * RB, 0, 0);
+    };
+    auto fill_wgt = [&](int n) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ws.rsrc, (LDS_AS void *)(lds + Sh::kWgtOff + wslot * Sh::kWgtTile + (wave + 8 * n) * 1024), 16,
+                                                 wgt_off + n * fill_step, ws.chunk * RB, 0, 0);
+    };
+    auto tok_done = [&]() {       // the chunk's fills are queued: on to the next one
+        tslot = next(tslot, ST);
+        if (++ts.chunk == nchunks) tok_tile(ts, ts.tile + stride);
+    };
+    auto wgt_done = [&]() {
+        wslot = next(wslot, SW);
+        if (++ws.chunk == nchunks) wgt_tile(ws, ws.tile + stride);
+    };
 
-    auto fill_chunk = [&](int buf, int c) {
-        LDS_AS unsigned char *tdst = lds + buf * kLinTile + (4 * wave) * 1024;
-        LDS_AS unsigned char *wdst = lds + (2 + buf) * kLinTile + (4 * wave) * 1024;
-        const char *ab = abase + (int64_t)c * kLinBk * 2, *wb = wbase + (int64_t)c * kLinBk * 2;
+    f32x4 acc[FB][TB];                               // [feature block of 16][token block of 16]
+    auto clear = [&]() {
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            __builtin_amdgcn_global_load_lds((const GLB_AS void *)(ab + tok_off[n]), (LDS_AS void *)(tdst + n * 1024), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const GLB_AS void *)(wb + wgt_off[n]), (LDS_AS void *)(wdst + n * 1024), 16, 0, 0);
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+            for (int t = 0; t < TB; ++t) acc[fb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+
+    // Chunk g (counted over all tiles) is worked in two phases of KPH k steps.  Sync point g lies in its second one, when
+    // every operand of chunk g is in registers: chunk g + 1 has landed, and the slots of chunk g are free for the
+    // weights of chunk g + SW (queued behind the sync point) and the tokens of chunk g + ST (queued in the next phase).
+    // Behind it the operands of chunk g + 1 are read between the MFMAs of chunk g, so neither a
+    // fill nor an LDS read is waited for unless it takes longer than the MFMAs above it.
+    bf16x8 xa[2][KPH * FB], xb[2][KPH * TB];          // two operand sets
+    constexpr int kReads = KPH * (TB + FB), kMfmas = KPH * TB * FB;
+    uint32_t ra = 0, rb = 0;                          // ring offsets of the chunk being read
+    auto read = [&](auto setc, auto ks0c, auto rc) {
+        constexpr int set = decltype(setc)::value, r = decltype(rc)::value % (TB + FB);
+        constexpr int s = decltype(rc)::value / (TB + FB), ks = decltype(ks0c)::value + s, fb = r - TB;
+        if constexpr (r < TB) lds_issue_b128<r * 16 * RB>(xb[set][s * TB + r], tok_addr[ks] + rb);
+        else lds_issue_b128<((fb / 2) * 32 + (fb % 2) * 4) * RB>(xa[set][s * FB + fb], wgt_addr[ks] + ra);
+    };
+    auto wait_reads = [&](auto setc) {
+        constexpr int set = decltype(setc)::value;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < KPH * FB; ++i) {
+            bf16x8 &x = xa[set][i];
+            asm volatile("" : "+v"(x));
+        }
+#pragma unroll
+        for (int i = 0; i < KPH * TB; ++i) {
+            bf16x8 &x = xb[set][i];
+            asm volatile("" : "+v"(x));
         }
     };
-
-    f32x4 acc[8][4];                                 // [feature block of 16][token block of 16]
-#pragma unroll
-    for (int fb = 0; fb < 8; ++fb)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[fb][t][e] = 0.f;
-
-    fill_chunk(0, 0);
-    auto stage = [&](auto bufc, int c) {
-        constexpr int BUF = decltype(bufc)::value;
-        constexpr int off = BUF * kLinTile;
-        wait_fills();
-        __syncthreads();          // chunk c is complete; nobody still reads the other buffer
-        if (c + 1 < nchunks) fill_chunk(BUF ^ 1, c + 1);
-        TwelveSlot ring[2];
-        auto issue = [&](auto n, TwelveSlot &slot) {
-            constexpr int ks = decltype(n)::value;
-            static_for<0, 4>([&](auto t) { lds_issue_b128<off + decltype(t)::value * 16 * 128>(slot.b[decltype(t)::value], tok_addr[ks]); });
-            static_for<0, 8>([&](auto f) { lds_issue_b128<off + decltype(f)::value * 16 * 128>(slot.a[decltype(f)::value], wgt_addr[ks]); });
-        };
-        lds_pipeline_prologue<2, 1, 12>(ring, issue);
-        lds_pipeline_body<2, 1, 12>(ring, issue, [&](auto n, TwelveSlot &slot) {
-#pragma unroll
-            for (int fb = 0; fb < 8; ++fb)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    acc[fb][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(slot.a[fb], slot.b[t], acc[fb][t], 0, 0, 0);
-        });
+    // In flight behind the chunk a sync point needs: younger fills, and the stores of a tile that was finished since
+    constexpr int kBehind = (ST - 2) * NT + (SW - 2) * NW, kStores = TB * FB / 2;
+    static_assert(kBehind + kStores <= 63, "vmcnt range");
+    constexpr int kNever = -2;
+    int stores_at = kNever;       // the sync point in front of which a whole tile's stores were issued
+    auto arrive = [&](int g) {
+        asm volatile("s_cmp_eq_u32 %0, %1\n\ts_cbranch_scc1 .Lstores%=\n\ts_waitcnt vmcnt(%2)\n.Lstores%=:\n\ts_waitcnt vmcnt(%3)"
+                     :: "s"(g), "s"(stores_at), "n"(kBehind), "n"(kBehind + kStores) : "memory", "scc");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     };
-    for (int c = 0; c < nchunks; c += 2) {
-        stage(IntC<0>{}, c);
-        if (c + 1 < nchunks) stage(IntC<1>{}, c + 1);
-    }
+    // one phase: MFMAs of operand set `set`, the reads of the other set (k steps from ks0), the sync point (SYNC) and
+    // the fills dealt out between them
+    auto phase = [&](auto setc, auto ks0c, auto syncc, int g) {
+        constexpr int set = decltype(setc)::value;
+        constexpr bool sync = decltype(syncc)::value != 0;
+        constexpr int first = kMfmas >= 32 && sync ? kMfmas / 4 : 0;            // MFMAs before the sync point
+        constexpr int span = kMfmas >= 32 ? kMfmas / 2 : (kMfmas + 1) / 2;
+        constexpr int nfills = sync ? NW : NT;
+        static_for<0, kMfmas>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            if constexpr (sync && m == first) {
+                arrive(g);
+                ra = (ra + Sh::kWgtTile == SW * Sh::kWgtTile) ? 0 : ra + Sh::kWgtTile;
+                rb = (rb + Sh::kTokTile == ST * Sh::kTokTile) ? 0 : rb + Sh::kTokTile;
+            }
+            if constexpr (m >= first) {
+                static_for<0, kReads>([&](auto rc) {
+                    if constexpr (first + decltype(rc)::value * span / kReads == m) read(IntC<set ^ 1>{}, ks0c, rc);
+                });
+                static_for<0, nfills>([&](auto nc) {
+                    constexpr int n = decltype(nc)::value;
+                    if constexpr (first + n * (kMfmas - first) / nfills == m) {
+                        if constexpr (sync) fill_wgt(n);
+                        else fill_tok(n);
+                    }
+                });
+            }
+            constexpr int s = m / (TB * FB), fb = m % (TB * FB) / TB, t = m % TB;
+            acc[fb][t] = mfma16(xa[set][s * FB + fb], xb[set][s * TB + t], acc[fb][t]);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (sync) wgt_done();
+        else tok_done();
+        wait_reads(IntC<set ^ 1>{});
+    };
 
-    // acc[fb][t][r] = out[token m0 + 64 tb + 16 t + l16][feature n0 + 128 fh + 16 fb + 4 g4 + r]
-    if (n0 + 128 * fh < N) {                          // N is a multiple of 128: a feature half is whole or absent
+    // acc[fb][t][r] is token m0 + 16 (TB wm + t) + l16, feature n0 + 16 FB wn + 32 (fb / 2) + 8 g4 + 4 (fb % 2) + r.
+    // True if every store of the tile was issued (a tile at the edge leaves some out)
+    auto finish = [&](uint32_t tile) {
+        const int64_t m0 = row_begin + (int64_t)(tile / ntn) * Sh::BM + 16 * TB * wm;
+        const int f0 = (int)(tile % ntn) * Sh::BN + 16 * FB * wn;
+        const bool whole = m0 + 16 * TB <= row_end && f0 + 16 * FB <= N;
+        int ln = lane;            // opaque copy: the addresses are formed here, once per tile, not kept in registers
+        asm volatile("" : "+v"(ln));
+        const int l16 = ln & 15, g4 = ln >> 4;
+        __bf16 *obase = out + (m0 + l16) * N + f0 + 8 * g4;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int64_t token = m0 + 64 * tb + 16 * t + l16;
-            if (token >= row_end) continue;
-            __bf16 *orow = out + token * N + n0 + 128 * fh + 4 * g4;
-            const __bf16 *brow = bias ? bias + n0 + 128 * fh + 4 * g4 : nullptr;
+        for (int p = 0; p < FB / 2; ++p) {
+            if (f0 + 32 * p >= N) continue;           // N is a multiple of 32: a pair of blocks is whole or absent
+            float b8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (bias) {                               // by scalar loads: a vector load would wait for the fills queued before it
+                const __attribute__((address_space(4))) uint32_t *bp =
+                    (const __attribute__((address_space(4))) uint32_t *)(bias + f0 + 32 * p);
 #pragma unroll
-            for (int fb = 0; fb < 8; ++fb) {
-                float b4[4] = {0.f, 0.f, 0.f, 0.f};
-                if (brow) {
-                    const u32x2 braw = *reinterpret_cast<const u32x2 *>(brow + 16 * fb);
-                    // elements copied to scalars first: a bit cast applied to a vector element
-                    // directly reads element 0 for both with this compiler
-                    const uint32_t r0 = braw[0], r1 = braw[1];
-                    const bf16x2 lo = __builtin_bit_cast(bf16x2, r0), hi = __builtin_bit_cast(bf16x2, r1);
-                    b4[0] = (float)lo[0]; b4[1] = (float)lo[1]; b4[2] = (float)hi[0]; b4[3] = (float)hi[1];
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t lo = g4 & 1 ? bp[4 + i] : bp[i], hi = g4 & 1 ? bp[12 + i] : bp[8 + i];
+                    const uint32_t two = g4 & 2 ? hi : lo;
+                    b8[2 * i] = __builtin_bit_cast(float, two << 16);
+                    b8[2 * i + 1] = __builtin_bit_cast(float, two & 0xffff0000u);
                 }
-                f32x2 p = {acc[fb][t][0] + b4[0], acc[fb][t][1] + b4[1]};
-                f32x2 q = {acc[fb][t][2] + b4[2], acc[fb][t][3] + b4[3]};
-                u32x2 wv;
-                wv[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2));
-                wv[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, bf16x2));
-                *reinterpret_cast<u32x2 *>(orow + 16 * fb) = wv;
+            }
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                const f32x4 &x = acc[2 * p][t], &y = acc[2 * p + 1][t];
+                const bf16x8 r = pack44(f32x4{x[0] + b8[0], x[1] + b8[1], x[2] + b8[2], x[3] + b8[3]},
+                                        f32x4{y[0] + b8[4], y[1] + b8[5], y[2] + b8[6], y[3] + b8[7]});
+                if (whole || m0 + 16 * t + l16 < row_end)
+                    *reinterpret_cast<u32x4 *>(obase + (int64_t)(16 * t) * N + 32 * p) = __builtin_bit_cast(u32x4, r);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        return whole;
+    };
+
+    // the fills of sync points -ST .. -2, then sync point -1
+#pragma unroll
+    for (int s = -ST; s < 0; ++s) {
+        if (s == -1) arrive(-1);
+        if (s + SW >= 0) {
+#pragma unroll
+            for (int n = 0; n < NW; ++n) fill_wgt(n);
+            wgt_done();
+        }
+        if (s < -1) {             // the tokens of sync point -1 follow in the first phase
+#pragma unroll
+            for (int n = 0; n < NT; ++n) fill_tok(n);
+            tok_done();
+        }
+    }
+    static_for<0, kReads>([&](auto rc) { read(IntC<0>{}, IntC<0>{}, rc); });
+    wait_reads(IntC<0>{});
+    int g = 0;
+#pragma clang loop unroll(disable)
+    for (uint32_t tile = tile0; tile < tile_end; tile += stride) {
+        clear();
+        const int tile_chunks = g + nchunks;
+#pragma clang loop unroll(disable)
+        do {
+            asm volatile("" : "+s"(fill_step));       // the fill offsets are formed where they are used, not kept in registers
+            phase(IntC<0>{}, IntC<KPH>{}, IntC<0>{}, g);
+            phase(IntC<1>{}, IntC<0>{}, IntC<1>{}, g);
+            ++g;
+        } while (g < tile_chunks);
+        stores_at = finish(tile) ? g : kNever;
     }
 }
 
@@ -256,19 +381,57 @@ hipError_t launch_layernorm_rows_bf16(const void *x, const void *gamma, const vo
     return hipGetLastError();
 }
 
+template <typename Sh>
+hipError_t launch_linear(const __bf16 *a, const __bf16 *w, const __bf16 *bias, __bf16 *out, int64_t row_begin, int64_t row_end,
+                         int K, int N, hipStream_t st)
+{
+    const int64_t tiles = ((row_end - row_begin + Sh::BM - 1) / Sh::BM) * ((N + Sh::BN - 1) / Sh::BN);
+    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int64_t resident = kXcds * kChunk;          // one workgroup per compute unit
+    linear_rows_bf16_kernel<Sh><<<dim3((unsigned)std::min(tiles, resident)), 512, 0, st>>>(a, w, bias, out, row_begin, row_end, K, N,
+                                                                                          (uint32_t)tiles);
+    return hipGetLastError();
+}
+
+// Tile shapes, and what a round of tiles costs: us per 128 of K with one compute unit busy and with all of them (the chip
+// clocks lower then), and us per tile around it.  Fitted to launches of 300 to 138937 rows, K = 1024 to 5120; the wave
+// grids and ring depths are the fastest of the two or three tried for each tile.
+struct LinChoice { int bm, bn; double us_alone, us_full, us_tile; };
+constexpr LinChoice kLinChoices[] = {
+    {256, 256, 2.16, 2.95, 5.0}, {256, 128, 1.28, 1.62, 3.5}, {192, 128, 0.95, 1.28, 2.5},
+    {128, 128, 0.70, 0.88, 2.0}, {128, 64, 0.48, 0.59, 1.0},  {64, 64, 0.37, 0.43, 0.7},
+};
+
+inline double lin_choice_us(const LinChoice &c, int64_t rows, int K, int N)
+{
+    const double tiles = std::ceil((double)rows / c.bm) * std::ceil((double)N / c.bn), units = kXcds * kChunk;
+    const double busy = std::min(1.0, tiles / units);
+    return std::ceil(tiles / units) * (K / 128.0 * (c.us_alone + busy * (c.us_full - c.us_alone)) + c.us_tile);
+}
+
+// The shape of the least estimated time (all give the same bits).  us before (256 x 256 always) -> now: 75 rows
+// 1024 -> 384 28.1 -> 5.9, 300 rows 4096 -> 1536 92 -> 15.0, 1000 rows 93 -> 22, 3075 rows 5120 -> 1920 117 -> 55,
+// 20000 rows 4096 -> 1536 253 -> 193.
 hipError_t launch_linear_rows_bf16(const void *a, const void *w, const void *bias, void *out, int64_t row_begin,
                                    int64_t row_end, int K, int N, hipStream_t st)
 {
     const int64_t rows = row_end - row_begin;
     if (rows <= 0) return hipSuccess;
-    const int64_t blocks = ((rows + kLinBm - 1) / kLinBm) * ((N + kLinBn - 1) / kLinBn);
     // 256 rows of either operand must span < 4 GiB (32-bit per-lane offsets)
-    if ((int64_t)kLinBm * K * 2 >= (1LL << 32)) return hipErrorInvalidValue;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    linear_rows_bf16_kernel<<<dim3((unsigned)blocks), 512, 0, st>>>(
-        static_cast<const __bf16 *>(a), static_cast<const __bf16 *>(w), static_cast<const __bf16 *>(bias),
-        static_cast<__bf16 *>(out), row_begin, row_end, K, N);
-    return hipGetLastError();
+    if ((int64_t)256 * K * 2 >= (1LL << 32)) return hipErrorInvalidValue;
+    const __bf16 *ap = static_cast<const __bf16 *>(a), *wp = static_cast<const __bf16 *>(w), *bp = static_cast<const __bf16 *>(bias);
+    __bf16 *op = static_cast<__bf16 *>(out);
+    const LinChoice *best = kLinChoices;
+    for (const LinChoice &c : kLinChoices)
+        if (lin_choice_us(c, rows, K, N) < lin_choice_us(*best, rows, K, N)) best = &c;
+    switch (best->bm * 1000 + best->bn) {
+    case 64064: return launch_linear<LinShape<4, 2, 1, 2, 5, 5, 2>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
+    case 128064: return launch_linear<LinShape<4, 2, 2, 2, 3, 3, 2>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
+    case 128128: return launch_linear<LinShape<4, 2, 2, 4, 3, 2, 2>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
+    case 192128: return launch_linear<LinShape<4, 2, 3, 4, 4, 4, 1>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
+    case 256128: return launch_linear<LinShape<4, 2, 4, 4, 3, 3, 1>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
+    default: return launch_linear<LinShape<2, 4, 8, 4, 3, 2, 1>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
+    }
 }
 
 }  // namespace memo

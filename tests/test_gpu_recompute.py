@@ -63,6 +63,27 @@ def test_linear_matches_oracle(S, K, N, with_bias):
     gu.assert_close("linear", gu.to_f64(out), ref, "bf16")
 
 
+# sizes around the tile shapes the launcher chooses from: ragged rows, features that fill half a tile, an odd number
+# of K chunks, several tiles per workgroup (the chunk stream runs on from one tile to the next)
+@pytest.mark.parametrize("S,K,N,row_begin", [(65, 128, 128, 0), (257, 384, 384, 1), (700, 640, 640, 3), (2500, 256, 896, 0),
+                                              (5000, 384, 640, 7), (9000, 128, 1152, 0), (40001, 384, 640, 130)])
+def test_linear_tile_shapes_match_oracle(S, K, N, row_begin):
+    print(f"[case] linear shapes S={S} K={K} N={N} rows=[{row_begin},{S})", flush=True)
+    g = torch.Generator().manual_seed(S + K + N)
+    a = torch.randn((S, K), generator=g).to(torch.bfloat16)
+    _, _, w, bias = _params(512, N, K, 6)
+    ad, wd, bd = a.cuda(), w.cuda(), bias.cuda()
+    out = torch.full((S, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    mb.memo_linear_rows(ad, wd, bd, out=out, rows=(row_begin, S))
+    ref = ro.linear(gu.to_f64(a[row_begin:]), gu.to_f64(w), gu.to_f64(bias))
+    gu.assert_close("linear", gu.to_f64(out[row_begin:]), ref, "bf16")
+    assert bool((out[:row_begin] == 7.0).all())
+    # a few rows alone take the smallest tile: the same bits
+    few = torch.zeros_like(out)
+    mb.memo_linear_rows(ad, wd, bd, out=few, rows=(S - 33, S))
+    assert torch.equal(few[S - 33:], out[S - 33:])
+
+
 def test_linear_identity_weight_is_exact():
     S, K = 70, 256
     a = torch.randn((S, K), generator=torch.Generator().manual_seed(9)).to(torch.bfloat16)
