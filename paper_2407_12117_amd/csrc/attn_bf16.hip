@@ -38,21 +38,41 @@ namespace {
 // takes the key tiles g, g + KS, ... of T rows through its own double-buffered LDS ring, filled
 // asynchronously (one barrier per step), and the groups of a row are combined at the end.
 //   QG = 8: 256 rows, no split.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
-//           each MFMA pays for: the best rate on a full chip (1205 TFLOP/s at S = 128K, H = 4).
-//   QG = 4: 128 rows, keys in two (1097); QG = 2: 64 rows, keys in four (885).
+//           each MFMA pays for: the best rate on a full chip (1216 TFLOP/s at S = 128K, H = 4).
+//   QG = 4: 128 rows, keys in two (1110).
+//   64 rows, keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel below (960).
 //   QG = 1: 32 rows, keys in eight (752); every wave has a tile of its own, so there is no barrier: one
 //           buffer, whose K half is refilled while V is worked and the other way round.
 // A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
 // last row: what bounds it is the longest workgroup, which QG = 1 makes 64 times shorter.  The launcher
 // takes the cheapest by estimate (kFwdChoices).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 8.7,
-// B = 2 S = 2000 H = 3 67.8 -> 19.5, S = 8192 H = 4 250 -> 93, S = 16461 H = 4 482 -> 285, S = 40000 H = 4 2202 -> 1516.
+// B = 2 S = 2000 H = 3 67.8 -> 19.2, S = 8192 H = 4 250 -> 79, S = 16461 H = 4 482 -> 269, S = 40000 H = 4 2202 -> 1516.
+// The fills address a tile as a buffer (TileOffsets::fill): no per-lane pointers to step and no second path for the
+// ragged last tile, 1 to 3 % of every shape.
 constexpr int kFwdWaves = 8;                 // waves per workgroup
 // A lane's 32 exponentials of a tile may sum to this much before the running maximum is brought up to
 // date: 2^40 per tile leaves the row sum over 2^20 keys and the output accumulators far inside fp32.
 constexpr float kRescaleAbove = 1099511627776.f;
 
+// a K operand and the Q operands of one or two row blocks
+template <int NQ> struct KqSlot { bf16x8 k, q[NQ]; };
+
+template <int N>
+__device__ __forceinline__ void lds_wait(KqSlot<1> &x)
+{
+    static_assert(N >= 0 && N <= 15, "lgkmcnt range");
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(x.k), "+v"(x.q[0]) : "n"(N));
+}
+
+template <int N>
+__device__ __forceinline__ void lds_wait(KqSlot<2> &x)
+{
+    static_assert(N >= 0 && N <= 15, "lgkmcnt range");
+    asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(x.k), "+v"(x.q[0]), "+v"(x.q[1]) : "n"(N));
+}
+
 template <int QG, int T>
-__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int order)
+__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int fold)
 {
     constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = T, JB = T / 32;
     constexpr int kTile = T * 256;              // bytes of one K or V tile
@@ -67,6 +87,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const LaneAddr la = make_lane_addr(lane);
     const int wq = wave % QG, grp = wave / QG;  // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
+    const int order = QG == 8 ? fold : kLongestFirst;   // the downward sweep of a pair takes every tile: KS = 1 only
     const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
@@ -81,7 +102,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
 
     // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
     // (online softmax takes the key tiles in any order)
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < (QG == 8 ? 2 : 1); ++pass) {
     const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
     if (tile < 0) break;
     const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq, i = i0w + l32;
@@ -90,13 +111,12 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
     const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
     if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
-    auto ks = make_tile_stream<QG, SwzA, T>(k, a.ss, (int64_t)jfirst * kBk, wq, lane);
-    auto vs = make_tile_stream<QG, SwzA, T>(v, a.ss, (int64_t)jfirst * kBk, wq, lane);
+    const TileOffsets<QG, T> toff = make_tile_offsets<QG, SwzA, T>(a.ss, wq, lane);
     auto fill_k = [&](int off, int jt) {
-        fill_tile_async<QG, SwzA, T>(lds + grp * kGroup + off, ks, k, a.ss, (int64_t)jt * kBk, a.S, wq, lane, jstep);
+        toff.fill(lds + grp * kGroup + off, k, a.ss, (int64_t)jt * kBk, a.S, wq);
     };
     auto fill_v = [&](int off, int jt) {
-        fill_tile_async<QG, SwzA, T>(lds + grp * kGroup + off + kTile, vs, v, a.ss, (int64_t)jt * kBk, a.S, wq, lane, jstep);
+        toff.fill(lds + grp * kGroup + off + kTile, v, a.ss, (int64_t)jt * kBk, a.S, wq);
     };
     if (QG > 1 && jfirst < ntiles) {
         fill_k(0, jfirst);
@@ -306,11 +326,206 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     }   // pass
 }
 
+// 64 rows, the keys in eight: every wave works all 64 rows (two blocks of 32) against key tiles of 32 of its own, so
+// there is no barrier in the sweep and a K or V operand read feeds two MFMAs.  Q stays in LDS: the accumulators of 64
+// rows leave no registers for it.  Bound, like all shapes below 256 rows, by what it streams per MFMA: as many bytes as
+// two waves per 32-key tile behind a barrier did, which ran at 885 TFLOP/s on a full chip (S = 8192, H = 4: 87 -> 79 us).
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(AttnArgs a)
+{
+    constexpr int kBq = 64, T = 32, kTile = T * 256, kQ = kFwdWaves * 2 * kTile, kStats = kQ + kBq * 256;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kFwdWaves * kBq * 8];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [wave][K|V] tiles, then the Q rows, then (maximum, sum)
+
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const LaneAddr la = make_lane_addr(lane);
+    const PairId t = decode_block(a, blockIdx.x, (a.S + kBq - 1) / kBq, kLongestFirst, true);
+    const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
+    const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
+    const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
+    const float c = a.scale * kLog2e;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int64_t row0 = t.first * kBq;
+    const int ntiles = (int)((min(row0 + kBq, a.S) - 1) / T) + 1;
+    LDS_AS unsigned char *ring = lds + wave * 2 * kTile;
+    // pieces of a row operand lie at address ^ (kc << 5), of a transposed one at address ^ (cb << 6)
+    const uint32_t q_row = (uint32_t)(uintptr_t)(lds + kQ) + (uint32_t)la.row_op[0];
+    const uint32_t k_row = (uint32_t)(uintptr_t)ring + (uint32_t)la.row_op[0];
+    const uint32_t v_lo = (uint32_t)(uintptr_t)ring + (uint32_t)la.tr_op[0][0], v_hi = (uint32_t)(uintptr_t)ring + (uint32_t)la.tr_op[0][1];
+
+    const TileOffsets<8, kBq> qoff = make_tile_offsets<8, SwzA, kBq>(a.ss, wave, lane);
+    qoff.fill(lds + kQ, static_cast<const __bf16 *>(a.q) + base, a.ss, row0, a.S, wave);
+    const TileOffsets<1, T> toff = make_tile_offsets<1, SwzA, T>(a.ss, 0, lane);
+    constexpr int kFills = TileOffsets<1, T>::kInstr;
+    auto fill_k = [&](int jt) { toff.fill(ring, k, a.ss, (int64_t)jt * T, a.S, 0); };
+    auto fill_v = [&](int jt) { toff.fill(ring + kTile, v, a.ss, (int64_t)jt * T, a.S, 0); };
+    if (wave < ntiles) {
+        fill_k(wave);
+        fill_v(wave);
+        wait_fills_but<2 * kFills>();
+    } else {
+        wait_fills();
+    }
+    __builtin_amdgcn_s_barrier();                     // the Q rows are complete
+    asm volatile("" ::: "memory");
+
+    f32x16 accO[2][4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) accO[b][cb] = zero;
+    float m[2] = {-INFINITY, -INFINITY}, mc[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
+
+    // one key tile against the row blocks from `first` on (the tile past the first block's diagonal is the second's alone)
+    auto tile_step = [&](auto firstc, int jt) {
+        constexpr int F = decltype(firstc)::value;
+        const int jn = jt + kFwdWaves;
+        uint32_t qa = q_row, ka = k_row, va = v_lo, vb = v_hi;
+        asm volatile("" : "+v"(qa), "+v"(ka), "+v"(va), "+v"(vb));   // the other addresses are formed where they are used
+        wait_fills_but<kFills>();                     // K has landed; V, queued behind it, may still be on its way
+        f32x16 s[2];
+        {
+            KqSlot<2 - F> kq[3];
+            auto issue = [&](auto n, KqSlot<2 - F> &slot) {
+                constexpr int kc = decltype(n)::value;
+                lds_issue_b128<0>(slot.k, ka ^ (kc << 5));
+                static_for<F, 2>([&](auto b) { lds_issue_b128<8192 * decltype(b)::value>(slot.q[decltype(b)::value - F], qa ^ (kc << 5)); });
+            };
+            lds_pipeline_prologue<8, 2, 3 - F>(kq, issue);
+            lds_pipeline_body<8, 2, 3 - F>(kq, issue, [&](auto n, KqSlot<2 - F> &slot) {
+                constexpr int kc = decltype(n)::value;
+#pragma unroll
+                for (int b = F; b < 2; ++b) s[b] = mfma32(slot.k, slot.q[b - F], kc == 0 ? zero : s[b]);
+            });
+        }
+        if (jn < ntiles) {                            // K is used up: the next K tile comes while V is worked
+            fill_k(jn);
+            wait_fills_but<kFills>();
+        } else {
+            wait_fills();
+        }
+        TrSlot vring[3];
+        auto v_issue = [&](auto n, TrSlot &slot) {
+            constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
+            lds_issue_tr<kj * 4096 + kTile>(slot, va ^ (cb << 6), vb ^ (cb << 6));
+        };
+        lds_pipeline_prologue<8, 2, 2>(vring, v_issue);
+        bf16x8 pB[2][2];
+#pragma unroll
+        for (int b = F; b < 2; ++b) {
+            const int64_t i0 = row0 + 32 * b;
+            if ((int64_t)jt * T >= i0) {              // diagonal tile: mask keys j > i
+                const int thr = l32 - 4 * half;
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (8 * (e >> 2) + (e & 3) > thr) s[b][e] = -INFINITY;
+            }
+            // against the running maximum as it stands (see attn_fwd_bf16_kernel)
+            float psum0, psum1;
+            auto exponentials = [&]() __attribute__((always_inline)) {
+                psum0 = psum1 = 0.f;
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) {
+                    const f32x2 two = {__builtin_amdgcn_exp2f(fmaf(s[b][e], c, -mc[b])), __builtin_amdgcn_exp2f(fmaf(s[b][e + 1], c, -mc[b]))};
+                    psum0 += two[0];
+                    psum1 += two[1];
+                    const bf16x2 r = __builtin_convertvector(two, bf16x2);
+                    pB[b][e >> 3][e & 7] = r[0];
+                    pB[b][e >> 3][(e & 7) + 1] = r[1];
+                }
+            };
+            exponentials();
+            if (__builtin_amdgcn_ballot_w64(!(psum0 + psum1 <= kRescaleAbove)) != 0) {
+                float mb = fmaxf(fmaxf(s[b][0], s[b][1]), s[b][2]);
+#pragma unroll
+                for (int e = 3; e < 15; e += 2) mb = fmaxf(fmaxf(mb, s[b][e]), s[b][e + 1]);
+                mb = fmaxf(mb, s[b][15]);
+                const float m_new = fmaxf(m[b], max_across_halves(mb));
+                const float corr = __builtin_amdgcn_exp2f((m[b] - m_new) * c);
+                m[b] = m_new;
+                mc[b] = m_new * c;
+                lsum[b] *= corr;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) accO[b][cb][e] *= corr;
+                exponentials();
+            }
+            lsum[b] += psum0 + psum1;
+        }
+        lds_pipeline_body<8, 2, 2>(vring, v_issue, [&](auto n, TrSlot &slot) {
+            constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
+#pragma unroll
+            for (int b = F; b < 2; ++b) accO[b][cb] = mfma32(tr_operand(slot), pB[b][kj], accO[b][cb]);
+        });
+        if (jn < ntiles) fill_v(jn);
+    };
+    const int last_both = (int)(row0 / T);            // tiles past it hold no key of the first block's rows
+    int jt = wave;
+#pragma clang loop unroll(disable)
+    for (; jt <= last_both; jt += kFwdWaves) tile_step(IntC<0>{}, jt);
+    if (jt < ntiles) tile_step(IntC<1>{}, jt);
+
+    // the waves' parts of a block of rows meet in LDS, one block after the other, as in attn_fwd_bf16_kernel
+    LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+    LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kStats);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int64_t i = row0 + 32 * b + l32;
+        const float ltot = add_across_halves(lsum[b]);
+        __syncthreads();          // every wave has left what lies there
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[b][e >> 2][4 * (e & 3)], accO[b][e >> 2][4 * (e & 3) + 1],
+                                                        accO[b][e >> 2][4 * (e & 3) + 2], accO[b][e >> 2][4 * (e & 3) + 3]};
+        if (half == 0) stats[wave * 32 + l32] = f32x2{mc[b], ltot};
+        __syncthreads();
+        float top = -INFINITY, total = 0.f, weight[kFwdWaves];
+        f32x2 st[kFwdWaves];
+#pragma unroll
+        for (int g = 0; g < kFwdWaves; ++g) {
+            st[g] = stats[g * 32 + l32];
+            top = fmaxf(top, st[g][0]);
+        }
+#pragma unroll
+        for (int g = 0; g < kFwdWaves; ++g) {
+            weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
+            total += weight[g] * st[g][1];
+        }
+        if (i < a.S) {
+            const float inv = 1.f / total;
+            __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                const int e = wave * 2 + n;
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int g = 0; g < kFwdWaves; ++g) {
+                    const f32x4 x = pieces[(g * 16 + e) * 64 + lane];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
+                }
+                store4(o + 8 * e + 4 * half, sum, inv);
+            }
+            if (wave == 0 && half == 0) a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
+        }
+    }
+}
+
+hipError_t launch_fwd_own(const AttnArgs &a, hipStream_t st)
+{
+    const int64_t blocks = order_grid((a.S + 63) / 64, (int64_t)a.H * a.B, kLongestFirst);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    attn_fwd_bf16_own_kernel<<<dim3((unsigned)blocks), 64 * kFwdWaves, 0, st>>>(a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 template <int QG, int T>
 hipError_t launch_fwd(const AttnArgs &a, int order, hipStream_t st)
 {
+    if (QG != 8) order = kLongestFirst;               // as in the kernel
     const int64_t nqt = (a.S + 32 * QG - 1) / (32 * QG);
     const int64_t blocks = order_grid(nqt, (int64_t)a.H * a.B, order);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -322,7 +537,7 @@ hipError_t launch_fwd(const AttnArgs &a, int order, hipStream_t st)
 // (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst.
 constexpr TileChoice kFwdChoices[] = {
     {256, kFolded, 115.5, 4.0}, {256, kLongestFirst, 117.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
-    {64, kLongestFirst, 155.0, 6.5}, {32, kLongestFirst, 185.0, 4.5},
+    {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
 };
 
 hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
@@ -330,7 +545,7 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
     const TileChoice &c = kFwdChoices[cheapest_tiles(kFwdChoices, a.S, (int64_t)a.H * a.B)];
     switch (c.rows) {
     case 32: return launch_fwd<1, 32>(a, c.order, st);
-    case 64: return launch_fwd<2, 32>(a, c.order, st);
+    case 64: return launch_fwd_own(a, st);
     case 128: return launch_fwd<4, 64>(a, c.order, st);
     default: return launch_fwd<8, 64>(a, c.order, st);
     }

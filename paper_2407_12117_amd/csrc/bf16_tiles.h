@@ -280,69 +280,29 @@ __device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, i
 }
 
 // ---- asynchronous tile fill: global -> LDS without passing through registers -------------
-// One global_load_lds_dwordx4 moves 64 x 16 bytes: lane l lands at LDS base + 16*l, i.e. four
+// One 16-byte fill instruction moves 64 x 16 bytes: lane l lands at LDS base + 16*l, i.e. four
 // tile rows of sixteen chunks.  With NW waves sharing a tile, wave w issues instruction n for
-// tile rows 4*(NI*w + n) + l/16 (NI = 16/NW); the lane at chunk position p = l%16 fetches
-// logical chunk p ^ swz(row), so the swizzle is applied on the global side.  Each lane keeps
-// the global address of its piece per instruction and steps it by one tile (a wave-uniform
-// stride) after every fill: one 64-bit add per instruction and tile, nothing else.
-template <int NW, int ROWS = 64>
-struct TileStream {
-    static constexpr int kInstr = ROWS / 4 / NW;
-    const char *p[kInstr];
-};
-
-template <int NW, typename SW = SwzA, int ROWS = 64>
-__device__ __forceinline__ TileStream<NW, ROWS> make_tile_stream(const __bf16 *src, int64_t ss, int64_t r0,
-                                                                 int wave, int lane)
-{
-    TileStream<NW, ROWS> f;
-#pragma unroll
-    for (int n = 0; n < TileStream<NW, ROWS>::kInstr; ++n) {
-        const int row = 4 * (TileStream<NW, ROWS>::kInstr * wave + n) + (lane >> 4);
-        const int chunk = (lane & 15) ^ SW::f(row);
-        f.p[n] = reinterpret_cast<const char *>(src + (r0 + row) * ss + chunk * 8);
-    }
-    return f;
-}
-
-// Queues the fill of the ROWS-row tile the stream points at (rows r0.. of the head view `src`) and
-// steps the stream `dir` tiles on (dir = -1: to the previous one).  A tile that reaches past row S-1 takes the
-// slow path: rows past S re-read row S-1 (finite values; every consumer masks them).
-template <int NW, typename SW = SwzA, int ROWS = 64>
-__device__ __forceinline__ void fill_tile_async(LDS_AS unsigned char *tile, TileStream<NW, ROWS> &f,
-                                                const __bf16 *src, int64_t ss, int64_t r0, int64_t S,
-                                                int wave, int lane, int dir = 1)
-{
-    constexpr int NI = TileStream<NW, ROWS>::kInstr;
-    if (__builtin_expect(r0 + ROWS <= S, 1)) {
-#pragma unroll
-        for (int n = 0; n < NI; ++n)
-            __builtin_amdgcn_global_load_lds((const GLB_AS void *)f.p[n],
-                                             (LDS_AS void *)(tile + (NI * wave + n) * 1024), 16, 0, 0);
-    } else {
-#pragma unroll
-        for (int n = 0; n < NI; ++n) {
-            const int row = 4 * (NI * wave + n) + (lane >> 4);
-            const int chunk = (lane & 15) ^ SW::f(row);
-            int64_t rg = r0 + row;
-            rg = rg < S ? rg : S - 1;
-            __builtin_amdgcn_global_load_lds((const GLB_AS void *)(src + rg * ss + chunk * 8),
-                                             (LDS_AS void *)(tile + (NI * wave + n) * 1024), 16, 0, 0);
-        }
-    }
-    const int64_t step = dir * ROWS * ss * 2;     // dir = -1: the stream walks towards row 0
-#pragma unroll
-    for (int n = 0; n < NI; ++n) f.p[n] += step;
-}
-
-// The same fill addressed as a wave-uniform tile base (scalar registers, stepped once per tile)
-// plus a per-lane 32-bit byte offset that never changes: half the address registers of
-// TileStream and no per-tile vector adds.  Needs 64 rows of the view to span < 4 GiB.
+// tile rows 4*(NI*w + n) + l/16 (NI = 16/NW for 64 rows); the lane at chunk position p = l%16 fetches
+// logical chunk p ^ swz(row), so the swizzle is applied on the global side.  A tile is addressed as a wave-uniform base
+// (scalar registers) plus a per-lane 32-bit byte offset that never changes.  Needs 64 rows of the view to span < 4 GiB.
 template <int NW, int ROWS = 64>
 struct TileOffsets {
     static constexpr int kInstr = ROWS / 4 / NW;
     uint32_t off[kInstr];
+
+    // Queues the fill of the tile whose first row is r0 of `src`, taken as a buffer that ends with row end - 1: rows past it are
+    // out of range and read as zero (every consumer masks them); r0 >= end is an empty buffer, whose fills are still counted.
+    __device__ __forceinline__ void fill(LDS_AS unsigned char *tile, const __bf16 *src, int64_t ss, int64_t r0, int64_t end, int wave) const
+    {
+#ifdef __HIP_DEVICE_COMPILE__      // the host pass does not know the 16-byte form of the builtin
+        const int rows = (int)max((int64_t)0, min((int64_t)ROWS, end - r0));
+        const uint32_t bytes = rows > 0 ? (uint32_t)(rows - 1) * (uint32_t)ss * 2 + 256 : 0;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(src + r0 * ss), 0, bytes, 0x00020000);
+#pragma unroll
+        for (int n = 0; n < kInstr; ++n)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (LDS_AS void *)(tile + (kInstr * wave + n) * 1024), 16, off[n], 0, 0, 0);
+#endif
+    }
 };
 
 template <int NW, typename SW = SwzA, int ROWS = 64>

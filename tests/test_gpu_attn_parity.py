@@ -99,6 +99,13 @@ def test_bf16_every_workgroup_shape(oracle, S, heads):
     _dense_case(oracle, 1, S, heads, 128, "bf16", 7000 + S + heads, scaled=True)
 
 
+@pytest.mark.parametrize("S", [321, 352, 353, 383])
+def test_bf16_forward_64_row_edges(oracle, S):
+    # 48 heads of this length take the 64-row forward: one row, one block of rows, one more, all but one in the last
+    # tile, whose second block sees a key tile that the first does not
+    _dense_case(oracle, 1, S, 48, 128, "bf16", 9000 + S, scaled=True)
+
+
 def test_bf16_scale_below_the_usual_one(oracle):
     _dense_case(oracle, 1, 500, 2, 128, "bf16", 41, scale=0.06)
 
