@@ -354,6 +354,7 @@ __global__ __launch_bounds__(512, 2) void linear_rows_bf16_kernel(const __bf16 *
         } while (g < tile_chunks);
         stores_at = finish(tile) ? g : kNever;
     }
+    wait_fills();                 // the empty fills behind the last chunk write LDS too: none may outlive the workgroup
 }
 
 }  // namespace
