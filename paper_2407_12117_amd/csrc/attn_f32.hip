@@ -6,8 +6,8 @@
 // What bounds it: the fp32 matrix rate, 256 flops per cycle and compute unit (157 TFLOP/s), the same as the
 // vector units'; but one MFMA instruction does 32 cycles of that work from two registers, where the
 // vector form needs an LDS read per multiply-add and lane.  An earlier VALU version of these kernels ran at 5 to
-// 7 TFLOP/s, bound by its scalar LDS reads.  LDS and fill traffic are light here (16 KB of operands per 2048
-// MFMA cycles), so small workgroups cost nothing per flop and the tiles are chosen to spread the work.
+// 7 TFLOP/s, bound by its scalar LDS reads; these reach 118 (forward) and 117 (backward, of its seven contractions) at
+// S = 5000, B = 2, H = 4, d = 128.
 //
 // Operand conventions of the 16x16x4 MFMA, D = A(16xK4) * B(K4x16), lane = 16*g4 + l16:
 //   A : lane holds row l16, k = g4;  B : lane holds col l16, k = g4;
@@ -20,8 +20,11 @@
 // LDS rows are D floats; the 16-byte piece c of row r lies at c ^ SwzB(r) (low four bits), conflict-free for both
 // reads as in the bf16 tiles.
 //
-// Workgroup: 8 waves = G row groups of 16 owned rows x 8/G groups that share out the streamed rows (16 per
-// tile, a double-buffered ring per group, one barrier per step) and are combined through LDS at the end.
+// Workgroup: 16 owned rows, 8 waves that share out the streamed rows: every wave has tiles of 16 of them to itself, so there is
+// no barrier in the sweep, and the waves' parts are combined through LDS at the end.  One buffer per wave: a half of
+// it is refilled as soon as it is used up, while the other half is worked.  (32 owned rows, two waves to a tile and a
+// barrier per step halve the fill traffic, and were ahead on a full chip while the fills computed 64-bit addresses; with
+// buffer fills they lose everywhere: S = 5000, H = 4, d = 128 forward 260 against 225 us, backward 808 against 781.)
 #include "bf16_tiles.h"
 
 namespace memo {
@@ -36,36 +39,58 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <int D, int G>
+template <int D>
 struct F32Shape {
-    static constexpr int kParts = kF32Waves / G;      // groups that share out the streamed rows
-    static constexpr bool kOwn = G == 1;              // every wave has a ring of its own: one stage, no barrier
-    static constexpr int kTile = kT * D * 4, kFills = kTile / 1024 / G;       // bytes; fill instructions per wave
-    static constexpr int kStage = 2 * kTile, kGroup = (kOwn ? 1 : 2) * kStage, kRing = kParts * kGroup;
+    static constexpr int kTile = kT * D * 4, kFills = kTile / 1024;       // bytes; fill instructions
+    static constexpr int kStage = 2 * kTile, kRing = kF32Waves * kStage;
     static constexpr int kPieces = D / 16;            // f32x4 per lane of one accumulator set
     static_assert(kRing >= kF32Waves * kPieces * 1024 && kRing <= 128 * 1024, "the combination lays the accumulators over the ring");
 };
 
-// two workgroups per compute unit where LDS has room for them and 128 registers hold a wave
-template <int D, int G> constexpr int kFwdWavesPerSimd = F32Shape<D, G>::kRing <= 65536 ? 4 : 2;
-template <int D, int G> constexpr int kBwdWavesPerSimd = D == 64 && G > 1 ? 4 : 2;
+// head dim 64: LDS has room for two workgroups per compute unit, and 128 registers hold a wave
+template <int D> constexpr int kWavesPerSimd = D == 64 ? 4 : 2;
 
-// fill of the 16-row tile at rows r0.. by the G waves of a group (rows past S repeat row S-1)
-template <int D, int G>
-__device__ __forceinline__ void f32_fill(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S,
-                                         int w, int lane)
-{
-    constexpr int rows = 256 / D, n_instr = kT / rows / G;        // rows per instruction, instructions per wave
-    static_assert(n_instr >= 1, "more waves than instructions");
-#pragma unroll
-    for (int n = 0; n < n_instr; ++n) {
-        const int row = rows * (n_instr * w + n) + lane / (D / 4), pos = lane % (D / 4);
-        const int piece = pos ^ SwzB::f(row);
-        const int64_t rg = r0 + row < S ? r0 + row : S - 1;
-        __builtin_amdgcn_global_load_lds((const GLB_AS void *)(src + rg * ss + piece * 4),
-                                         (LDS_AS void *)(tile + (n_instr * w + n) * 1024), 16, 0, 0);
+// Fill of the 16-row tile at rows r0..  The tile is a buffer that ends with row S - 1: rows past it are
+// out of range and read as zero (every consumer masks them).  A lane's offset within an instruction's rows never
+// changes; the next instruction is kRows rows on and, the swizzle being linear in the bits of the row, one XOR away.
+// (With a 64-bit address and a clamped row per instruction: S = 3000 d = 128 H = 4 forward 114 us, now 96.)
+// FAR: rows so far apart (2^26 floats) that 16 of them leave a buffer's 4 GiB; full addresses, rows past S repeat row S-1.
+constexpr int64_t kFarStride = (int64_t)1 << 26;
+template <int D, bool FAR>
+struct F32Fill {
+    static constexpr int kRows = 256 / D, kInstr = kT / kRows;        // rows per instruction, instructions
+    uint32_t row_off, piece_off;
+
+    __device__ __forceinline__ F32Fill(int64_t ss, int lane)
+    {
+        const int row = lane / (D / 4), pos = lane % (D / 4);
+        row_off = (uint32_t)row * (uint32_t)ss * 4;
+        piece_off = (uint32_t)(pos ^ SwzB::f(row)) * 16;
     }
-}
+    __device__ __forceinline__ void operator()(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane) const
+    {
+        if constexpr (FAR) {
+#pragma unroll
+            for (int n = 0; n < kInstr; ++n) {
+                const int row = kRows * n + lane / (D / 4), piece = lane % (D / 4) ^ SwzB::f(row);
+                const int64_t rg = r0 + row < S ? r0 + row : S - 1;
+                __builtin_amdgcn_global_load_lds((const GLB_AS void *)(src + rg * ss + piece * 4),
+                                                 (LDS_AS void *)(tile + n * 1024), 16, 0, 0);
+            }
+        } else {
+#ifdef __HIP_DEVICE_COMPILE__      // the host pass does not know the 16-byte form of the builtin
+            const int rows = (int)max((int64_t)0, min((int64_t)kT, S - r0));
+            const uint32_t bytes = rows > 0 ? (uint32_t)(rows - 1) * (uint32_t)ss * 4 + D * 4 : 0;
+            const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src + r0 * ss), 0, bytes, 0x00020000);
+#pragma unroll
+            for (int n = 0; n < kInstr; ++n)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (LDS_AS void *)(tile + n * 1024), 16,
+                                                         row_off + (piece_off ^ (uint32_t)(SwzB::f(kRows * n) * 16)) +
+                                                             (uint32_t)(kRows * n) * (uint32_t)ss * 4, 0, 0, 0);
+#endif
+        }
+    }
+};
 
 // LDS addresses of a lane's operand reads within a tile (bf16_tiles.h has the hand-issued pipeline they go through):
 //   row[c % 4] + 256 (c / 4)   row-major operand: row l16, floats 16c + 4*g4 ..
@@ -99,22 +124,21 @@ __device__ __forceinline__ void f32_load_row(f32x4 (&dst)[D / 16], const float *
 
 constexpr int kDepth = 3;         // operand reads in flight ahead of their MFMAs
 
-// acc^T[dim][col] += tile^T x (tile rows 4*g4 + r), tile OFF bytes past `at`: item n = (r = n / (D/64), h = n % (D/64)),
+// acc^T[dim][col] += tile^T x (tile rows 4*g4 + r), tile OFF bytes into the buffer: item n = (r = n / (D/64), h = n % (D/64)),
 // one read, four MFMAs.  f32_outer_issue asks for the first operands ahead of the element-wise work.
 template <int D, int OFF>
 struct F32Outer {
     static constexpr int H = D / 64, N = 4 * H;
     f32x4 ring[kDepth + 1];
     const F32Addr &ad;
-    uint32_t at;
-    __device__ __forceinline__ F32Outer(const F32Addr &addr, uint32_t off) : ad(addr), at(off)
+    __device__ __forceinline__ F32Outer(const F32Addr &addr) : ad(addr)
     {
         lds_pipeline_prologue<N, kDepth, 1>(ring, [&](auto n, f32x4 &slot) { issue(n, slot); });
     }
     template <typename I>
     __device__ __forceinline__ void issue(I, f32x4 &slot)
     {
-        lds_issue_b128<OFF + 256 * (I::value % H)>(slot, ad.tr[I::value / H] + at);
+        lds_issue_b128<OFF + 256 * (I::value % H)>(slot, ad.tr[I::value / H]);
     }
     __device__ __forceinline__ void run(f32x4 (&acc)[D / 16], const f32x4 &x)
     {
@@ -128,15 +152,15 @@ struct F32Outer {
 
 // s += (rows of tile 0) x b0 and dp += (rows of tile 1) x b1 over the head dim: item c, two reads, eight MFMAs
 template <int D>
-__device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Addr &ad, uint32_t at, const f32x4 (&b0)[D / 16],
+__device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Addr &ad, const f32x4 (&b0)[D / 16],
                                                const f32x4 (&b1)[D / 16])
 {
     constexpr int kTile = kT * D * 4;
     F32Pair ring[2];
     auto issue = [&](auto n, F32Pair &slot) {
         constexpr int c = decltype(n)::value;
-        lds_issue_b128<256 * (c / 4)>(slot.x, ad.row[c % 4] + at);
-        lds_issue_b128<kTile + 256 * (c / 4)>(slot.y, ad.row[c % 4] + at);
+        lds_issue_b128<256 * (c / 4)>(slot.x, ad.row[c % 4]);
+        lds_issue_b128<kTile + 256 * (c / 4)>(slot.y, ad.row[c % 4]);
     };
     lds_pipeline_prologue<D / 16, 1, 2>(ring, issue);
     lds_pipeline_body<D / 16, 1, 2>(ring, issue, [&](auto n, F32Pair &slot) {
@@ -157,29 +181,28 @@ __device__ __forceinline__ f32x4 f32_piece(const f32x4 (&acc)[D / 16], int p)
     return f32x4{acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]};
 }
 
-template <int D, int G>
-__global__ __launch_bounds__(512, (kFwdWavesPerSimd<D, G>)) void attn_fwd_f32_kernel(AttnArgs a)
+template <int D, bool FAR>
+__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(AttnArgs a)
 {
-    using Shape = F32Shape<D, G>;
-    constexpr int KS = Shape::kParts, NP = Shape::kPieces;
+    using Shape = F32Shape<D>;
+    constexpr int KS = kF32Waves, NP = Shape::kPieces;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[Shape::kRing + kF32Waves * 16 * 8];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [key group][buf][K|V] tiles, then (c m, sum) per wave and row
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, then (c m, sum) per wave and row
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wq = wave % G, grp = wave / G;
-    const PairId t = decode_block(a, blockIdx.x, (a.S + 16 * G - 1) / (16 * G), kLongestFirst, true);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const PairId t = decode_block(a, blockIdx.x, (a.S + kT - 1) / kT, kLongestFirst, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const float *k = static_cast<const float *>(a.k) + base, *v = static_cast<const float *>(a.v) + base;
-    const int64_t row0 = t.first * 16 * G, i0w = row0 + 16 * wq, i = i0w + l16;
-    const int ntiles = (int)((min(row0 + 16 * G, a.S) - 1) / kT) + 1;
+    const int64_t row0 = t.first * kT, i = row0 + l16;
+    const int ntiles = (int)((min(row0 + kT, a.S) - 1) / kT) + 1;
     const float c = a.scale * kLog2e;
-    LDS_AS unsigned char *ring = lds + grp * Shape::kGroup;
-    auto fill_k = [&](int buf, int jt) { f32_fill<D, G>(ring + buf * Shape::kStage, k, a.ss, (int64_t)jt * kT, a.S, wq, lane); };
-    auto fill_v = [&](int buf, int jt) {
-        f32_fill<D, G>(ring + buf * Shape::kStage + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, wq, lane);
-    };
-    if (grp < ntiles) {
-        fill_k(0, grp);
-        fill_v(0, grp);
+    LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
+    const F32Fill<D, FAR> fill(a.ss, lane);
+    auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
+    auto fill_v = [&](int jt) { fill(ring + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, lane); };
+    if (wave < ntiles) {
+        fill_k(wave);
+        fill_v(wave);
     }
     const F32Addr ad = f32_addr<D>(ring, l16, g4);
     f32x4 q[D / 16], acc[D / 16];
@@ -187,28 +210,16 @@ __global__ __launch_bounds__(512, (kFwdWavesPerSimd<D, G>)) void attn_fwd_f32_ke
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) acc[n] = kZero4;
     float mc = -INFINITY, lsum = 0.f;                 // running maximum (times c) and sum of this lane's keys
-    const int diag = (int)(i0w / kT);                 // tiles past this one are fully masked for the wave
 
-    for (int jt = grp, n = 0; n * KS < ntiles; ++n, jt += KS) {
+    for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
-        if constexpr (Shape::kOwn) {
-            wait_fills_but<Shape::kFills>();          // K has landed; V, queued behind it, may still be on its way
-        } else {
-            wait_fills();
-            __syncthreads();      // tile jt is complete; nobody still reads the other buffer
-            if (more) {
-                fill_k((n + 1) & 1, jt + KS);
-                fill_v((n + 1) & 1, jt + KS);
-            }
-        }
-        if (jt > diag || jt >= ntiles) continue;
-        const uint32_t at = Shape::kOwn ? 0u : (uint32_t)((n & 1) * Shape::kStage);
+        wait_fills_but<Shape::kFills>();              // K has landed; V, queued behind it, may still be on its way
         f32x4 s = kZero4, s1 = kZero4;                // two chains
         {
             f32x4 kring[kDepth + 1];
             auto issue = [&](auto m, f32x4 &slot) {
                 constexpr int cc = decltype(m)::value;
-                lds_issue_b128<256 * (cc / 4)>(slot, ad.row[cc % 4] + at);
+                lds_issue_b128<256 * (cc / 4)>(slot, ad.row[cc % 4]);
             };
             lds_pipeline_prologue<D / 16, kDepth, 1>(kring, issue);
             lds_pipeline_body<D / 16, kDepth, 1>(kring, issue, [&](auto m, f32x4 &slot) {
@@ -219,17 +230,15 @@ __global__ __launch_bounds__(512, (kFwdWavesPerSimd<D, G>)) void attn_fwd_f32_ke
                 s1 = mfma4(slot[3], q[cc][3], s1);
             });
         }
-        if constexpr (Shape::kOwn) {
-            if (more) {
-                fill_k(0, jt + KS);                   // K is used up
-                wait_fills_but<Shape::kFills>();
-            } else {
-                wait_fills();
-            }
+        if (more) {
+            fill_k(jt + KS);      // K is used up
+            wait_fills_but<Shape::kFills>();
+        } else {
+            wait_fills();
         }
-        F32Outer<D, Shape::kTile> pv(ad, at);         // the first V operands: their latency hides behind the softmax
+        F32Outer<D, Shape::kTile> pv(ad);         // the first V operands: their latency hides behind the softmax
         s += s1;
-        if (jt == diag) {         // key 4*g4 + r of the tile is visible to query l16 iff it is <= l16
+        if (jt == ntiles - 1) {         // key 4*g4 + r of the tile is visible to query l16 iff it is <= l16
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (4 * g4 + r > l16) s[r] = -INFINITY;
@@ -255,8 +264,7 @@ __global__ __launch_bounds__(512, (kFwdWavesPerSimd<D, G>)) void attn_fwd_f32_ke
         }
         lsum += (p[0] + p[1]) + (p[2] + p[3]);
         pv.run(acc, p);                               // O^T += V^T P^T
-        if constexpr (Shape::kOwn)
-            if (more) fill_v(0, jt + KS);
+        if (more) fill_v(jt + KS);
     }
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
@@ -272,7 +280,7 @@ __global__ __launch_bounds__(512, (kFwdWavesPerSimd<D, G>)) void attn_fwd_f32_ke
     f32x2 st[KS];
 #pragma unroll
     for (int g = 0; g < KS; ++g) {
-        st[g] = stats[(g * G + wq) * 16 + l16];
+        st[g] = stats[g * 16 + l16];
         top = fmaxf(top, st[g][0]);
     }
 #pragma unroll
@@ -283,57 +291,56 @@ __global__ __launch_bounds__(512, (kFwdWavesPerSimd<D, G>)) void attn_fwd_f32_ke
     if (i >= a.S) return;
     float *o = static_cast<float *>(a.o_out) + base + i * a.ss + 16 * g4;
     const float inv = 1.f / total;
-    for (int p = grp; p < NP; p += KS) {
+    for (int p = wave; p < NP; p += KS) {
         f32x4 sum = kZero4;
 #pragma unroll
-        for (int g = 0; g < KS; ++g) sum += weight[g] * pieces[((g * G + wq) * NP + p) * 64 + lane];
+        for (int g = 0; g < KS; ++g) sum += weight[g] * pieces[(g * NP + p) * 64 + lane];
         *reinterpret_cast<f32x4 *>(o + 64 * (p >> 2) + 4 * (p & 3)) = sum * inv;
     }
-    if (grp == 0 && g4 == 0) a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
+    if (wave == 0 && g4 == 0) a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
 }
 
-// Adds up the accumulators of the row group's waves and writes mul times them: out points at the lane's row.
-template <int D, int G>
+// Adds up the accumulators of the eight waves and writes mul times them: out points at the lane's row.
+template <int D>
 __device__ __forceinline__ void f32_combine(LDS_AS unsigned char *lds, const f32x4 (&acc)[D / 16], float *out, bool live, float mul,
-                                            int w, int grp, int lane)
+                                            int wave, int lane)
 {
-    using Shape = F32Shape<D, G>;
-    constexpr int NP = Shape::kPieces, KS = Shape::kParts;
+    using Shape = F32Shape<D>;
+    constexpr int NP = Shape::kPieces, KS = kF32Waves;
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
     __syncthreads();              // every wave has left what lies there
 #pragma unroll
-    for (int p = 0; p < NP; ++p) pieces[((grp * G + w) * NP + p) * 64 + lane] = f32_piece<D>(acc, p);
+    for (int p = 0; p < NP; ++p) pieces[(wave * NP + p) * 64 + lane] = f32_piece<D>(acc, p);
     __syncthreads();
-    for (int p = grp; p < NP; p += KS) {
+    for (int p = wave; p < NP; p += KS) {
         f32x4 sum = kZero4;
 #pragma unroll
-        for (int g = 0; g < KS; ++g) sum += pieces[((g * G + w) * NP + p) * 64 + lane];
+        for (int g = 0; g < KS; ++g) sum += pieces[(g * NP + p) * 64 + lane];
         if (live) *reinterpret_cast<f32x4 *>(out + 64 * (p >> 2) + 4 * (p & 3)) = sum * mul;
     }
 }
 
 // dQ_i = scale * sum_{j<=i} dS_ij k_j, dS_ij = P_ij (dO_i.v_j - D_i), P_ij = exp(s_ij - LSE_i); rows = queries
-template <int D, int G>
-__device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
+template <int D, bool FAR>
+__device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, bool longest_first)
 {
-    using Shape = F32Shape<D, G>;
-    constexpr int KS = Shape::kParts;
+    using Shape = F32Shape<D>;
+    constexpr int KS = kF32Waves;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wq = wave % G, grp = wave / G;
-    const PairId t = decode_block(a, id, (a.S + 16 * G - 1) / (16 * G), kLongestFirst, true);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const PairId t = decode_block(a, id, (a.S + kT - 1) / kT, kLongestFirst, longest_first);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh, stat = ((int64_t)t.b * a.H + t.h) * a.S;
     const float *k = static_cast<const float *>(a.k) + base, *v = static_cast<const float *>(a.v) + base;
-    const int64_t row0 = t.first * 16 * G, i0w = row0 + 16 * wq, i = i0w + l16, iq = i < a.S ? i : a.S - 1;
-    const int ntiles = (int)((min(row0 + 16 * G, a.S) - 1) / kT) + 1;
+    const int64_t row0 = t.first * kT, i = row0 + l16, iq = i < a.S ? i : a.S - 1;
+    const int ntiles = (int)((min(row0 + kT, a.S) - 1) / kT) + 1;
     const float c = a.scale * kLog2e;
-    LDS_AS unsigned char *ring = lds + grp * Shape::kGroup;
-    auto fill_k = [&](int buf, int jt) { f32_fill<D, G>(ring + buf * Shape::kStage, k, a.ss, (int64_t)jt * kT, a.S, wq, lane); };
-    auto fill_v = [&](int buf, int jt) {
-        f32_fill<D, G>(ring + buf * Shape::kStage + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, wq, lane);
-    };
-    if (grp < ntiles) {
-        fill_k(0, grp);
-        fill_v(0, grp);
+    LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
+    const F32Fill<D, FAR> fill(a.ss, lane);
+    auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
+    auto fill_v = [&](int jt) { fill(ring + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, lane); };
+    if (wave < ntiles) {
+        fill_k(wave);
+        fill_v(wave);
     }
     const F32Addr ad = f32_addr<D>(ring, l16, g4);
     f32x4 q[D / 16], go[D / 16], acc[D / 16];
@@ -342,25 +349,14 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     const float lse2 = a.lse[stat + iq] * kLog2e, nd = -a.delta[stat + iq];
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) acc[n] = kZero4;
-    const int diag = (int)(i0w / kT);
-    for (int jt = grp, n = 0; n * KS < ntiles; ++n, jt += KS) {
-        wait_fills();
+    for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
-        if constexpr (!Shape::kOwn) {
-            __syncthreads();      // tile jt is complete; nobody still reads the other buffer
-            if (more) {
-                fill_k((n + 1) & 1, jt + KS);
-                fill_v((n + 1) & 1, jt + KS);
-            }
-        }
-        if (jt > diag || jt >= ntiles) continue;
-        const uint32_t at = Shape::kOwn ? 0u : (uint32_t)((n & 1) * Shape::kStage);
+        wait_fills();
         f32x4 s = kZero4, dp = {nd, nd, nd, nd};      // keys 4*g4 + r x query l16
-        f32_two_scores<D>(s, dp, ad, at, q, go);
-        if constexpr (Shape::kOwn)
-            if (more) fill_v(0, jt + KS);             // V is used up
-        F32Outer<D, 0> kds(ad, at);
-        if (jt == diag) {
+        f32_two_scores<D>(s, dp, ad, q, go);
+        if (more) fill_v(jt + KS);                    // V is used up
+        F32Outer<D, 0> kds(ad);
+        if (jt == ntiles - 1) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (4 * g4 + r > l16) s[r] = -INFINITY;
@@ -369,31 +365,29 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
 #pragma unroll
         for (int r = 0; r < 4; ++r) ds[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse2)) * dp[r];
         kds.run(acc, ds);                             // dQ^T += K^T dS^T
-        if constexpr (Shape::kOwn)
-            if (more) fill_k(0, jt + KS);
+        if (more) fill_k(jt + KS);
     }
-    f32_combine<D, G>(lds, acc, static_cast<float *>(a.dq) + base + iq * a.ss + 16 * g4, i < a.S, a.scale, wq, grp, lane);
+    f32_combine<D>(lds, acc, static_cast<float *>(a.dq) + base + iq * a.ss + 16 * g4, i < a.S, a.scale, wave, lane);
 }
 
 // dV_j = sum_{i>=j} P_ij dO_i,  dK_j = scale * sum_{i>=j} dS_ij q_i; rows = keys, K and V rows in registers
-template <int D, int G>
+template <int D, bool FAR>
 __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
 {
-    using Shape = F32Shape<D, G>;
-    constexpr int QS = Shape::kParts;
+    using Shape = F32Shape<D>;
+    constexpr int QS = kF32Waves;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wk = wave % G, grp = wave / G;
-    const PairId t = decode_block(a, id, (a.S + 16 * G - 1) / (16 * G), kLongestFirst, false);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const PairId t = decode_block(a, id, (a.S + kT - 1) / kT, kLongestFirst, false);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh, stat = ((int64_t)t.b * a.H + t.h) * a.S;
     const float *q = static_cast<const float *>(a.q) + base, *g = static_cast<const float *>(a.d_o) + base;
-    const int64_t col0 = t.first * 16 * G, j0w = col0 + 16 * wk, j = j0w + l16, jk = j < a.S ? j : a.S - 1;
+    const int64_t col0 = t.first * kT, j = col0 + l16, jk = j < a.S ? j : a.S - 1;
     const int it0 = (int)(col0 / kT), ntiles = (int)((a.S + kT - 1) / kT);
     const float c = a.scale * kLog2e;
-    LDS_AS unsigned char *ring = lds + grp * Shape::kGroup;
-    auto fill_q = [&](int buf, int it) { f32_fill<D, G>(ring + buf * Shape::kStage, q, a.ss, (int64_t)it * kT, a.S, wk, lane); };
-    auto fill_g = [&](int buf, int it) {
-        f32_fill<D, G>(ring + buf * Shape::kStage + Shape::kTile, g, a.ss, (int64_t)it * kT, a.S, wk, lane);
-    };
+    LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
+    const F32Fill<D, FAR> fill(a.ss, lane);
+    auto fill_q = [&](int it) { fill(ring, q, a.ss, (int64_t)it * kT, a.S, lane); };
+    auto fill_g = [&](int it) { fill(ring + Shape::kTile, g, a.ss, (int64_t)it * kT, a.S, lane); };
     auto load_stats = [&](int it, f32x4 &l, f32x4 &d) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {                 // rows past S: LSE = +inf makes their P exactly zero
@@ -404,37 +398,27 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
     };
     const F32Addr ad = f32_addr<D>(ring, l16, g4);
     f32x4 lse_n = kZero4, dl_n = kZero4;
-    if (it0 + grp < ntiles) {
-        fill_q(0, it0 + grp);
-        fill_g(0, it0 + grp);
-        load_stats(it0 + grp, lse_n, dl_n);
+    if (it0 + wave < ntiles) {
+        fill_q(it0 + wave);
+        fill_g(it0 + wave);
+        load_stats(it0 + wave, lse_n, dl_n);
     }
     f32x4 kr[D / 16], vr[D / 16], dk[D / 16], dv[D / 16];
     f32_load_row<D>(kr, static_cast<const float *>(a.k) + base + jk * a.ss, g4);
     f32_load_row<D>(vr, static_cast<const float *>(a.v) + base + jk * a.ss, g4);
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) dk[n] = dv[n] = kZero4;
-    const int diag = (int)(j0w / kT);                 // tiles before this one precede all of the wave's keys
-    for (int it = it0 + grp, n = 0; it0 + n * QS < ntiles; ++n, it += QS) {
-        wait_fills();
+        for (int it = it0 + wave; it < ntiles; it += QS) {
         const bool more = it + QS < ntiles;
+        wait_fills();
         const f32x4 lse = lse_n, dl = dl_n;
-        if constexpr (!Shape::kOwn) {
-            __syncthreads();      // tile `it` is complete; nobody still reads the other buffer
-            if (more) {
-                fill_q((n + 1) & 1, it + QS);
-                fill_g((n + 1) & 1, it + QS);
-            }
-        }
         if (more) load_stats(it + QS, lse_n, dl_n);
-        if (it < diag || it >= ntiles) continue;
-        const uint32_t at = Shape::kOwn ? 0u : (uint32_t)((n & 1) * Shape::kStage);
         f32x4 s = kZero4, dp;                         // queries 4*g4 + r x key l16
 #pragma unroll
         for (int r = 0; r < 4; ++r) dp[r] = -dl[r];
-        f32_two_scores<D>(s, dp, ad, at, kr, vr);
-        F32Outer<D, Shape::kTile> gp(ad, at);
-        if (it == diag) {         // query 4*g4 + r of the tile sees key l16 iff it is >= l16
+        f32_two_scores<D>(s, dp, ad, kr, vr);
+        F32Outer<D, Shape::kTile> gp(ad);
+        if (it == it0) {         // query 4*g4 + r of the tile sees key l16 iff it is >= l16
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (4 * g4 + r < l16) s[r] = -INFINITY;
@@ -446,25 +430,27 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
             ds[r] = p[r] * dp[r];
         }
         gp.run(dv, p);                                // dV^T += dO^T P
-        if constexpr (Shape::kOwn)
-            if (more) fill_g(0, it + QS);             // dO is used up
-        F32Outer<D, 0> qds(ad, at);
+        if (more) fill_g(it + QS);                    // dO is used up
+        F32Outer<D, 0> qds(ad);
         qds.run(dk, ds);                              // dK^T += Q^T dS
-        if constexpr (Shape::kOwn)
-            if (more) fill_q(0, it + QS);
+        if (more) fill_q(it + QS);
     }
-    f32_combine<D, G>(lds, dv, static_cast<float *>(a.dv) + base + jk * a.ss + 16 * g4, j < a.S, 1.f, wk, grp, lane);
-    f32_combine<D, G>(lds, dk, static_cast<float *>(a.dk) + base + jk * a.ss + 16 * g4, j < a.S, a.scale, wk, grp, lane);
+    f32_combine<D>(lds, dv, static_cast<float *>(a.dv) + base + jk * a.ss + 16 * g4, j < a.S, 1.f, wave, lane);
+    f32_combine<D>(lds, dk, static_cast<float *>(a.dk) + base + jk * a.ss + 16 * g4, j < a.S, a.scale, wave, lane);
 }
 
-// One launch for the gradients asked for: first the dkdv_blocks key-stationary workgroups, then the query-stationary ones.
-template <int D, int G>
-__global__ __launch_bounds__(512, (kBwdWavesPerSimd<D, G>)) void attn_bwd_f32_kernel(AttnArgs a, uint32_t dkdv_blocks)
+// One launch for the gradients asked for: first the dkdv_blocks key-stationary workgroups, then the query-stationary ones.  Longest
+// first, except where all of them are resident at once, two per unit (head dim 64): then a unit gets the key tile
+// of a rank and the query tile of the same rank, and the query tiles go shortest first to even that out
+// (S = 2000, H = 2: 66 us both longest first).
+template <int D, bool FAR>
+__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t dkdv_blocks)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D, G>::kRing];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D>::kRing];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    if (blockIdx.x < dkdv_blocks) f32_dkdv_rows<D, G>(a, lds, blockIdx.x);
-    else f32_dq_rows<D, G>(a, lds, blockIdx.x - dkdv_blocks);
+    const bool resident = D == 64 && gridDim.x <= 2 * kXcds * kChunk;
+    if (blockIdx.x < dkdv_blocks) f32_dkdv_rows<D, FAR>(a, lds, blockIdx.x);
+    else f32_dq_rows<D, FAR>(a, lds, blockIdx.x - dkdv_blocks, !resident);
 }
 
 // D_i = sum_c dO_ic O_ic.  16 lanes per row, 16 rows per 256-thread workgroup.
@@ -496,48 +482,31 @@ inline dim3 row_grid(const AttnArgs &a, int rows)
     return dim3((unsigned)((a.S + rows - 1) / rows), (unsigned)a.H, (unsigned)a.B);
 }
 
-template <int D, int G>
+template <int D, bool FAR>
 hipError_t launch_fwd_f32(const AttnArgs &a, hipStream_t st)
 {
-    const int64_t blocks = order_grid((a.S + 16 * G - 1) / (16 * G), (int64_t)a.H * a.B, kLongestFirst);
+    const int64_t blocks = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    attn_fwd_f32_kernel<D, G><<<dim3((unsigned)blocks), 64 * kF32Waves, 0, st>>>(a);
+    attn_fwd_f32_kernel<D, FAR><<<dim3((unsigned)blocks), 64 * kF32Waves, 0, st>>>(a);
     return hipGetLastError();
 }
 
 // dkdv, dq: which of the two to launch
-template <int D, int G>
+template <int D, bool FAR>
 hipError_t launch_bwd_f32(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 {
-    const int64_t n = order_grid((a.S + 16 * G - 1) / (16 * G), (int64_t)a.H * a.B, kLongestFirst);
+    const int64_t n = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst);
     if (2 * n > 0x7fffffffLL) return hipErrorInvalidValue;
-    attn_bwd_f32_kernel<D, G><<<dim3((unsigned)(n * (dkdv + dq))), 64 * kF32Waves, 0, st>>>(a, dkdv ? (uint32_t)n : 0u);
+    attn_bwd_f32_kernel<D, FAR><<<dim3((unsigned)(n * (dkdv + dq))), 64 * kF32Waves, 0, st>>>(a, dkdv ? (uint32_t)n : 0u);
     return hipGetLastError();
 }
-
-// Costs per 2^20 pairs as in the bf16 kernels (fitted to S = 300 .. 16000, 1 to 8 heads): {head dim 64, head dim 128} x {16, 32 rows}.
-// 16-row workgroups fill the chip first, 32-row ones run 5 to 25 % faster per pair once it is full.
-constexpr TileChoice kF32Fwd[2][2] = {
-    {{16, kLongestFirst, 835.0, 4.0}, {32, kLongestFirst, 664.0, 4.0}},
-    {{16, kLongestFirst, 1400.0, 5.0}, {32, kLongestFirst, 1264.0, 5.0}},
-};
-constexpr TileChoice kF32Dkdv[2][2] = {
-    {{16, kLongestFirst, 1445.0, 0.0}, {32, kLongestFirst, 1233.0, 0.0}},
-    {{16, kLongestFirst, 2563.0, 0.0}, {32, kLongestFirst, 2338.0, 0.0}},
-};
-constexpr TileChoice kF32Dq[2][2] = {
-    {{16, kLongestFirst, 1084.0, 0.0}, {32, kLongestFirst, 925.0, 0.0}},
-    {{16, kLongestFirst, 1922.0, 0.0}, {32, kLongestFirst, 1753.0, 0.0}},
-};
 
 }  // namespace
 
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, hipStream_t st)
 {
-    const bool wide = a.d == 128;
-    const bool small = cheapest_tiles(kF32Fwd[wide], a.S, (int64_t)a.H * a.B) == 0;
-    if (wide) return small ? launch_fwd_f32<128, 1>(a, st) : launch_fwd_f32<128, 2>(a, st);
-    return small ? launch_fwd_f32<64, 1>(a, st) : launch_fwd_f32<64, 2>(a, st);
+    if (a.ss >= kFarStride) return a.d == 128 ? launch_fwd_f32<128, true>(a, st) : launch_fwd_f32<64, true>(a, st);
+    return a.d == 128 ? launch_fwd_f32<128, false>(a, st) : launch_fwd_f32<64, false>(a, st);
 }
 
 hipError_t launch_attn_delta(const AttnArgs &a, bool is_bf16, hipStream_t st)
@@ -559,12 +528,9 @@ hipError_t launch_attn_delta(const AttnArgs &a, bool is_bf16, hipStream_t st)
 
 hipError_t launch_attn_bwd_f32(const AttnArgs &a, hipStream_t st)
 {
-    const bool wide = a.d == 128;
-    const int64_t hb = (int64_t)a.H * a.B;
-    const bool small = both_us(kF32Dkdv[wide][0], kF32Dq[wide][0], a.S, hb) < both_us(kF32Dkdv[wide][1], kF32Dq[wide][1], a.S, hb);
     auto launch = [&](bool dkdv, bool dq) {
-        if (wide) return small ? launch_bwd_f32<128, 1>(a, dkdv, dq, st) : launch_bwd_f32<128, 2>(a, dkdv, dq, st);
-        return small ? launch_bwd_f32<64, 1>(a, dkdv, dq, st) : launch_bwd_f32<64, 2>(a, dkdv, dq, st);
+        if (a.ss >= kFarStride) return a.d == 128 ? launch_bwd_f32<128, true>(a, dkdv, dq, st) : launch_bwd_f32<64, true>(a, dkdv, dq, st);
+        return a.d == 128 ? launch_bwd_f32<128, false>(a, dkdv, dq, st) : launch_bwd_f32<64, false>(a, dkdv, dq, st);
     };
     hipError_t e = record_stage(a, 0, st);
     if (e != hipSuccess) return e;

@@ -28,7 +28,7 @@ inline hipError_t record_stage(const AttnArgs &a, int idx, hipStream_t st)
     return a.stage_events ? hipEventRecord(a.stage_events[idx], st) : hipSuccess;
 }
 
-// fp32 path (VALU arithmetic, fp32 throughout), d in {64, 128}
+// fp32 path (fp32 matrix instructions, fp32 throughout), d in {64, 128}
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, hipStream_t st);
 hipError_t launch_attn_bwd_f32(const AttnArgs &a, hipStream_t st);
 

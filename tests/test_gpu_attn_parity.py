@@ -252,3 +252,22 @@ def test_bf16_is_deterministic():
     b = gpu_fwd_bwd(q, k, v, g, synth.default_scale(d))
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_rows_far_apart(d):
+    # rows 2^26 floats apart take the fills with full addresses: the same bits as a contiguous copy
+    S, ss = 19, 1 << 26
+    scale = synth.default_scale(d)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(1, S, 1, d, "f32", seed=77))
+    o, lse = mb.memo_attn_fwd(q, k, v, scale)
+    grads = mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+    buf = torch.zeros((S - 1) * ss + 8 * d, dtype=torch.float32, device="cuda")
+    far = [torch.as_strided(buf, (1, S, 1, d), (S * ss, ss, d, 1), n * d) for n in range(8)]
+    for dst, src in zip(far, (q, k, v, g)):
+        dst.copy_(src)
+    _, lse_far = mb.memo_attn_fwd(far[0], far[1], far[2], scale, o=far[4])
+    mb.memo_attn_bwd(far[0], far[1], far[2], far[4], lse_far, far[3], scale, dq=far[5], dk=far[6], dv=far[7])
+    assert torch.equal(far[4], o) and torch.equal(lse_far, lse)
+    for got, ref in zip(far[5:], grads):
+        assert torch.equal(got, ref)
