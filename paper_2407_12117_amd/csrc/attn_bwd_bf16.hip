@@ -555,6 +555,293 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, 
     else dq_rows<QG, T>(a, lds, blockIdx.x - dkdv_blocks, kLongestFirst);
 }
 
+// ============================================================================ backward, 32-row workgroups
+// For short sequences: 32 keys (or query rows) per workgroup, the other side of the sweep in eight.  Every wave works all 32
+// rows against 32-row tiles of its own, one buffer each, so there is no barrier in the sweep; a half of the buffer
+// is refilled as soon as it is used up.  The sums meet in LDS at the end.  Twice the fill traffic of 64-row workgroups, and
+// sweeps of half the steps: ahead where the longest sweep, not the work, is what a launch takes (own_us below).  us, 64-row
+// workgroups -> these: S = 1000 H = 4 20.5 -> 15.4, S = 1500 H = 4 26.4 -> 22.5, S = 2500 H = 2 37.6 -> 25.1, S = 640 H = 2
+// 16.1 -> 15.3; but S = 2000, 6 heads 36.2 -> 45.9, S = 8192 H = 4 227 -> 259.
+constexpr int kOwnTile = 32 * 256, kOwnRing = 8 * 2 * kOwnTile;
+
+// piece of every wave -> its sum in the wave that owns the piece (two of sixteen): out(e, sum)
+template <typename Out>
+__device__ __forceinline__ void sum_over_waves(LDS_AS unsigned char *lds, const f32x4 (&acc)[8][2], int wave, int lane, Out &&out)
+{
+    LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+    __syncthreads();              // every wave has left what lies there
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) pieces[(wave * 16 + 8 * b + dt) * 64 + lane] = acc[dt][b];
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < 2; ++n) out(2 * wave + n, sum_pieces<8, 1>(pieces, 0, 2 * wave + n, lane));
+}
+
+__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
+{
+    // lds: [wave][Q|dO] tiles, then the K and V rows
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nit = (int)((a.S + 31) / 32);
+    const PairId t = decode_block(a, id, nit, kLongestFirst, false);
+    const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
+    const __bf16 *q = static_cast<const __bf16 *>(a.q) + base, *g = static_cast<const __bf16 *>(a.d_o) + base;
+    const float *lse = a.lse + ((int64_t)t.b * a.H + t.h) * a.S, *dlt = a.delta + ((int64_t)t.b * a.H + t.h) * a.S;
+    const float c = a.scale * kLog2e, neg_inv_scale = -1.f / a.scale;
+    const int it0 = (int)t.first;                     // key tile and first query tile: the diagonal
+    LDS_AS unsigned char *ring = lds + wave * 2 * kOwnTile;
+    const TileOffsets<8, 32> koff = make_tile_offsets<8, SwzB, 32>(a.ss, wave, lane);
+    koff.fill(lds + kOwnRing, static_cast<const __bf16 *>(a.k) + base, a.ss, (int64_t)it0 * 32, a.S, wave);
+    koff.fill(lds + kOwnRing + kOwnTile, static_cast<const __bf16 *>(a.v) + base, a.ss, (int64_t)it0 * 32, a.S, wave);
+    const OwnTileFill fill(a.ss, lane);
+    // a tile past the last one is an empty buffer: its fills are still counted by the waits
+    auto fill_q = [&](int it) { fill(ring, q, a.ss, (int64_t)it * 32, it < nit ? a.S : (int64_t)it * 32); };
+    auto fill_g = [&](int it) { fill(ring + kOwnTile, g, a.ss, (int64_t)it * 32, it < nit ? a.S : (int64_t)it * 32); };
+    // row statistics: one value per lane, spread by a 4x4x1 MFMA (see dkdv_rows)
+    const int stat_lane = 4 * g4 + (lane & 3);
+    float raw_l[2], raw_d[2];
+    auto load_stats = [&](int it) {
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            const int64_t row = (int64_t)it * 32 + 16 * qt + stat_lane;
+            raw_l[qt] = row < a.S ? lse[row] : INFINITY;
+            raw_d[qt] = row < a.S ? dlt[row] : 0.f;
+        }
+    };
+    int it = it0 + wave;
+    load_stats(min(it, nit - 1));
+    fill_q(it);
+    fill_g(it);
+    const LdsAddr16 ad = make_lds_addr16(ring, lane);
+    const uint32_t kv_base = (uint32_t)(kOwnRing - wave * 2 * kOwnTile);
+    f32x4 accV[8][2], accK[8][2];                     // dV^T, dK^T: [head-dim block][key block]; lane = key
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) accV[dt][kt] = accK[dt][kt] = kZero4;
+    wait_fills_but<16>();
+    __builtin_amdgcn_s_barrier();                     // the K and V rows are complete
+    asm volatile("" ::: "memory");
+
+    // S before dP, dK before dV: Q is needed first and used up first, dO half a step later, so that the fill of either
+    // half of the buffer has the work on the other one to hide under
+#pragma clang loop unroll(disable)
+    for (; it < nit; it += 8) {
+        f32x4 nl[2], nd[2];       // -LSE_i/scale and -D_i
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            nl[qt] = __builtin_amdgcn_mfma_f32_4x4x1f32(raw_l[qt], neg_inv_scale, kZero4, 0, 0, 0);
+            nd[qt] = __builtin_amdgcn_mfma_f32_4x4x1f32(raw_d[qt], -1.f, kZero4, 0, 0, 0);
+        }
+        f32x4 s[2][2], dp[2][2];                      // [query block][key block]; register r = query 16*qt + 4*g4 + r
+        {
+            // item n = k step n: the Q (dO) rows of both query blocks and the K (V) rows of both key blocks
+            auto contract = [&](auto whichc, f32x4 (&x)[2][2], const f32x4 (&init)[2]) {
+                constexpr int off = decltype(whichc)::value * kOwnTile;
+                QuadSlot slots[2];
+                auto issue = [&](auto n, QuadSlot &slot) {
+                    lds_issue_b128<off>(slot.a0, ad.row16[decltype(n)::value]);
+                    lds_issue_b128<off + 4096>(slot.a1, ad.row16[decltype(n)::value]);
+                    lds_issue_b128<off>(slot.b0, ad.row16[decltype(n)::value] + kv_base);
+                    lds_issue_b128<off + 4096>(slot.b1, ad.row16[decltype(n)::value] + kv_base);
+                };
+                lds_pipeline_prologue<4, 1, 4>(slots, issue);
+                lds_pipeline_body<4, 1, 4>(slots, issue, [&](auto n, QuadSlot &slot) {
+                    constexpr int kk = decltype(n)::value;
+                    x[0][0] = mfma16(slot.a0, slot.b0, kk == 0 ? init[0] : x[0][0]);
+                    x[0][1] = mfma16(slot.a0, slot.b1, kk == 0 ? init[0] : x[0][1]);
+                    x[1][0] = mfma16(slot.a1, slot.b0, kk == 0 ? init[1] : x[1][0]);
+                    x[1][1] = mfma16(slot.a1, slot.b1, kk == 0 ? init[1] : x[1][1]);
+                });
+            };
+            wait_fills_but<8>();  // Q has landed; dO, queued behind it, may still be on its way
+            contract(IntC<0>{}, s, nl);
+            wait_fills();
+            if (it + 8 < nit) load_stats(it + 8);
+            contract(IntC<1>{}, dp, nd);
+        }
+        TrSlot tring[3];
+        auto t_issue = [&](auto n, TrSlot &slot) {
+            constexpr int dt = decltype(n)::value % 8;
+            lds_issue_tr_pair<(decltype(n)::value < 8 ? 0 : kOwnTile)>(slot, ad.tr16[dt]);
+        };
+        lds_pipeline_prologue<16, 2, 2>(tring, t_issue);
+        if (it == it0) {          // the causal mask: query 16qt + 4g4 + r sees key 16kt + l16 iff it is not before it
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (r < 16 * kt + l16 - (16 * qt + 4 * g4)) s[qt][kt][r] = -INFINITY;
+        }
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float p = __builtin_amdgcn_exp2f(s[qt][kt][r] * c);   // s already holds S - LSE_i/scale
+                    s[qt][kt][r] = p;
+                    dp[qt][kt][r] = p * dp[qt][kt][r];                          // dp already holds dP - D_i
+                }
+        bf16x8 pB[2], dsB[2];
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+            pB[kt] = pack44(s[0][kt], s[1][kt]);
+            dsB[kt] = pack44(dp[0][kt], dp[1][kt]);
+        }
+        lds_pipeline_body<16, 2, 2>(tring, t_issue, [&](auto n, TrSlot &slot) {
+            constexpr int dt = decltype(n)::value % 8;
+            if constexpr (decltype(n)::value == 8) fill_q(it + 8);    // Q is used up
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                if constexpr (decltype(n)::value < 8) accK[dt][kt] = mfma16(tr_operand(slot), dsB[kt], accK[dt][kt]);
+                else accV[dt][kt] = mfma16(tr_operand(slot), pB[kt], accV[dt][kt]);
+            }
+        });
+        fill_g(it + 8);
+    }
+    wait_fills();                 // the empty ones too: they write LDS
+
+    const int64_t j0 = (int64_t)it0 * 32 + l16;
+    __bf16 *dv = static_cast<__bf16 *>(a.dv) + base + j0 * a.ss + 4 * g4;
+    __bf16 *dk = static_cast<__bf16 *>(a.dk) + base + j0 * a.ss + 4 * g4;
+    auto store = [&](__bf16 *out, float mul) {
+        return [=, &a](int e, const f32x4 &sum) {
+            const int kt = e >> 3, dt = e & 7;
+            if (j0 + 16 * kt < a.S) store4(out + 16 * kt * a.ss + 16 * dt, sum, mul);
+        };
+    };
+    sum_over_waves(lds, accV, wave, lane, store(dv, 1.f));
+    sum_over_waves(lds, accK, wave, lane, store(dk, a.scale));
+}
+
+__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
+{
+    // lds: [wave][K|V] tiles
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const PairId t = decode_block(a, id, (a.S + 31) / 32, kLongestFirst, true);
+    const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
+    const __bf16 *q = static_cast<const __bf16 *>(a.q) + base, *g = static_cast<const __bf16 *>(a.d_o) + base;
+    const __bf16 *k = static_cast<const __bf16 *>(a.k) + base, *v = static_cast<const __bf16 *>(a.v) + base;
+    const int64_t stat = ((int64_t)t.b * a.H + t.h) * a.S;
+    const float c = a.scale * kLog2e;
+    const int ntiles = (int)t.first + 1;              // the last one is the diagonal
+    const int64_t i0 = t.first * 32 + l16;
+    LDS_AS unsigned char *ring = lds + wave * 2 * kOwnTile;
+    const OwnTileFill fill(a.ss, lane);
+    // a tile past the last one is an empty buffer: its fills are still counted by the waits
+    auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * 32, jt < ntiles ? a.S : (int64_t)jt * 32); };
+    auto fill_v = [&](int jt) { fill(ring + kOwnTile, v, a.ss, (int64_t)jt * 32, jt < ntiles ? a.S : (int64_t)jt * 32); };
+    fill_v(wave);
+    fill_k(wave);
+    const LdsAddr16 ad = make_lds_addr16(ring, lane);
+    // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
+    bf16x8 qB[2][4], gB[2][4];
+    float lse2[2];
+    f32x4 neg_d[2];
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        const int64_t i = i0 + 16 * qt < a.S ? i0 + 16 * qt : a.S - 1;          // rows past S are computed and never stored
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            qB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + i * a.ss + 32 * kk + 8 * g4));
+            gB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(g + i * a.ss + 32 * kk + 8 * g4));
+        }
+        lse2[qt] = a.lse[stat + i] * kLog2e;
+        const float nd = -a.delta[stat + i];
+        neg_d[qt] = f32x4{nd, nd, nd, nd};
+    }
+    f32x4 accQ[8][2];             // dQ^T: [head-dim block of 16][query block]; lane = query, rows = head dim
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) accQ[dt][qt] = kZero4;
+
+#pragma clang loop unroll(disable)
+    for (int jt = wave; jt < ntiles; jt += 8) {
+        // dP before S: V is needed first and used up first, K follows
+        f32x4 s[2][2], dp[2][2];                      // [key block][query block]
+        {
+            // item n = (k step n/2, key block n%2): one row operand, two MFMAs
+            auto contract = [&](auto offc, f32x4 (&x)[2][2], const bf16x8 (&b)[2][4], const f32x4 (&init)[2]) {
+                bf16x8 slots[3];
+                auto issue = [&](auto n, bf16x8 &slot) {
+                    lds_issue_b128<(decltype(n)::value % 2) * 4096 + decltype(offc)::value>(slot, ad.row16[decltype(n)::value / 2]);
+                };
+                lds_pipeline_prologue<8, 2, 1>(slots, issue);
+                lds_pipeline_body<8, 2, 1>(slots, issue, [&](auto n, bf16x8 &slot) {
+                    constexpr int kk = decltype(n)::value / 2, kt = decltype(n)::value % 2;
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt) x[kt][qt] = mfma16(slot, b[qt][kk], kk == 0 ? init[qt] : x[kt][qt]);
+                });
+            };
+            const f32x4 zeros[2] = {kZero4, kZero4};
+            wait_fills_but<8>();
+            contract(IntC<kOwnTile>{}, dp, gB, neg_d);
+            fill_v(jt + 8);
+            wait_fills_but<8>();
+            contract(IntC<0>{}, s, qB, zeros);
+        }
+        TrSlot kring[3];
+        auto k_issue = [&](auto n, TrSlot &slot) { lds_issue_tr_pair<0>(slot, ad.tr16[decltype(n)::value]); };
+        lds_pipeline_prologue<8, 2, 2>(kring, k_issue);
+        if (jt == ntiles - 1) {
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (r > 16 * qt + l16 - (16 * kt + 4 * g4)) s[kt][qt][r] = -INFINITY;
+        }
+        bf16x8 dsB[2];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[kt][qt][r], c, -lse2[qt]));
+                    s[kt][qt][r] = p * dp[kt][qt][r];               // dS (dp already holds dP - D_i)
+                }
+            dsB[qt] = pack44(s[0][qt], s[1][qt]);
+        }
+        lds_pipeline_body<8, 2, 2>(kring, k_issue, [&](auto n, TrSlot &slot) {
+            constexpr int dt = decltype(n)::value;
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) accQ[dt][qt] = mfma16(tr_operand(slot), dsB[qt], accQ[dt][qt]);
+        });
+        fill_k(jt + 8);
+    }
+    wait_fills();                 // the empty ones too: they write LDS
+    __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + i0 * a.ss + 4 * g4;
+    sum_over_waves(lds, accQ, wave, lane, [=, &a](int e, const f32x4 &sum) {
+        const int qt = e >> 3, dt = e & 7;
+        if (i0 + 16 * qt < a.S) store4(dq + 16 * qt * a.ss + 16 * dt, sum, a.scale);
+    });
+}
+
+__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    if (blockIdx.x < dkdv_blocks) dkdv_own_rows(a, lds, blockIdx.x);
+    else dq_own_rows(a, lds, blockIdx.x - dkdv_blocks);
+}
+
+hipError_t launch_bwd_own(const AttnArgs &a, hipStream_t st)
+{
+    const int64_t n = order_grid((a.S + 31) / 32, (int64_t)a.H * a.B, kLongestFirst);
+    if (2 * n > 0x7fffffffLL) return hipErrorInvalidValue;
+    attn_bwd_own_bf16_kernel<<<dim3((unsigned)(2 * n)), 512, 0, st>>>(a, (uint32_t)n);
+    return hipGetLastError();
+}
+
 template <int KG>
 hipError_t launch_dkdv(const AttnArgs &a, int order, hipStream_t st)
 {
@@ -595,7 +882,16 @@ constexpr TileChoice kDqChoices[] = {
     {256, kFolded, 146.0, 4.0}, {256, kLongestFirst, 149.0, 8.0}, {128, kLongestFirst, 156.0, 8.0}, {64, kLongestFirst, 181.0, 6.5},
 };
 
-// D_i preprocess, then dK, dV and dQ: in one launch of 64-, 128- or 256-row workgroups, or, where whole rounds
+// A launch of 32-row workgroups: no shorter than its longest key tile, nor than all work spread over the chip with the start and
+// the end of every workgroup (4.5 us); fitted to S = 250 .. 8192, 1 to 6 heads (within 10 %).
+static double own_us(int64_t S, int64_t heads)
+{
+    const double per_row = (double)S / (1 << 20), items = 2.0 * ((S + 31) / 32) * heads;
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
+    return std::max(0.87 * 32 * per_row * 232.0, mean * 450.0 + 4.5 * items / (kXcds * kChunk)) + 10.0;
+}
+
+// D_i preprocess, then dK, dV and dQ: in one launch of 32-, 64-, 128- or 256-row workgroups, or, where whole rounds
 // of folded pairs are cheaper (or events between the stages are asked for), the key-stationary kernel and
 // then the query-stationary one.  The single launch fills the chip where neither kernel does alone (S = 2000, 6
 // heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups, 207 as two launches of 256-row pairs) and lets the dQ
@@ -620,7 +916,9 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
                 rows = kDkdvChoices[n].rows;
             }
         }
+        if (own_us(a.S, hb) < best) rows = 32;
         switch (rows) {
+        case 32: return launch_bwd_own(a, st);
         case 64: return launch_both<2, 2, 32>(a, st);
         case 128: return launch_both<4, 4, 64>(a, st);
         case 256: return launch_both<8, 8, 64>(a, st);

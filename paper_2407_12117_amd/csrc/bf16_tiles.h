@@ -318,6 +318,30 @@ __device__ __forceinline__ TileOffsets<NW, ROWS> make_tile_offsets(int64_t ss, i
     return f;
 }
 
+// Fill of a 32-row SwzB tile by one wave (eight instructions) from two registers: a lane's row and chunk in the first four rows
+// never change, the next instruction is four rows on and, the swizzle being linear in the bits of the row, one XOR away.
+// The tile is a buffer as in TileOffsets::fill.
+struct OwnTileFill {
+    uint32_t row_off, chunk_off;
+    __device__ __forceinline__ OwnTileFill(int64_t ss, int lane)
+    {
+        row_off = (uint32_t)(lane >> 4) * (uint32_t)ss * 2;
+        chunk_off = (uint32_t)((lane & 15) ^ SwzB::f(lane >> 4)) * 16;
+    }
+    __device__ __forceinline__ void operator()(LDS_AS unsigned char *tile, const __bf16 *src, int64_t ss, int64_t r0, int64_t end) const
+    {
+#ifdef __HIP_DEVICE_COMPILE__      // the host pass does not know the 16-byte form of the builtin
+        const int rows = (int)max((int64_t)0, min((int64_t)32, end - r0));
+        const uint32_t bytes = rows > 0 ? (uint32_t)(rows - 1) * (uint32_t)ss * 2 + 256 : 0;
+        const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(src + r0 * ss), 0, bytes, 0x00020000);
+#pragma unroll
+        for (int n = 0; n < 8; ++n)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (LDS_AS void *)(tile + n * 1024), 16,
+                                                     row_off + (chunk_off ^ (uint32_t)(SwzB::f(4 * n) * 16)) + (uint32_t)(4 * n) * (uint32_t)ss * 2, 0, 0, 0);
+#endif
+    }
+};
+
 // instruction n of the fill of the full tile whose first row is at `tile_base`
 template <int NW, int ROWS>
 __device__ __forceinline__ void fill_full_tile_part(LDS_AS unsigned char *tile, const TileOffsets<NW, ROWS> &f, int n,

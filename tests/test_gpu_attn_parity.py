@@ -106,6 +106,12 @@ def test_bf16_forward_64_row_edges(oracle, S):
     _dense_case(oracle, 1, S, 48, 128, "bf16", 9000 + S, scaled=True)
 
 
+@pytest.mark.parametrize("S", [31, 32, 33, 257, 1000])
+def test_bf16_backward_32_row_edges(oracle, S):
+    # the 32-row backward: one tile and its neighbours, waves without a tile, a ragged last tile behind a whole sweep
+    _dense_case(oracle, 1, S, 3, 128, "bf16", 9100 + S)
+
+
 def test_bf16_scale_below_the_usual_one(oracle):
     _dense_case(oracle, 1, 500, 2, 128, "bf16", 41, scale=0.06)
 
