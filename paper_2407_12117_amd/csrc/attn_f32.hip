@@ -33,6 +33,7 @@ namespace {
 constexpr int kF32Waves = 8, kT = 16;                 // waves per workgroup; rows of a streamed tile
 constexpr f32x4 kZero4 = {0.f, 0.f, 0.f, 0.f};
 constexpr float kF32RescaleAbove = 1099511627776.f;   // 2^40, as in the bf16 forward
+constexpr float kLowest = -3.402823466e38f;           // the lowest finite fp32
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
 {
@@ -115,6 +116,14 @@ __device__ __forceinline__ void lds_wait(F32Pair &p)
     asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(p.x), "+v"(p.y) : "n"(N));
 }
 
+// exp(scale s - lse), the probability of a raw score.  The product is rounded before the subtraction, as the forward rounds it
+// for its logsumexp: inside an fma the exact product of a score of 1e20 (a masked key) is 1e12 away from that logsumexp.
+__device__ __forceinline__ float f32_prob(float s, float scale, float lse)
+{
+#pragma clang fp contract(off)
+    return __builtin_amdgcn_exp2f((s * scale - lse) * kLog2e);
+}
+
 template <int D>
 __device__ __forceinline__ void f32_load_row(f32x4 (&dst)[D / 16], const float *row, int g4)
 {
@@ -187,7 +196,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     using Shape = F32Shape<D>;
     constexpr int KS = kF32Waves, NP = Shape::kPieces;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[Shape::kRing + kF32Waves * 16 * 8];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, then (c m, sum) per wave and row
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, then (maximum, sum) per wave and row
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const PairId t = decode_block(a, blockIdx.x, (a.S + kT - 1) / kT, kLongestFirst, true);
@@ -209,7 +218,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     f32_load_row<D>(q, static_cast<const float *>(a.q) + base + (i < a.S ? i : a.S - 1) * a.ss, g4);
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) acc[n] = kZero4;
-    float mc = -INFINITY, lsum = 0.f;                 // running maximum (times c) and sum of this lane's keys
+    float m = -INFINITY, lsum = 0.f;                  // running maximum and sum of this lane's keys
 
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
@@ -243,20 +252,22 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
             for (int r = 0; r < 4; ++r)
                 if (4 * g4 + r > l16) s[r] = -INFINITY;
         }
-        // against the running maximum as it stands: it only has to keep the exponentials in range (as in the bf16 forward)
+        // against the running maximum as it stands: it only has to keep the exponentials in range (as in the bf16 forward).
+        // The difference comes before the scale: exact for the maximum itself, however large (a row of masked keys only)
         f32x4 p;
         auto exponentials = [&]() {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -mc));
+            for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f((s[r] - m) * c);
         };
         exponentials();
         if (__builtin_amdgcn_ballot_w64(!(p[0] + p[1] + p[2] + p[3] <= kF32RescaleAbove)) != 0) {
-            float m = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c;
-            m = fmaxf(m, __shfl_xor(m, 16));
-            m = fmaxf(m, __shfl_xor(m, 32));
-            const float m_new = fmaxf(mc, m);         // finite: key 0 of a processed tile is visible to every row
-            const float corr = __builtin_amdgcn_exp2f(mc - m_new);
-            mc = m_new;
+            float mt = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+            mt = fmaxf(mt, __shfl_xor(mt, 16));
+            mt = fmaxf(mt, __shfl_xor(mt, 32));
+            // finite also where a row sees nothing but scores of -inf in the tile: they weigh zero then
+            const float m_new = fmaxf(fmaxf(m, mt), kLowest);
+            const float corr = __builtin_amdgcn_exp2f((m - m_new) * c);
+            m = m_new;
             lsum *= corr;
 #pragma unroll
             for (int e = 0; e < D / 16; ++e) acc[e] *= corr;
@@ -274,7 +285,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     __syncthreads();              // every wave has left the last LDS buffer
 #pragma unroll
     for (int p = 0; p < NP; ++p) pieces[(wave * NP + p) * 64 + lane] = f32_piece<D>(acc, p);
-    if (g4 == 0) stats[wave * 16 + l16] = f32x2{mc, lsum};
+    if (g4 == 0) stats[wave * 16 + l16] = f32x2{m, lsum};
     __syncthreads();
     float top = -INFINITY, total = 0.f, weight[KS];
     f32x2 st[KS];
@@ -285,7 +296,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     }
 #pragma unroll
     for (int g = 0; g < KS; ++g) {
-        weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);       // a group without a tile: m = -inf, weight zero
+        weight[g] = __builtin_amdgcn_exp2f((st[g][0] - top) * c); // a group without a tile: m = -inf, weight zero
         total += weight[g] * st[g][1];
     }
     if (i >= a.S) return;
@@ -297,7 +308,10 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
         for (int g = 0; g < KS; ++g) sum += weight[g] * pieces[(g * NP + p) * 64 + lane];
         *reinterpret_cast<f32x4 *>(o + 64 * (p >> 2) + 4 * (p & 3)) = sum * inv;
     }
-    if (wave == 0 && g4 == 0) a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
+    if (wave == 0 && g4 == 0) {
+#pragma clang fp contract(off)    // the rounded product, as in f32_prob
+        a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = top * a.scale + __builtin_amdgcn_logf(total) * kLn2;
+    }
 }
 
 // Adds up the accumulators of the eight waves and writes mul times them: out points at the lane's row.
@@ -333,7 +347,6 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     const float *k = static_cast<const float *>(a.k) + base, *v = static_cast<const float *>(a.v) + base;
     const int64_t row0 = t.first * kT, i = row0 + l16, iq = i < a.S ? i : a.S - 1;
     const int ntiles = (int)((min(row0 + kT, a.S) - 1) / kT) + 1;
-    const float c = a.scale * kLog2e;
     LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
@@ -346,7 +359,7 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     f32x4 q[D / 16], go[D / 16], acc[D / 16];
     f32_load_row<D>(q, static_cast<const float *>(a.q) + base + iq * a.ss, g4);
     f32_load_row<D>(go, static_cast<const float *>(a.d_o) + base + iq * a.ss, g4);
-    const float lse2 = a.lse[stat + iq] * kLog2e, nd = -a.delta[stat + iq];
+    const float lse = a.lse[stat + iq], nd = -a.delta[stat + iq];
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) acc[n] = kZero4;
     for (int jt = wave; jt < ntiles; jt += KS) {
@@ -363,7 +376,7 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
         }
         f32x4 ds;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ds[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse2)) * dp[r];
+        for (int r = 0; r < 4; ++r) ds[r] = f32_prob(s[r], a.scale, lse) * dp[r];
         kds.run(acc, ds);                             // dQ^T += K^T dS^T
         if (more) fill_k(jt + KS);
     }
@@ -383,7 +396,6 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
     const float *q = static_cast<const float *>(a.q) + base, *g = static_cast<const float *>(a.d_o) + base;
     const int64_t col0 = t.first * kT, j = col0 + l16, jk = j < a.S ? j : a.S - 1;
     const int it0 = (int)(col0 / kT), ntiles = (int)((a.S + kT - 1) / kT);
-    const float c = a.scale * kLog2e;
     LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_q = [&](int it) { fill(ring, q, a.ss, (int64_t)it * kT, a.S, lane); };
@@ -426,7 +438,7 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
         f32x4 p, ds;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lse[r] * kLog2e));
+            p[r] = f32_prob(s[r], a.scale, lse[r]);
             ds[r] = p[r] * dp[r];
         }
         gp.run(dv, p);                                // dV^T += dO^T P

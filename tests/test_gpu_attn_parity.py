@@ -277,3 +277,65 @@ def test_fp32_rows_far_apart(d):
     assert torch.equal(far[4], o) and torch.equal(lse_far, lse)
     for got, ref in zip(far[5:], grads):
         assert torch.equal(got, ref)
+
+
+def _key_mask_case(oracle, S, H, d, dtype, value, tile, scaled=False):
+    # a key mask carried in a head-dim column: q is 1 there, k is `value` at the masked keys and 0 elsewhere.  Head h masks
+    # the h-th tile of `tile` keys (past tile 0, so that every row keeps some key), modulo the tiles there are: every wave
+    # of every workgroup shape gets a first tile of which a row sees nothing else
+    print(f"[case] key mask {value} S={S} H={H} d={d} {dtype} tile={tile}", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = synth.attn_inputs(1, S, H, d, dtype, 40 + S)
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    for h in range(H):
+        first = tile * (1 + h % ((S - 1) // tile))
+        k[:, first:first + tile, h, 0] = value
+    got = gpu_fwd_bwd(*(t.cuda() for t in (q, k, v, g)), scale)
+    qf, kf, vf, gf = (to_f64(t) for t in (q, k, v, g))
+    ref = oracle.attn_fwd(qf, kf, vf, scale) + tuple(oracle.attn_bwd(qf, kf, vf, gf, scale))
+    for name, x, r in zip(("O", "LSE", "dQ", "dK", "dV"), got, ref):
+        x = to_f64(x)
+        if name == "dQ":          # its mask column is zero times an infinity
+            x, r = x[..., 1:], r[..., 1:]
+        if name == "LSE":
+            assert np.abs(x - r).max() <= LSE_MAX_ABS_BF16
+        else:
+            assert_close(name, x, r, dtype, scaled and name != "O")
+
+
+# S is a whole number of tiles, masks from "never" to values whose products with the scale lose whole powers of two to rounding
+@pytest.mark.parametrize("value", [-math.inf, float(np.finfo(np.float32).min), -1e20, -1e9])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_masked_first_tiles(oracle, d, value):
+    _key_mask_case(oracle, 288, 9, d, "f32", value, 16)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_rows_without_a_key(oracle, d):
+    # the first 20 keys masked: rows 0 .. 19 see nothing.  -inf: those rows are NaN, the others as if the keys were not there;
+    # a finite mask leaves a uniform softmax over them, and a zero dO keeps them out of the gradients
+    S, H, dead = 150, 2, 20
+    print(f"[case] fp32 rows without a key d={d}", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = synth.attn_inputs(1, S, H, d, "f32", 77)
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    g[:, :dead] = 0.0
+    for value in (-math.inf, float(np.finfo(np.float32).min), -1e20):
+        k[:, :dead, :, 0] = value
+        qd, kd, vd, gd = (t.cuda() for t in (q, k, v, g))
+        o, lse = mb.memo_attn_fwd(qd, kd, vd, scale)
+        live = [to_f64(t[:, dead:]) for t in (q, k, v, g)]
+        ro, rlse = oracle.attn_fwd(*live[:3], scale)
+        assert_close("O", to_f64(o[:, dead:]), ro, "f32")
+        assert np.abs(to_f64(lse[:, :, dead:]) - rlse).max() <= 1e-4
+        if value == -math.inf:
+            assert torch.isnan(o[:, :dead]).all() and torch.isneginf(lse[:, :, :dead]).all()
+            continue
+        assert torch.isfinite(o[:, :dead]).all()
+        dq, dk, dv = mb.memo_attn_bwd(qd, kd, vd, o, lse, gd, scale)
+        rdq, rdk, rdv = oracle.attn_bwd(*live, scale)
+        assert_close("dQ", to_f64(dq[:, dead:, :, 1:]), rdq[..., 1:], "f32")
+        assert_close("dK", to_f64(dk[:, dead:]), rdk, "f32")
+        assert_close("dV", to_f64(dv[:, dead:]), rdv, "f32")
+        for name, x in (("dQ", dq[..., 1:]), ("dK", dk), ("dV", dv)):
+            assert (x[:, :dead] == 0).all(), f"{name}: a row without a key is touched by its zero dO"
