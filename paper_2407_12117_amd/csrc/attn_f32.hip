@@ -54,7 +54,7 @@ template <int D> constexpr int kWavesPerSimd = D == 64 ? 4 : 2;
 // Fill of the 16-row tile at rows r0..  The tile is a buffer that ends with row S - 1: rows past it are
 // out of range and read as zero (every consumer masks them).  A lane's offset within an instruction's rows never
 // changes; the next instruction is kRows rows on and, the swizzle being linear in the bits of the row, one XOR away.
-// (With a 64-bit address and a clamped row per instruction: S = 3000 d = 128 H = 4 forward 114 us, now 96.)
+// (With a 64-bit address and a clamped row per instruction: S = 3000 d = 128 H = 4 forward 114 us, 96 without.)
 // FAR: rows so far apart (2^26 floats) that 16 of them leave a buffer's 4 GiB; full addresses, rows past S repeat row S-1.
 constexpr int64_t kFarStride = (int64_t)1 << 26;
 template <int D, bool FAR>
@@ -159,13 +159,28 @@ struct F32Outer {
     }
 };
 
-// s += (rows of tile 0) x b0 and dp += (rows of tile 1) x b1 over the head dim: item c, two reads, eight MFMAs
+// A score is added up in four chains, in the forward and in the backward alike.  The logsumexp fits the scores of the backward
+// only if their bits are those of the forward, and a longer chain rounds more often: relative error of dV against 64 bits at
+// S = 1500, d = 64, scores of +-40: two chains in the forward and one in the backward 4.5e-6, two in both 1.28e-6, four in both
+// 1.19e-6 (O: 7.2e-7, 7.2e-7, 5.2e-7).  The sums at the end cost the forward 2 to 5 % (S = 3000, H = 4, d = 128: 93.5 -> 97.5 us).
+struct F32Chains {
+    f32x4 part[4] = {kZero4, kZero4, kZero4, kZero4};
+    __device__ __forceinline__ void add(const f32x4 &a, const f32x4 &b)
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part[j] = mfma4(a[j], b[j], part[j]);
+    }
+    __device__ __forceinline__ f32x4 sum() const { return (part[0] + part[1]) + (part[2] + part[3]); }
+};
+
+// s = (rows of tile 0) x b0 and dp += (rows of tile 1) x b1 over the head dim: item c, two reads, eight MFMAs
 template <int D>
 __device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Addr &ad, const f32x4 (&b0)[D / 16],
                                                const f32x4 (&b1)[D / 16])
 {
     constexpr int kTile = kT * D * 4;
     F32Pair ring[2];
+    F32Chains scores;
     auto issue = [&](auto n, F32Pair &slot) {
         constexpr int c = decltype(n)::value;
         lds_issue_b128<256 * (c / 4)>(slot.x, ad.row[c % 4]);
@@ -174,12 +189,11 @@ __device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Add
     lds_pipeline_prologue<D / 16, 1, 2>(ring, issue);
     lds_pipeline_body<D / 16, 1, 2>(ring, issue, [&](auto n, F32Pair &slot) {
         constexpr int c = decltype(n)::value;
+        scores.add(slot.x, b0[c]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            s = mfma4(slot.x[j], b0[c][j], s);
-            dp = mfma4(slot.y[j], b1[c][j], dp);
-        }
+        for (int j = 0; j < 4; ++j) dp = mfma4(slot.y[j], b1[c][j], dp);
     });
+    s = scores.sum();
 }
 
 // Accumulator piece 4h + r of a lane: the four consecutive dims 64h + 16*g4 + 4r .. of its column.
@@ -223,7 +237,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
         wait_fills_but<Shape::kFills>();              // K has landed; V, queued behind it, may still be on its way
-        f32x4 s = kZero4, s1 = kZero4;                // two chains
+        F32Chains scores;
         {
             f32x4 kring[kDepth + 1];
             auto issue = [&](auto m, f32x4 &slot) {
@@ -232,11 +246,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
             };
             lds_pipeline_prologue<D / 16, kDepth, 1>(kring, issue);
             lds_pipeline_body<D / 16, kDepth, 1>(kring, issue, [&](auto m, f32x4 &slot) {
-                constexpr int cc = decltype(m)::value;
-                s = mfma4(slot[0], q[cc][0], s);
-                s1 = mfma4(slot[1], q[cc][1], s1);
-                s = mfma4(slot[2], q[cc][2], s);
-                s1 = mfma4(slot[3], q[cc][3], s1);
+                scores.add(slot, q[decltype(m)::value]);
             });
         }
         if (more) {
@@ -246,7 +256,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
             wait_fills();
         }
         F32Outer<D, Shape::kTile> pv(ad);         // the first V operands: their latency hides behind the softmax
-        s += s1;
+        f32x4 s = scores.sum();
         if (jt == ntiles - 1) {         // key 4*g4 + r of the tile is visible to query l16 iff it is <= l16
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -365,7 +375,7 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
         wait_fills();
-        f32x4 s = kZero4, dp = {nd, nd, nd, nd};      // keys 4*g4 + r x query l16
+        f32x4 s, dp = {nd, nd, nd, nd};               // keys 4*g4 + r x query l16
         f32_two_scores<D>(s, dp, ad, q, go);
         if (more) fill_v(jt + KS);                    // V is used up
         F32Outer<D, 0> kds(ad);
@@ -425,7 +435,7 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
         wait_fills();
         const f32x4 lse = lse_n, dl = dl_n;
         if (more) load_stats(it + QS, lse_n, dl_n);
-        f32x4 s = kZero4, dp;                         // queries 4*g4 + r x key l16
+        f32x4 s, dp;                                  // queries 4*g4 + r x key l16
 #pragma unroll
         for (int r = 0; r < 4; ++r) dp[r] = -dl[r];
         f32_two_scores<D>(s, dp, ad, kr, vr);

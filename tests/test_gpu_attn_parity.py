@@ -339,3 +339,22 @@ def test_fp32_rows_without_a_key(oracle, d):
         assert_close("dV", to_f64(dv[:, dead:]), rdv, "f32")
         for name, x in (("dQ", dq[..., 1:]), ("dK", dk), ("dV", dv)):
             assert (x[:, :dead] == 0).all(), f"{name}: a row without a key is touched by its zero dO"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_large_scores(oracle, d):
+    # scores of +-40: the softmax is peaked, and an error e of a score is a relative error e of its probability.  Bound: a scaled
+    # score below 2^6 is held to 2^-19 (half an ulp is 2^-19), its sum of d/4 products per chain and the logsumexp add about
+    # as much again in the 2-norm; the forward must form the scores in the order of the backward for the two to cancel
+    S, H = 1500, 2
+    print(f"[case] fp32 large scores d={d}", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = synth.attn_inputs(1, S, H, d, "f32", 61)
+    q = q * 10
+    got = gpu_fwd_bwd(*(t.cuda() for t in (q, k, v, g)), scale)
+    qf, kf, vf, gf = (to_f64(t) for t in (q, k, v, g))
+    ref = oracle.attn_fwd(qf, kf, vf, scale)[:1] + tuple(oracle.attn_bwd(qf, kf, vf, gf, scale))
+    for name, x, r in zip(("O", "dQ", "dK", "dV"), (got[0],) + got[2:], ref):
+        rel = np.linalg.norm(to_f64(x) - r) / np.linalg.norm(r)
+        print(f"  {name} rel {rel:.2e}", flush=True)
+        assert rel <= 2 ** -19 + 2 ** -22, f"{name}: rel_l2={rel:.2e}"
