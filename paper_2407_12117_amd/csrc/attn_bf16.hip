@@ -54,6 +54,12 @@ constexpr int kFwdWaves = 8;                 // waves per workgroup
 // date: 2^40 per tile leaves the row sum over 2^20 keys and the output accumulators far inside fp32.
 constexpr float kRescaleAbove = 1099511627776.f;
 
+// The running maximum of a wave that has met keys, never below the lowest finite value: a row may see nothing but scores of
+// -inf in a wave's tile (masked keys), and -inf - -inf is NaN.  Times c it stays above -2^31, where the rounding of the
+// product moves an exponent by up to 2^6, which fp32 holds; scores further down weigh zero against any key that is not masked.
+__device__ __forceinline__ float finite_max(float m, float tile_max) { return fmaxf(fmaxf(m, tile_max), -3.402823466e38f); }
+__device__ __forceinline__ float scaled_max(float m, float c) { return fmaxf(m * c, -2147483648.f); }
+
 // a K operand and the Q operands of one or two row blocks
 template <int NQ> struct KqSlot { bf16x8 k, q[NQ]; };
 
@@ -244,11 +250,10 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
                 mb[jb] = fmaxf(mb[jb], s[jb][15]);
             }
             const float mt = max_across_halves(JB == 2 ? fmaxf(mb[0], mb[JB - 1]) : mb[0]);
-            // Every processed tile has key j0 visible to all 32 rows, so the maximum is finite.
-            const float m_new = fmaxf(m, mt);
+            const float m_new = finite_max(m, mt);
             const float corr = __builtin_amdgcn_exp2f((m - m_new) * c);
             m = m_new;
-            mc = m_new * c;
+            mc = scaled_max(m_new, c);
             lsum *= corr;
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb)
@@ -440,10 +445,10 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
 #pragma unroll
                 for (int e = 3; e < 15; e += 2) mb = fmaxf(fmaxf(mb, s[b][e]), s[b][e + 1]);
                 mb = fmaxf(mb, s[b][15]);
-                const float m_new = fmaxf(m[b], max_across_halves(mb));
+                const float m_new = finite_max(m[b], max_across_halves(mb));
                 const float corr = __builtin_amdgcn_exp2f((m[b] - m_new) * c);
                 m[b] = m_new;
-                mc[b] = m_new * c;
+                mc[b] = scaled_max(m_new, c);
                 lsum[b] *= corr;
 #pragma unroll
                 for (int cb = 0; cb < 4; ++cb)

@@ -358,3 +358,25 @@ def test_fp32_large_scores(oracle, d):
         rel = np.linalg.norm(to_f64(x) - r) / np.linalg.norm(r)
         print(f"  {name} rel {rel:.2e}", flush=True)
         assert rel <= 2 ** -19 + 2 ** -22, f"{name}: rel_l2={rel:.2e}"
+
+
+# the 32-, 64-, 128-row forward and the 256-row ones in both orders; all lengths whole 32-row tiles
+@pytest.mark.parametrize("value", [-math.inf, float(torch.finfo(torch.bfloat16).min), -1e20, -1e9])
+@pytest.mark.parametrize("S,heads,tile", [(288, 9, 32), (320, 48, 32), (352, 48, 64), (704, 160, 64), (704, 100, 64)])
+def test_bf16_masked_first_tiles(oracle, S, heads, tile, value):
+    _key_mask_case(oracle, S, heads, 128, "bf16", value, tile, scaled=True)
+
+
+def test_bf16_rows_without_a_key(oracle):
+    # keys 0 .. 19 at -inf: rows 0 .. 19 are NaN (their logsumexp too, or -inf), the others as if the keys were not there
+    for S, H in ((300, 2), (320, 48), (352, 48), (700, 100)):
+        print(f"[case] bf16 rows without a key S={S} H={H}", flush=True)
+        dead, scale = 20, synth.default_scale(128)
+        q, k, v, _ = synth.attn_inputs(1, S, H, 128, "bf16", 78)
+        q[..., 0], k[..., 0] = 1.0, 0.0
+        k[:, :dead, :, 0] = -math.inf
+        o, lse = mb.memo_attn_fwd(q.cuda(), k.cuda(), v.cuda(), scale)
+        ro, rlse = oracle.attn_fwd(*(to_f64(t[:, dead:]) for t in (q, k, v)), scale)
+        assert_close("O", to_f64(o[:, dead:]), ro, "bf16")
+        assert np.abs(to_f64(lse[:, :, dead:]) - rlse).max() <= LSE_MAX_ABS_BF16
+        assert torch.isnan(o[:, :dead].float()).all() and not torch.isfinite(lse[:, :, :dead]).any()
