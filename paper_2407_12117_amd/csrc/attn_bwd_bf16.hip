@@ -677,6 +677,14 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
                     for (int r = 0; r < 4; ++r)
                         if (r < 16 * kt + l16 - (16 * qt + 4 * g4)) s[qt][kt][r] = -INFINITY;
         }
+        if (it == nit - 1) {      // rows past S were read as zero, and zero times an infinite key is NaN: their LSE of +inf does not do
+            const int left = (int)(a.S - (int64_t)it * 32);
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r >= left - (16 * qt + 4 * g4)) s[qt][0][r] = s[qt][1][r] = -INFINITY;
+        }
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll

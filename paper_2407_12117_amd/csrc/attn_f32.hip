@@ -430,7 +430,7 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
     f32_load_row<D>(vr, static_cast<const float *>(a.v) + base + jk * a.ss, g4);
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) dk[n] = dv[n] = kZero4;
-        for (int it = it0 + wave; it < ntiles; it += QS) {
+    for (int it = it0 + wave; it < ntiles; it += QS) {
         const bool more = it + QS < ntiles;
         wait_fills();
         const f32x4 lse = lse_n, dl = dl_n;
@@ -444,6 +444,11 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (4 * g4 + r < l16) s[r] = -INFINITY;
+        }
+        if (it == ntiles - 1) {   // rows past S were read as zero, and zero times an infinite key is NaN: their LSE of +inf does not do
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if ((int64_t)it * kT + 4 * g4 + r >= a.S) s[r] = -INFINITY;
         }
         f32x4 p, ds;
 #pragma unroll

@@ -380,3 +380,15 @@ def test_bf16_rows_without_a_key(oracle):
         assert_close("O", to_f64(o[:, dead:]), ro, "bf16")
         assert np.abs(to_f64(lse[:, :, dead:]) - rlse).max() <= LSE_MAX_ABS_BF16
         assert torch.isnan(o[:, :dead].float()).all() and not torch.isfinite(lse[:, :, :dead]).any()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_masked_keys_before_a_ragged_end(oracle, d):
+    # key rows of -inf meet the rows past S of the last query tile
+    _key_mask_case(oracle, 300, 18, d, "f32", -math.inf, 16)
+
+
+@pytest.mark.parametrize("S,heads", [(300, 3), (1000, 4), (353, 48), (513, 64), (700, 160)])
+def test_bf16_masked_keys_before_a_ragged_end(oracle, S, heads):
+    # as above, in the 32-, 64-, 128- and 256-row backward
+    _key_mask_case(oracle, S, heads, 128, "bf16", -math.inf, 32, scaled=True)
