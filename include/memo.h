@@ -77,6 +77,7 @@ typedef struct {
  *   o   [same layout as q]  = softmax(scale * q k^T, causal) v
  *   lse [B,H,S] fp32        = natural-log sum_j exp(scale * q_i . k_j), j <= i
  * Queued on `stream`.  Returns MEMO_OK or an error; on error nothing is queued.
+ * o may be the buffer of q; any other overlap of an output with an input is undefined.
  */
 memo_status memo_attn_fwd(const memo_attn_desc *desc, const void *q, const void *k, const void *v,
                           void *o, float *lse, void *stream);
@@ -87,6 +88,8 @@ memo_status memo_attn_fwd(const memo_attn_desc *desc, const void *q, const void 
  * Needs o and lse from the forward.  `workspace` is device memory of at least
  * memo_attn_bwd_workspace_bytes(desc) bytes, 256-byte aligned, owned by the
  * caller, contents undefined on entry and exit.  Deterministic: no atomics.
+ * dq may be the buffer of q or of d_o, and dq, dk or dv the buffer of o: each is read before it is
+ * overwritten.  Any other overlap of an output with an input or with another output is undefined.
  */
 size_t memo_attn_bwd_workspace_bytes(const memo_attn_desc *desc);
 memo_status memo_attn_bwd(const memo_attn_desc *desc, const void *q, const void *k, const void *v,

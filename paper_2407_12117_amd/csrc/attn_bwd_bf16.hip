@@ -544,15 +544,16 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, 
 }
 
 // both gradients in one launch, longest tiles first: the first `dkdv_blocks` workgroups are the key-stationary
-// ones, the others the query-stationary ones
+// ones, the others the query-stationary ones.  The launch starts at workgroup `first`
 template <int KG, int QG, int T>
-__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks, uint32_t first)
 {
     constexpr int kLds = DkdvShape<KG>::kLds > DqShape<QG, T>::kLds ? DkdvShape<KG>::kLds : DqShape<QG, T>::kLds;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    if (blockIdx.x < dkdv_blocks) dkdv_rows<KG>(a, lds, blockIdx.x, kLongestFirst);
-    else dq_rows<QG, T>(a, lds, blockIdx.x - dkdv_blocks, kLongestFirst);
+    const uint32_t id = first + blockIdx.x;
+    if (id < dkdv_blocks) dkdv_rows<KG>(a, lds, id, kLongestFirst);
+    else dq_rows<QG, T>(a, lds, id - dkdv_blocks, kLongestFirst);
 }
 
 // ============================================================================ backward, 32-row workgroups
@@ -834,20 +835,30 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
     });
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks, uint32_t first)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    if (blockIdx.x < dkdv_blocks) dkdv_own_rows(a, lds, blockIdx.x);
-    else dq_own_rows(a, lds, blockIdx.x - dkdv_blocks);
+    const uint32_t id = first + blockIdx.x;
+    if (id < dkdv_blocks) dkdv_own_rows(a, lds, id);
+    else dq_own_rows(a, lds, id - dkdv_blocks);
 }
 
-hipError_t launch_bwd_own(const AttnArgs &a, hipStream_t st)
+// nk key-stationary workgroups and nq query-stationary ones, in one launch or, `apart`, the ones after the others
+hipError_t launch_joint(void (*kernel)(AttnArgs, uint32_t, uint32_t), const AttnArgs &a, int64_t nk, int64_t nq, bool apart, hipStream_t st)
+{
+    if (nk + nq > 0x7fffffffLL) return hipErrorInvalidValue;
+    kernel<<<dim3((unsigned)(apart ? nk : nk + nq)), 512, 0, st>>>(a, (uint32_t)nk, 0u);
+    const hipError_t e = hipGetLastError();
+    if (!apart || e != hipSuccess) return e;
+    kernel<<<dim3((unsigned)nq), 512, 0, st>>>(a, (uint32_t)nk, (uint32_t)nk);
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_own(const AttnArgs &a, bool apart, hipStream_t st)
 {
     const int64_t n = order_grid((a.S + 31) / 32, (int64_t)a.H * a.B, kLongestFirst);
-    if (2 * n > 0x7fffffffLL) return hipErrorInvalidValue;
-    attn_bwd_own_bf16_kernel<<<dim3((unsigned)(2 * n)), 512, 0, st>>>(a, (uint32_t)n);
-    return hipGetLastError();
+    return launch_joint(attn_bwd_own_bf16_kernel, a, n, n, apart, st);
 }
 
 template <int KG>
@@ -869,14 +880,12 @@ hipError_t launch_dq(const AttnArgs &a, int order, hipStream_t st)
 }
 
 template <int KG, int QG, int T>
-hipError_t launch_both(const AttnArgs &a, hipStream_t st)
+hipError_t launch_both(const AttnArgs &a, bool apart, hipStream_t st)
 {
     const int64_t hb = (int64_t)a.H * a.B;
     const int64_t nk = order_grid((a.S + 32 * KG - 1) / (32 * KG), hb, kLongestFirst);
     const int64_t nq = order_grid((a.S + 32 * QG - 1) / (32 * QG), hb, kLongestFirst);
-    if (nk + nq > 0x7fffffffLL) return hipErrorInvalidValue;
-    attn_bwd_both_bf16_kernel<KG, QG, T><<<dim3((unsigned)(nk + nq)), 512, 0, st>>>(a, (uint32_t)nk);
-    return hipGetLastError();
+    return launch_joint(attn_bwd_both_bf16_kernel<KG, QG, T>, a, nk, nq, apart, st);
 }
 
 }  // namespace
@@ -905,6 +914,7 @@ static double own_us(int64_t S, int64_t heads)
 // heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups, 207 as two launches of 256-row pairs) and lets the dQ
 // tiles run in the tail of the dK/dV ones (S = 16461, H = 4: 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us);
 // two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 27.8 + 18.8 against 47.3 ms).
+// A joint launch goes out in two parts where dQ takes the place of Q or dO, which all key-stationary workgroups read.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
 {
     const int64_t hb = (int64_t)a.H * a.B;
@@ -925,11 +935,12 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
             }
         }
         if (own_us(a.S, hb) < best) rows = 32;
+        const bool apart = dq_in_place(a);
         switch (rows) {
-        case 32: return launch_bwd_own(a, st);
-        case 64: return launch_both<2, 2, 32>(a, st);
-        case 128: return launch_both<4, 4, 64>(a, st);
-        case 256: return launch_both<8, 8, 64>(a, st);
+        case 32: return launch_bwd_own(a, apart, st);
+        case 64: return launch_both<2, 2, 32>(a, apart, st);
+        case 128: return launch_both<4, 4, 64>(a, apart, st);
+        case 256: return launch_both<8, 8, 64>(a, apart, st);
         }
     }
     switch (kc.rows) {

@@ -563,7 +563,7 @@ hipError_t launch_attn_bwd_f32(const AttnArgs &a, hipStream_t st)
     if (e != hipSuccess) return e;
     if ((e = launch_attn_delta(a, false, st)) != hipSuccess) return e;
     if ((e = record_stage(a, 1, st)) != hipSuccess) return e;
-    if (!a.stage_events) return launch(true, true);
+    if (!a.stage_events && !dq_in_place(a)) return launch(true, true);
     if ((e = launch(true, false)) != hipSuccess) return e;
     if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
     if ((e = launch(false, true)) != hipSuccess) return e;

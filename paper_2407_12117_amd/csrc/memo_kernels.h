@@ -28,6 +28,10 @@ inline hipError_t record_stage(const AttnArgs &a, int idx, hipStream_t st)
     return a.stage_events ? hipEventRecord(a.stage_events[idx], st) : hipSuccess;
 }
 
+// dQ may take the place of Q or of dO (all have one layout): a query-stationary workgroup reads only the rows it
+// writes later, so that it is enough to work all key-stationary ones first
+inline bool dq_in_place(const AttnArgs &a) { return a.dq == a.q || a.dq == a.d_o; }
+
 // fp32 path (fp32 matrix instructions, fp32 throughout), d in {64, 128}
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, hipStream_t st);
 hipError_t launch_attn_bwd_f32(const AttnArgs &a, hipStream_t st);

@@ -392,3 +392,23 @@ def test_fp32_masked_keys_before_a_ragged_end(oracle, d):
 def test_bf16_masked_keys_before_a_ragged_end(oracle, S, heads):
     # as above, in the 32-, 64-, 128- and 256-row backward
     _key_mask_case(oracle, S, heads, 128, "bf16", -math.inf, 32, scaled=True)
+
+
+# one case for each workgroup shape of the backward, and the pair of launches of the longer sequences
+@pytest.mark.parametrize("dtype,S,H,d", [("f32", 333, 2, 64), ("f32", 700, 40, 128), ("bf16", 300, 3, 128), ("bf16", 353, 48, 128),
+                                         ("bf16", 513, 64, 128), ("bf16", 700, 160, 128), ("bf16", 8155, 16, 128)])
+def test_outputs_in_place_of_inputs(dtype, S, H, d):
+    print(f"[case] in place {dtype} S={S} H={H} d={d}", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(1, S, H, d, dtype, 31 + S))
+    want = gpu_fwd_bwd(q, k, v, g, scale)
+    # the forward writes o over q
+    q2 = q.clone()
+    o, lse = mb.memo_attn_fwd(q2, k, v, scale, o=q2)
+    assert torch.equal(o, want[0]) and torch.equal(lse, want[1])
+    # the backward writes dq over q, then over d_o, and dk over o
+    for place in ("q", "d_o"):
+        q2, g2, o2 = q.clone(), g.clone(), want[0].clone()
+        got = mb.memo_attn_bwd(q2, k, v, o2, want[1], g2, scale, dq=q2 if place == "q" else g2, dk=o2)
+        for name, x, y in zip(("dQ", "dK", "dV"), got, want[2:]):
+            assert torch.equal(x, y), f"{name} differs with dQ in place of {place}"
