@@ -99,11 +99,14 @@ memo_status memo_attn_bwd(const memo_attn_desc *desc, const void *q, const void 
 
 /*
  * Same as memo_attn_bwd, and additionally records caller-owned events on `stream` between the
- * stages of the backward, so that a profiler or benchmark can time each kernel where it runs:
+ * stages of the backward, so that a profiler or benchmark can time each stage where it runs:
  *   stage_events[0] before the first kernel,
  *   stage_events[1] after the D_i = sum_c dO_ic O_ic preprocess,
- *   stage_events[2] after the dK/dV kernel,
- *   stage_events[3] after the dQ kernel.
+ *   stage_events[2] after dK and dV,
+ *   stage_events[3] after dQ.
+ * The workgroups, and the gradients bit for bit, are those of memo_attn_bwd.  Where that call works
+ * dK, dV and dQ in one launch (fp32; bf16 short of whole rounds of the device) they go out in two
+ * here, so that an event can lie between them: the stage times then add up to more than its time.
  * stage_events is a host array of 4 hipEvent_t (created with timing enabled), or NULL.
  */
 memo_status memo_attn_bwd_staged(const memo_attn_desc *desc, const void *q, const void *k,

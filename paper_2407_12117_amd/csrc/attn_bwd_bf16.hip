@@ -844,13 +844,15 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, u
     else dq_own_rows(a, lds, id - dkdv_blocks);
 }
 
-// nk key-stationary workgroups and nq query-stationary ones, in one launch or, `apart`, the ones after the others
+// nk key-stationary workgroups and nq query-stationary ones, in one launch or, `apart`, the ones after the others with the
+// stage event between them
 hipError_t launch_joint(void (*kernel)(AttnArgs, uint32_t, uint32_t), const AttnArgs &a, int64_t nk, int64_t nq, bool apart, hipStream_t st)
 {
     if (nk + nq > 0x7fffffffLL) return hipErrorInvalidValue;
     kernel<<<dim3((unsigned)(apart ? nk : nk + nq)), 512, 0, st>>>(a, (uint32_t)nk, 0u);
-    const hipError_t e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (!apart || e != hipSuccess) return e;
+    if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
     kernel<<<dim3((unsigned)nq), 512, 0, st>>>(a, (uint32_t)nk, (uint32_t)nk);
     return hipGetLastError();
 }
@@ -909,12 +911,12 @@ static double own_us(int64_t S, int64_t heads)
 }
 
 // D_i preprocess, then dK, dV and dQ: in one launch of 32-, 64-, 128- or 256-row workgroups, or, where whole rounds
-// of folded pairs are cheaper (or events between the stages are asked for), the key-stationary kernel and
-// then the query-stationary one.  The single launch fills the chip where neither kernel does alone (S = 2000, 6
+// of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch fills the chip where neither kernel does alone (S = 2000, 6
 // heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups, 207 as two launches of 256-row pairs) and lets the dQ
 // tiles run in the tail of the dK/dV ones (S = 16461, H = 4: 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us);
 // two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 27.8 + 18.8 against 47.3 ms).
-// A joint launch goes out in two parts where dQ takes the place of Q or dO, which all key-stationary workgroups read.
+// A joint launch goes out in two parts, with the same bits, where dQ takes the place of Q or dO, which all key-stationary
+// workgroups read, and where an event between the stages is asked for.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
 {
     const int64_t hb = (int64_t)a.H * a.B;
@@ -924,24 +926,25 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
     if (e != hipSuccess) return e;
     if ((e = launch_attn_delta(a, true, st)) != hipSuccess) return e;
     if ((e = record_stage(a, 1, st)) != hipSuccess) return e;
-    if (!a.stage_events) {
-        double best = tile_choice_us(kc, a.S, hb) + tile_choice_us(qc, a.S, hb);
-        int rows = 0;
-        for (int n = 1; n < 4; ++n) {
-            const double us = both_us(kDkdvChoices[n], kDqChoices[n], a.S, hb);
-            if (us < best) {
-                best = us;
-                rows = kDkdvChoices[n].rows;
-            }
+    double best = tile_choice_us(kc, a.S, hb) + tile_choice_us(qc, a.S, hb);
+    int rows = 0;
+    for (int n = 1; n < 4; ++n) {
+        const double us = both_us(kDkdvChoices[n], kDqChoices[n], a.S, hb);
+        if (us < best) {
+            best = us;
+            rows = kDkdvChoices[n].rows;
         }
-        if (own_us(a.S, hb) < best) rows = 32;
-        const bool apart = dq_in_place(a);
+    }
+    if (own_us(a.S, hb) < best) rows = 32;
+    if (rows) {
+        const bool apart = a.stage_events || dq_in_place(a);
         switch (rows) {
-        case 32: return launch_bwd_own(a, apart, st);
-        case 64: return launch_both<2, 2, 32>(a, apart, st);
-        case 128: return launch_both<4, 4, 64>(a, apart, st);
-        case 256: return launch_both<8, 8, 64>(a, apart, st);
+        case 32: e = launch_bwd_own(a, apart, st); break;
+        case 64: e = launch_both<2, 2, 32>(a, apart, st); break;
+        case 128: e = launch_both<4, 4, 64>(a, apart, st); break;
+        default: e = launch_both<8, 8, 64>(a, apart, st); break;
         }
+        return e == hipSuccess ? record_stage(a, 3, st) : e;
     }
     switch (kc.rows) {
     case 64: e = launch_dkdv<2>(a, kc.order, st); break;

@@ -412,3 +412,19 @@ def test_outputs_in_place_of_inputs(dtype, S, H, d):
         got = mb.memo_attn_bwd(q2, k, v, o2, want[1], g2, scale, dq=q2 if place == "q" else g2, dk=o2)
         for name, x, y in zip(("dQ", "dK", "dV"), got, want[2:]):
             assert torch.equal(x, y), f"{name} differs with dQ in place of {place}"
+
+
+@pytest.mark.parametrize("dtype,S,H,d", [("f32", 333, 2, 64), ("bf16", 300, 3, 128), ("bf16", 640, 2, 128), ("bf16", 353, 48, 128),
+                                         ("bf16", 513, 64, 128), ("bf16", 700, 160, 128), ("bf16", 8155, 16, 128)])
+def test_stage_events_do_not_change_the_gradients(dtype, S, H, d):
+    print(f"[case] stage events {dtype} S={S} H={H} d={d}", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(1, S, H, d, dtype, 33 + S))
+    o, lse = mb.memo_attn_fwd(q, k, v, scale)
+    want = mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    got = mb.memo_attn_bwd(q, k, v, o, lse, g, scale, stage_events=events)
+    torch.cuda.synchronize()
+    for name, x, y in zip(("dQ", "dK", "dV"), got, want):
+        assert torch.equal(x, y), f"{name} differs"
+    assert all(a.elapsed_time(b) > 0 for a, b in zip(events, events[1:]))
