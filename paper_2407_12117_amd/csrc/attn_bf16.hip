@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const LaneAddr la = make_lane_addr(lane);
     const int wq = wave % QG, grp = wave / QG;  // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const int order = QG == 8 ? fold : kLongestFirst;   // the downward sweep of a pair takes every tile: KS = 1 only
+    const int order = tile_order(kBq, fold);
     const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
@@ -530,7 +530,7 @@ hipError_t launch_fwd_own(const AttnArgs &a, hipStream_t st)
 template <int QG, int T>
 hipError_t launch_fwd(const AttnArgs &a, int order, hipStream_t st)
 {
-    if (QG != 8) order = kLongestFirst;               // as in the kernel
+    order = tile_order(32 * QG, order);               // as in the kernel
     const int64_t nqt = (a.S + 32 * QG - 1) / (32 * QG);
     const int64_t blocks = order_grid(nqt, (int64_t)a.H * a.B, order);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -538,16 +538,9 @@ hipError_t launch_fwd(const AttnArgs &a, int order, hipStream_t st)
     return hipGetLastError();
 }
 
-// Costs fitted to launches of every variant (N(0,1) inputs, S = 200 .. 200K, 1 to 10 heads): over 40 random
-// (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst.
-constexpr TileChoice kFwdChoices[] = {
-    {256, kFolded, 115.5, 4.0}, {256, kLongestFirst, 117.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
-    {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
-};
-
 hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
 {
-    const TileChoice &c = kFwdChoices[cheapest_tiles(kFwdChoices, a.S, (int64_t)a.H * a.B)];
+    const TileChoice &c = fwd_plan(a.S, (int64_t)a.H * a.B);
     switch (c.rows) {
     case 32: return launch_fwd<1, 32>(a, c.order, st);
     case 64: return launch_fwd_own(a, st);

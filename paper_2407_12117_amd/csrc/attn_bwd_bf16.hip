@@ -81,7 +81,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wq = wave % QG, grp = wave / QG;        // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const PairId t = decode_block(a, id, nqt, order, true);
+    const PairId t = decode_block(a, id, nqt, tile_order(kBq, order), true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -93,7 +93,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     const float c = a.scale * kLog2e;
 
     // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < (QG == 8 ? 2 : 1); ++pass) {
     const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
     if (tile < 0) break;
     const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq;
@@ -313,7 +313,7 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     // The long tile walks the query tiles downwards from the last one to its diagonal, the short tile
     // upwards from its diagonal to the last one (the sums take the query tiles in any order): the
     // workgroups of a chunk, which share an XCD and its L2, then read the same Q/dO rows at about the
-    // same time in both sweeps (bf16_tiles.h, folded order).
+    // same time in both sweeps (launch_plan.h, folded order).
     for (int pass = 0; pass < 2; ++pass) {
     const int64_t tile = pass == 0 ? t.first : t.second;
     if (tile < 0) break;
@@ -875,6 +875,7 @@ hipError_t launch_dkdv(const AttnArgs &a, int order, hipStream_t st)
 template <int QG, int T>
 hipError_t launch_dq(const AttnArgs &a, int order, hipStream_t st)
 {
+    order = tile_order(32 * QG, order);               // as in the kernel
     const int64_t blocks = order_grid((a.S + 32 * QG - 1) / (32 * QG), (int64_t)a.H * a.B, order);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     attn_bwd_dq_bf16_kernel<QG, T><<<dim3((unsigned)blocks), 64 * kDqWaves, 0, st>>>(a, order);
@@ -892,24 +893,6 @@ hipError_t launch_both(const AttnArgs &a, bool apart, hipStream_t st)
 
 }  // namespace
 
-// Costs of the workgroup shapes alone (see tile_choice_us), fitted as the forward's.  64-row workgroups pay
-// 5 to 20 % more per pair than 256-row ones for their four times larger fill traffic.
-constexpr TileChoice kDkdvChoices[] = {
-    {256, kFolded, 216.0, 4.0}, {256, kLongestFirst, 218.0, 8.0}, {128, kLongestFirst, 222.0, 8.0}, {64, kLongestFirst, 232.0, 6.5},
-};
-constexpr TileChoice kDqChoices[] = {
-    {256, kFolded, 146.0, 4.0}, {256, kLongestFirst, 149.0, 8.0}, {128, kLongestFirst, 156.0, 8.0}, {64, kLongestFirst, 181.0, 6.5},
-};
-
-// A launch of 32-row workgroups: no shorter than its longest key tile, nor than all work spread over the chip with the start and
-// the end of every workgroup (4.5 us); fitted to S = 250 .. 8192, 1 to 6 heads (within 10 %).
-static double own_us(int64_t S, int64_t heads)
-{
-    const double per_row = (double)S / (1 << 20), items = 2.0 * ((S + 31) / 32) * heads;
-    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
-    return std::max(0.87 * 32 * per_row * 232.0, mean * 450.0 + 4.5 * items / (kXcds * kChunk)) + 10.0;
-}
-
 // D_i preprocess, then dK, dV and dQ: in one launch of 32-, 64-, 128- or 256-row workgroups, or, where whole rounds
 // of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch fills the chip where neither kernel does alone (S = 2000, 6
 // heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups, 207 as two launches of 256-row pairs) and lets the dQ
@@ -919,26 +902,14 @@ static double own_us(int64_t S, int64_t heads)
 // workgroups read, and where an event between the stages is asked for.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
 {
-    const int64_t hb = (int64_t)a.H * a.B;
-    const TileChoice &kc = kDkdvChoices[cheapest_tiles(kDkdvChoices, a.S, hb)];
-    const TileChoice &qc = kDqChoices[cheapest_tiles(kDqChoices, a.S, hb)];
+    const BwdPlan p = bwd_plan(a.S, (int64_t)a.H * a.B);
     hipError_t e = record_stage(a, 0, st);
     if (e != hipSuccess) return e;
     if ((e = launch_attn_delta(a, true, st)) != hipSuccess) return e;
     if ((e = record_stage(a, 1, st)) != hipSuccess) return e;
-    double best = tile_choice_us(kc, a.S, hb) + tile_choice_us(qc, a.S, hb);
-    int rows = 0;
-    for (int n = 1; n < 4; ++n) {
-        const double us = both_us(kDkdvChoices[n], kDqChoices[n], a.S, hb);
-        if (us < best) {
-            best = us;
-            rows = kDkdvChoices[n].rows;
-        }
-    }
-    if (own_us(a.S, hb) < best) rows = 32;
-    if (rows) {
+    if (p.joint_rows) {
         const bool apart = a.stage_events || dq_in_place(a);
-        switch (rows) {
+        switch (p.joint_rows) {
         case 32: e = launch_bwd_own(a, apart, st); break;
         case 64: e = launch_both<2, 2, 32>(a, apart, st); break;
         case 128: e = launch_both<4, 4, 64>(a, apart, st); break;
@@ -946,17 +917,17 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
         }
         return e == hipSuccess ? record_stage(a, 3, st) : e;
     }
-    switch (kc.rows) {
-    case 64: e = launch_dkdv<2>(a, kc.order, st); break;
-    case 128: e = launch_dkdv<4>(a, kc.order, st); break;
-    default: e = launch_dkdv<8>(a, kc.order, st); break;
+    switch (p.k->rows) {
+    case 64: e = launch_dkdv<2>(a, p.k->order, st); break;
+    case 128: e = launch_dkdv<4>(a, p.k->order, st); break;
+    default: e = launch_dkdv<8>(a, p.k->order, st); break;
     }
     if (e != hipSuccess) return e;
     if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
-    switch (qc.rows) {
-    case 64: e = launch_dq<2, 32>(a, qc.order, st); break;
-    case 128: e = launch_dq<4, 64>(a, qc.order, st); break;
-    default: e = launch_dq<8, 64>(a, qc.order, st); break;
+    switch (p.q->rows) {
+    case 64: e = launch_dq<2, 32>(a, p.q->order, st); break;
+    case 128: e = launch_dq<4, 64>(a, p.q->order, st); break;
+    default: e = launch_dq<8, 64>(a, p.q->order, st); break;
     }
     if (e != hipSuccess) return e;
     return record_stage(a, 3, st);

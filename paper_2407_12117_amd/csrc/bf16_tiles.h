@@ -3,11 +3,9 @@
 // global -> LDS tile fills, and hand-issued, software-pipelined LDS operand reads.
 // Included by the kernel sources only; everything has internal linkage.
 #pragma once
+#include "launch_plan.h"
 #include "memo_kernels.h"
 #include <hip/hip_bf16.h>
-
-#include <algorithm>
-#include <cmath>
 
 namespace memo {
 namespace {
@@ -167,91 +165,8 @@ __device__ __forceinline__ void store_acc_T(__bf16 *out_row, const f32x16 (&acc)
         }
 }
 
-constexpr int kXcds = 8, kChunk = 32;   // XCDs per device; compute units (one workgroup each) per XCD
-
-// Two orders of work.  Every workgroup of a head streams that head's K/V rows (forward, dQ) or Q/dO
-// rows (dK/dV), and a tile's sweep is as long as its distance from the end of the causal triangle.
-//
-// Folded (launches of many whole rounds): a workgroup works a PAIR of tiles of one head, the p-th longest
-// and the p-th shortest, so every workgroup of a launch has the same length (ntiles + 1 tile units).
-// Chunks of kChunk consecutive pairs go to one XCD (the dispatcher deals consecutive workgroup
-// ids round-robin to the 8 XCDs; an XCD has 32 compute units and these kernels run one workgroup
-// per unit), consecutive chunks to the 8 XCDs of a round.  The long tile is swept from the end all
-// tiles share towards its own end, the short tile the other way round (forward and dQ: keys upwards
-// from row 0, then downwards to row 0; dK/dV: queries downwards from row S-1, then upwards to it).
-// Workgroup s of a chunk ends its first sweep a fixed number of steps per s before workgroup 0 and
-// begins its second one as many steps further from the shared end, so the lengths cancel and the
-// workgroups of an XCD read the same rows at about the same time in both sweeps, which is what
-// lets that XCD's L2 serve most of those reads (measured: 32 workgroups, one fetch from the fabric,
-// up to S = 256K; at S = 1M the forward keeps that, the two backward kernels drift apart over their
-// 16384 steps and fetch about half of what they stream).
-//
-// Longest first (everything else): one tile per workgroup, in order of falling length, heads fastest, each
-// unit taking the next tile when it is done.  A launch of 1.2 rounds of pairs costs two rounds, in
-// this order 1.2 to 1.3 (S = 40000, H = 4: forward 2202 -> 1516 us); on whole rounds it is 2 % slower
-// than folded (S = 128K: 14.84 against 14.59 ms), because the units of an XCD no longer sweep together.
+// a workgroup's work (launch_plan.h)
 struct PairId { int64_t first, second; int h, b; };   // first < 0: nothing to do; second < 0: one tile only
-
-enum BlockOrder { kFolded = 0, kLongestFirst = 1 };
-
-inline int64_t order_grid(int64_t ntiles, int64_t heads, int order)
-{
-    if (order == kLongestFirst) return ntiles * heads;
-    const int64_t round = kXcds * kChunk;
-    return ((ntiles + 1) / 2 * heads + round - 1) / round * round;
-}
-
-// One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
-// 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
-// and after its sweep.
-struct TileChoice { int rows, order; double us_per_mpair, us_per_item; };
-
-// Estimated time of a launch, us.  Folded: rounds of 256 equal pairs of tiles.  Longest first: the n
-// tiles an XCD gets have lengths n, n-1, .. 1 (in units of ntiles / n tiles); the first 32 start
-// together, the next 32 go to the units that end first, so that two layers add up to equal sums, and
-// what remains after whole double layers ends with the longest remaining tile.
-inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads)
-{
-    const int64_t ntiles = (S + c.rows - 1) / c.rows;
-    const double mpairs = (double)c.rows * c.rows / (1 << 20);            // a tile unit: rows x rows
-    if (c.order == kFolded) {
-        const int64_t round = kXcds * kChunk, rounds = ((ntiles + 1) / 2 * heads + round - 1) / round;
-        return rounds * ((ntiles + 1) * mpairs * c.us_per_mpair + 2 * c.us_per_item);
-    }
-    const double n = (double)(ntiles * heads) / kXcds, P = kChunk, j = std::floor(n / (2 * P));
-    double makespan = 2 * n * j - 2 * P * j * j + j + n - 2 * P * j;
-    if (n < 1) makespan = 1;                                              // fewer tiles than XCDs
-    const double busy = n < P ? n / P : 1.0;                              // a partly idle chip clocks higher
-    return makespan * (ntiles / (n < 1 ? 1 : n)) * mpairs * c.us_per_mpair * (0.8 + 0.2 * busy) +
-           std::ceil(n / P) * c.us_per_item;
-}
-
-template <int N>
-inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t heads)
-{
-    int best = 0;
-    double best_us = tile_choice_us(choices[0], S, heads);
-    for (int i = 1; i < N; ++i) {
-        const double us = tile_choice_us(choices[i], S, heads);
-        if (us < best_us) {
-            best = i;
-            best_us = us;
-        }
-    }
-    return best;
-}
-
-// Estimated time of one launch that works the key tiles k and then the query tiles q, each longest first: all
-// work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
-// tenth of the longest one uneven.
-inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
-{
-    const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
-    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
-    const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
-    const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
-    return std::max(longest, spread) + 10.0;
-}
 
 __device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, int64_t ntiles, int order, bool last_is_longest)
 {

@@ -1,0 +1,181 @@
+// How a launch is cut into workgroups: the orders of work, and the choice of shape and order by estimated time.
+// Host arithmetic on sizes alone (no HIP), included by the kernel sources and by the test that asks which shape a size gets.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace memo {
+
+inline constexpr int kXcds = 8, kChunk = 32;   // XCDs per device; compute units (one workgroup each) per XCD
+
+// Two orders of work.  Every workgroup of a head streams that head's K/V rows (forward, dQ) or Q/dO
+// rows (dK/dV), and a tile's sweep is as long as its distance from the end of the causal triangle.
+//
+// Folded (launches of many whole rounds): a workgroup works a PAIR of tiles of one head, the p-th longest
+// and the p-th shortest, so every workgroup of a launch has the same length (ntiles + 1 tile units).
+// Chunks of kChunk consecutive pairs go to one XCD (the dispatcher deals consecutive workgroup
+// ids round-robin to the 8 XCDs; an XCD has 32 compute units and these kernels run one workgroup
+// per unit), consecutive chunks to the 8 XCDs of a round.  The long tile is swept from the end all
+// tiles share towards its own end, the short tile the other way round (forward and dQ: keys upwards
+// from row 0, then downwards to row 0; dK/dV: queries downwards from row S-1, then upwards to it).
+// Workgroup s of a chunk ends its first sweep a fixed number of steps per s before workgroup 0 and
+// begins its second one as many steps further from the shared end, so the lengths cancel and the
+// workgroups of an XCD read the same rows at about the same time in both sweeps, which is what
+// lets that XCD's L2 serve most of those reads (measured: 32 workgroups, one fetch from the fabric,
+// up to S = 256K; at S = 1M the forward keeps that, the two backward kernels drift apart over their
+// 16384 steps and fetch about half of what they stream).
+//
+// Longest first (everything else): one tile per workgroup, in order of falling length, heads fastest, each
+// unit taking the next tile when it is done.  A launch of 1.2 rounds of pairs costs two rounds, in
+// this order 1.2 to 1.3 (S = 40000, H = 4: forward 2202 -> 1516 us); on whole rounds it is 2 % slower
+// than folded (S = 128K: 14.84 against 14.59 ms), because the units of an XCD no longer sweep together.
+enum BlockOrder { kFolded = 0, kLongestFirst = 1 };
+
+inline int64_t order_grid(int64_t ntiles, int64_t heads, int order)
+{
+    if (order == kLongestFirst) return ntiles * heads;
+    const int64_t round = kXcds * kChunk;
+    return ((ntiles + 1) / 2 * heads + round - 1) / round * round;
+}
+
+// One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
+// 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
+// and after its sweep.
+struct TileChoice { int rows, order; double us_per_mpair, us_per_item; };
+
+// Estimated time of a launch, us.  Folded: rounds of 256 equal pairs of tiles.  Longest first: the n
+// tiles an XCD gets have lengths n, n-1, .. 1 (in units of ntiles / n tiles); the first 32 start
+// together, the next 32 go to the units that end first, so that two layers add up to equal sums, and
+// what remains after whole double layers ends with the longest remaining tile.
+inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads)
+{
+    const int64_t ntiles = (S + c.rows - 1) / c.rows;
+    const double mpairs = (double)c.rows * c.rows / (1 << 20);            // a tile unit: rows x rows
+    if (c.order == kFolded) {
+        const int64_t round = kXcds * kChunk, rounds = ((ntiles + 1) / 2 * heads + round - 1) / round;
+        return rounds * ((ntiles + 1) * mpairs * c.us_per_mpair + 2 * c.us_per_item);
+    }
+    const double n = (double)(ntiles * heads) / kXcds, P = kChunk, j = std::floor(n / (2 * P));
+    double makespan = 2 * n * j - 2 * P * j * j + j + n - 2 * P * j;
+    if (n < 1) makespan = 1;                                              // fewer tiles than XCDs
+    const double busy = n < P ? n / P : 1.0;                              // a partly idle chip clocks higher
+    return makespan * (ntiles / (n < 1 ? 1 : n)) * mpairs * c.us_per_mpair * (0.8 + 0.2 * busy) +
+           std::ceil(n / P) * c.us_per_item;
+}
+
+template <int N>
+inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t heads)
+{
+    int best = 0;
+    double best_us = tile_choice_us(choices[0], S, heads);
+    for (int i = 1; i < N; ++i) {
+        const double us = tile_choice_us(choices[i], S, heads);
+        if (us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+// Estimated time of one launch that works the key tiles k and then the query tiles q, each longest first: all
+// work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
+// tenth of the longest one uneven.
+inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
+{
+    const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
+    const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
+    const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
+    return std::max(longest, spread) + 10.0;
+}
+
+// The order a workgroup shape can work.  The downward sweep over the second tile of a pair starts every key group at the last
+// key tile and steps over all of them: it is right for 256-row workgroups alone, whose waves share every key tile.
+constexpr int tile_order(int rows, int order) { return rows == 256 ? order : kLongestFirst; }
+
+// ---- bf16 forward
+// Costs fitted to launches of every variant (N(0,1) inputs, S = 200 .. 200K, 1 to 10 heads): over 40 random
+// (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst.
+inline constexpr TileChoice kFwdChoices[] = {
+    {256, kFolded, 115.5, 4.0}, {256, kLongestFirst, 117.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
+    {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
+};
+
+inline const TileChoice &fwd_plan(int64_t S, int64_t heads) { return kFwdChoices[cheapest_tiles(kFwdChoices, S, heads)]; }
+
+// ---- bf16 backward
+// Costs of the workgroup shapes alone (see tile_choice_us), fitted as the forward's.  64-row workgroups pay
+// 5 to 20 % more per pair than 256-row ones for their four times larger fill traffic.
+inline constexpr TileChoice kDkdvChoices[] = {
+    {256, kFolded, 216.0, 4.0}, {256, kLongestFirst, 218.0, 8.0}, {128, kLongestFirst, 222.0, 8.0}, {64, kLongestFirst, 232.0, 6.5},
+};
+inline constexpr TileChoice kDqChoices[] = {
+    {256, kFolded, 146.0, 4.0}, {256, kLongestFirst, 149.0, 8.0}, {128, kLongestFirst, 156.0, 8.0}, {64, kLongestFirst, 181.0, 6.5},
+};
+
+// A launch of 32-row workgroups: no shorter than its longest key tile, nor than all work spread over the chip with the start and
+// the end of every workgroup (4.5 us); fitted to S = 250 .. 8192, 1 to 6 heads (within 10 %).
+inline double own_us(int64_t S, int64_t heads)
+{
+    const double per_row = (double)S / (1 << 20), items = 2.0 * ((S + 31) / 32) * heads;
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
+    return std::max(0.87 * 32 * per_row * 232.0, mean * 450.0 + 4.5 * items / (kXcds * kChunk)) + 10.0;
+}
+
+// joint_rows: one launch of workgroups of that many rows; 0: dK/dV as k says, then dQ as q says
+struct BwdPlan { int joint_rows; const TileChoice *k, *q; };
+
+inline BwdPlan bwd_plan(int64_t S, int64_t heads)
+{
+    BwdPlan p = {0, &kDkdvChoices[cheapest_tiles(kDkdvChoices, S, heads)], &kDqChoices[cheapest_tiles(kDqChoices, S, heads)]};
+    double best = tile_choice_us(*p.k, S, heads) + tile_choice_us(*p.q, S, heads);
+    for (int n = 1; n < 4; ++n) {
+        const double us = both_us(kDkdvChoices[n], kDqChoices[n], S, heads);
+        if (us < best) {
+            best = us;
+            p.joint_rows = kDkdvChoices[n].rows;
+        }
+    }
+    if (own_us(S, heads) < best) p.joint_rows = 32;
+    return p;
+}
+
+// ---- projection
+// Tile shapes, and what a round of tiles costs: us per 128 of K with one compute unit busy and with all of them (the chip
+// clocks lower then), and us per tile around it.  Fitted to launches of 300 to 138937 rows, K = 1024 to 5120; the wave
+// grids and ring depths are the fastest of the two or three tried for each tile.
+struct LinChoice { int bm, bn; double us_alone, us_full, us_tile; };
+inline constexpr LinChoice kLinChoices[] = {
+    {256, 256, 2.16, 2.95, 5.0}, {256, 128, 1.28, 1.62, 3.5}, {192, 128, 0.95, 1.28, 2.5},
+    {128, 128, 0.70, 0.88, 2.0}, {128, 64, 0.48, 0.59, 1.0},  {64, 64, 0.37, 0.43, 0.7},
+};
+
+inline double lin_choice_us(const LinChoice &c, int64_t rows, int K, int N)
+{
+    const double tiles = std::ceil((double)rows / c.bm) * std::ceil((double)N / c.bn), units = kXcds * kChunk;
+    const double busy = std::min(1.0, tiles / units);
+    return std::ceil(tiles / units) * (K / 128.0 * (c.us_alone + busy * (c.us_full - c.us_alone)) + c.us_tile);
+}
+
+inline const LinChoice &lin_plan(int64_t rows, int K, int N)
+{
+    const LinChoice *best = kLinChoices;
+    for (const LinChoice &c : kLinChoices)
+        if (lin_choice_us(c, rows, K, N) < lin_choice_us(*best, rows, K, N)) best = &c;
+    return *best;
+}
+
+// every choice of an order is one that its shape can work
+template <int N>
+constexpr bool orders_fit(const TileChoice (&choices)[N])
+{
+    for (int i = 0; i < N; ++i)
+        if (tile_order(choices[i].rows, choices[i].order) != choices[i].order) return false;
+    return true;
+}
+static_assert(orders_fit(kFwdChoices) && orders_fit(kDkdvChoices) && orders_fit(kDqChoices), "a pair of tiles needs 256-row workgroups");
+
+}  // namespace memo

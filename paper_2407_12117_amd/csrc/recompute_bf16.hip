@@ -394,22 +394,6 @@ hipError_t launch_linear(const __bf16 *a, const __bf16 *w, const __bf16 *bias, _
     return hipGetLastError();
 }
 
-// Tile shapes, and what a round of tiles costs: us per 128 of K with one compute unit busy and with all of them (the chip
-// clocks lower then), and us per tile around it.  Fitted to launches of 300 to 138937 rows, K = 1024 to 5120; the wave
-// grids and ring depths are the fastest of the two or three tried for each tile.
-struct LinChoice { int bm, bn; double us_alone, us_full, us_tile; };
-constexpr LinChoice kLinChoices[] = {
-    {256, 256, 2.16, 2.95, 5.0}, {256, 128, 1.28, 1.62, 3.5}, {192, 128, 0.95, 1.28, 2.5},
-    {128, 128, 0.70, 0.88, 2.0}, {128, 64, 0.48, 0.59, 1.0},  {64, 64, 0.37, 0.43, 0.7},
-};
-
-inline double lin_choice_us(const LinChoice &c, int64_t rows, int K, int N)
-{
-    const double tiles = std::ceil((double)rows / c.bm) * std::ceil((double)N / c.bn), units = kXcds * kChunk;
-    const double busy = std::min(1.0, tiles / units);
-    return std::ceil(tiles / units) * (K / 128.0 * (c.us_alone + busy * (c.us_full - c.us_alone)) + c.us_tile);
-}
-
 // The shape of the least estimated time (all give the same bits).  us before (256 x 256 always) -> now: 75 rows
 // 1024 -> 384 28.1 -> 5.9, 300 rows 4096 -> 1536 92 -> 15.0, 1000 rows 93 -> 22, 3075 rows 5120 -> 1920 117 -> 55,
 // 20000 rows 4096 -> 1536 253 -> 193.
@@ -422,10 +406,8 @@ hipError_t launch_linear_rows_bf16(const void *a, const void *w, const void *bia
     if ((int64_t)256 * K * 2 >= (1LL << 32)) return hipErrorInvalidValue;
     const __bf16 *ap = static_cast<const __bf16 *>(a), *wp = static_cast<const __bf16 *>(w), *bp = static_cast<const __bf16 *>(bias);
     __bf16 *op = static_cast<__bf16 *>(out);
-    const LinChoice *best = kLinChoices;
-    for (const LinChoice &c : kLinChoices)
-        if (lin_choice_us(c, rows, K, N) < lin_choice_us(*best, rows, K, N)) best = &c;
-    switch (best->bm * 1000 + best->bn) {
+    const LinChoice &c = lin_plan(rows, K, N);
+    switch (c.bm * 1000 + c.bn) {
     case 64064: return launch_linear<LinShape<4, 2, 1, 2, 5, 5, 2>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
     case 128064: return launch_linear<LinShape<4, 2, 2, 2, 3, 3, 2>>(ap, wp, bp, op, row_begin, row_end, K, N, st);
     case 128128: return launch_linear<LinShape<4, 2, 2, 4, 3, 2, 2>>(ap, wp, bp, op, row_begin, row_end, K, N, st);

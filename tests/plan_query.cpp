@@ -1,0 +1,33 @@
+// Answers, on stdout, which launch plan the library takes for the sizes asked for on stdin, one question a line:
+//   fwd S heads      -> rows order              order: 0 folded pairs, 1 longest first
+//   bwd S heads      -> rows of a joint launch, or "pair" and rows, order of dK/dV and of dQ
+//   lin rows K N     -> tokens and features of a tile
+//   order rows order -> the order that a shape of that many rows works when asked for `order`
+#include "../paper_2407_12117_amd/csrc/launch_plan.h"
+
+#include <cstdio>
+#include <cstring>
+
+int main()
+{
+    char what[16];
+    long long a, b, c;
+    while (std::scanf("%15s %lld %lld", what, &a, &b) == 3) {
+        if (!std::strcmp(what, "fwd")) {
+            const memo::TileChoice &t = memo::fwd_plan(a, b);
+            std::printf("%d %d\n", t.rows, t.order);
+        } else if (!std::strcmp(what, "bwd")) {
+            const memo::BwdPlan p = memo::bwd_plan(a, b);
+            if (p.joint_rows) std::printf("%d\n", p.joint_rows);
+            else std::printf("pair %d %d %d %d\n", p.k->rows, p.k->order, p.q->rows, p.q->order);
+        } else if (!std::strcmp(what, "order")) {
+            std::printf("%d\n", memo::tile_order((int)a, (int)b));
+        } else if (!std::strcmp(what, "lin") && std::scanf("%lld", &c) == 1) {
+            const memo::LinChoice &l = memo::lin_plan(a, (int)b, (int)c);
+            std::printf("%d %d\n", l.bm, l.bn);
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}
