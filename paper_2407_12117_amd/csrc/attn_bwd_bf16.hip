@@ -237,11 +237,10 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     }   // pass
 }
 
-template <int QG, int T>
 __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<QG, T>::kLds];
-    dq_rows<QG, T>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<8, 64>::kLds];
+    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
 }
 
 // ============================================================================ backward: dK, dV
@@ -536,11 +535,10 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     }   // pass
 }
 
-template <int KG>
 __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<KG>::kLds];
-    dkdv_rows<KG>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<8>::kLds];
+    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
 }
 
 // both gradients in one launch, longest tiles first: the first `dkdv_blocks` workgroups are the key-stationary
@@ -863,22 +861,12 @@ hipError_t launch_bwd_own(const AttnArgs &a, bool apart, hipStream_t st)
     return launch_joint(attn_bwd_own_bf16_kernel, a, n, n, apart, st);
 }
 
-template <int KG>
-hipError_t launch_dkdv(const AttnArgs &a, int order, hipStream_t st)
+// one of the two kernels alone, 256 rows
+hipError_t launch_alone(void (*kernel)(AttnArgs, int), const AttnArgs &a, int order, hipStream_t st)
 {
-    const int64_t blocks = order_grid((a.S + 32 * KG - 1) / (32 * KG), (int64_t)a.H * a.B, order);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;       // the front end checks too
-    attn_bwd_dkdv_bf16_kernel<KG><<<dim3((unsigned)blocks), 512, 0, st>>>(a, order);
-    return hipGetLastError();
-}
-
-template <int QG, int T>
-hipError_t launch_dq(const AttnArgs &a, int order, hipStream_t st)
-{
-    order = tile_order(32 * QG, order);               // as in the kernel
-    const int64_t blocks = order_grid((a.S + 32 * QG - 1) / (32 * QG), (int64_t)a.H * a.B, order);
+    const int64_t blocks = order_grid((a.S + 255) / 256, (int64_t)a.H * a.B, order);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    attn_bwd_dq_bf16_kernel<QG, T><<<dim3((unsigned)blocks), 64 * kDqWaves, 0, st>>>(a, order);
+    kernel<<<dim3((unsigned)blocks), 512, 0, st>>>(a, order);
     return hipGetLastError();
 }
 
@@ -907,27 +895,15 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
     if (e != hipSuccess) return e;
     if ((e = launch_attn_delta(a, true, st)) != hipSuccess) return e;
     if ((e = record_stage(a, 1, st)) != hipSuccess) return e;
-    if (p.joint_rows) {
-        const bool apart = a.stage_events || dq_in_place(a);
-        switch (p.joint_rows) {
-        case 32: e = launch_bwd_own(a, apart, st); break;
-        case 64: e = launch_both<2, 2, 32>(a, apart, st); break;
-        case 128: e = launch_both<4, 4, 64>(a, apart, st); break;
-        default: e = launch_both<8, 8, 64>(a, apart, st); break;
-        }
-        return e == hipSuccess ? record_stage(a, 3, st) : e;
-    }
-    switch (p.k->rows) {
-    case 64: e = launch_dkdv<2>(a, p.k->order, st); break;
-    case 128: e = launch_dkdv<4>(a, p.k->order, st); break;
-    default: e = launch_dkdv<8>(a, p.k->order, st); break;
-    }
-    if (e != hipSuccess) return e;
-    if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
-    switch (p.q->rows) {
-    case 64: e = launch_dq<2, 32>(a, p.q->order, st); break;
-    case 128: e = launch_dq<4, 64>(a, p.q->order, st); break;
-    default: e = launch_dq<8, 64>(a, p.q->order, st); break;
+    const bool apart = !p.joint || a.stage_events || dq_in_place(a);
+    if (p.rows == 32) e = launch_bwd_own(a, apart, st);
+    else if (p.rows == 64) e = launch_both<2, 2, 32>(a, apart, st);
+    else if (p.rows == 128) e = launch_both<4, 4, 64>(a, apart, st);
+    else if (p.joint) e = launch_both<8, 8, 64>(a, apart, st);
+    else {
+        if ((e = launch_alone(attn_bwd_dkdv_bf16_kernel, a, p.k_order, st)) != hipSuccess) return e;
+        if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
+        e = launch_alone(attn_bwd_dq_bf16_kernel, a, p.q_order, st);
     }
     if (e != hipSuccess) return e;
     return record_stage(a, 3, st);

@@ -5,6 +5,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <numeric>
+#include <utility>
 
 namespace memo {
 
@@ -80,13 +82,27 @@ inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t hea
     return best;
 }
 
+// What the backward loses longest first when an XCD works many heads at a time.  Heads run fastest and workgroups are dealt
+// round-robin, so an XCD meets heads / gcd(heads, 8) different ones, up to one per unit, and its L2 serves the fewer units
+// the more heads it holds; folded chunks keep an XCD on one or two.  It costs nothing while the Q, K, V and dO rows (1 KB a row
+// in all) are few enough for the cache behind the L2s, and grows with the doublings of the heads beyond that.  Measured,
+// one joint launch against a pair of folded ones, us: S = 8192, 64 heads 3128 : 3052, 128 heads 6722 : 6272, 256 heads
+// 14358 : 12799; S = 50000, 5 heads 8649 : 8290; but S = 4096, 32 heads (2^17 rows) 423 : 430, S = 25000, 8 heads (one per
+// XCD) 3358 : 4221.
+inline double crowding(int64_t S, int64_t heads)
+{
+    const double met = (double)std::min<int64_t>(kChunk, heads / std::gcd(heads, (int64_t)kXcds));
+    return std::log2(met) * std::max(0.0, 1.0 - (double)(1 << 17) / ((double)S * heads));
+}
+inline constexpr double kCrowdedJoint = 0.06, kCrowdedAlone = 0.015;      // of the time, per doubling; 256-row launches of one kernel lose less
+
 // Estimated time of one launch that works the key tiles k and then the query tiles q, each longest first: all
 // work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
 // tenth of the longest one uneven.
 inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
 {
     const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
-    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk);
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk) * (1.0 + kCrowdedJoint * crowding(S, heads));
     const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
     const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
     return std::max(longest, spread) + 10.0;
@@ -125,22 +141,37 @@ inline double own_us(int64_t S, int64_t heads)
     return std::max(0.87 * 32 * per_row * 232.0, mean * 450.0 + 4.5 * items / (kXcds * kChunk)) + 10.0;
 }
 
-// joint_rows: one launch of workgroups of that many rows; 0: dK/dV as k says, then dQ as q says
-struct BwdPlan { int joint_rows; const TileChoice *k, *q; };
+// Workgroups of `rows` rows: dK/dV and dQ in one joint launch, or the one after the other in the orders k_order and q_order.
+struct BwdPlan { int rows; bool joint; int k_order, q_order; };
 
+// The estimate's choice over 80 sizes of 1024 to 262144 rows and 1 to 256 heads with at least 2^16.8 rows in all: 0.1 % slower
+// than the fastest of the variants on average, 1.4 % at worst; against a pair of folded launches 0.5 % at worst (15 %
+// without `crowding`).
 inline BwdPlan bwd_plan(int64_t S, int64_t heads)
 {
-    BwdPlan p = {0, &kDkdvChoices[cheapest_tiles(kDkdvChoices, S, heads)], &kDqChoices[cheapest_tiles(kDqChoices, S, heads)]};
-    double best = tile_choice_us(*p.k, S, heads) + tile_choice_us(*p.q, S, heads);
-    for (int n = 1; n < 4; ++n) {
-        const double us = both_us(kDkdvChoices[n], kDqChoices[n], S, heads);
-        if (us < best) {
-            best = us;
-            p.joint_rows = kDkdvChoices[n].rows;
-        }
+    const double crowd = crowding(S, heads);
+    auto alone_us = [&](const TileChoice &c) {
+        TileChoice t = c;
+        if (c.order == kLongestFirst) t.us_per_mpair *= 1.0 + (c.rows == 256 ? kCrowdedAlone : kCrowdedJoint) * crowd;
+        return tile_choice_us(t, S, heads);
+    };
+    BwdPlan best = {256, false, kFolded, kFolded};
+    double best_us = 0;
+    for (auto [choices, order] : {std::make_pair(kDkdvChoices, &best.k_order), std::make_pair(kDqChoices, &best.q_order)}) {
+        const double folded = alone_us(choices[0]), longest_first = alone_us(choices[1]);
+        *order = longest_first < folded ? kLongestFirst : kFolded;
+        best_us += std::min(folded, longest_first);
     }
-    if (own_us(S, heads) < best) p.joint_rows = 32;
-    return p;
+    auto offer = [&](int rows, bool joint, double us) {
+        if (us >= best_us) return;
+        best = {rows, joint, kLongestFirst, kLongestFirst};
+        best_us = us;
+    };
+    // apart: S = 32768, 2 heads 1508 us against 1565 joint (two long sweeps per unit either way); nowhere else
+    offer(128, false, alone_us(kDkdvChoices[2]) + alone_us(kDqChoices[2]));
+    for (int n = 1; n < 4; ++n) offer(kDkdvChoices[n].rows, true, both_us(kDkdvChoices[n], kDqChoices[n], S, heads));
+    offer(32, true, own_us(S, heads));
+    return best;
 }
 
 // ---- projection

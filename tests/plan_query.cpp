@@ -1,6 +1,6 @@
 // Answers, on stdout, which launch plan the library takes for the sizes asked for on stdin, one question a line:
 //   fwd S heads      -> rows order              order: 0 folded pairs, 1 longest first
-//   bwd S heads      -> rows of a joint launch, or "pair" and rows, order of dK/dV and of dQ
+//   bwd S heads      -> rows, 1 if dK/dV and dQ go out in one launch, order of dK/dV, order of dQ
 //   lin rows K N     -> tokens and features of a tile
 //   order rows order -> the order that a shape of that many rows works when asked for `order`
 #include "../paper_2407_12117_amd/csrc/launch_plan.h"
@@ -18,8 +18,7 @@ int main()
             std::printf("%d %d\n", t.rows, t.order);
         } else if (!std::strcmp(what, "bwd")) {
             const memo::BwdPlan p = memo::bwd_plan(a, b);
-            if (p.joint_rows) std::printf("%d\n", p.joint_rows);
-            else std::printf("pair %d %d %d %d\n", p.k->rows, p.k->order, p.q->rows, p.q->order);
+            std::printf("%d %d %d %d\n", p.rows, p.joint, p.k_order, p.q_order);
         } else if (!std::strcmp(what, "order")) {
             std::printf("%d\n", memo::tile_order((int)a, (int)b));
         } else if (!std::strcmp(what, "lin") && std::scanf("%lld", &c) == 1) {

@@ -16,7 +16,7 @@ def plans(tmp_path_factory):
     def ask(questions):
         text = "".join(" ".join(map(str, q)) + "\n" for q in questions)
         res = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60)
-        return [tuple(x if x == "pair" else int(x) for x in line.split()) for line in res.stdout.splitlines()]
+        return [tuple(map(int, line.split())) for line in res.stdout.splitlines()]
 
     return ask
 
@@ -27,9 +27,21 @@ def test_only_256_row_workgroups_work_pairs_of_tiles(plans):
     sizes = [(int(1.13 ** n), heads) for n in range(1, 115) for heads in (1, 2, 3, 5, 8, 24, 64, 100, 256)]
     for rows, order in plans([("fwd", S, h) for S, h in sizes]):
         assert rows in (32, 64, 128, 256) and (order == LONGEST_FIRST or rows == 256)
-    for plan in plans([("bwd", S, h) for S, h in sizes]):
-        if plan[0] != "pair":
-            assert plan[0] in (32, 64, 128, 256)
-            continue
-        for rows, order in (plan[1:3], plan[3:5]):
-            assert order == LONGEST_FIRST or rows == 256
+    for rows, joint, k_order, q_order in plans([("bwd", S, h) for S, h in sizes]):
+        assert rows in (32, 64, 128, 256)
+        assert k_order == q_order == LONGEST_FIRST or (rows == 256 and not joint)
+
+
+# the sizes at which a joint launch was measured slower than a pair of folded ones by more than the runs differ
+@pytest.mark.parametrize("S,heads", [(4096, 256), (8192, 64), (8192, 128), (8192, 256), (16384, 64), (32768, 32), (50000, 5), (65536, 10),
+                                     (131072, 3), (131072, 5), (262144, 5)])
+def test_backward_of_many_heads_keeps_the_folded_order(plans, S, heads):
+    assert plans([("bwd", S, heads)]) == [(256, 0, FOLDED, FOLDED)]
+
+
+# and faster
+@pytest.mark.parametrize("S,heads", [(2048, 96), (3000, 48), (4096, 48), (6000, 32), (12288, 16), (16384, 10), (25000, 8), (32768, 5), (50000, 4),
+                                     (50000, 8), (65536, 5), (150000, 3)])
+def test_backward_between_whole_rounds_stays_joint(plans, S, heads):
+    rows, joint, k_order, q_order = plans([("bwd", S, heads)])[0]
+    assert (rows, joint) == (256, 1) or (rows, k_order) == (256, LONGEST_FIRST)
