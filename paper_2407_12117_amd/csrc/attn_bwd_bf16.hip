@@ -237,10 +237,10 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     }   // pass
 }
 
-__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order)
+__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order, uint32_t first)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<8, 64>::kLds];
-    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, first + blockIdx.x, order);
 }
 
 // ============================================================================ backward: dK, dV
@@ -535,10 +535,10 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     }   // pass
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order)
+__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order, uint32_t first)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<8>::kLds];
-    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, first + blockIdx.x, order);
 }
 
 // both gradients in one launch, longest tiles first: the first `dkdv_blocks` workgroups are the key-stationary
@@ -846,13 +846,10 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, u
 // stage event between them
 hipError_t launch_joint(void (*kernel)(AttnArgs, uint32_t, uint32_t), const AttnArgs &a, int64_t nk, int64_t nq, bool apart, hipStream_t st)
 {
-    if (nk + nq > 0x7fffffffLL) return hipErrorInvalidValue;
-    kernel<<<dim3((unsigned)(apart ? nk : nk + nq)), 512, 0, st>>>(a, (uint32_t)nk, 0u);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_blocks(kernel, 0, apart ? nk : nk + nq, st, a, (uint32_t)nk);
     if (!apart || e != hipSuccess) return e;
     if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
-    kernel<<<dim3((unsigned)nq), 512, 0, st>>>(a, (uint32_t)nk, (uint32_t)nk);
-    return hipGetLastError();
+    return launch_blocks(kernel, nk, nk + nq, st, a, (uint32_t)nk);
 }
 
 hipError_t launch_bwd_own(const AttnArgs &a, bool apart, hipStream_t st)
@@ -862,12 +859,10 @@ hipError_t launch_bwd_own(const AttnArgs &a, bool apart, hipStream_t st)
 }
 
 // one of the two kernels alone, 256 rows
-hipError_t launch_alone(void (*kernel)(AttnArgs, int), const AttnArgs &a, int order, hipStream_t st)
+hipError_t launch_alone(void (*kernel)(AttnArgs, int, uint32_t), const AttnArgs &a, int order, hipStream_t st)
 {
     const int64_t blocks = order_grid((a.S + 255) / 256, (int64_t)a.H * a.B, order);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    kernel<<<dim3((unsigned)blocks), 512, 0, st>>>(a, order);
-    return hipGetLastError();
+    return launch_blocks(kernel, 0, blocks, st, a, order);
 }
 
 template <int KG, int QG, int T>
