@@ -193,6 +193,16 @@ inline double lin_choice_us(const LinChoice &c, int64_t rows, int K, int N)
     return std::ceil(tiles / units) * (K / 128.0 * (c.us_alone + busy * (c.us_full - c.us_alone)) + c.us_tile);
 }
 
+// The rows that the buffer of tile `tile` of the rows [begin, end) covers.  Not live (behind a workgroup's last tile): none, and
+// first stays inside the matrix, since the address is formed all the same.
+struct RowWindow { int64_t first; int rows; };
+constexpr RowWindow row_window(int64_t begin, int64_t end, int64_t tile, int tile_rows, bool live)
+{
+    if (!live) return {begin, 0};
+    const int64_t first = begin + tile * tile_rows, left = end - first;
+    return {first, left < tile_rows ? (int)left : tile_rows};
+}
+
 inline const LinChoice &lin_plan(int64_t rows, int K, int N)
 {
     const LinChoice *best = kLinChoices;

@@ -120,11 +120,14 @@ struct LinShape {
 
 // One operand's sequence of chunks over the tiles of a workgroup, as a buffer whose base is the tile's first row:
 // rows past the end of the matrix are out of the buffer's range and read as zero (their results are never stored).
-// Behind the last chunk the buffer is empty: the fills are still issued, so that every wait counts the same.
+// Behind the last chunk the buffer is empty: the fills are still issued, so that every wait counts the same.  The range check
+// subtracts the scalar offset from the buffer's size, so that an empty buffer's stays zero (a larger one would wrap and let
+// the fill read).
 struct ChunkStream {
     __amdgpu_buffer_rsrc_t rsrc;
     uint32_t tile;                // the tile that is being fetched
     int chunk;                    // its next chunk
+    uint32_t off, step;           // the chunk's byte offset in a row; from one chunk to the next
 };
 
 template <typename Sh>
@@ -167,18 +170,20 @@ __global__ __launch_bounds__(512, 2) void linear_rows_bf16_kernel(const __bf16 *
     const uint32_t wgt_off = (uint32_t)frow * (uint32_t)K * 2 + (uint32_t)(fpiece ^ wgt_swz<RB>(frow)) * 16;
     uint32_t fill_step = (uint32_t)K * (2 * 8192 / RB);         // bytes between the rows of instructions n and n + 1
     const uint32_t row_bytes = (uint32_t)K * 2;
-    auto tok_tile = [&](ChunkStream &s, uint32_t tile) {
-        const int64_t m0 = row_begin + (int64_t)(tile / ntn) * Sh::BM;
-        const int64_t left = tile < tile_end ? row_end - m0 : 0, rows = left < Sh::BM ? left : Sh::BM;
-        s.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(a + m0 * K), 0, (uint32_t)rows * row_bytes, 0x00020000);
+    auto start = [&](ChunkStream &s, uint32_t tile, const __bf16 *rows_at, int rows) {
+        s.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(rows_at), 0, (uint32_t)rows * row_bytes, 0x00020000);
         s.tile = tile;
         s.chunk = 0;
+        s.off = 0;
+        s.step = rows > 0 ? RB : 0;
+    };
+    auto tok_tile = [&](ChunkStream &s, uint32_t tile) {
+        const RowWindow r = row_window(row_begin, row_end, tile / ntn, Sh::BM, tile < tile_end);
+        start(s, tile, a + r.first * K, r.rows);
     };
     auto wgt_tile = [&](ChunkStream &s, uint32_t tile) {
-        const int n0 = (int)(tile % ntn) * Sh::BN, left = tile < tile_end ? N - n0 : 0, rows = left < Sh::BN ? left : Sh::BN;
-        s.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(w + (int64_t)n0 * K), 0, (uint32_t)rows * row_bytes, 0x00020000);
-        s.tile = tile;
-        s.chunk = 0;
+        const RowWindow r = row_window(0, N, tile % ntn, Sh::BN, tile < tile_end);
+        start(s, tile, w + r.first * K, r.rows);
     };
     ChunkStream ts, ws;
     tok_tile(ts, tile0);
@@ -187,18 +192,20 @@ __global__ __launch_bounds__(512, 2) void linear_rows_bf16_kernel(const __bf16 *
     auto next = [](int slot, int depth) { return slot + 1 == depth ? 0 : slot + 1; };
     auto fill_tok = [&](int n) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ts.rsrc, (LDS_AS void *)(lds + tslot * Sh::kTokTile + (wave + 8 * n) * 1024), 16,
-                                                 tok_off + n * fill_step, ts.chunk * RB, 0, 0);
+                                                 tok_off + n * fill_step, ts.off, 0, 0);
     };
     auto fill_wgt = [&](int n) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ws.rsrc, (LDS_AS void *)(lds + Sh::kWgtOff + wslot * Sh::kWgtTile + (wave + 8 * n) * 1024), 16,
-                                                 wgt_off + n * fill_step, ws.chunk * RB, 0, 0);
+                                                 wgt_off + n * fill_step, ws.off, 0, 0);
     };
     auto tok_done = [&]() {       // the chunk's fills are queued: on to the next one
         tslot = next(tslot, ST);
+        ts.off += ts.step;
         if (++ts.chunk == nchunks) tok_tile(ts, ts.tile + stride);
     };
     auto wgt_done = [&]() {
         wslot = next(wslot, SW);
+        ws.off += ws.step;
         if (++ws.chunk == nchunks) wgt_tile(ws, ws.tile + stride);
     };
 

@@ -2,6 +2,7 @@
 //   fwd S heads      -> rows order              order: 0 folded pairs, 1 longest first
 //   bwd S heads      -> rows, 1 if dK/dV and dQ go out in one launch, order of dK/dV, order of dQ
 //   lin rows K N     -> tokens and features of a tile
+//   window begin end tile tile_rows live -> first row and number of rows of a tile's buffer
 //   order rows order -> the order that a shape of that many rows works when asked for `order`
 #include "../paper_2407_12117_amd/csrc/launch_plan.h"
 
@@ -11,7 +12,8 @@
 int main()
 {
     char what[16];
-    long long a, b, c;
+    long long a, b, c, d;
+    int live;
     while (std::scanf("%15s %lld %lld", what, &a, &b) == 3) {
         if (!std::strcmp(what, "fwd")) {
             const memo::TileChoice &t = memo::fwd_plan(a, b);
@@ -24,6 +26,9 @@ int main()
         } else if (!std::strcmp(what, "lin") && std::scanf("%lld", &c) == 1) {
             const memo::LinChoice &l = memo::lin_plan(a, (int)b, (int)c);
             std::printf("%d %d\n", l.bm, l.bn);
+        } else if (!std::strcmp(what, "window") && std::scanf("%lld %lld %d", &c, &d, &live) == 3) {
+            const memo::RowWindow w = memo::row_window(a, b, c, (int)d, live);
+            std::printf("%lld %d\n", (long long)w.first, w.rows);
         } else {
             return 1;
         }

@@ -45,3 +45,17 @@ def test_backward_of_many_heads_keeps_the_folded_order(plans, S, heads):
 def test_backward_between_whole_rounds_stays_joint(plans, S, heads):
     rows, joint, k_order, q_order = plans([("bwd", S, heads)])[0]
     assert (rows, joint) == (256, 1) or (rows, k_order) == (256, LONGEST_FIRST)
+
+
+def test_projection_buffers_stay_inside_the_matrix(plans):
+    # every tile a workgroup may name: its own, and the ones behind its last, whose buffers are empty
+    for begin, end, tile_rows in ((0, 1, 64), (0, 64, 64), (130, 40001, 256), (7, 5000, 192), (4096, 4100, 128)):
+        tiles = (end - begin + tile_rows - 1) // tile_rows
+        ask = [("window", begin, end, t, tile_rows, int(t < tiles)) for t in range(tiles + 300)]
+        covered = 0
+        for (first, rows), (_, _, _, t, _, live) in zip(plans(ask), ask):
+            assert begin <= first < end and first + rows <= end and (rows > 0) == bool(live)
+            if live:
+                assert first == begin + t * tile_rows
+                covered += rows
+        assert covered == end - begin
