@@ -10,6 +10,7 @@ import torch
 
 from paper_2407_12117_amd import binding as mb
 from paper_2407_12117_amd import synth
+import shape_cases as shapes
 from gpu_util import LSE_MAX_ABS_BF16, assert_close, gpu_fwd_bwd, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -44,8 +45,8 @@ def test_fp32_ragged_and_small(oracle, B, S, H, d):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("S,heads", [(15, 2), (17, 70), (128, 3), (289, 24), (289, 64), (500, 100), (1025, 2)])
 def test_fp32_every_workgroup_shape(oracle, S, heads, d):
-    # 16- and 32-row workgroups (few and many heads), lengths on and off the 16-row tiles, fewer tiles than
-    # the wave groups that share them out
+    # few and many workgroups (all of them resident at once or not), lengths on and off their 16-row tiles, fewer tiles
+    # than the waves that share them out
     _dense_case(oracle, 1, S, heads, d, "f32", 900 + S + heads)
 
 
@@ -83,8 +84,9 @@ def test_bf16_multi_tile(oracle, B, S, H):
 
 
 def test_bf16_many_query_tiles_dense(oracle):
-    # every element of dK, dV compared where the dK/dV kernel's query loop runs up to 515 times
-    # (key tile 0) and the forward / dQ kernels walk up to 258 key tiles; ragged tail
+    # every element compared over a long sweep of one head, with a ragged tail: the 32-row forward (eight waves that
+    # take up to 65 key tiles each) and the 64-row joint backward (four query groups of up to 129 query tiles
+    # each beside dQ workgroups of four key groups)
     _dense_case(oracle, 1, 16461, 1, 128, "bf16", 333)
 
 
@@ -99,17 +101,35 @@ def test_bf16_every_workgroup_shape(oracle, S, heads):
     _dense_case(oracle, 1, S, heads, 128, "bf16", 7000 + S + heads, scaled=True)
 
 
-@pytest.mark.parametrize("S", [321, 352, 353, 383])
-def test_bf16_forward_64_row_edges(oracle, S):
-    # 48 heads of this length take the 64-row forward: one row, one block of rows, one more, all but one in the last
-    # tile, whose second block sees a key tile that the first does not
-    _dense_case(oracle, 1, S, 48, 128, "bf16", 9000 + S, scaled=True)
+@pytest.mark.parametrize("S,heads", shapes.FWD_64_EDGES)
+def test_bf16_forward_64_row_edges(oracle, S, heads):
+    # the 64-row forward with one row, one block of rows, one more and all but one in the last tile, whose second block
+    # sees a key tile that the first does not
+    _dense_case(oracle, 1, S, heads, 128, "bf16", 9000 + S, scaled=True)
 
 
-@pytest.mark.parametrize("S", [31, 32, 33, 257, 1000])
-def test_bf16_backward_32_row_edges(oracle, S):
-    # the 32-row backward: one tile and its neighbours, waves without a tile, a ragged last tile behind a whole sweep
-    _dense_case(oracle, 1, S, 3, 128, "bf16", 9100 + S)
+@pytest.mark.parametrize("S,heads", shapes.BWD_32_EDGES)
+def test_bf16_backward_32_row_edges(oracle, S, heads):
+    _dense_case(oracle, 1, S, heads, 128, "bf16", 9100 + S)
+
+
+@pytest.mark.parametrize("S,heads", list(shapes.BWD_LONG_SHAPES))
+def test_bf16_ragged_lengths_of_256_row_workgroups(oracle, S, heads):
+    # whole rounds of pairs (an even and an odd number of tiles, so that a pair may be one tile), one tile at a time, and both in
+    # one backward: the first, a middle and the last head compared in full
+    print(f"[case] ragged 256-row S={S} H={heads}", flush=True)
+    scale = synth.default_scale(128)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    q, k, v, g = (torch.randn((1, S, heads, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    got = gpu_fwd_bwd(q, k, v, g, scale)
+    for h in (0, heads // 2 - 1, heads - 1):
+        qf, kf, vf, gf = (to_f64(t[:, :, h:h + 1]) for t in (q, k, v, g))
+        ro, rlse = oracle.attn_fwd(qf, kf, vf, scale)
+        assert_close("O", to_f64(got[0][:, :, h:h + 1]), ro, "bf16")
+        assert np.abs(to_f64(got[1][:, h:h + 1]) - rlse).max() <= LSE_MAX_ABS_BF16
+        for name, x, r in zip(("dQ", "dK", "dV"), got[2:], oracle.attn_bwd(qf, kf, vf, gf, scale)):
+            assert_close(name, to_f64(x[:, :, h:h + 1]), r, "bf16", scaled=True)
 
 
 def test_bf16_scale_below_the_usual_one(oracle):
@@ -360,9 +380,9 @@ def test_fp32_large_scores(oracle, d):
         assert rel <= 2 ** -19 + 2 ** -22, f"{name}: rel_l2={rel:.2e}"
 
 
-# the 32-, 64-, 128-row forward and the 256-row ones in both orders; all lengths whole 32-row tiles
+# every shape of the forward; all lengths whole 32-row tiles
 @pytest.mark.parametrize("value", [-math.inf, float(torch.finfo(torch.bfloat16).min), -1e20, -1e9])
-@pytest.mark.parametrize("S,heads,tile", [(288, 9, 32), (320, 48, 32), (352, 48, 64), (704, 160, 64), (704, 100, 64)])
+@pytest.mark.parametrize("S,heads,tile", list(shapes.FWD_SHAPES))
 def test_bf16_masked_first_tiles(oracle, S, heads, tile, value):
     _key_mask_case(oracle, S, heads, 128, "bf16", value, tile, scaled=True)
 
@@ -388,9 +408,9 @@ def test_fp32_masked_keys_before_a_ragged_end(oracle, d):
     _key_mask_case(oracle, 300, 18, d, "f32", -math.inf, 16)
 
 
-@pytest.mark.parametrize("S,heads", [(300, 3), (1000, 4), (353, 48), (513, 64), (700, 160)])
+@pytest.mark.parametrize("S,heads", list(shapes.BWD_SHAPES))
 def test_bf16_masked_keys_before_a_ragged_end(oracle, S, heads):
-    # as above, in the 32-, 64-, 128- and 256-row backward
+    # as above, in every joint shape of the backward
     _key_mask_case(oracle, S, heads, 128, "bf16", -math.inf, 32, scaled=True)
 
 
@@ -446,3 +466,34 @@ def test_more_workgroups_than_one_launch_takes(dtype, d):
     dq, dk, dv = mb.memo_attn_bwd(x, x, x, o, lse, x, 0.125)
     # dP - D cancels but for the order of its sums: sqrt(d) roundings of 2^-24 of |v|^2 < 400, times scale |k| < 1
     assert torch.equal(dv, x) and dq.float().abs().max() <= 3e-4 and dk.float().abs().max() <= 3e-4
+
+
+def _far_rows(dtype, S, H, d, ss):
+    # rows `ss` elements apart, eight tensors side by side in them, against contiguous copies: the same bits
+    print(f"[case] rows far apart {dtype} S={S} H={H} d={d} stride {ss}", flush=True)
+    scale = synth.default_scale(d)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(1, S, H, d, dtype, seed=78))
+    o, lse = mb.memo_attn_fwd(q, k, v, scale)
+    grads = mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+    buf = torch.zeros((S - 1) * ss + 8 * H * d, dtype=q.dtype, device="cuda")
+    far = [torch.as_strided(buf, (1, S, H, d), (S * ss, ss, d, 1), n * H * d) for n in range(8)]
+    for dst, src in zip(far, (q, k, v, g)):
+        dst.copy_(src)
+    _, lse_far = mb.memo_attn_fwd(far[0], far[1], far[2], scale, o=far[4])
+    mb.memo_attn_bwd(far[0], far[1], far[2], far[4], lse_far, far[3], scale, dq=far[5], dk=far[6], dv=far[7])
+    assert torch.equal(far[4], o) and torch.equal(lse_far, lse)
+    for got, ref in zip(far[5:], grads):
+        assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("ss", [(1 << 25) + 4, (1 << 26) - 4])
+def test_fp32_rows_almost_too_far_for_a_buffer(d, ss):
+    # a 16-row tile spans 2 to 4 GiB: offsets above 2^31 in the fills
+    _far_rows("f32", 35, 1, d, ss)
+
+
+@pytest.mark.parametrize("S,heads", [(70, 1), (257, 48), (353, 48), (513, 64), (700, 160)])
+def test_bf16_rows_as_far_apart_as_accepted(S, heads):
+    # the largest row stride that is not refused: a 64-row tile spans 2 GiB, in every shape of both directions
+    _far_rows("bf16", S, heads, 128, 1 << 24)

@@ -15,6 +15,7 @@ from oracle import memo_recompute_oracle as ro
 from paper_2407_12117_amd import binding as mb
 
 import gpu_util as gu
+import shape_cases as shapes
 
 pytestmark = pytest.mark.gpu
 
@@ -63,10 +64,9 @@ def test_linear_matches_oracle(S, K, N, with_bias):
     gu.assert_close("linear", gu.to_f64(out), ref, "bf16")
 
 
-# sizes around the tile shapes the launcher chooses from: ragged rows, features that fill half a tile, an odd number
+# every tile shape the launcher chooses from: ragged rows, features that fill half a tile, an odd number
 # of K chunks, several tiles per workgroup (the chunk stream runs on from one tile to the next)
-@pytest.mark.parametrize("S,K,N,row_begin", [(65, 128, 128, 0), (257, 384, 384, 1), (700, 640, 640, 3), (2500, 256, 896, 0),
-                                              (5000, 384, 640, 7), (9000, 128, 1152, 0), (40001, 384, 640, 130)])
+@pytest.mark.parametrize("S,K,N,row_begin", list(shapes.LINEAR_SHAPES))
 def test_linear_tile_shapes_match_oracle(S, K, N, row_begin):
     print(f"[case] linear shapes S={S} K={K} N={N} rows=[{row_begin},{S})", flush=True)
     g = torch.Generator().manual_seed(S + K + N)

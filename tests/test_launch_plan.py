@@ -4,8 +4,10 @@ import subprocess
 
 import pytest
 
+import shape_cases as shapes
+from shape_cases import FOLDED, LONGEST_FIRST
+
 HERE = os.path.dirname(os.path.abspath(__file__))
-FOLDED, LONGEST_FIRST = 0, 1
 
 
 @pytest.fixture(scope="module")
@@ -59,3 +61,15 @@ def test_projection_buffers_stay_inside_the_matrix(plans):
                 assert first == begin + t * tile_rows
                 covered += rows
         assert covered == end - begin
+
+
+def test_gpu_tests_get_the_shapes_they_are_written_for(plans):
+    assert plans([("fwd", S, h) for S, h in shapes.FWD_64_EDGES]) == [(64, LONGEST_FIRST)] * len(shapes.FWD_64_EDGES)
+    assert [p[0] for p in plans([("bwd", S, h) for S, h in shapes.BWD_32_EDGES])] == [32] * len(shapes.BWD_32_EDGES)
+    assert plans([("fwd", S, h) for S, h, _ in shapes.FWD_SHAPES]) == list(shapes.FWD_SHAPES.values())
+    for table in (shapes.BWD_SHAPES, shapes.BWD_LONG_SHAPES):
+        assert plans([("bwd", S, h) for S, h in table]) == list(table.values())
+    assert plans([("lin", S - begin, K, N) for S, K, N, begin in shapes.LINEAR_SHAPES]) == list(shapes.LINEAR_SHAPES.values())
+    # every shape that there is has its case
+    assert {rows for rows, _ in shapes.FWD_SHAPES.values()} == {32, 64, 128, 256}
+    assert set(shapes.LINEAR_SHAPES.values()) == {(64, 64), (128, 64), (128, 128), (192, 128), (256, 128), (256, 256)}
