@@ -44,6 +44,21 @@ inline int64_t order_grid(int64_t ntiles, int64_t heads, int order)
     return ((ntiles + 1) / 2 * heads + round - 1) / round * round;
 }
 
+// What a launch loses longest first when an XCD works many heads at a time.  Heads run fastest and workgroups are dealt
+// round-robin, so an XCD meets heads / gcd(heads, 8) different ones, up to one per unit, and its L2 serves the fewer units
+// the more heads it holds; folded chunks keep an XCD on one or two.  It costs nothing while the rows (1 KB of Q, K, V and dO
+// each) are few enough for the cache behind the L2s, and grows with the doublings of the heads beyond that.  Measured,
+// us, longest first against folded pairs.  Backward, one joint launch: S = 8192, 64 heads 3128 : 3052, 128 heads 6722 : 6272,
+// 256 heads 14358 : 12799; S = 50000, 5 heads 8649 : 8290; but S = 4096, 32 heads 423 : 430, S = 25000, 8 heads (one per XCD)
+// 3358 : 4221.  Forward: S = 400000, 5 heads 179997 : 173781, 4 heads (one) 137131 : 140589.
+inline constexpr double kCrowdRows = 180e3;
+inline double crowding(int64_t S, int64_t heads)
+{
+    const double met = (double)std::min<int64_t>(kChunk, heads / std::gcd(heads, (int64_t)kXcds));
+    return std::log2(met) * std::max(0.0, 1.0 - kCrowdRows / ((double)S * heads));
+}
+inline constexpr double kCrowdedJoint = 0.08, kCrowdedAlone = 0.02;       // of the time, per doubling; 256-row launches of one kernel lose less
+
 // One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
 // 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
 // and after its sweep.
@@ -53,7 +68,7 @@ struct TileChoice { int rows, order; double us_per_mpair, us_per_item; };
 // tiles an XCD gets have lengths n, n-1, .. 1 (in units of ntiles / n tiles); the first 32 start
 // together, the next 32 go to the units that end first, so that two layers add up to equal sums, and
 // what remains after whole double layers ends with the longest remaining tile.
-inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads)
+inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads, double crowded = kCrowdedAlone)
 {
     const int64_t ntiles = (S + c.rows - 1) / c.rows;
     const double mpairs = (double)c.rows * c.rows / (1 << 20);            // a tile unit: rows x rows
@@ -65,7 +80,7 @@ inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads)
     double makespan = 2 * n * j - 2 * P * j * j + j + n - 2 * P * j;
     if (n < 1) makespan = 1;                                              // fewer tiles than XCDs
     const double busy = n < P ? n / P : 1.0;                              // a partly idle chip clocks higher
-    return makespan * (ntiles / (n < 1 ? 1 : n)) * mpairs * c.us_per_mpair * (0.8 + 0.2 * busy) +
+    return makespan * (ntiles / (n < 1 ? 1 : n)) * mpairs * c.us_per_mpair * (0.8 + 0.2 * busy) * (1.0 + crowded * crowding(S, heads)) +
            std::ceil(n / P) * c.us_per_item;
 }
 
@@ -83,20 +98,6 @@ inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t hea
     }
     return best;
 }
-
-// What the backward loses longest first when an XCD works many heads at a time.  Heads run fastest and workgroups are dealt
-// round-robin, so an XCD meets heads / gcd(heads, 8) different ones, up to one per unit, and its L2 serves the fewer units
-// the more heads it holds; folded chunks keep an XCD on one or two.  It costs nothing while the Q, K, V and dO rows (1 KB a row
-// in all) are few enough for the cache behind the L2s, and grows with the doublings of the heads beyond that.  Measured,
-// one joint launch against a pair of folded ones, us: S = 8192, 64 heads 3128 : 3052, 128 heads 6722 : 6272, 256 heads
-// 14358 : 12799; S = 50000, 5 heads 8649 : 8290; but S = 4096, 32 heads (2^17 rows) 423 : 430, S = 25000, 8 heads (one per
-// XCD) 3358 : 4221.
-inline double crowding(int64_t S, int64_t heads)
-{
-    const double met = (double)std::min<int64_t>(kChunk, heads / std::gcd(heads, (int64_t)kXcds));
-    return std::log2(met) * std::max(0.0, 1.0 - (double)(1 << 17) / ((double)S * heads));
-}
-inline constexpr double kCrowdedJoint = 0.06, kCrowdedAlone = 0.015;      // of the time, per doubling; 256-row launches of one kernel lose less
 
 // Estimated time of one launch that works the key tiles k and then the query tiles q, each longest first: all
 // work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
@@ -116,7 +117,9 @@ constexpr int tile_order(int rows, int order) { return rows == 256 ? order : kLo
 
 // ---- bf16 forward
 // Costs fitted to launches of every variant (N(0,1) inputs, S = 200 .. 200K, 1 to 10 heads): over 40 random
-// (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst.
+// (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst; over 36 sizes of 2048 to
+// 400000 rows and 2 to 256 heads 0.3 % and, at S = 40000 with 5 heads (128 rows for 256), 4.6 %.  The worst are sizes
+// of less than a round of workgroups and a few heads (S = 3000, 16 heads: 64 rows for 128, 19 %).
 inline constexpr TileChoice kFwdChoices[] = {
     {256, kFolded, 115.5, 4.0}, {256, kLongestFirst, 117.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
     {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
@@ -151,16 +154,10 @@ struct BwdPlan { int rows; bool joint; int k_order, q_order; };
 // without `crowding`).
 inline BwdPlan bwd_plan(int64_t S, int64_t heads)
 {
-    const double crowd = crowding(S, heads);
-    auto alone_us = [&](const TileChoice &c) {
-        TileChoice t = c;
-        if (c.order == kLongestFirst) t.us_per_mpair *= 1.0 + (c.rows == 256 ? kCrowdedAlone : kCrowdedJoint) * crowd;
-        return tile_choice_us(t, S, heads);
-    };
     BwdPlan best = {256, false, kFolded, kFolded};
     double best_us = 0;
     for (auto [choices, order] : {std::make_pair(kDkdvChoices, &best.k_order), std::make_pair(kDqChoices, &best.q_order)}) {
-        const double folded = alone_us(choices[0]), longest_first = alone_us(choices[1]);
+        const double folded = tile_choice_us(choices[0], S, heads), longest_first = tile_choice_us(choices[1], S, heads);
         *order = longest_first < folded ? kLongestFirst : kFolded;
         best_us += std::min(folded, longest_first);
     }
@@ -170,7 +167,7 @@ inline BwdPlan bwd_plan(int64_t S, int64_t heads)
         best_us = us;
     };
     // apart: S = 32768, 2 heads 1508 us against 1565 joint (two long sweeps per unit either way); nowhere else
-    offer(128, false, alone_us(kDkdvChoices[2]) + alone_us(kDqChoices[2]));
+    offer(128, false, tile_choice_us(kDkdvChoices[2], S, heads, kCrowdedJoint) + tile_choice_us(kDqChoices[2], S, heads, kCrowdedJoint));
     for (int n = 1; n < 4; ++n) offer(kDkdvChoices[n].rows, true, both_us(kDkdvChoices[n], kDqChoices[n], S, heads));
     offer(32, true, own_us(S, heads));
     return best;

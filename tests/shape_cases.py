@@ -19,7 +19,7 @@ BWD_SHAPES = {(300, 3): (32, 1, LONGEST_FIRST, LONGEST_FIRST), (1000, 4): (32, 1
               (700, 160): (256, 1, LONGEST_FIRST, LONGEST_FIRST)}
 
 # the same for the longer sequences that work 256 rows, an even and an odd number of tiles
-BWD_LONG_SHAPES = {(8155, 16): (256, 0, FOLDED, FOLDED), (7773, 48): (256, 0, FOLDED, FOLDED), (7914, 32): (256, 0, LONGEST_FIRST, FOLDED),
+BWD_LONG_SHAPES = {(8155, 16): (256, 0, FOLDED, FOLDED), (7773, 48): (256, 0, FOLDED, FOLDED), (5799, 64): (256, 0, LONGEST_FIRST, FOLDED),
                    (5611, 64): (256, 0, LONGEST_FIRST, LONGEST_FIRST),
                    (4248, 20): (256, 1, LONGEST_FIRST, LONGEST_FIRST)}
 

@@ -41,6 +41,16 @@ def test_backward_of_many_heads_keeps_the_folded_order(plans, S, heads):
     assert plans([("bwd", S, heads)]) == [(256, 0, FOLDED, FOLDED)]
 
 
+@pytest.mark.parametrize("S,heads", [(50000, 5), (200000, 5), (400000, 5), (25000, 10), (131072, 5), (4096, 96)])
+def test_forward_of_five_heads_keeps_the_folded_order(plans, S, heads):
+    assert plans([("fwd", S, heads)]) == [(256, FOLDED)]
+
+
+@pytest.mark.parametrize("S,heads", [(65536, 5), (81920, 5), (98304, 5), (40000, 10), (150000, 4), (400000, 4), (250000, 2)])
+def test_forward_between_whole_rounds_stays_longest_first(plans, S, heads):
+    assert plans([("fwd", S, heads)]) == [(256, LONGEST_FIRST)]
+
+
 # and faster
 @pytest.mark.parametrize("S,heads", [(2048, 96), (3000, 48), (4096, 48), (6000, 32), (12288, 16), (16384, 10), (25000, 8), (32768, 5), (50000, 4),
                                      (50000, 8), (65536, 5), (150000, 3)])
