@@ -50,16 +50,18 @@ typedef enum { MEMO_F32 = 0, MEMO_BF16 = 1 } memo_dtype;
  *            MEMO_F32 with d in {64, 128} (fp32 throughout).
  * S may be any positive length (ragged last tile is handled); causal must be 1.
  * Rows must be 16-byte aligned: base pointers 16-byte aligned and strides a
- * multiple of 8 (bf16) or 4 (fp32) elements.  MEMO_BF16: stride_s <= 2^24 elements and
- * about S * H * B < 2^40 (one workgroup per pair of 256-row tiles, in chunks of 32 pairs per head
- * rounded up to 8 chunks, must fit a 2^31 grid); MEMO_ERR_UNSUPPORTED otherwise.
+ * multiple of 8 (bf16) or 4 (fp32) elements.  MEMO_BF16: stride_s <= 2^24 elements and at most
+ * about 2^26 stretches of 16384 rows, ceil(S / 16384) * H * B, so that the workgroups fit a 2^31
+ * grid; MEMO_ERR_UNSUPPORTED otherwise.
  * Non-finite inputs: the kernels keep IEEE semantics, so a NaN or an infinity in q, k, v or d_o
  * reaches every output element that depends on it: a NaN in key row j makes o, lse, dq of all
  * query rows i >= j non-finite and, through them, all of dk and dv of that head.  It may also
  * reach rows that only share a tile with row j (masked probabilities are zeros that still meet
  * the NaN inside a contraction): rows within the same 256-row block.  Rows outside that block
  * that do not depend on the value, other heads and other batch entries are bit-identical to a
- * run without it.
+ * run without it.  A score of -inf or a large negative one (a key mask carried in a column of q and
+ * k) weighs zero beside the other scores of its row.  The o of a row that sees nothing but scores of
+ * -inf is NaN; so it is in MEMO_BF16 where all of them are below -2^31 once scaled.
  */
 typedef struct {
     int32_t B, H, d;

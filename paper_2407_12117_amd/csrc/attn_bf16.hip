@@ -22,7 +22,7 @@
 // transpose load ds_read_b64_tr_b16 (two per operand: rows 4*half+0..3 and 8+4*half+0..3).
 // All operand reads are issued by hand several MFMAs ahead (see lds_pipeline_* below).
 //
-// LDS tiles are 64 rows x 128 bf16, row-major, 256 bytes per row, no padding; the sixteen
+// LDS tiles are 64 or 32 rows x 128 bf16, row-major, 256 bytes per row, no padding; the sixteen
 // 16-byte chunks of row r are stored at chunk position  c ^ swz(r),
 //   swz(r) = ((r & 3) << 2) | ((r >> 2) & 3),
 // which makes both access patterns bank-conflict free: 16 lanes reading the same chunk of
@@ -45,8 +45,8 @@ namespace {
 //           buffer, whose K half is refilled while V is worked and the other way round.
 // A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
 // last row: what bounds it is the longest workgroup, which QG = 1 makes 64 times shorter.  The launcher
-// takes the cheapest by estimate (kFwdChoices).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 8.7,
-// B = 2 S = 2000 H = 3 67.8 -> 19.2, S = 8192 H = 4 250 -> 79, S = 16461 H = 4 482 -> 269, S = 40000 H = 4 2202 -> 1516.
+// takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 8.7,
+// B = 2 S = 2000 H = 3 67.8 -> 18.4, S = 8192 H = 4 250 -> 79, S = 16461 H = 4 482 -> 265, S = 40000 H = 4 2202 -> 1516.
 // The fills address a tile as a buffer (TileOffsets::fill): no per-lane pointers to step and no second path for the
 // ragged last tile, 1 to 3 % of every shape.
 constexpr int kFwdWaves = 8;                 // waves per workgroup

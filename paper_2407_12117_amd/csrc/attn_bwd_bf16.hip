@@ -558,7 +558,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, 
 // For short sequences: 32 keys (or query rows) per workgroup, the other side of the sweep in eight.  Every wave works all 32
 // rows against 32-row tiles of its own, one buffer each, so there is no barrier in the sweep; a half of the buffer
 // is refilled as soon as it is used up.  The sums meet in LDS at the end.  Twice the fill traffic of 64-row workgroups, and
-// sweeps of half the steps: ahead where the longest sweep, not the work, is what a launch takes (own_us below).  us, 64-row
+// sweeps of half the steps: ahead where the longest sweep, not the work, is what a launch takes (own_us, launch_plan.h).  us, 64-row
 // workgroups -> these: S = 1000 H = 4 20.5 -> 15.4, S = 1500 H = 4 26.4 -> 22.5, S = 2500 H = 2 37.6 -> 25.1, S = 640 H = 2
 // 16.1 -> 15.3; but S = 2000, 6 heads 36.2 -> 45.9, S = 8192 H = 4 227 -> 259.
 constexpr int kOwnTile = 32 * 256, kOwnRing = 8 * 2 * kOwnTile;

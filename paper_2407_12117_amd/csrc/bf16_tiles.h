@@ -1,6 +1,6 @@
-// Building blocks shared by the bf16 MFMA kernels (gfx950): vector types, the 32x32x16 MFMA
-// wrapper, the swizzled 64-row x 256-byte LDS tile and its per-lane addresses, asynchronous
-// global -> LDS tile fills, and hand-issued, software-pipelined LDS operand reads.
+// Building blocks shared by the MFMA kernels (gfx950): vector types, MFMA wrappers, the swizzled LDS tile of
+// 256-byte rows and its per-lane addresses, asynchronous global -> LDS tile fills, hand-issued,
+// software-pipelined LDS operand reads, and the launch of a grid of workgroups.
 // Included by the kernel sources only; everything has internal linkage.
 #pragma once
 #include "launch_plan.h"
@@ -22,7 +22,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 #define LDS_AS __attribute__((address_space(3)))
 #define GLB_AS __attribute__((address_space(1)))
 
-constexpr int kTileBytes = 64 * 256;   // one 64 x 128 bf16 tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -36,7 +35,7 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Chunk swizzles of the 64-row x 256-byte LDS tile: the sixteen 16-byte chunks of row r are
+// Chunk swizzles of an LDS tile of 256-byte rows: the sixteen 16-byte chunks of row r are
 // stored at chunk position c ^ f(r), f of period 16 in r.  SwzA serves the 32x32x16 kernels
 // (lane 32*half + l32 reading chunk 2*kc + half of row l32; 32 lanes reading 4 rows x 64 bytes
 // transposed).  SwzB serves the 16x16x32 kernels (lane 16*g4 + l16 reading chunk 4*ks + g4 of row

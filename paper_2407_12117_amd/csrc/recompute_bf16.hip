@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void layernorm_rows_bf16_kernel(const __bf16 *
 // stores of the one before.
 //
 // What bounds it: a 256 x 256 tile is worked at the rate the MFMAs sustain under the power limit, within a tenth; short
-// launches are bound by how few tiles there are, so that the tile shrinks with the work (kLinChoices), and the smallest
+// launches are bound by how few tiles there are, so that the tile shrinks with the work (launch_plan.h), and the smallest
 // by the latency of a chunk: barrier, operand reads, MFMAs.  Steps of the 256 x 256 shape at 138937 x 4096 -> 1536:
 // one barrier, the fills and the wait for the operands in front of every chunk's MFMAs 1531 us; operands and fills a
 // chunk ahead as described at `phase` 1370; stream not stopped between tiles, 16-byte stores 1309.
