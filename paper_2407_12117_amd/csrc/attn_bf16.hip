@@ -78,7 +78,7 @@ __device__ __forceinline__ void lds_wait(KqSlot<2> &x)
 }
 
 template <int QG, int T>
-__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int fold, uint32_t first)
+__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int fold)
 {
     constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = T, JB = T / 32;
     constexpr int kTile = T * 256;              // bytes of one K or V tile
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const int wq = wave % QG, grp = wave / QG;  // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
     const int order = tile_order(kBq, fold);
-    const PairId t = decode_block(a, first + blockIdx.x, nqt, order, true);
+    const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
 // there is no barrier in the sweep and a K or V operand read feeds two MFMAs.  Q stays in LDS: the accumulators of 64
 // rows leave no registers for it.  Bound, like all shapes below 256 rows, by what it streams per MFMA: as many bytes as
 // two waves per 32-key tile behind a barrier did, which ran at 885 TFLOP/s on a full chip (S = 8192, H = 4: 87 -> 79 us).
-__global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(AttnArgs a, uint32_t first)
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(AttnArgs a)
 {
     constexpr int kBq = 64, T = 32, kTile = T * 256, kQ = kFwdWaves * 2 * kTile, kStats = kQ + kBq * 256;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kFwdWaves * kBq * 8];
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const LaneAddr la = make_lane_addr(lane);
-    const PairId t = decode_block(a, first + blockIdx.x, (a.S + kBq - 1) / kBq, kLongestFirst, true);
+    const PairId t = decode_block(a, blockIdx.x, (a.S + kBq - 1) / kBq, kLongestFirst, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
     const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
@@ -517,31 +517,21 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
     }
 }
 
-hipError_t launch_fwd_own(const AttnArgs &a, hipStream_t st)
-{
-    const int64_t blocks = order_grid((a.S + 63) / 64, (int64_t)a.H * a.B, kLongestFirst);
-    return launch_blocks(attn_fwd_bf16_own_kernel, 0, blocks, st, a);
-}
-
 }  // namespace
-
-template <int QG, int T>
-hipError_t launch_fwd(const AttnArgs &a, int order, hipStream_t st)
-{
-    order = tile_order(32 * QG, order);               // as in the kernel
-    const int64_t nqt = (a.S + 32 * QG - 1) / (32 * QG);
-    const int64_t blocks = order_grid(nqt, (int64_t)a.H * a.B, order);
-    return launch_blocks(attn_fwd_bf16_kernel<QG, T>, 0, blocks, st, a, order);
-}
 
 hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
 {
-    const TileChoice &c = fwd_plan(a.S, (int64_t)a.H * a.B);
+    const int64_t heads = (int64_t)a.H * a.B;
+    const TileChoice &c = fwd_plan(a.S, heads);
+    const int order = tile_order(c.rows, c.order);    // as in the kernel
+    const int64_t blocks = order_grid((a.S + c.rows - 1) / c.rows, heads, order);
+    if (blocks > kMaxBlocks)
+        return launch_fewer_heads(a, sizeof(__bf16), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_attn_fwd_bf16(part, st); });
     switch (c.rows) {
-    case 32: return launch_fwd<1, 32>(a, c.order, st);
-    case 64: return launch_fwd_own(a, st);
-    case 128: return launch_fwd<4, 64>(a, c.order, st);
-    default: return launch_fwd<8, 64>(a, c.order, st);
+    case 32: return launch_blocks(attn_fwd_bf16_kernel<1, 32>, blocks, st, a, order);
+    case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a);
+    case 128: return launch_blocks(attn_fwd_bf16_kernel<4, 64>, blocks, st, a, order);
+    default: return launch_blocks(attn_fwd_bf16_kernel<8, 64>, blocks, st, a, order);
     }
 }
 

@@ -237,10 +237,10 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     }   // pass
 }
 
-__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order, uint32_t first)
+__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<8, 64>::kLds];
-    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, first + blockIdx.x, order);
+    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
 }
 
 // ============================================================================ backward: dK, dV
@@ -535,23 +535,22 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     }   // pass
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order, uint32_t first)
+__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<8>::kLds];
-    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, first + blockIdx.x, order);
+    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
 }
 
 // both gradients in one launch, longest tiles first: the first `dkdv_blocks` workgroups are the key-stationary
-// ones, the others the query-stationary ones.  The launch starts at workgroup `first`
+// ones, the others the query-stationary ones
 template <int KG, int QG, int T>
-__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks, uint32_t first)
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
 {
     constexpr int kLds = DkdvShape<KG>::kLds > DqShape<QG, T>::kLds ? DkdvShape<KG>::kLds : DqShape<QG, T>::kLds;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    const uint32_t id = first + blockIdx.x;
-    if (id < dkdv_blocks) dkdv_rows<KG>(a, lds, id, kLongestFirst);
-    else dq_rows<QG, T>(a, lds, id - dkdv_blocks, kLongestFirst);
+    if (blockIdx.x < dkdv_blocks) dkdv_rows<KG>(a, lds, blockIdx.x, kLongestFirst);
+    else dq_rows<QG, T>(a, lds, blockIdx.x - dkdv_blocks, kLongestFirst);
 }
 
 // ============================================================================ backward, 32-row workgroups
@@ -833,74 +832,64 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
     });
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks, uint32_t first)
+__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    const uint32_t id = first + blockIdx.x;
-    if (id < dkdv_blocks) dkdv_own_rows(a, lds, id);
-    else dq_own_rows(a, lds, id - dkdv_blocks);
+    if (blockIdx.x < dkdv_blocks) dkdv_own_rows(a, lds, blockIdx.x);
+    else dq_own_rows(a, lds, blockIdx.x - dkdv_blocks);
 }
 
-// nk key-stationary workgroups and nq query-stationary ones, in one launch or, `apart`, the ones after the others with the
-// stage event between them
-hipError_t launch_joint(void (*kernel)(AttnArgs, uint32_t, uint32_t), const AttnArgs &a, int64_t nk, int64_t nq, bool apart, hipStream_t st)
+// dkdv, dq: which of the gradients to launch; both in one launch where the plan says so
+hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 {
-    hipError_t e = launch_blocks(kernel, 0, apart ? nk : nk + nq, st, a, (uint32_t)nk);
-    if (!apart || e != hipSuccess) return e;
-    if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
-    return launch_blocks(kernel, nk, nk + nq, st, a, (uint32_t)nk);
-}
-
-hipError_t launch_bwd_own(const AttnArgs &a, bool apart, hipStream_t st)
-{
-    const int64_t n = order_grid((a.S + 31) / 32, (int64_t)a.H * a.B, kLongestFirst);
-    return launch_joint(attn_bwd_own_bf16_kernel, a, n, n, apart, st);
-}
-
-// one of the two kernels alone, 256 rows
-hipError_t launch_alone(void (*kernel)(AttnArgs, int, uint32_t), const AttnArgs &a, int order, hipStream_t st)
-{
-    const int64_t blocks = order_grid((a.S + 255) / 256, (int64_t)a.H * a.B, order);
-    return launch_blocks(kernel, 0, blocks, st, a, order);
-}
-
-template <int KG, int QG, int T>
-hipError_t launch_both(const AttnArgs &a, bool apart, hipStream_t st)
-{
-    const int64_t hb = (int64_t)a.H * a.B;
-    const int64_t nk = order_grid((a.S + 32 * KG - 1) / (32 * KG), hb, kLongestFirst);
-    const int64_t nq = order_grid((a.S + 32 * QG - 1) / (32 * QG), hb, kLongestFirst);
-    return launch_joint(attn_bwd_both_bf16_kernel<KG, QG, T>, a, nk, nq, apart, st);
+    const int64_t heads = (int64_t)a.H * a.B;
+    const BwdPlan p = bwd_plan(a.S, heads);
+    const bool joint = p.joint || p.rows < 256;       // one kernel for both kinds of workgroup
+    const int64_t tiles = (a.S + p.rows - 1) / p.rows;
+    const int64_t nk = order_grid(tiles, heads, p.k_order), nq = order_grid(tiles, heads, p.q_order);
+    const int64_t most = joint ? nk + nq : std::max(nk, nq);          // whatever is asked for, so that the parts are the same
+    if (most > kMaxBlocks)
+        return launch_fewer_heads(a, sizeof(__bf16), most, kMaxBlocks, [&](const AttnArgs &part) { return launch_main(part, dkdv, dq, st); });
+    hipError_t e = hipSuccess;
+    if (!joint) {
+        if (dkdv) e = launch_blocks(attn_bwd_dkdv_bf16_kernel, nk, st, a, p.k_order);
+        if (dq && e == hipSuccess) e = launch_blocks(attn_bwd_dq_bf16_kernel, nq, st, a, p.q_order);
+        return e;
+    }
+    if (dkdv && dq && !p.joint) {
+        e = launch_main(a, true, false, st);
+        return e == hipSuccess ? launch_main(a, false, true, st) : e;
+    }
+    const uint32_t dkdv_blocks = dkdv ? (uint32_t)nk : 0;
+    const int64_t blocks = dkdv_blocks + (dq ? nq : 0);
+    switch (p.rows) {
+    case 32: return launch_blocks(attn_bwd_own_bf16_kernel, blocks, st, a, dkdv_blocks);
+    case 64: return launch_blocks(attn_bwd_both_bf16_kernel<2, 2, 32>, blocks, st, a, dkdv_blocks);
+    case 128: return launch_blocks(attn_bwd_both_bf16_kernel<4, 4, 64>, blocks, st, a, dkdv_blocks);
+    default: return launch_blocks(attn_bwd_both_bf16_kernel<8, 8, 64>, blocks, st, a, dkdv_blocks);
+    }
 }
 
 }  // namespace
 
 // D_i preprocess, then dK, dV and dQ: in one launch of 32-, 64-, 128- or 256-row workgroups, or, where whole rounds
-// of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch fills the chip where neither kernel does alone (S = 2000, 6
-// heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups, 207 as two launches of 256-row pairs) and lets the dQ
-// tiles run in the tail of the dK/dV ones (S = 16461, H = 4: 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us);
-// two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 27.8 + 18.8 against 47.3 ms).
+// of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch
+// fills the chip where neither kernel does alone (S = 2000, 6 heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups,
+// 207 as two launches of 256-row pairs) and lets the dQ tiles run in the tail of the dK/dV ones (S = 16461, H = 4:
+// 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us); two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 27.8 + 18.8 against 47.3 ms).
 // A joint launch goes out in two parts, with the same bits, where dQ takes the place of Q or dO, which all key-stationary
 // workgroups read, and where an event between the stages is asked for.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)
 {
-    const BwdPlan p = bwd_plan(a.S, (int64_t)a.H * a.B);
     hipError_t e = record_stage(a, 0, st);
     if (e != hipSuccess) return e;
     if ((e = launch_attn_delta(a, true, st)) != hipSuccess) return e;
     if ((e = record_stage(a, 1, st)) != hipSuccess) return e;
-    const bool apart = !p.joint || a.stage_events || dq_in_place(a);
-    if (p.rows == 32) e = launch_bwd_own(a, apart, st);
-    else if (p.rows == 64) e = launch_both<2, 2, 32>(a, apart, st);
-    else if (p.rows == 128) e = launch_both<4, 4, 64>(a, apart, st);
-    else if (p.joint) e = launch_both<8, 8, 64>(a, apart, st);
-    else {
-        if ((e = launch_alone(attn_bwd_dkdv_bf16_kernel, a, p.k_order, st)) != hipSuccess) return e;
-        if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
-        e = launch_alone(attn_bwd_dq_bf16_kernel, a, p.q_order, st);
-    }
-    if (e != hipSuccess) return e;
+    if (!a.stage_events && !dq_in_place(a)) return launch_main(a, true, true, st);
+    if ((e = launch_main(a, true, false, st)) != hipSuccess) return e;
+    if ((e = record_stage(a, 2, st)) != hipSuccess) return e;
+    if ((e = launch_main(a, false, true, st)) != hipSuccess) return e;
     return record_stage(a, 3, st);
 }
 

@@ -205,7 +205,7 @@ __device__ __forceinline__ f32x4 f32_piece(const f32x4 (&acc)[D / 16], int p)
 }
 
 template <int D, bool FAR>
-__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(AttnArgs a, uint32_t first)
+__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(AttnArgs a)
 {
     using Shape = F32Shape<D>;
     constexpr int KS = kF32Waves, NP = Shape::kPieces;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, then (maximum, sum) per wave and row
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const PairId t = decode_block(a, first + blockIdx.x, (a.S + kT - 1) / kT, kLongestFirst, true);
+    const PairId t = decode_block(a, blockIdx.x, (a.S + kT - 1) / kT, kLongestFirst, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const float *k = static_cast<const float *>(a.k) + base, *v = static_cast<const float *>(a.v) + base;
     const int64_t row0 = t.first * kT, i = row0 + l16;
@@ -471,13 +471,13 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
 // of a rank and the query tile of the same rank, and the query tiles go shortest first to even that out
 // (S = 2000, H = 2: 66 us both longest first).
 template <int D, bool FAR>
-__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t dkdv_blocks, bool resident, uint32_t first)
+__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t dkdv_blocks)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D>::kRing];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    const uint32_t id = first + blockIdx.x;
-    if (id < dkdv_blocks) f32_dkdv_rows<D, FAR>(a, lds, id);
-    else f32_dq_rows<D, FAR>(a, lds, id - dkdv_blocks, !resident);
+    const bool resident = D == 64 && gridDim.x <= 2 * kXcds * kChunk;
+    if (blockIdx.x < dkdv_blocks) f32_dkdv_rows<D, FAR>(a, lds, blockIdx.x);
+    else f32_dq_rows<D, FAR>(a, lds, blockIdx.x - dkdv_blocks, !resident);
 }
 
 // D_i = sum_c dO_ic O_ic.  16 lanes per row, 16 rows per 256-thread workgroup.
@@ -513,16 +513,19 @@ template <int D, bool FAR>
 hipError_t launch_fwd_f32(const AttnArgs &a, hipStream_t st)
 {
     const int64_t blocks = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst);
-    return launch_blocks(attn_fwd_f32_kernel<D, FAR>, 0, blocks, st, a);
+    if (blocks > kMaxBlocks)
+        return launch_fewer_heads(a, sizeof(float), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_fwd_f32<D, FAR>(part, st); });
+    return launch_blocks(attn_fwd_f32_kernel<D, FAR>, blocks, st, a);
 }
 
 // dkdv, dq: which of the two to launch
 template <int D, bool FAR>
 hipError_t launch_bwd_f32(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 {
-    const int64_t n = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst);
-    const bool resident = D == 64 && n * (dkdv + dq) <= 2 * kXcds * kChunk;
-    return launch_blocks(attn_bwd_f32_kernel<D, FAR>, 0, n * (dkdv + dq), st, a, dkdv ? (uint32_t)n : 0u, resident);
+    const int64_t n = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst), blocks = n * (dkdv + dq);
+    if (blocks > kMaxBlocks)
+        return launch_fewer_heads(a, sizeof(float), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_bwd_f32<D, FAR>(part, dkdv, dq, st); });
+    return launch_blocks(attn_bwd_f32_kernel<D, FAR>, blocks, st, a, dkdv ? (uint32_t)n : 0u);
 }
 
 }  // namespace

@@ -1,6 +1,6 @@
 // Building blocks shared by the MFMA kernels (gfx950): vector types, MFMA wrappers, the swizzled LDS tile of
 // 256-byte rows and its per-lane addresses, asynchronous global -> LDS tile fills, hand-issued,
-// software-pipelined LDS operand reads, and the launch of a grid of workgroups.
+// software-pipelined LDS operand reads.
 // Included by the kernel sources only; everything has internal linkage.
 #pragma once
 #include "launch_plan.h"
@@ -167,26 +167,18 @@ __device__ __forceinline__ void store_acc_T(__bf16 *out_row, const f32x16 (&acc)
 // a workgroup's work (launch_plan.h)
 struct PairId { int64_t first, second; int h, b; };   // first < 0: nothing to do; second < 0: one tile only
 
-// Launches the workgroups [begin, end) of a grid; the kernel adds its last argument, the first workgroup of the launch, to its
-// id.  A launch holds fewer than 2^32 threads (a longer one runs in part, without an error), so a longer grid goes out in
-// parts, of whole rounds so that the XCDs are dealt the same workgroups.
+// Launches `blocks` workgroups of 512 threads.
 template <typename... P, typename... A>
-hipError_t launch_blocks(void (*kernel)(P...), int64_t begin, int64_t end, hipStream_t st, const A &...args)
+hipError_t launch_blocks(void (*kernel)(P...), int64_t blocks, hipStream_t st, const A &...args)
 {
-    constexpr int64_t kThreads = 512, kPart = (int64_t)1 << 22;
-    static_assert(kPart * kThreads < (int64_t)1 << 32 && kPart % (kXcds * kChunk) == 0, "a part is a launch of whole rounds");
-    if (end > kMaxBlocks) return hipErrorInvalidValue;
-    for (int64_t first = begin; first < end; first += kPart) {
-        kernel<<<dim3((unsigned)std::min(kPart, end - first)), kThreads, 0, st>>>(args..., (uint32_t)first);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (blocks > kMaxBlocks) return hipErrorInvalidValue;
+    kernel<<<dim3((unsigned)blocks), kThreads, 0, st>>>(args...);
+    return hipGetLastError();
 }
 
 __device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, int64_t ntiles, int order, bool last_is_longest)
 {
-    // a grid is below 2^31 workgroups (kMaxBlocks): 32-bit divisions (a 64-bit one is a hundred instructions of start-up)
+    // a grid is below 2^31 workgroups: 32-bit divisions (a 64-bit one is a hundred instructions of start-up)
     const uint32_t heads = (uint32_t)a.H * (uint32_t)a.B;
     PairId t;
     uint32_t hbi;

@@ -35,7 +35,8 @@ inline constexpr int kXcds = 8, kChunk = 32;   // XCDs per device; compute units
 // than folded (S = 128K: 14.84 against 14.59 ms), because the units of an XCD no longer sweep together.
 enum BlockOrder { kFolded = 0, kLongestFirst = 1 };
 
-inline constexpr int64_t kMaxBlocks = 0x7fffffff;     // workgroup ids are decoded in 32 bits
+// Every workgroup has 512 threads, and a HIP launch takes fewer than 2^32 of them: a longer grid would run in part, without an error.
+inline constexpr int64_t kThreads = 512, kMaxBlocks = ((int64_t)1 << 32) / kThreads - 1;
 
 inline int64_t order_grid(int64_t ntiles, int64_t heads, int order)
 {

@@ -2,7 +2,10 @@
 // Not installed; the public contract is include/memo.h.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
+
+#include <initializer_list>
 
 namespace memo {
 
@@ -31,6 +34,35 @@ inline hipError_t record_stage(const AttnArgs &a, int idx, hipStream_t st)
 // dQ may take the place of Q or of dO (all have one layout): a query-stationary workgroup reads only the rows it
 // writes later, so that it is enough to work all key-stationary ones first
 inline bool dq_in_place(const AttnArgs &a) { return a.dq == a.q || a.dq == a.d_o; }
+
+// Works a problem of more workgroups than one launch takes (max_blocks) as problems of fewer heads: some batch entries at a
+// time, or some heads of a single one.  launch(part) may split its part again.  On the host, so that no kernel has to know
+// (an offset of the workgroup id as a kernel argument moved the loops of the long backward by one instruction: 2.5 % at
+// S = 1M).
+template <typename Launch>
+hipError_t launch_fewer_heads(const AttnArgs &a, size_t element_bytes, int64_t blocks, int64_t max_blocks, Launch &&launch)
+{
+    const int64_t heads = (int64_t)a.B * a.H, per = heads / ((blocks + max_blocks - 1) / max_blocks);
+    if (heads == 1) return hipErrorInvalidValue;
+    const bool by_batch = a.B > 1;
+    const int32_t n = by_batch ? a.B : a.H;
+    const int64_t want = by_batch ? per / a.H : per;
+    const int32_t step = want < 1 ? 1 : (int32_t)want;
+    for (int32_t i = 0; i < n; i += step) {
+        AttnArgs part = a;
+        (by_batch ? part.B : part.H) = step < n - i ? step : n - i;
+        const int64_t bytes = i * (by_batch ? a.sb : a.sh) * (int64_t)element_bytes, rows = i * (by_batch ? (int64_t)a.H : 1) * a.S;
+        for (const void **p : {&part.q, &part.k, &part.v, &part.o_in, &part.d_o})
+            if (*p) *p = static_cast<const char *>(*p) + bytes;
+        for (void **p : {&part.o_out, &part.dq, &part.dk, &part.dv})
+            if (*p) *p = static_cast<char *>(*p) + bytes;
+        part.lse += rows;
+        if (part.delta) part.delta += rows;
+        const hipError_t e = launch(part);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 // fp32 path (fp32 matrix instructions, fp32 throughout), d in {64, 128}
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, hipStream_t st);
