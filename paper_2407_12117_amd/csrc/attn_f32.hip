@@ -159,18 +159,31 @@ struct F32Outer {
     }
 };
 
-// A score is added up in four chains, in the forward and in the backward alike.  The logsumexp fits the scores of the backward
-// only if their bits are those of the forward, and a longer chain rounds more often: relative error of dV against 64 bits at
-// S = 1500, d = 64, scores of +-40: two chains in the forward and one in the backward 4.5e-6, two in both 1.28e-6, four in both
-// 1.19e-6 (O: 7.2e-7, 7.2e-7, 5.2e-7).  The sums at the end cost the forward 2 to 5 % (S = 3000, H = 4, d = 128: 93.5 -> 97.5 us).
+// A score is added up in four chains, two over each half of the head dim, in the forward and in the backward alike.  The
+// logsumexp fits the scores of the backward only if their bits are those of the forward, and a longer chain rounds more often:
+// relative error of dV against 64 bits at S = 1500, d = 64, scores of +-40: two chains in the forward and one in the backward
+// 4.5e-6, two in both 1.28e-6, four in both 1.18e-6 (O: 7.2e-7, 7.2e-7, 5.2e-7).  The first two are added up under the MFMAs of
+// the others.  Forward at S = 5000, H = 4, d = 128: two chains 229 us, four as here 234, four at a time 240.
+template <int D>
 struct F32Chains {
-    f32x4 part[4] = {kZero4, kZero4, kZero4, kZero4};
+    f32x4 chain[2] = {kZero4, kZero4}, first;
+    template <int C>              // item C of the head dim: 16 floats
     __device__ __forceinline__ void add(const f32x4 &a, const f32x4 &b)
     {
+        constexpr bool second_half = C == D / 32;
+        f32x4 x, y;
+        if constexpr (second_half) {
+            x = chain[0], y = chain[1];
+            chain[0] = chain[1] = kZero4;
+        }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[j] = mfma4(a[j], b[j], part[j]);
+        for (int j = 0; j < 4; ++j) chain[j % 2] = mfma4(a[j], b[j], chain[j % 2]);
+        if constexpr (second_half) {
+            first = x + y;
+            asm volatile("" : "+v"(first));           // formed here, not at the end
+        }
     }
-    __device__ __forceinline__ f32x4 sum() const { return (part[0] + part[1]) + (part[2] + part[3]); }
+    __device__ __forceinline__ f32x4 sum() const { return first + (chain[0] + chain[1]); }
 };
 
 // s = (rows of tile 0) x b0 and dp += (rows of tile 1) x b1 over the head dim: item c, two reads, eight MFMAs
@@ -180,7 +193,7 @@ __device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Add
 {
     constexpr int kTile = kT * D * 4;
     F32Pair ring[2];
-    F32Chains scores;
+    F32Chains<D> scores;
     auto issue = [&](auto n, F32Pair &slot) {
         constexpr int c = decltype(n)::value;
         lds_issue_b128<256 * (c / 4)>(slot.x, ad.row[c % 4]);
@@ -189,7 +202,7 @@ __device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Add
     lds_pipeline_prologue<D / 16, 1, 2>(ring, issue);
     lds_pipeline_body<D / 16, 1, 2>(ring, issue, [&](auto n, F32Pair &slot) {
         constexpr int c = decltype(n)::value;
-        scores.add(slot.x, b0[c]);
+        scores.template add<c>(slot.x, b0[c]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) dp = mfma4(slot.y[j], b1[c][j], dp);
     });
@@ -237,7 +250,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
         wait_fills_but<Shape::kFills>();              // K has landed; V, queued behind it, may still be on its way
-        F32Chains scores;
+        F32Chains<D> scores;
         {
             f32x4 kring[kDepth + 1];
             auto issue = [&](auto m, f32x4 &slot) {
@@ -246,7 +259,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
             };
             lds_pipeline_prologue<D / 16, kDepth, 1>(kring, issue);
             lds_pipeline_body<D / 16, kDepth, 1>(kring, issue, [&](auto m, f32x4 &slot) {
-                scores.add(slot, q[decltype(m)::value]);
+                scores.template add<decltype(m)::value>(slot, q[decltype(m)::value]);
             });
         }
         if (more) {
