@@ -41,12 +41,11 @@ namespace {
 //           each MFMA pays for: the best rate on a full chip (1216 TFLOP/s at S = 128K, H = 4).
 //   QG = 4: 128 rows, keys in two (1110).
 //   64 rows, keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel below (960).
-//   QG = 1: 32 rows, keys in eight (752); every wave has a tile of its own, so there is no barrier: one
-//           buffer, whose K half is refilled while V is worked and the other way round.
+//   32 rows, keys in eight: attn_fwd_bf16_short_kernel below (752).
 // A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
-// last row: what bounds it is the longest workgroup, which QG = 1 makes 64 times shorter.  The launcher
-// takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 8.7,
-// B = 2 S = 2000 H = 3 67.8 -> 18.4, S = 8192 H = 4 250 -> 79, S = 16461 H = 4 482 -> 265, S = 40000 H = 4 2202 -> 1516.
+// last row: what bounds it is the longest workgroup, which 32 rows make 64 times shorter.  The launcher
+// takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 6.8,
+// B = 2 S = 2000 H = 3 67.8 -> 14.8, S = 8192 H = 4 250 -> 78, S = 16461 H = 4 482 -> 265, S = 40000 H = 4 2202 -> 1516.
 // The fills address a tile as a buffer (TileOffsets::fill): no per-lane pointers to step and no second path for the
 // ragged last tile, 1 to 3 % of every shape.
 constexpr int kFwdWaves = 8;                 // waves per workgroup
@@ -82,7 +81,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
 {
     constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = T, JB = T / 32;
     constexpr int kTile = T * 256;              // bytes of one K or V tile
-    constexpr int kStage = 2 * kTile, kGroup = (QG == 1 ? 1 : 2) * kStage, kRing = KS * kGroup;
+    constexpr int kStage = 2 * kTile, kGroup = 2 * kStage, kRing = KS * kGroup;
     constexpr int kMerge = KS > 1 ? 8 * 32 * 8 : 0;             // (maximum, sum) of every row of every wave
     static_assert(KS == 1 || kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kRing + kMerge];
@@ -124,7 +123,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     auto fill_v = [&](int off, int jt) {
         toff.fill(lds + grp * kGroup + off + kTile, v, a.ss, (int64_t)jt * kBk, a.S, wq);
     };
-    if (QG > 1 && jfirst < ntiles) {
+    if (jfirst < ntiles) {
         fill_k(0, jfirst);
         fill_v(0, jfirst);
     }
@@ -138,13 +137,6 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
             qB[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq * a.ss + 16 * kc + 8 * half));
     }
 
-    if (QG == 1) {                // the loads of Q come first: the loop counts the fills queued after them
-        wait_fills();
-        if (jfirst < ntiles) {
-            fill_k(0, jfirst);
-            fill_v(0, jfirst);
-        }
-    }
     f32x16 accO[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
@@ -161,19 +153,13 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
         constexpr int kOff = BUF * kStage, vOff = kOff + kTile;
         constexpr int nOff = (BUF ^ 1) * kStage;
         const int jn = jt + jstep;
-        if constexpr (QG > 1) {
-            wait_fills();
-            __syncthreads();      // tile jt is complete; nobody still reads the other buffer
-            if (jn >= 0 && jn < ntiles) {
-                fill_k(nOff, jn);
-                fill_v(nOff, jn);
-            }
-            if (jt >= wave_first_tile_masked) return;     // every key of this tile is masked for this wave
-        } else {
-            // the tiles are this wave's own: no barrier.  K has landed; V (queued behind it) may still be on its way
-            if (jt >= ntiles) return;
-            wait_fills_but<T / 4>();
+        wait_fills();
+        __syncthreads();          // tile jt is complete; nobody still reads the other buffer
+        if (jn >= 0 && jn < ntiles) {
+            fill_k(nOff, jn);
+            fill_v(nOff, jn);
         }
+        if (jt >= wave_first_tile_masked) return;         // every key of this tile is masked for this wave
 
         // S^T tile: rows = T keys (JB blocks of 32), cols = this wave's 32 queries.
         // item n = (jb = n%JB, kc = n/JB): one row operand of K, read 2 MFMAs ahead; two key blocks
@@ -190,14 +176,6 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
                 constexpr int jb = decltype(n)::value % JB, kc = decltype(n)::value / JB;
                 s[jb] = mfma32(slot, qB[kc], kc == 0 ? zero : s[jb]);
             });
-        }
-        if constexpr (QG == 1) {  // K is used up: the next K tile overwrites it while V is worked, and the next V tile while K is
-            if (jn < ntiles) {
-                fill_k(0, jn);
-                wait_fills_but<T / 4>();
-            } else {
-                wait_fills();
-            }
         }
         // the first V^T operands are requested now: their latency hides behind the softmax
         TrSlot vring[3];
@@ -269,13 +247,11 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
             constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
             accO[cb] = mfma32(tr_operand(slot), pB[kj], accO[cb]);
         });
-        if constexpr (QG == 1)
-            if (jn < ntiles) fill_v(0, jn);
     };
 
     for (int n = 0; n < nsteps; n += 2) {
         tile_step(IntC<0>{}, jfirst + jstep * n);
-        if (n + 1 < nsteps) tile_step(IntC<(QG > 1 ? 1 : 0)>{}, jfirst + jstep * (n + 1));
+        if (n + 1 < nsteps) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
     }
 
     const float ltot = add_across_halves(lsum);
@@ -331,62 +307,265 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     }   // pass
 }
 
+// The end of the kernels whose eight waves share out the keys of 32 rows: every wave has left its accumulators as sixteen
+// pieces and, per row, its (c m, row sum); each combines two pieces over the waves.  A wave without a tile has m = -inf
+// and weighs exactly zero.
+__device__ __forceinline__ void merge_waves(const AttnArgs &a, const LDS_AS f32x4 *pieces, const LDS_AS f32x2 *stats, int64_t base, int64_t stat,
+                                            int64_t i, int wave, int l32, int half, int lane)
+{
+    f32x2 st[kFwdWaves];
+    f32x4 x[2][kFwdWaves];
+#pragma unroll
+    for (int g = 0; g < kFwdWaves; ++g) st[g] = stats[g * 32 + l32];
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int g = 0; g < kFwdWaves; ++g) x[n][g] = pieces[(g * 16 + 2 * wave + n) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);                // all reads are on their way before the first is waited for
+    float top = -INFINITY, total = 0.f, weight[kFwdWaves];
+#pragma unroll
+    for (int g = 0; g < kFwdWaves; ++g) top = fmaxf(top, st[g][0]);
+#pragma unroll
+    for (int g = 0; g < kFwdWaves; ++g) {
+        weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
+        total += weight[g] * st[g][1];
+    }
+    if (i >= a.S) return;
+    const float inv = 1.f / total;
+    __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < kFwdWaves; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[n][g][r];
+        store4(o + 8 * (2 * wave + n) + 4 * half, sum, inv);
+    }
+    if (wave == 0 && half == 0) a.lse[stat + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
+}
+
+// 32 rows, the keys in eight: every wave works all rows against key tiles of 32 of its own, without a barrier in the sweep; one
+// buffer, whose K half is refilled while V is worked and the other way round.  For sequences so short that a launch is
+// little more than its start and its end (S = 640: 13000 of 17000 cycles before), and both are bound by what passes
+// through the compute unit's 64 B per cycle from the L2, its 128 B per cycle into the LDS, and single waves' chains of
+// instructions.  So the loads go out first and once (kernel arguments in one go; Q to the LDS, not to every wave's registers in
+// pieces of 32 bytes), the set-up of addresses and accumulators comes behind them, and at the end a wave leaves its
+// accumulators in its own buffer without waiting for the others.  us: S = 32 H = 2 6.0 -> 4.0, S = 640 H = 2 8.1 -> 6.8,
+// B = 2 S = 2000 H = 3 17.8 -> 14.8, S = 3000 H = 4 20.3 -> 17.8.
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(AttnArgs a, Divisor heads, Divisor H)
+{
+    constexpr int T = 32, kTile = T * 256, kQ = kFwdWaves * 2 * kTile, kStats = kQ + kTile;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kFwdWaves * T * 8];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [wave][K|V] tiles, then the Q rows, then (maximum, sum)
+    load_args_at_once(a);
+
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const TileId t = decode_tile(blockIdx.x, (int)((a.S + T - 1) / T), heads, H, true);
+    const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh, row0 = (int64_t)t.tile * T;
+    const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
+    const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
+    const int ntiles = t.tile + 1;                    // the last one is the diagonal
+    const int ring = wave * 2 * kTile;
+    const TileOffsets<1, T> toff = make_tile_offsets<1, SwzA, T>(a.ss, 0, lane);
+    constexpr int kFills = TileOffsets<1, T>::kInstr;
+    auto fill_k = [&](int jt, int to) { toff.fill(lds + to, k, a.ss, (int64_t)jt * T, a.S, 0); };
+    auto fill_v = [&](int jt, int to) { toff.fill(lds + to + kTile, v, a.ss, (int64_t)jt * T, a.S, 0); };
+    const TileOffsets<8, T> qoff = make_tile_offsets<8, SwzA, T>(a.ss, wave, lane);
+    qoff.fill(lds + kQ, static_cast<const __bf16 *>(a.q) + base, a.ss, row0, a.S, wave);
+    if (wave < ntiles) {
+        fill_k(wave, ring);
+        fill_v(wave, ring);
+    } else {
+        wait_fills();
+        __builtin_amdgcn_s_barrier();                 // as below
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const LaneAddr la = make_lane_addr(lane);
+    // pieces of a row operand lie at address ^ (kc << 5), of a transposed one at address ^ (cb << 6)
+    const uint32_t row = (uint32_t)(uintptr_t)lds + (uint32_t)la.row_op[0], own = (uint32_t)(uintptr_t)lds + (uint32_t)ring;
+    uint32_t ka[8], va[4][2];
+#pragma unroll
+    for (int kc = 0; kc < 8; ++kc) ka[kc] = (row + ring) ^ (kc << 5);
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int sec = 0; sec < 2; ++sec) va[cb][sec] = (own + (uint32_t)la.tr_op[0][sec]) ^ (cb << 6);
+    const float c = a.scale * kLog2e;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 accO[4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) accO[cb] = zero;
+    float m = -INFINITY, mc = -INFINITY, lsum = 0.f;
+    bf16x8 qB[8];                 // Q^T as B operand: lane = query row l32, 8 head-dim values per 16-wide chunk
+
+#pragma clang loop unroll(disable)
+    for (int jt = wave; jt < ntiles; jt += kFwdWaves) {
+        const int jn = jt + kFwdWaves;
+        const bool first = jt == wave;
+        int to = ring;            // opaque: the addresses of the fills are formed where they are used, not in a long preamble of the loop
+        asm volatile("" : "+s"(to));
+        if (first) {              // in the loop, so that what the compiler moves in front of it is done while the loads are on their way
+            wait_fills_but<2 * kFills>();
+            __builtin_amdgcn_s_barrier();             // the Q rows are complete
+            static_for<0, 8>([&](auto n) { lds_issue_b128<0>(qB[decltype(n)::value], (row + kQ) ^ (decltype(n)::value << 5)); });
+            static_for<0, 8>([&](auto n) { lds_wait<0>(qB[decltype(n)::value]); });
+        }
+        wait_fills_but<kFills>();                     // K has landed; V, queued behind it, may still be on its way
+        f32x16 s;                                     // S^T tile: rows = 32 keys, cols = the 32 queries
+        {
+            bf16x8 slots[3];
+            auto issue = [&](auto n, bf16x8 &slot) { lds_issue_b128<0>(slot, ka[decltype(n)::value]); };
+            lds_pipeline_prologue<8, 2, 1>(slots, issue);
+            lds_pipeline_body<8, 2, 1>(slots, issue, [&](auto n, bf16x8 &slot) {
+                constexpr int kc = decltype(n)::value;
+                s = mfma32(slot, qB[kc], kc == 0 ? zero : s);
+            });
+        }
+        if (jn < ntiles) {                            // K is used up: the next K tile comes while V is worked
+            fill_k(jn, to);
+            wait_fills_but<kFills>();
+        } else {
+            wait_fills();
+        }
+        TrSlot vring[3];
+        auto v_issue = [&](auto n, TrSlot &slot) {
+            constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
+            lds_issue_tr<kj * 4096 + kTile>(slot, va[cb][0], va[cb][1]);
+        };
+        lds_pipeline_prologue<8, 2, 2>(vring, v_issue);
+        if (jt == ntiles - 1) {                       // diagonal tile: mask keys j > i
+            int thr = l32 - 4 * half;
+            asm volatile("" : "+v"(thr));
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (8 * (e >> 2) + (e & 3) > thr) s[e] = -INFINITY;
+        }
+        // against the running maximum as it stands (see attn_fwd_bf16_kernel); the first tile has none yet
+        bf16x8 pB[2];
+        float psum0 = INFINITY, psum1 = 0.f;
+        auto exponentials = [&]() __attribute__((always_inline)) {
+            psum0 = psum1 = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const f32x2 two = {__builtin_amdgcn_exp2f(fmaf(s[e], c, -mc)), __builtin_amdgcn_exp2f(fmaf(s[e + 1], c, -mc))};
+                psum0 += two[0];
+                psum1 += two[1];
+                const bf16x2 r = __builtin_convertvector(two, bf16x2);
+                pB[e >> 3][e & 7] = r[0];
+                pB[e >> 3][(e & 7) + 1] = r[1];
+            }
+        };
+        if (!first) exponentials();
+        if (__builtin_amdgcn_ballot_w64(!(psum0 + psum1 <= kRescaleAbove)) != 0) {
+            float mt = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+            for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, s[e]), s[e + 1]);
+            const float m_new = finite_max(m, max_across_halves(fmaxf(mt, s[15])));
+            if (!first) {
+                const float corr = __builtin_amdgcn_exp2f((m - m_new) * c);
+                lsum *= corr;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) accO[cb][e] *= corr;
+            }
+            m = m_new;
+            mc = scaled_max(m_new, c);
+            exponentials();
+        }
+        lsum += psum0 + psum1;
+        // O^T += V^T P^T
+        lds_pipeline_body<8, 2, 2>(vring, v_issue, [&](auto n, TrSlot &slot) {
+            constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
+            accO[cb] = mfma32(tr_operand(slot), pB[kj], accO[cb]);
+        });
+        if (jn < ntiles) fill_v(jn, to);
+    }
+
+    // the waves' parts meet in LDS, as in attn_fwd_bf16_kernel; a wave's sixteen pieces take the place of its own buffer
+    LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+    LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kStats);
+    const float ltot = add_across_halves(lsum);
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
+                                                    accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
+    if (half == 0) stats[wave * T + l32] = f32x2{mc, ltot};
+    __syncthreads();
+    merge_waves(a, pieces, stats, base, ((int64_t)t.b * a.H + t.h) * a.S, row0 + l32, wave, l32, half, lane);
+}
+
 // 64 rows, the keys in eight: every wave works all 64 rows (two blocks of 32) against key tiles of 32 of its own, so
 // there is no barrier in the sweep and a K or V operand read feeds two MFMAs.  Q stays in LDS: the accumulators of 64
 // rows leave no registers for it.  Bound, like all shapes below 256 rows, by what it streams per MFMA: as many bytes as
 // two waves per 32-key tile behind a barrier did, which ran at 885 TFLOP/s on a full chip (S = 8192, H = 4: 87 -> 79 us).
-__global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(AttnArgs a)
+// Its start and end are those of the 32-row kernel.
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(AttnArgs a, Divisor heads, Divisor H)
 {
     constexpr int kBq = 64, T = 32, kTile = T * 256, kQ = kFwdWaves * 2 * kTile, kStats = kQ + kBq * 256;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kFwdWaves * kBq * 8];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [wave][K|V] tiles, then the Q rows, then (maximum, sum)
+    load_args_at_once(a);
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const LaneAddr la = make_lane_addr(lane);
-    const PairId t = decode_block(a, blockIdx.x, (a.S + kBq - 1) / kBq, kLongestFirst, true);
+    const TileId t = decode_tile(blockIdx.x, (int)((a.S + kBq - 1) / kBq), heads, H, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
     const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
-    const float c = a.scale * kLog2e;
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int64_t row0 = t.first * kBq;
+    const int64_t row0 = (int64_t)t.tile * kBq;
     const int ntiles = (int)((min(row0 + kBq, a.S) - 1) / T) + 1;
-    LDS_AS unsigned char *ring = lds + wave * 2 * kTile;
-    // pieces of a row operand lie at address ^ (kc << 5), of a transposed one at address ^ (cb << 6)
-    const uint32_t q_row = (uint32_t)(uintptr_t)(lds + kQ) + (uint32_t)la.row_op[0];
-    const uint32_t k_row = (uint32_t)(uintptr_t)ring + (uint32_t)la.row_op[0];
-    const uint32_t v_lo = (uint32_t)(uintptr_t)ring + (uint32_t)la.tr_op[0][0], v_hi = (uint32_t)(uintptr_t)ring + (uint32_t)la.tr_op[0][1];
+    const int ring = wave * 2 * kTile;
 
     const TileOffsets<8, kBq> qoff = make_tile_offsets<8, SwzA, kBq>(a.ss, wave, lane);
     qoff.fill(lds + kQ, static_cast<const __bf16 *>(a.q) + base, a.ss, row0, a.S, wave);
     const TileOffsets<1, T> toff = make_tile_offsets<1, SwzA, T>(a.ss, 0, lane);
     constexpr int kFills = TileOffsets<1, T>::kInstr;
-    auto fill_k = [&](int jt) { toff.fill(ring, k, a.ss, (int64_t)jt * T, a.S, 0); };
-    auto fill_v = [&](int jt) { toff.fill(ring + kTile, v, a.ss, (int64_t)jt * T, a.S, 0); };
+    auto fill_k = [&](int jt, int to) { toff.fill(lds + to, k, a.ss, (int64_t)jt * T, a.S, 0); };
+    auto fill_v = [&](int jt, int to) { toff.fill(lds + to + kTile, v, a.ss, (int64_t)jt * T, a.S, 0); };
     if (wave < ntiles) {
-        fill_k(wave);
-        fill_v(wave);
-        wait_fills_but<2 * kFills>();
-    } else {
-        wait_fills();
+        fill_k(wave, ring);
+        fill_v(wave, ring);
     }
-    __builtin_amdgcn_s_barrier();                     // the Q rows are complete
-    asm volatile("" ::: "memory");
-
+    __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
+    const LaneAddr la = make_lane_addr(lane);
+    const float c = a.scale * kLog2e;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // pieces of a row operand lie at address ^ (kc << 5), of a transposed one at address ^ (cb << 6)
+    const uint32_t own = (uint32_t)(uintptr_t)(lds + ring);
+    uint32_t q_row = (uint32_t)(uintptr_t)(lds + kQ) + (uint32_t)la.row_op[0], k_row = own + (uint32_t)la.row_op[0];
+    uint32_t v_lo = own + (uint32_t)la.tr_op[0][0], v_hi = own + (uint32_t)la.tr_op[0][1];
+    asm volatile("" : "+v"(q_row), "+v"(k_row), "+v"(v_lo), "+v"(v_hi));
     f32x16 accO[2][4];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) accO[b][cb] = zero;
+        for (int cb = 0; cb < 4; ++cb) {
+            accO[b][cb] = zero;
+            asm volatile("" : "+v"(accO[b][cb]));
+        }
     float m[2] = {-INFINITY, -INFINITY}, mc[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
+    if (wave < ntiles) wait_fills_but<2 * kFills>();
+    else wait_fills();
+    __builtin_amdgcn_s_barrier();                     // the Q rows are complete
+    asm volatile("" ::: "memory");
 
-    // one key tile against the row blocks from `first` on (the tile past the first block's diagonal is the second's alone)
+    // Of the two waves of a SIMD the older one is served first and would end its keys a fifth of the sweep ahead; from here on the
+    // younger one is, so that they end together and neither works alone (S = 8192, H = 4: 81.3 -> 78.1 us; the place, between a third and
+    // a half of the sweep, matters by 0.5 %).
+    const int even_out = ntiles * 7 / 16;
+
+    // one key tile against the row blocks from `F` on (the tile past the first block's diagonal is the second's alone)
     auto tile_step = [&](auto firstc, int jt) {
         constexpr int F = decltype(firstc)::value;
         const int jn = jt + kFwdWaves;
+        const bool first = jt == wave;
+        if (wave >= 4 && jt >= even_out) __builtin_amdgcn_s_setprio(1);
         uint32_t qa = q_row, ka = k_row, va = v_lo, vb = v_hi;
-        asm volatile("" : "+v"(qa), "+v"(ka), "+v"(va), "+v"(vb));   // the other addresses are formed where they are used
+        int to = ring;
+        asm volatile("" : "+v"(qa), "+v"(ka), "+v"(va), "+v"(vb), "+s"(to));   // the other addresses are formed where they are used
         wait_fills_but<kFills>();                     // K has landed; V, queued behind it, may still be on its way
         f32x16 s[2];
         {
@@ -404,7 +583,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
             });
         }
         if (jn < ntiles) {                            // K is used up: the next K tile comes while V is worked
-            fill_k(jn);
+            fill_k(jn, to);
             wait_fills_but<kFills>();
         } else {
             wait_fills();
@@ -420,13 +599,14 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
         for (int b = F; b < 2; ++b) {
             const int64_t i0 = row0 + 32 * b;
             if ((int64_t)jt * T >= i0) {              // diagonal tile: mask keys j > i
-                const int thr = l32 - 4 * half;
+                int thr = l32 - 4 * half;
+                asm volatile("" : "+v"(thr));
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     if (8 * (e >> 2) + (e & 3) > thr) s[b][e] = -INFINITY;
             }
-            // against the running maximum as it stands (see attn_fwd_bf16_kernel)
-            float psum0, psum1;
+            // against the running maximum as it stands (see attn_fwd_bf16_kernel); the first tile has none yet
+            float psum0 = INFINITY, psum1 = 0.f;
             auto exponentials = [&]() __attribute__((always_inline)) {
                 psum0 = psum1 = 0.f;
 #pragma unroll
@@ -439,21 +619,23 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
                     pB[b][e >> 3][(e & 7) + 1] = r[1];
                 }
             };
-            exponentials();
+            if (!first) exponentials();
             if (__builtin_amdgcn_ballot_w64(!(psum0 + psum1 <= kRescaleAbove)) != 0) {
                 float mb = fmaxf(fmaxf(s[b][0], s[b][1]), s[b][2]);
 #pragma unroll
                 for (int e = 3; e < 15; e += 2) mb = fmaxf(fmaxf(mb, s[b][e]), s[b][e + 1]);
                 mb = fmaxf(mb, s[b][15]);
                 const float m_new = finite_max(m[b], max_across_halves(mb));
-                const float corr = __builtin_amdgcn_exp2f((m[b] - m_new) * c);
+                if (!first) {
+                    const float corr = __builtin_amdgcn_exp2f((m[b] - m_new) * c);
+                    lsum[b] *= corr;
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) accO[b][cb][e] *= corr;
+                }
                 m[b] = m_new;
                 mc[b] = scaled_max(m_new, c);
-                lsum[b] *= corr;
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) accO[b][cb][e] *= corr;
                 exponentials();
             }
             lsum[b] += psum0 + psum1;
@@ -463,7 +645,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
 #pragma unroll
             for (int b = F; b < 2; ++b) accO[b][cb] = mfma32(tr_operand(slot), pB[b][kj], accO[b][cb]);
         });
-        if (jn < ntiles) fill_v(jn);
+        if (jn < ntiles) fill_v(jn, to);
     };
     const int last_both = (int)(row0 / T);            // tiles past it hold no key of the first block's rows
     int jt = wave;
@@ -471,49 +653,21 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
     for (; jt <= last_both; jt += kFwdWaves) tile_step(IntC<0>{}, jt);
     if (jt < ntiles) tile_step(IntC<1>{}, jt);
 
-    // the waves' parts of a block of rows meet in LDS, one block after the other, as in attn_fwd_bf16_kernel
+    // the waves' parts of a block of rows meet in LDS, one block after the other; those of the first take the place of the wave's own buffer
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
     LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kStats);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         const int64_t i = row0 + 32 * b + l32;
         const float ltot = add_across_halves(lsum[b]);
-        __syncthreads();          // every wave has left what lies there
+        if (b == 1) __syncthreads();                  // every wave has read the first block's
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[b][e >> 2][4 * (e & 3)], accO[b][e >> 2][4 * (e & 3) + 1],
                                                         accO[b][e >> 2][4 * (e & 3) + 2], accO[b][e >> 2][4 * (e & 3) + 3]};
         if (half == 0) stats[wave * 32 + l32] = f32x2{mc[b], ltot};
         __syncthreads();
-        float top = -INFINITY, total = 0.f, weight[kFwdWaves];
-        f32x2 st[kFwdWaves];
-#pragma unroll
-        for (int g = 0; g < kFwdWaves; ++g) {
-            st[g] = stats[g * 32 + l32];
-            top = fmaxf(top, st[g][0]);
-        }
-#pragma unroll
-        for (int g = 0; g < kFwdWaves; ++g) {
-            weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
-            total += weight[g] * st[g][1];
-        }
-        if (i < a.S) {
-            const float inv = 1.f / total;
-            __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
-#pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                const int e = wave * 2 + n;
-                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int g = 0; g < kFwdWaves; ++g) {
-                    const f32x4 x = pieces[(g * 16 + e) * 64 + lane];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
-                }
-                store4(o + 8 * e + 4 * half, sum, inv);
-            }
-            if (wave == 0 && half == 0) a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
-        }
+        merge_waves(a, pieces, stats, base, ((int64_t)t.b * a.H + t.h) * a.S, i, wave, l32, half, lane);
     }
 }
 
@@ -528,8 +682,8 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
     if (blocks > kMaxBlocks)
         return launch_fewer_heads(a, sizeof(__bf16), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_attn_fwd_bf16(part, st); });
     switch (c.rows) {
-    case 32: return launch_blocks(attn_fwd_bf16_kernel<1, 32>, blocks, st, a, order);
-    case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a);
+    case 32: return launch_blocks(attn_fwd_bf16_short_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
+    case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
     case 128: return launch_blocks(attn_fwd_bf16_kernel<4, 64>, blocks, st, a, order);
     default: return launch_blocks(attn_fwd_bf16_kernel<8, 64>, blocks, st, a, order);
     }

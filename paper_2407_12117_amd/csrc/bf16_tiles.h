@@ -202,6 +202,38 @@ __device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, i
     return t;
 }
 
+// Division by a launch constant d >= 1 as one high product: floor(2^32 / d) makes the quotient right or one too small.
+struct Divisor {
+    uint32_t d, inv;
+    explicit Divisor(int64_t by) : d((uint32_t)by), inv((uint32_t)std::min<uint64_t>(((uint64_t)1 << 32) / (uint64_t)by, 0xffffffffu)) {}
+    __device__ __forceinline__ void operator()(uint32_t x, uint32_t &quot, uint32_t &rem) const
+    {
+        quot = __umulhi(x, inv);
+        rem = x - quot * d;
+        if (rem >= d) {
+            ++quot;
+            rem -= d;
+        }
+    }
+};
+
+// The start of a short launch is a wave's serial chain of instructions (8 cycles each) and of waits for kernel arguments: the
+// compiler asks for these one after the other where they are used, 200 cycles and more each time.  Here they come in one go.
+__device__ __forceinline__ void load_args_at_once(const AttnArgs &a)
+{
+    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.S), "s"(a.sb), "s"(a.ss), "s"(a.sh), "s"(a.lse), "s"(a.scale), "s"(a.H));
+}
+
+// Longest-first work of one tile per workgroup, without the divisions of decode_block.
+struct TileId { int tile, h, b; };
+__device__ __forceinline__ TileId decode_tile(uint32_t id, int ntiles, Divisor heads, Divisor H, bool last_is_longest)
+{
+    uint32_t rank, hb, h, b;
+    heads(id, rank, hb);
+    H(hb, b, h);
+    return {last_is_longest ? ntiles - 1 - (int)rank : (int)rank, (int)h, (int)b};
+}
+
 // ---- asynchronous tile fill: global -> LDS without passing through registers -------------
 // One 16-byte fill instruction moves 64 x 16 bytes: lane l lands at LDS base + 16*l, i.e. four
 // tile rows of sixteen chunks.  With NW waves sharing a tile, wave w issues instruction n for

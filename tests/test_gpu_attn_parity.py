@@ -108,6 +108,13 @@ def test_bf16_forward_64_row_edges(oracle, S, heads):
     _dense_case(oracle, 1, S, heads, 128, "bf16", 9000 + S, scaled=True)
 
 
+@pytest.mark.parametrize("B,H", [(1, 1), (3, 1), (1, 7), (5, 3), (2, 13)])
+def test_bf16_short_forward_batches_and_heads(oracle, B, H):
+    # 32-row workgroups: which head and batch entry a workgroup id stands for, for divisors that are a power of two, one
+    # and neither; nine tiles, of which the first eight leave waves without a key tile
+    _dense_case(oracle, B, 257, H, 128, "bf16", 9500 + 16 * B + H)
+
+
 @pytest.mark.parametrize("S,heads", shapes.BWD_32_EDGES)
 def test_bf16_backward_32_row_edges(oracle, S, heads):
     _dense_case(oracle, 1, S, heads, 128, "bf16", 9100 + S)
