@@ -560,35 +560,53 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, 
 // sweeps of half the steps: ahead where the longest sweep, not the work, is what a launch takes (own_us, launch_plan.h).  us, 64-row
 // workgroups -> these: S = 1000 H = 4 20.5 -> 15.4, S = 1500 H = 4 26.4 -> 22.5, S = 2500 H = 2 37.6 -> 25.1, S = 640 H = 2
 // 16.1 -> 15.3; but S = 2000, 6 heads 36.2 -> 45.9, S = 8192 H = 4 227 -> 259.
+// A start is bound by the 144 KB that eight waves fetch through a unit's 64 B per cycle (dQ: Q and dO once to the LDS, not to every wave's
+// registers) with the set-up behind it, an end by 128 KB through the LDS per sum.  us with these, without, the D_i launch in both: S = 256 H = 2
+// 9.5, 10.5; S = 640 H = 2 11.8, 12.1; S = 1000 H = 4 14.7, 15.0; S = 1536 H = 2 17.6, 18.1.  Tried at the end without gain: dK's pieces put
+// while dV's are added up, barriers that do not wait for stores.
 constexpr int kOwnTile = 32 * 256, kOwnRing = 8 * 2 * kOwnTile;
 
-// piece of every wave -> its sum in the wave that owns the piece (two of sixteen): out(e, sum)
-template <typename Out>
+// piece of every wave -> its sum in the wave that owns the piece (two of sixteen): out(e, sum).  A wave's pieces take the place of its
+// own ring, so that the first sum needs no barrier before them.
+template <bool kFirst, typename Out>
 __device__ __forceinline__ void sum_over_waves(LDS_AS unsigned char *lds, const f32x4 (&acc)[8][2], int wave, int lane, Out &&out)
 {
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
-    __syncthreads();              // every wave has left what lies there
+    if (!kFirst) __syncthreads(); // every wave has read the sum before
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) pieces[(wave * 16 + 8 * b + dt) * 64 + lane] = acc[dt][b];
     __syncthreads();
+    f32x4 x[2][8];
 #pragma unroll
-    for (int n = 0; n < 2; ++n) out(2 * wave + n, sum_pieces<8, 1>(pieces, 0, 2 * wave + n, lane));
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int g = 0; g < 8; ++g) x[n][g] = pieces[(g * 16 + 2 * wave + n) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);                // all reads are on their way before the first is waited for
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        f32x4 sum = x[n][0];
+#pragma unroll
+        for (int g = 1; g < 8; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[r] += x[n][g][r];
+        out(2 * wave + n, sum);
+    }
 }
 
-__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
+__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, Divisor heads, Divisor H)
 {
     // lds: [wave][Q|dO] tiles, then the K and V rows
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nit = (int)((a.S + 31) / 32);
-    const PairId t = decode_block(a, id, nit, kLongestFirst, false);
+    const TileId t = decode_tile(id, nit, heads, H, false);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base, *g = static_cast<const __bf16 *>(a.d_o) + base;
     const float *lse = a.lse + ((int64_t)t.b * a.H + t.h) * a.S, *dlt = a.delta + ((int64_t)t.b * a.H + t.h) * a.S;
     const float c = a.scale * kLog2e, neg_inv_scale = -1.f / a.scale;
-    const int it0 = (int)t.first;                     // key tile and first query tile: the diagonal
+    const int it0 = t.tile;                           // key tile and first query tile: the diagonal
     LDS_AS unsigned char *ring = lds + wave * 2 * kOwnTile;
     const TileOffsets<8, 32> koff = make_tile_offsets<8, SwzB, 32>(a.ss, wave, lane);
     koff.fill(lds + kOwnRing, static_cast<const __bf16 *>(a.k) + base, a.ss, (int64_t)it0 * 32, a.S, wave);
@@ -612,13 +630,17 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
     load_stats(min(it, nit - 1));
     fill_q(it);
     fill_g(it);
+    __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const LdsAddr16 ad = make_lds_addr16(ring, lane);
     const uint32_t kv_base = (uint32_t)(kOwnRing - wave * 2 * kOwnTile);
     f32x4 accV[8][2], accK[8][2];                     // dV^T, dK^T: [head-dim block][key block]; lane = key
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) accV[dt][kt] = accK[dt][kt] = kZero4;
+        for (int kt = 0; kt < 2; ++kt) {
+            accV[dt][kt] = accK[dt][kt] = kZero4;
+            asm volatile("" : "+v"(accV[dt][kt]), "+v"(accK[dt][kt]));
+        }
     wait_fills_but<16>();
     __builtin_amdgcn_s_barrier();                     // the K and V rows are complete
     asm volatile("" ::: "memory");
@@ -721,55 +743,75 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
             if (j0 + 16 * kt < a.S) store4(out + 16 * kt * a.ss + 16 * dt, sum, mul);
         };
     };
-    sum_over_waves(lds, accV, wave, lane, store(dv, 1.f));
-    sum_over_waves(lds, accK, wave, lane, store(dk, a.scale));
+    sum_over_waves<true>(lds, accV, wave, lane, store(dv, 1.f));
+    sum_over_waves<false>(lds, accK, wave, lane, store(dk, a.scale));
 }
 
-__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
+__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, Divisor heads, Divisor H)
 {
-    // lds: [wave][K|V] tiles
+    // lds: [wave][K|V] tiles, then the Q and dO rows
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const PairId t = decode_block(a, id, (a.S + 31) / 32, kLongestFirst, true);
+    const TileId t = decode_tile(id, (int)((a.S + 31) / 32), heads, H, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base, *g = static_cast<const __bf16 *>(a.d_o) + base;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base, *v = static_cast<const __bf16 *>(a.v) + base;
     const int64_t stat = ((int64_t)t.b * a.H + t.h) * a.S;
     const float c = a.scale * kLog2e;
-    const int ntiles = (int)t.first + 1;              // the last one is the diagonal
-    const int64_t i0 = t.first * 32 + l16;
-    LDS_AS unsigned char *ring = lds + wave * 2 * kOwnTile;
-    const OwnTileFill fill(a.ss, lane);
-    // a tile past the last one is an empty buffer: its fills are still counted by the waits
-    auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * 32, jt < ntiles ? a.S : (int64_t)jt * 32); };
-    auto fill_v = [&](int jt) { fill(ring + kOwnTile, v, a.ss, (int64_t)jt * 32, jt < ntiles ? a.S : (int64_t)jt * 32); };
-    fill_v(wave);
-    fill_k(wave);
-    const LdsAddr16 ad = make_lds_addr16(ring, lane);
-    // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
-    bf16x8 qB[2][4], gB[2][4];
-    float lse2[2];
-    f32x4 neg_d[2];
+    const int ntiles = t.tile + 1;                    // the last one is the diagonal
+    const int64_t i0 = (int64_t)t.tile * 32 + l16;
+    float lse2[2], nd[2];
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
         const int64_t i = i0 + 16 * qt < a.S ? i0 + 16 * qt : a.S - 1;          // rows past S are computed and never stored
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            qB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + i * a.ss + 32 * kk + 8 * g4));
-            gB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(g + i * a.ss + 32 * kk + 8 * g4));
-        }
-        lse2[qt] = a.lse[stat + i] * kLog2e;
-        const float nd = -a.delta[stat + i];
-        neg_d[qt] = f32x4{nd, nd, nd, nd};
+        lse2[qt] = a.lse[stat + i];
+        nd[qt] = a.delta[stat + i];
     }
+    const int ring = wave * 2 * kOwnTile;
+    const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzB, 32>(a.ss, wave, lane);
+    qoff.fill(lds + kOwnRing, q, a.ss, (int64_t)t.tile * 32, a.S, wave);
+    qoff.fill(lds + kOwnRing + kOwnTile, g, a.ss, (int64_t)t.tile * 32, a.S, wave);
+    const TileOffsets<1, 32> toff = make_tile_offsets<1, SwzB, 32>(a.ss, 0, lane);
+    // a tile past the last one is an empty buffer: its fills are still counted by the waits
+    auto fill_k = [&](int jt) { toff.fill(lds + ring, k, a.ss, (int64_t)jt * 32, jt < ntiles ? a.S : (int64_t)jt * 32, 0); };
+    auto fill_v = [&](int jt) { toff.fill(lds + ring + kOwnTile, v, a.ss, (int64_t)jt * 32, jt < ntiles ? a.S : (int64_t)jt * 32, 0); };
+    fill_v(wave);
+    fill_k(wave);
+    __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
+    const LdsAddr16 ad = make_lds_addr16(lds + ring, lane);
     f32x4 accQ[8][2];             // dQ^T: [head-dim block of 16][query block]; lane = query, rows = head dim
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt) accQ[dt][qt] = kZero4;
+        for (int qt = 0; qt < 2; ++qt) {
+            accQ[dt][qt] = kZero4;
+            asm volatile("" : "+v"(accQ[dt][qt]));
+        }
+    wait_fills_but<16>();
+    __builtin_amdgcn_s_barrier();                     // the Q and dO rows are complete
+    asm volatile("" ::: "memory");
+    // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
+    bf16x8 qB[2][4], gB[2][4];
+    static_for<0, 8>([&](auto n) {
+        constexpr int qt = decltype(n)::value / 4, kk = decltype(n)::value % 4;
+        lds_issue_b128<4096 * qt>(gB[qt][kk], ad.row16[kk] + (uint32_t)(kOwnRing + kOwnTile - ring));
+        lds_issue_b128<4096 * qt>(qB[qt][kk], ad.row16[kk] + (uint32_t)(kOwnRing - ring));
+    });
+    static_for<0, 8>([&](auto n) {
+        lds_wait<0>(gB[decltype(n)::value / 4][decltype(n)::value % 4]);
+        lds_wait<0>(qB[decltype(n)::value / 4][decltype(n)::value % 4]);
+    });
+    f32x4 neg_d[2];
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        lse2[qt] *= kLog2e;
+        neg_d[qt] = f32x4{-nd[qt], -nd[qt], -nd[qt], -nd[qt]};
+    }
 
 #pragma clang loop unroll(disable)
     for (int jt = wave; jt < ntiles; jt += 8) {
+        int l = l16;              // opaque: the masks of the diagonal are formed there, not in front of the loop
+        asm volatile("" : "+v"(l));
         // dP before S: V is needed first and used up first, K follows
         f32x4 s[2][2], dp[2][2];                      // [key block][query block]
         {
@@ -803,7 +845,7 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
                 for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (r > 16 * qt + l16 - (16 * kt + 4 * g4)) s[kt][qt][r] = -INFINITY;
+                        if (r > 16 * qt + l - (16 * kt + 4 * g4)) s[kt][qt][r] = -INFINITY;
         }
         bf16x8 dsB[2];
 #pragma unroll
@@ -826,18 +868,20 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
     }
     wait_fills();                 // the empty ones too: they write LDS
     __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + i0 * a.ss + 4 * g4;
-    sum_over_waves(lds, accQ, wave, lane, [=, &a](int e, const f32x4 &sum) {
+    sum_over_waves<true>(lds, accQ, wave, lane, [=, &a](int e, const f32x4 &sum) {
         const int qt = e >> 3, dt = e & 7;
         if (i0 + 16 * qt < a.S) store4(dq + 16 * qt * a.ss + 16 * dt, sum, a.scale);
     });
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks, Divisor heads, Divisor H)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    if (blockIdx.x < dkdv_blocks) dkdv_own_rows(a, lds, blockIdx.x);
-    else dq_own_rows(a, lds, blockIdx.x - dkdv_blocks);
+    load_args_at_once(a);
+    asm volatile("" ::"s"(a.d_o), "s"(a.delta));
+    if (blockIdx.x < dkdv_blocks) dkdv_own_rows(a, lds, blockIdx.x, heads, H);
+    else dq_own_rows(a, lds, blockIdx.x - dkdv_blocks, heads, H);
 }
 
 // dkdv, dq: which of the gradients to launch; both in one launch where the plan says so
@@ -864,7 +908,7 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
     const uint32_t dkdv_blocks = dkdv ? (uint32_t)nk : 0;
     const int64_t blocks = dkdv_blocks + (dq ? nq : 0);
     switch (p.rows) {
-    case 32: return launch_blocks(attn_bwd_own_bf16_kernel, blocks, st, a, dkdv_blocks);
+    case 32: return launch_blocks(attn_bwd_own_bf16_kernel, blocks, st, a, dkdv_blocks, Divisor(heads), Divisor(a.H));
     case 64: return launch_blocks(attn_bwd_both_bf16_kernel<2, 2, 32>, blocks, st, a, dkdv_blocks);
     case 128: return launch_blocks(attn_bwd_both_bf16_kernel<4, 4, 64>, blocks, st, a, dkdv_blocks);
     default: return launch_blocks(attn_bwd_both_bf16_kernel<8, 8, 64>, blocks, st, a, dkdv_blocks);
