@@ -69,8 +69,8 @@ struct DqShape {
     static_assert(KS == 1 || kLds == 8 * 16384, "the sum over the key groups lays eight accumulator sets over the ring");
 };
 
-template <int QG, int T>
-__device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, int order)
+template <int QG, int T, typename Find>       // find(number of tiles): the workgroup's work
+__device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, Find &&find)
 {
     using Shape = DqShape<QG, T>;
     constexpr int KS = Shape::KS, kTile = Shape::kTile, kStage = Shape::kStage, kGroup = Shape::kGroup;
@@ -81,7 +81,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wq = wave % QG, grp = wave / QG;        // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const PairId t = decode_block(a, id, nqt, tile_order(kBq, order), true);
+    const PairId t = find(nqt);
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -240,7 +240,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
 __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<8, 64>::kLds];
-    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, [&](int64_t nqt) { return decode_block(a, blockIdx.x, nqt, order, true); });
 }
 
 // ============================================================================ backward: dK, dV
@@ -282,8 +282,8 @@ struct DkdvShape {
     static_assert(QS == 1 || kLds >= 8 * 16384, "the sum over the query groups lays eight accumulator sets over it");
 };
 
-template <int KG>
-__device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, int order)
+template <int KG, typename Find>
+__device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, Find &&find)
 {
     using Shape = DkdvShape<KG>;
     constexpr int QS = Shape::QS, kKvOff = Shape::kKvOff, kBwdBk = 32 * KG;
@@ -293,7 +293,7 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = wave % KG, grp = wave / KG;        // key block, query group
     const int64_t nkt = (a.S + kBwdBk - 1) / kBwdBk;
-    const PairId t = decode_block(a, id, nkt, order, false);      // key tile p (long) and key tile nkt-1-p (short)
+    const PairId t = find(nkt);                       // key tile p (long) and key tile nkt-1-p (short)
     if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
@@ -538,19 +538,23 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
 __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<8>::kLds];
-    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, blockIdx.x, order);
+    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, [&](int64_t nkt) { return decode_block(a, blockIdx.x, nkt, order, false); });
 }
 
-// both gradients in one launch, longest tiles first: the first `dkdv_blocks` workgroups are the key-stationary
-// ones, the others the query-stationary ones
+// both gradients in one launch, longest tiles of either kind first (JointOrder)
 template <int KG, int QG, int T>
-__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, JointOrder order, Divisor heads, Divisor H)
 {
     constexpr int kLds = DkdvShape<KG>::kLds > DqShape<QG, T>::kLds ? DkdvShape<KG>::kLds : DqShape<QG, T>::kLds;
+    static_assert(KG == QG, "a position stands for a key tile or a query tile of as many rows");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
-    if (blockIdx.x < dkdv_blocks) dkdv_rows<KG>(a, lds, blockIdx.x, kLongestFirst);
-    else dq_rows<QG, T>(a, lds, blockIdx.x - dkdv_blocks, kLongestFirst);
+    const auto [pos, hb] = heads(blockIdx.x);
+    const JointSlot slot = joint_slot(order, pos);
+    const auto [b, h] = H(hb);
+    const PairId t = {(int64_t)slot.rank, -1, (int)h, (int)b};
+    if (slot.key) dkdv_rows<KG>(a, lds, [&](int64_t) { return t; });
+    else dq_rows<QG, T>(a, lds, [&](int64_t nqt) { return PairId{nqt - 1 - t.first, -1, t.h, t.b}; });
 }
 
 // ============================================================================ backward, 32-row workgroups
@@ -595,13 +599,12 @@ __device__ __forceinline__ void sum_over_waves(LDS_AS unsigned char *lds, const 
     }
 }
 
-__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, Divisor heads, Divisor H)
+__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t)
 {
     // lds: [wave][Q|dO] tiles, then the K and V rows
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nit = (int)((a.S + 31) / 32);
-    const TileId t = decode_tile(id, nit, heads, H, false);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base, *g = static_cast<const __bf16 *>(a.d_o) + base;
     const float *lse = a.lse + ((int64_t)t.b * a.H + t.h) * a.S, *dlt = a.delta + ((int64_t)t.b * a.H + t.h) * a.S;
@@ -747,12 +750,11 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
     sum_over_waves<false>(lds, accK, wave, lane, store(dk, a.scale));
 }
 
-__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, Divisor heads, Divisor H)
+__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t)
 {
     // lds: [wave][K|V] tiles, then the Q and dO rows
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const TileId t = decode_tile(id, (int)((a.S + 31) / 32), heads, H, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base, *g = static_cast<const __bf16 *>(a.d_o) + base;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base, *v = static_cast<const __bf16 *>(a.v) + base;
@@ -874,14 +876,17 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
     });
 }
 
-__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks, Divisor heads, Divisor H)
+__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, JointOrder order, Divisor heads, Divisor H)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     load_args_at_once(a);
     asm volatile("" ::"s"(a.d_o), "s"(a.delta));
-    if (blockIdx.x < dkdv_blocks) dkdv_own_rows(a, lds, blockIdx.x, heads, H);
-    else dq_own_rows(a, lds, blockIdx.x - dkdv_blocks, heads, H);
+    const auto [pos, hb] = heads(blockIdx.x);
+    const JointSlot slot = joint_slot(order, pos);
+    const TileId t = head_of(hb, slot.key ? (int)slot.rank : (int)((a.S + 31) / 32) - 1 - (int)slot.rank, H);
+    if (slot.key) dkdv_own_rows(a, lds, t);
+    else dq_own_rows(a, lds, t);
 }
 
 // dkdv, dq: which of the gradients to launch; both in one launch where the plan says so
@@ -905,13 +910,14 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
         e = launch_main(a, true, false, st);
         return e == hipSuccess ? launch_main(a, false, true, st) : e;
     }
-    const uint32_t dkdv_blocks = dkdv ? (uint32_t)nk : 0;
-    const int64_t blocks = dkdv_blocks + (dq ? nq : 0);
+    const JointOrder order(dkdv ? tiles : 0, dq ? tiles : 0, heads);
+    const int64_t blocks = (dkdv + dq) * tiles * heads;
+    auto launch = [&](auto kernel) { return launch_blocks(kernel, blocks, st, a, order, Divisor(heads), Divisor(a.H)); };
     switch (p.rows) {
-    case 32: return launch_blocks(attn_bwd_own_bf16_kernel, blocks, st, a, dkdv_blocks, Divisor(heads), Divisor(a.H));
-    case 64: return launch_blocks(attn_bwd_both_bf16_kernel<2, 2, 32>, blocks, st, a, dkdv_blocks);
-    case 128: return launch_blocks(attn_bwd_both_bf16_kernel<4, 4, 64>, blocks, st, a, dkdv_blocks);
-    default: return launch_blocks(attn_bwd_both_bf16_kernel<8, 8, 64>, blocks, st, a, dkdv_blocks);
+    case 32: return launch(attn_bwd_own_bf16_kernel);
+    case 64: return launch(attn_bwd_both_bf16_kernel<2, 2, 32>);
+    case 128: return launch(attn_bwd_both_bf16_kernel<4, 4, 64>);
+    default: return launch(attn_bwd_both_bf16_kernel<8, 8, 64>);
     }
 }
 

@@ -202,21 +202,6 @@ __device__ __forceinline__ PairId decode_block(const AttnArgs &a, uint32_t id, i
     return t;
 }
 
-// Division by a launch constant d >= 1 as one high product: floor(2^32 / d) makes the quotient right or one too small.
-struct Divisor {
-    uint32_t d, inv;
-    explicit Divisor(int64_t by) : d((uint32_t)by), inv((uint32_t)std::min<uint64_t>(((uint64_t)1 << 32) / (uint64_t)by, 0xffffffffu)) {}
-    __device__ __forceinline__ void operator()(uint32_t x, uint32_t &quot, uint32_t &rem) const
-    {
-        quot = __umulhi(x, inv);
-        rem = x - quot * d;
-        if (rem >= d) {
-            ++quot;
-            rem -= d;
-        }
-    }
-};
-
 // The start of a short launch is a wave's serial chain of instructions (8 cycles each) and of waits for kernel arguments: the
 // compiler asks for these one after the other where they are used, 200 cycles and more each time.  Here they come in one go.
 __device__ __forceinline__ void load_args_at_once(const AttnArgs &a)
@@ -226,12 +211,15 @@ __device__ __forceinline__ void load_args_at_once(const AttnArgs &a)
 
 // Longest-first work of one tile per workgroup, without the divisions of decode_block.
 struct TileId { int tile, h, b; };
+__device__ __forceinline__ TileId head_of(uint32_t hb, int tile, Divisor H)
+{
+    const auto [b, h] = H(hb);
+    return {tile, (int)h, (int)b};
+}
 __device__ __forceinline__ TileId decode_tile(uint32_t id, int ntiles, Divisor heads, Divisor H, bool last_is_longest)
 {
-    uint32_t rank, hb, h, b;
-    heads(id, rank, hb);
-    H(hb, b, h);
-    return {last_is_longest ? ntiles - 1 - (int)rank : (int)rank, (int)h, (int)b};
+    const auto [rank, hb] = heads(id);
+    return head_of(hb, last_is_longest ? ntiles - 1 - (int)rank : (int)rank, H);
 }
 
 // ---- asynchronous tile fill: global -> LDS without passing through registers -------------

@@ -60,6 +60,49 @@ inline double crowding(int64_t S, int64_t heads)
 }
 inline constexpr double kCrowdedJoint = 0.08, kCrowdedAlone = 0.02;       // of the time, per doubling; 256-row launches of one kernel lose less
 
+// Division by a launch constant d >= 1 as one high product: floor(2^32 / d) makes the quotient right or one too small.
+struct Division { uint32_t quot, rem; };
+struct Divisor {
+    uint32_t d, inv;
+    constexpr explicit Divisor(int64_t by) : d((uint32_t)by), inv(by == 1 ? 0xffffffffu : (uint32_t)(((uint64_t)1 << 32) / (uint64_t)by)) {}
+    constexpr Division operator()(uint32_t x) const
+    {
+        const uint32_t quot = (uint32_t)(((uint64_t)x * inv) >> 32), rem = x - quot * d;
+        return rem >= d ? Division{quot + 1, rem - d} : Division{quot, rem};
+    }
+};
+
+// The order of one launch that works key tiles (dK/dV) and query tiles (dQ), longest first over both kinds: a query tile takes
+// `ratio` of the time of the key tile of the same length, so the longest 1 - ratio of the key tiles lead and the others are
+// spread evenly among the query tiles.  Position p stands for one tile of every head.
+// In launches of up to two rounds, whose second round is what the units with the shorter first tiles can take; with all key tiles
+// in front these end early beside the longest ones (us, key tiles in front : spread by a ratio of 0.8, which matters little: 64 rows, S = 2000
+// with 6 heads 36.4 : 34.6, S = 3000 H = 4 44.6 : 44.7, S = 4000 H = 4 67.0 : 67.0; 128 rows, S = 8192 H = 4 223 : 217).  Beyond that the key tiles in front
+// fill the end with short query tiles anyhow, and units that work tiles of one kind share what they stream: S = 5000 H = 5 125 : 131,
+// S = 12000 H = 5 554 : 571, S = 16461 H = 4 791 : 801, S = 90000 H = 4 22307 : 22762.
+struct JointOrder {
+    uint32_t lead, spread;        // key tiles in front, and among the query tiles
+    Divisor mixed;                // spread + query tiles
+
+    JointOrder(int64_t keys, int64_t queries, int64_t heads)
+        : lead((uint32_t)keys), spread(0), mixed(std::max<int64_t>(queries, 1))
+    {
+        if (queries == 0 || (keys + queries) * heads > 2 * kXcds * kChunk) return;
+        const int64_t behind = keys * 4 / 5;
+        lead = (uint32_t)(keys - behind);
+        spread = (uint32_t)behind;
+        mixed = Divisor(behind + queries);
+    }
+};
+struct JointSlot { bool key; uint32_t rank; };      // rank 0: the longest tile of its kind
+constexpr JointSlot joint_slot(const JointOrder &o, uint32_t pos)
+{
+    if (pos < o.lead) return {true, pos};
+    const uint32_t m = pos - o.lead, keys = o.mixed(m * o.spread).quot;
+    if (o.mixed((m + 1) * o.spread).quot > keys) return {true, o.lead + keys};
+    return {false, m - keys};
+}
+
 // One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
 // 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
 // and after its sweep.

@@ -3,6 +3,8 @@
 //   bwd S heads      -> rows, 1 if dK/dV and dQ go out in one launch, order of dK/dV, order of dQ
 //   lin rows K N     -> tokens and features of a tile
 //   window begin end tile tile_rows live -> first row and number of rows of a tile's buffer
+//   joint keys queries heads -> for each position of a joint launch the rank of its key tile, or -1 - rank of its query tile
+//   divide x d       -> quotient and remainder
 //   order rows order -> the order that a shape of that many rows works when asked for `order`
 #include "../paper_2407_12117_amd/csrc/launch_plan.h"
 
@@ -23,6 +25,16 @@ int main()
             std::printf("%d %d %d %d\n", p.rows, p.joint, p.k_order, p.q_order);
         } else if (!std::strcmp(what, "order")) {
             std::printf("%d\n", memo::tile_order((int)a, (int)b));
+        } else if (!std::strcmp(what, "divide")) {
+            const memo::Division r = memo::Divisor(b)((uint32_t)a);
+            std::printf("%u %u\n", r.quot, r.rem);
+        } else if (!std::strcmp(what, "joint") && std::scanf("%lld", &c) == 1) {
+            const memo::JointOrder o(a, b, c);
+            for (uint32_t pos = 0; pos < a + b; ++pos) {
+                const memo::JointSlot s = memo::joint_slot(o, pos);
+                std::printf("%d ", s.key ? (int)s.rank : -1 - (int)s.rank);
+            }
+            std::printf("\n");
         } else if (!std::strcmp(what, "lin") && std::scanf("%lld", &c) == 1) {
             const memo::LinChoice &l = memo::lin_plan(a, (int)b, (int)c);
             std::printf("%d %d\n", l.bm, l.bn);

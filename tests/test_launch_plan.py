@@ -59,6 +59,21 @@ def test_backward_between_whole_rounds_stays_joint(plans, S, heads):
     assert (rows, joint) == (256, 1) or (rows, k_order) == (256, LONGEST_FIRST)
 
 
+@pytest.mark.parametrize("tiles,heads", [(1, 1), (2, 3), (5, 40), (31, 8), (32, 6), (63, 4), (64, 4), (65, 4), (256, 1), (512, 1), (7000, 2)])
+def test_joint_order_works_every_tile_once_and_longest_first(plans, tiles, heads):
+    for keys, queries in ((tiles, tiles), (tiles, 0), (0, tiles)):
+        order = plans([("joint", keys, queries, heads)])[0]
+        assert [r for r in order if r >= 0] == list(range(keys))
+        assert [-1 - r for r in order if r < 0] == list(range(queries))
+
+
+def test_division_by_a_launch_constant(plans):
+    top = (1 << 32) - 1
+    for d in (1, 2, 3, 5, 7, 40, 65535, 65536, 1000003, (1 << 26) - 1, (1 << 31) + 1, top):
+        xs = sorted({x for m in (0, 1, 2, 1000, top // d) for x in (m * d - 1, m * d, m * d + 1) if 0 <= x <= top} | {top})
+        assert plans([("divide", x, d) for x in xs]) == [divmod(x, d) for x in xs]
+
+
 def test_projection_buffers_stay_inside_the_matrix(plans):
     # every tile a workgroup may name: its own, and the ones behind its last, whose buffers are empty
     for begin, end, tile_rows in ((0, 1, 64), (0, 64, 64), (130, 40001, 256), (7, 5000, 192), (4096, 4100, 128)):
