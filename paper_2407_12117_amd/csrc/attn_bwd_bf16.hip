@@ -557,6 +557,18 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, 
     else dq_rows<QG, T>(a, lds, [&](int64_t nqt) { return PairId{nqt - 1 - t.first, -1, t.h, t.b}; });
 }
 
+// the same of 256 rows, whose launches are all beyond two rounds: first the key tiles, then the query tiles
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_long_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
+{
+    constexpr int kLds = DkdvShape<8>::kLds > DqShape<8, 64>::kLds ? DkdvShape<8>::kLds : DqShape<8, 64>::kLds;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    if (blockIdx.x < dkdv_blocks)
+        dkdv_rows<8>(a, lds, [&](int64_t nkt) { return decode_block(a, blockIdx.x, nkt, kLongestFirst, false); });
+    else
+        dq_rows<8, 64>(a, lds, [&](int64_t nqt) { return decode_block(a, blockIdx.x - dkdv_blocks, nqt, kLongestFirst, true); });
+}
+
 // ============================================================================ backward, 32-row workgroups
 // For short sequences: 32 keys (or query rows) per workgroup, the other side of the sweep in eight.  Every wave works all 32
 // rows against 32-row tiles of its own, one buffer each, so there is no barrier in the sweep; a half of the buffer
@@ -917,7 +929,7 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
     case 32: return launch(attn_bwd_own_bf16_kernel);
     case 64: return launch(attn_bwd_both_bf16_kernel<2, 2, 32>);
     case 128: return launch(attn_bwd_both_bf16_kernel<4, 4, 64>);
-    default: return launch(attn_bwd_both_bf16_kernel<8, 8, 64>);
+    default: return launch_blocks(attn_bwd_both_long_bf16_kernel, blocks, st, a, dkdv ? (uint32_t)nk : 0u);
     }
 }
 
