@@ -310,17 +310,20 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
 // The end of the kernels whose eight waves share out the keys of 32 rows: every wave has left its accumulators as sixteen
 // pieces and, per row, its (c m, row sum); each combines two pieces over the waves.  A wave without a tile has m = -inf
 // and weighs exactly zero.
+template <int CS = 1>
 __device__ __forceinline__ void merge_waves(const AttnArgs &a, const LDS_AS f32x4 *pieces, const LDS_AS f32x2 *stats, int64_t base, int64_t stat,
-                                            int64_t i, int wave, int l32, int half, int lane)
+                                            int64_t i, int wave, int l32, int half, int lane, int part = 0)
 {
+    constexpr int kOwn = CS == 1 ? 2 : 1, kPieces = 16 / CS;
+    if (kOwn * wave >= kPieces) return;               // fewer pieces than waves
     f32x2 st[kFwdWaves];
-    f32x4 x[2][kFwdWaves];
+    f32x4 x[kOwn][kFwdWaves];
 #pragma unroll
     for (int g = 0; g < kFwdWaves; ++g) st[g] = stats[g * 32 + l32];
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < kOwn; ++n)
 #pragma unroll
-        for (int g = 0; g < kFwdWaves; ++g) x[n][g] = pieces[(g * 16 + 2 * wave + n) * 64 + lane];
+        for (int g = 0; g < kFwdWaves; ++g) x[n][g] = pieces[(g * 16 + kOwn * wave + n) * 64 + lane];
     __builtin_amdgcn_sched_barrier(0);                // all reads are on their way before the first is waited for
     float top = -INFINITY, total = 0.f, weight[kFwdWaves];
 #pragma unroll
@@ -332,17 +335,17 @@ __device__ __forceinline__ void merge_waves(const AttnArgs &a, const LDS_AS f32x
     }
     if (i >= a.S) return;
     const float inv = 1.f / total;
-    __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
+    __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss + 128 / CS * part;
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < kOwn; ++n) {
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int g = 0; g < kFwdWaves; ++g)
 #pragma unroll
             for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[n][g][r];
-        store4(o + 8 * (2 * wave + n) + 4 * half, sum, inv);
+        store4(o + 8 * (kOwn * wave + n) + 4 * half, sum, inv);
     }
-    if (wave == 0 && half == 0) a.lse[stat + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
+    if (wave == 0 && half == 0 && part == 0) a.lse[stat + i] = (top + __builtin_amdgcn_logf(total)) * kLn2;
 }
 
 // 32 rows, the keys in eight: every wave works all rows against key tiles of 32 of its own, without a barrier in the sweep; one
@@ -353,8 +356,11 @@ __device__ __forceinline__ void merge_waves(const AttnArgs &a, const LDS_AS f32x
 // pieces of 32 bytes), the set-up of addresses and accumulators comes behind them, and at the end a wave leaves its
 // accumulators in its own buffer without waiting for the others.  us: S = 32 H = 2 6.0 -> 4.0, S = 640 H = 2 8.1 -> 6.8,
 // B = 2 S = 2000 H = 3 17.8 -> 14.8, S = 3000 H = 4 20.3 -> 17.8.
+// CS: the columns of O of a tile go to so many workgroups where units would be idle (column_parts, launch_plan.h).
+template <int CS>
 __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(AttnArgs a, Divisor heads, Divisor H)
 {
+    constexpr int NB = 4 / CS;    // blocks of 32 columns of O that the workgroup forms
     constexpr int T = 32, kTile = T * 256, kQ = kFwdWaves * 2 * kTile, kStats = kQ + kTile;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kFwdWaves * T * 8];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [wave][K|V] tiles, then the Q rows, then (maximum, sum)
@@ -362,7 +368,9 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const TileId t = decode_tile(blockIdx.x, (int)((a.S + T - 1) / T), heads, H, true);
+    const auto [rank, hbp] = heads(blockIdx.x);       // CS parts of a head beside each other
+    const int part = (int)(hbp % CS);
+    const TileId t = head_of(hbp / CS, (int)((a.S + T - 1) / T) - 1 - (int)rank, H);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh, row0 = (int64_t)t.tile * T;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
     const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
@@ -385,18 +393,18 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(
     const LaneAddr la = make_lane_addr(lane);
     // pieces of a row operand lie at address ^ (kc << 5), of a transposed one at address ^ (cb << 6)
     const uint32_t row = (uint32_t)(uintptr_t)lds + (uint32_t)la.row_op[0], own = (uint32_t)(uintptr_t)lds + (uint32_t)ring;
-    uint32_t ka[8], va[4][2];
+    uint32_t ka[8], va[NB][2];
 #pragma unroll
     for (int kc = 0; kc < 8; ++kc) ka[kc] = (row + ring) ^ (kc << 5);
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
+    for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
-        for (int sec = 0; sec < 2; ++sec) va[cb][sec] = (own + (uint32_t)la.tr_op[0][sec]) ^ (cb << 6);
+        for (int sec = 0; sec < 2; ++sec) va[cb][sec] = (own + (uint32_t)la.tr_op[0][sec]) ^ (uint32_t)((part * NB + cb) << 6);
     const float c = a.scale * kLog2e;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 accO[4];
+    f32x16 accO[NB];
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) accO[cb] = zero;
+    for (int cb = 0; cb < NB; ++cb) accO[cb] = zero;
     float m = -INFINITY, mc = -INFINITY, lsum = 0.f;
     bf16x8 qB[8];                 // Q^T as B operand: lane = query row l32, 8 head-dim values per 16-wide chunk
 
@@ -431,10 +439,10 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(
         }
         TrSlot vring[3];
         auto v_issue = [&](auto n, TrSlot &slot) {
-            constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
+            constexpr int kj = decltype(n)::value / NB, cb = decltype(n)::value % NB;
             lds_issue_tr<kj * 4096 + kTile>(slot, va[cb][0], va[cb][1]);
         };
-        lds_pipeline_prologue<8, 2, 2>(vring, v_issue);
+        lds_pipeline_prologue<2 * NB, 2, 2>(vring, v_issue);
         if (jt == ntiles - 1) {                       // diagonal tile: mask keys j > i
             int thr = l32 - 4 * half;
             asm volatile("" : "+v"(thr));
@@ -467,7 +475,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(
                 const float corr = __builtin_amdgcn_exp2f((m - m_new) * c);
                 lsum *= corr;
 #pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
+                for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) accO[cb][e] *= corr;
             }
@@ -477,8 +485,8 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(
         }
         lsum += psum0 + psum1;
         // O^T += V^T P^T
-        lds_pipeline_body<8, 2, 2>(vring, v_issue, [&](auto n, TrSlot &slot) {
-            constexpr int kj = decltype(n)::value / 4, cb = decltype(n)::value % 4;
+        lds_pipeline_body<2 * NB, 2, 2>(vring, v_issue, [&](auto n, TrSlot &slot) {
+            constexpr int kj = decltype(n)::value / NB, cb = decltype(n)::value % NB;
             accO[cb] = mfma32(tr_operand(slot), pB[kj], accO[cb]);
         });
         if (jn < ntiles) fill_v(jn, to);
@@ -489,12 +497,12 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(
     LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kStats);
     const float ltot = add_across_halves(lsum);
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
+    for (int e = 0; e < 4 * NB; ++e)
         pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
                                                     accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
     if (half == 0) stats[wave * T + l32] = f32x2{mc, ltot};
     __syncthreads();
-    merge_waves(a, pieces, stats, base, ((int64_t)t.b * a.H + t.h) * a.S, row0 + l32, wave, l32, half, lane);
+    merge_waves<CS>(a, pieces, stats, base, ((int64_t)t.b * a.H + t.h) * a.S, row0 + l32, wave, l32, half, lane, part);
 }
 
 // 64 rows, the keys in eight: every wave works all 64 rows (two blocks of 32) against key tiles of 32 of its own, so
@@ -682,7 +690,12 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
     if (blocks > kMaxBlocks)
         return launch_fewer_heads(a, sizeof(__bf16), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_attn_fwd_bf16(part, st); });
     switch (c.rows) {
-    case 32: return launch_blocks(attn_fwd_bf16_short_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
+    case 32: {
+        const int parts = a.o_out == a.q ? 1 : column_parts(blocks);         // in place of Q: another part may not have read it yet
+        auto launch = [&](auto kernel) { return launch_blocks(kernel, blocks * parts, st, a, Divisor(heads * parts), Divisor(a.H)); };
+        return parts == 4 ? launch(attn_fwd_bf16_short_kernel<4>) : parts == 2 ? launch(attn_fwd_bf16_short_kernel<2>)
+                                                                              : launch(attn_fwd_bf16_short_kernel<1>);
+    }
     case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
     case 128: return launch_blocks(attn_fwd_bf16_kernel<4, 64>, blocks, st, a, order);
     default: return launch_blocks(attn_fwd_bf16_kernel<8, 64>, blocks, st, a, order);

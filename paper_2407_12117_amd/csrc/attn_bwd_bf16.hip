@@ -580,39 +580,45 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_both_long_bf16_kernel(AttnArg
 // registers) with the set-up behind it, an end by 128 KB through the LDS per sum.  us with these, without, the D_i launch in both: S = 256 H = 2
 // 9.5, 10.5; S = 640 H = 2 11.8, 12.1; S = 1000 H = 4 14.7, 15.0; S = 1536 H = 2 17.6, 18.1.  Tried at the end without gain: dK's pieces put
 // while dV's are added up, barriers that do not wait for stores.
+// CS: the output columns of a tile go to so many workgroups where units would be idle (column_parts, launch_plan.h).
 constexpr int kOwnTile = 32 * 256, kOwnRing = 8 * 2 * kOwnTile;
 
-// piece of every wave -> its sum in the wave that owns the piece (two of sixteen): out(e, sum).  A wave's pieces take the place of its
-// own ring, so that the first sum needs no barrier before them.
-template <bool kFirst, typename Out>
-__device__ __forceinline__ void sum_over_waves(LDS_AS unsigned char *lds, const f32x4 (&acc)[8][2], int wave, int lane, Out &&out)
+// piece of every wave -> its sum in the wave that owns the piece (two of sixteen for NB = 8 blocks of columns): out(block of rows, block of
+// columns, sum).  A wave's pieces take the place of its own ring, so that the first sum needs no barrier before them.
+template <bool kFirst, int NB, typename Out>
+__device__ __forceinline__ void sum_over_waves(LDS_AS unsigned char *lds, const f32x4 (&acc)[NB][2], int wave, int lane, Out &&out)
 {
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
     if (!kFirst) __syncthreads(); // every wave has read the sum before
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) pieces[(wave * 16 + 8 * b + dt) * 64 + lane] = acc[dt][b];
+        for (int dt = 0; dt < NB; ++dt) pieces[(wave * 16 + NB * b + dt) * 64 + lane] = acc[dt][b];
     __syncthreads();
-    f32x4 x[2][8];
+    constexpr int kOwn = NB >= 4 ? NB / 4 : 1;
+    if (kOwn * wave >= 2 * NB) return;                // fewer pieces than waves
+    f32x4 x[kOwn][8];
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < kOwn; ++n)
 #pragma unroll
-        for (int g = 0; g < 8; ++g) x[n][g] = pieces[(g * 16 + 2 * wave + n) * 64 + lane];
+        for (int g = 0; g < 8; ++g) x[n][g] = pieces[(g * 16 + kOwn * wave + n) * 64 + lane];
     __builtin_amdgcn_sched_barrier(0);                // all reads are on their way before the first is waited for
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < kOwn; ++n) {
         f32x4 sum = x[n][0];
 #pragma unroll
         for (int g = 1; g < 8; ++g)
 #pragma unroll
             for (int r = 0; r < 4; ++r) sum[r] += x[n][g][r];
-        out(2 * wave + n, sum);
+        const int e = kOwn * wave + n;
+        out(e / NB, e % NB, sum);
     }
 }
 
-__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t)
+template <int CS>
+__device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t, int part)
 {
+    constexpr int NB = 8 / CS;                        // blocks of 16 columns of dK and dV that the workgroup forms
     // lds: [wave][Q|dO] tiles, then the K and V rows
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -648,9 +654,12 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
     __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const LdsAddr16 ad = make_lds_addr16(ring, lane);
     const uint32_t kv_base = (uint32_t)(kOwnRing - wave * 2 * kOwnTile);
-    f32x4 accV[8][2], accK[8][2];                     // dV^T, dK^T: [head-dim block][key block]; lane = key
+    uint32_t tr[NB];              // the workgroup's blocks of the transposed operands
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt)
+    for (int dt = 0; dt < NB; ++dt) tr[dt] = ad.tr16[dt] ^ (uint32_t)(part * NB << 5);
+    f32x4 accV[NB][2], accK[NB][2];                   // dV^T, dK^T: [head-dim block][key block]; lane = key
+#pragma unroll
+    for (int dt = 0; dt < NB; ++dt)
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
             accV[dt][kt] = accK[dt][kt] = kZero4;
@@ -699,10 +708,10 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
         }
         TrSlot tring[3];
         auto t_issue = [&](auto n, TrSlot &slot) {
-            constexpr int dt = decltype(n)::value % 8;
-            lds_issue_tr_pair<(decltype(n)::value < 8 ? 0 : kOwnTile)>(slot, ad.tr16[dt]);
+            constexpr int dt = decltype(n)::value % NB;
+            lds_issue_tr_pair<(decltype(n)::value < NB ? 0 : kOwnTile)>(slot, tr[dt]);
         };
-        lds_pipeline_prologue<16, 2, 2>(tring, t_issue);
+        lds_pipeline_prologue<2 * NB, 2, 2>(tring, t_issue);
         if (it == it0) {          // the causal mask: query 16qt + 4g4 + r sees key 16kt + l16 iff it is not before it
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt)
@@ -736,12 +745,12 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
             pB[kt] = pack44(s[0][kt], s[1][kt]);
             dsB[kt] = pack44(dp[0][kt], dp[1][kt]);
         }
-        lds_pipeline_body<16, 2, 2>(tring, t_issue, [&](auto n, TrSlot &slot) {
-            constexpr int dt = decltype(n)::value % 8;
-            if constexpr (decltype(n)::value == 8) fill_q(it + 8);    // Q is used up
+        lds_pipeline_body<2 * NB, 2, 2>(tring, t_issue, [&](auto n, TrSlot &slot) {
+            constexpr int dt = decltype(n)::value % NB;
+            if constexpr (decltype(n)::value == NB) fill_q(it + 8);   // Q is used up
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
-                if constexpr (decltype(n)::value < 8) accK[dt][kt] = mfma16(tr_operand(slot), dsB[kt], accK[dt][kt]);
+                if constexpr (decltype(n)::value < NB) accK[dt][kt] = mfma16(tr_operand(slot), dsB[kt], accK[dt][kt]);
                 else accV[dt][kt] = mfma16(tr_operand(slot), pB[kt], accV[dt][kt]);
             }
         });
@@ -750,11 +759,10 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
     wait_fills();                 // the empty ones too: they write LDS
 
     const int64_t j0 = (int64_t)it0 * 32 + l16;
-    __bf16 *dv = static_cast<__bf16 *>(a.dv) + base + j0 * a.ss + 4 * g4;
-    __bf16 *dk = static_cast<__bf16 *>(a.dk) + base + j0 * a.ss + 4 * g4;
+    const int64_t first = base + j0 * a.ss + 16 * NB * part + 4 * g4;
+    __bf16 *dv = static_cast<__bf16 *>(a.dv) + first, *dk = static_cast<__bf16 *>(a.dk) + first;
     auto store = [&](__bf16 *out, float mul) {
-        return [=, &a](int e, const f32x4 &sum) {
-            const int kt = e >> 3, dt = e & 7;
+        return [=, &a](int kt, int dt, const f32x4 &sum) {
             if (j0 + 16 * kt < a.S) store4(out + 16 * kt * a.ss + 16 * dt, sum, mul);
         };
     };
@@ -762,8 +770,10 @@ __device__ __forceinline__ void dkdv_own_rows(const AttnArgs &a, LDS_AS unsigned
     sum_over_waves<false>(lds, accK, wave, lane, store(dk, a.scale));
 }
 
-__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t)
+template <int CS>
+__device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t, int part)
 {
+    constexpr int NB = 8 / CS;                        // blocks of 16 columns of dQ that the workgroup forms
     // lds: [wave][K|V] tiles, then the Q and dO rows
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -793,9 +803,12 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
     fill_k(wave);
     __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const LdsAddr16 ad = make_lds_addr16(lds + ring, lane);
-    f32x4 accQ[8][2];             // dQ^T: [head-dim block of 16][query block]; lane = query, rows = head dim
+    uint32_t tr[NB];              // the workgroup's blocks of the transposed operand
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt)
+    for (int dt = 0; dt < NB; ++dt) tr[dt] = ad.tr16[dt] ^ (uint32_t)(part * NB << 5);
+    f32x4 accQ[NB][2];            // dQ^T: [head-dim block of 16][query block]; lane = query, rows = head dim
+#pragma unroll
+    for (int dt = 0; dt < NB; ++dt)
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
             accQ[dt][qt] = kZero4;
@@ -850,8 +863,8 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
             contract(IntC<0>{}, s, qB, zeros);
         }
         TrSlot kring[3];
-        auto k_issue = [&](auto n, TrSlot &slot) { lds_issue_tr_pair<0>(slot, ad.tr16[decltype(n)::value]); };
-        lds_pipeline_prologue<8, 2, 2>(kring, k_issue);
+        auto k_issue = [&](auto n, TrSlot &slot) { lds_issue_tr_pair<0>(slot, tr[decltype(n)::value]); };
+        lds_pipeline_prologue<NB, 2, 2>(kring, k_issue);
         if (jt == ntiles - 1) {
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
@@ -873,7 +886,7 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
                 }
             dsB[qt] = pack44(s[0][qt], s[1][qt]);
         }
-        lds_pipeline_body<8, 2, 2>(kring, k_issue, [&](auto n, TrSlot &slot) {
+        lds_pipeline_body<NB, 2, 2>(kring, k_issue, [&](auto n, TrSlot &slot) {
             constexpr int dt = decltype(n)::value;
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt) accQ[dt][qt] = mfma16(tr_operand(slot), dsB[qt], accQ[dt][qt]);
@@ -881,24 +894,25 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
         fill_k(jt + 8);
     }
     wait_fills();                 // the empty ones too: they write LDS
-    __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + i0 * a.ss + 4 * g4;
-    sum_over_waves<true>(lds, accQ, wave, lane, [=, &a](int e, const f32x4 &sum) {
-        const int qt = e >> 3, dt = e & 7;
+    __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + i0 * a.ss + 16 * NB * part + 4 * g4;
+    sum_over_waves<true>(lds, accQ, wave, lane, [=, &a](int qt, int dt, const f32x4 &sum) {
         if (i0 + 16 * qt < a.S) store4(dq + 16 * qt * a.ss + 16 * dt, sum, a.scale);
     });
 }
 
+template <int CS>
 __global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, JointOrder order, Divisor heads, Divisor H)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     load_args_at_once(a);
     asm volatile("" ::"s"(a.d_o), "s"(a.delta));
-    const auto [pos, hb] = heads(blockIdx.x);
+    const auto [pos, hbp] = heads(blockIdx.x);        // CS parts of a head beside each other
+    const int part = (int)(hbp % CS);
     const JointSlot slot = joint_slot(order, pos);
-    const TileId t = head_of(hb, slot.key ? (int)slot.rank : (int)((a.S + 31) / 32) - 1 - (int)slot.rank, H);
-    if (slot.key) dkdv_own_rows(a, lds, t);
-    else dq_own_rows(a, lds, t);
+    const TileId t = head_of(hbp / CS, slot.key ? (int)slot.rank : (int)((a.S + 31) / 32) - 1 - (int)slot.rank, H);
+    if (slot.key) dkdv_own_rows<CS>(a, lds, t, part);
+    else dq_own_rows<CS>(a, lds, t, part);
 }
 
 // dkdv, dq: which of the gradients to launch; both in one launch where the plan says so
@@ -923,13 +937,20 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
         return e == hipSuccess ? launch_main(a, false, true, st) : e;
     }
     const JointOrder order(dkdv ? tiles : 0, dq ? tiles : 0, heads);
-    const int64_t blocks = (dkdv + dq) * tiles * heads;
-    auto launch = [&](auto kernel) { return launch_blocks(kernel, blocks, st, a, order, Divisor(heads), Divisor(a.H)); };
+    auto launch = [&](auto kernel, int parts = 1) {
+        return launch_blocks(kernel, (dkdv + dq) * tiles * heads * parts, st, a, order, Divisor(heads * parts), Divisor(a.H));
+    };
     switch (p.rows) {
-    case 32: return launch(attn_bwd_own_bf16_kernel);
+    case 32:
+        // a dQ that takes the place of Q or dO is not split: another part may not have read them yet
+        switch (dq_in_place(a) ? 1 : column_parts(2 * tiles * heads)) {
+        case 4: return launch(attn_bwd_own_bf16_kernel<4>, 4);
+        case 2: return launch(attn_bwd_own_bf16_kernel<2>, 2);
+        default: return launch(attn_bwd_own_bf16_kernel<1>);
+        }
     case 64: return launch(attn_bwd_both_bf16_kernel<2, 2, 32>);
     case 128: return launch(attn_bwd_both_bf16_kernel<4, 4, 64>);
-    default: return launch_blocks(attn_bwd_both_long_bf16_kernel, blocks, st, a, dkdv ? (uint32_t)nk : 0u);
+    default: return launch_blocks(attn_bwd_both_long_bf16_kernel, (dkdv + dq) * tiles * heads, st, a, dkdv ? (uint32_t)nk : 0u);
     }
 }
 

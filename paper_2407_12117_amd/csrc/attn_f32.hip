@@ -7,7 +7,9 @@
 // vector units'; but one MFMA instruction does 32 cycles of that work from two registers, where the
 // vector form needs an LDS read per multiply-add and lane.  An earlier VALU version of these kernels ran at 5 to
 // 7 TFLOP/s, bound by its scalar LDS reads; these reach 118 (forward) and 117 (backward, of its seven contractions) at
-// S = 5000, B = 2, H = 4, d = 128.
+// S = 5000, B = 2, H = 4, d = 128.  Where units would be idle a tile's output columns go to two or four workgroups, which halves or quarters
+// the second contractions of the longest tile, the one that such a launch takes (us, with the D_i launch: S = 1024 H = 1 d = 64 forward
+// 12.9 -> 10.8, backward 26.8 -> 23.0; d = 128 21.5 -> 17.9 and 43.1 -> 37.2).
 //
 // Operand conventions of the 16x16x4 MFMA, D = A(16xK4) * B(K4x16), lane = 16*g4 + l16:
 //   A : lane holds row l16, k = g4;  B : lane holds col l16, k = g4;
@@ -45,7 +47,8 @@ struct F32Shape {
     static constexpr int kTile = kT * D * 4, kFills = kTile / 1024;       // bytes; fill instructions
     static constexpr int kStage = 2 * kTile, kRing = kF32Waves * kStage;
     static constexpr int kPieces = D / 16;            // f32x4 per lane of one accumulator set
-    static_assert(kRing >= kF32Waves * kPieces * 1024 && kRing <= 128 * 1024, "the combination lays the accumulators over the ring");
+    static constexpr int kSet = kStage / 1024;        // a wave's pieces lie in its own buffer, this many apart from the next wave's
+    static_assert(kPieces <= kSet && kRing <= 128 * 1024, "the combination lays the accumulators over the ring");
 };
 
 // head dim 64: LDS has room for two workgroups per compute unit, and 128 registers hold a wave
@@ -95,17 +98,17 @@ struct F32Fill {
 
 // LDS addresses of a lane's operand reads within a tile (bf16_tiles.h has the hand-issued pipeline they go through):
 //   row[c % 4] + 256 (c / 4)   row-major operand: row l16, floats 16c + 4*g4 ..
-//   tr[r] + 256 h              transposed operand: row 4*g4 + r, floats 64h + 4*l16 ..
+//   tr[r] + 256 h              transposed operand: row 4*g4 + r, floats 64h + 4*l16 .. (of these the workgroup's part)
 struct F32Addr { uint32_t row[4], tr[4]; };
-template <int D>
-__device__ __forceinline__ F32Addr f32_addr(const LDS_AS unsigned char *base, int l16, int g4)
+template <int D, int CS>
+__device__ __forceinline__ F32Addr f32_addr(const LDS_AS unsigned char *base, int l16, int g4, int part)
 {
     F32Addr ad;
     const uint32_t b = (uint32_t)(uintptr_t)base;
 #pragma unroll
     for (int c = 0; c < 4; ++c) ad.row[c] = b + (uint32_t)(l16 * D * 4 + (((4 * c + g4) ^ SwzB::f(l16)) << 4));
 #pragma unroll
-    for (int r = 0; r < 4; ++r) ad.tr[r] = b + (uint32_t)((4 * g4 + r) * D * 4 + ((l16 ^ SwzB::f(4 * g4 + r)) << 4));
+    for (int r = 0; r < 4; ++r) ad.tr[r] = b + (uint32_t)((4 * g4 + r) * D * 4 + ((l16 ^ SwzB::f(4 * g4 + r)) << 4) + 16 / CS * part);
     return ad;
 }
 
@@ -133,28 +136,48 @@ __device__ __forceinline__ void f32_load_row(f32x4 (&dst)[D / 16], const float *
 
 constexpr int kDepth = 3;         // operand reads in flight ahead of their MFMAs
 
+// CS workgroups share out the output columns of a tile (column_parts, launch_plan.h): block e of a half is in part e / (4 / CS), and a
+// workgroup has kBlocks = D / 16 / CS accumulators.
+template <int CS> struct F32Cols { float x[4 / CS]; };
+template <> struct F32Cols<1> { f32x4 x; };
+template <> struct F32Cols<2> { f32x2 x; };
+template <int N, int CS>
+__device__ __forceinline__ void lds_wait(F32Cols<CS> &c)
+{
+    if constexpr (CS == 4) asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(c.x[0]) : "n"(N));
+    else asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(c.x) : "n"(N));
+}
+template <int OFF, int CS>
+__device__ __forceinline__ void lds_issue_cols(F32Cols<CS> &dst, uint32_t addr)
+{
+    static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");
+    if constexpr (CS == 1) lds_issue_b128<OFF>(dst.x, addr);
+    else if constexpr (CS == 2) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst.x) : "v"(addr), "n"(OFF) : "memory");
+    else asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst.x[0]) : "v"(addr), "n"(OFF) : "memory");
+}
+
 // acc^T[dim][col] += tile^T x (tile rows 4*g4 + r), tile OFF bytes into the buffer: item n = (r = n / (D/64), h = n % (D/64)),
-// one read, four MFMAs.  f32_outer_issue asks for the first operands ahead of the element-wise work.
-template <int D, int OFF>
+// one read, 4 / CS MFMAs.  The constructor asks for the first operands ahead of the element-wise work.
+template <int D, int OFF, int CS>
 struct F32Outer {
-    static constexpr int H = D / 64, N = 4 * H;
-    f32x4 ring[kDepth + 1];
+    static constexpr int H = D / 64, N = 4 * H, E = 4 / CS;
+    F32Cols<CS> ring[kDepth + 1];
     const F32Addr &ad;
     __device__ __forceinline__ F32Outer(const F32Addr &addr) : ad(addr)
     {
-        lds_pipeline_prologue<N, kDepth, 1>(ring, [&](auto n, f32x4 &slot) { issue(n, slot); });
+        lds_pipeline_prologue<N, kDepth, 1>(ring, [&](auto n, F32Cols<CS> &slot) { issue(n, slot); });
     }
     template <typename I>
-    __device__ __forceinline__ void issue(I, f32x4 &slot)
+    __device__ __forceinline__ void issue(I, F32Cols<CS> &slot)
     {
-        lds_issue_b128<OFF + 256 * (I::value % H)>(slot, ad.tr[I::value / H]);
+        lds_issue_cols<OFF + 256 * (I::value % H)>(slot, ad.tr[I::value / H]);
     }
-    __device__ __forceinline__ void run(f32x4 (&acc)[D / 16], const f32x4 &x)
+    __device__ __forceinline__ void run(f32x4 (&acc)[D / 16 / CS], const f32x4 &x)
     {
-        lds_pipeline_body<N, kDepth, 1>(ring, [&](auto n, f32x4 &slot) { issue(n, slot); }, [&](auto n, f32x4 &slot) {
+        lds_pipeline_body<N, kDepth, 1>(ring, [&](auto n, F32Cols<CS> &slot) { issue(n, slot); }, [&](auto n, F32Cols<CS> &slot) {
             constexpr int r = decltype(n)::value / H, h = decltype(n)::value % H;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[4 * h + e] = mfma4(slot[e], x[r], acc[4 * h + e]);
+            for (int e = 0; e < E; ++e) acc[E * h + e] = mfma4(slot.x[e], x[r], acc[E * h + e]);
         });
     }
 };
@@ -209,28 +232,51 @@ __device__ __forceinline__ void f32_two_scores(f32x4 &s, f32x4 &dp, const F32Add
     s = scores.sum();
 }
 
-// Accumulator piece 4h + r of a lane: the four consecutive dims 64h + 16*g4 + 4r .. of its column.
-template <int D>
-__device__ __forceinline__ f32x4 f32_piece(const f32x4 (&acc)[D / 16], int p)
+// Accumulator piece p = h * 4/CS + i of a lane, four values: blocks e of rows r = CS * i .. of half h, which are the dims
+// 64h + 16*g4 + 4r + 4/CS * part + e of its column (CS = 1: four consecutive ones).
+template <int D, int CS>
+__device__ __forceinline__ f32x4 f32_piece(const f32x4 (&acc)[D / 16 / CS], int p)
 {
-    const int h = p >> 2, r = p & 3;
-    return f32x4{acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]};
+    constexpr int E = 4 / CS;
+    f32x4 x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = acc[E * (p / E) + k % E][CS * (p % E) + k / E];
+    return x;
 }
 
-template <int D, bool FAR>
-__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(AttnArgs a)
+// out: the lane's column at dim 16*g4 + 4/CS * part
+template <int CS>
+__device__ __forceinline__ void f32_store_piece(float *out, int p, const f32x4 &x)
+{
+    constexpr int E = 4 / CS;
+    float *at = out + 64 * (p / E) + 4 * CS * (p % E);
+    if constexpr (CS == 1) {
+        *reinterpret_cast<f32x4 *>(at) = x;
+    } else if constexpr (CS == 2) {
+        *reinterpret_cast<f32x2 *>(at) = f32x2{x[0], x[1]};
+        *reinterpret_cast<f32x2 *>(at + 4) = f32x2{x[2], x[3]};
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) at[4 * k] = x[k];
+    }
+}
+
+template <int D, bool FAR, int CS>
+__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(AttnArgs a, Divisor heads, Divisor H)
 {
     using Shape = F32Shape<D>;
-    constexpr int KS = kF32Waves, NP = Shape::kPieces;
+    constexpr int KS = kF32Waves, NP = Shape::kPieces / CS;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[Shape::kRing + kF32Waves * 16 * 8];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, then (maximum, sum) per wave and row
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const PairId t = decode_block(a, blockIdx.x, (a.S + kT - 1) / kT, kLongestFirst, true);
+    const auto [rank, hbp] = heads(blockIdx.x);       // CS parts of a head beside each other
+    const int part = (int)(hbp % CS);
+    const TileId t = head_of(hbp / CS, (int)((a.S + kT - 1) / kT) - 1 - (int)rank, H);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const float *k = static_cast<const float *>(a.k) + base, *v = static_cast<const float *>(a.v) + base;
-    const int64_t row0 = t.first * kT, i = row0 + l16;
-    const int ntiles = (int)((min(row0 + kT, a.S) - 1) / kT) + 1;
+    const int64_t row0 = (int64_t)t.tile * kT, i = row0 + l16;
+    const int ntiles = t.tile + 1;                    // the last one is the diagonal
     const float c = a.scale * kLog2e;
     LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
     const F32Fill<D, FAR> fill(a.ss, lane);
@@ -240,11 +286,11 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
         fill_k(wave);
         fill_v(wave);
     }
-    const F32Addr ad = f32_addr<D>(ring, l16, g4);
-    f32x4 q[D / 16], acc[D / 16];
+    const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
+    f32x4 q[D / 16], acc[D / 16 / CS];
     f32_load_row<D>(q, static_cast<const float *>(a.q) + base + (i < a.S ? i : a.S - 1) * a.ss, g4);
 #pragma unroll
-    for (int n = 0; n < D / 16; ++n) acc[n] = kZero4;
+    for (int n = 0; n < D / 16 / CS; ++n) acc[n] = kZero4;
     float m = -INFINITY, lsum = 0.f;                  // running maximum and sum of this lane's keys
 
     for (int jt = wave; jt < ntiles; jt += KS) {
@@ -268,7 +314,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
         } else {
             wait_fills();
         }
-        F32Outer<D, Shape::kTile> pv(ad);         // the first V operands: their latency hides behind the softmax
+        F32Outer<D, Shape::kTile, CS> pv(ad);         // the first V operands: their latency hides behind the softmax
         f32x4 s = scores.sum();
         if (jt == ntiles - 1) {         // key 4*g4 + r of the tile is visible to query l16 iff it is <= l16
 #pragma unroll
@@ -293,7 +339,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
             m = m_new;
             lsum *= corr;
 #pragma unroll
-            for (int e = 0; e < D / 16; ++e) acc[e] *= corr;
+            for (int e = 0; e < D / 16 / CS; ++e) acc[e] *= corr;
             exponentials();
         }
         lsum += (p[0] + p[1]) + (p[2] + p[3]);
@@ -305,9 +351,8 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
 
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
     LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + Shape::kRing);
-    __syncthreads();              // every wave has left the last LDS buffer
 #pragma unroll
-    for (int p = 0; p < NP; ++p) pieces[(wave * NP + p) * 64 + lane] = f32_piece<D>(acc, p);
+    for (int p = 0; p < NP; ++p) pieces[(wave * Shape::kSet + p) * 64 + lane] = f32_piece<D, CS>(acc, p);
     if (g4 == 0) stats[wave * 16 + l16] = f32x2{m, lsum};
     __syncthreads();
     float top = -INFINITY, total = 0.f, weight[KS];
@@ -323,53 +368,52 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
         total += weight[g] * st[g][1];
     }
     if (i >= a.S) return;
-    float *o = static_cast<float *>(a.o_out) + base + i * a.ss + 16 * g4;
+    float *o = static_cast<float *>(a.o_out) + base + i * a.ss + 16 * g4 + 4 / CS * part;
     const float inv = 1.f / total;
     for (int p = wave; p < NP; p += KS) {
         f32x4 sum = kZero4;
 #pragma unroll
-        for (int g = 0; g < KS; ++g) sum += weight[g] * pieces[(g * NP + p) * 64 + lane];
-        *reinterpret_cast<f32x4 *>(o + 64 * (p >> 2) + 4 * (p & 3)) = sum * inv;
+        for (int g = 0; g < KS; ++g) sum += weight[g] * pieces[(g * Shape::kSet + p) * 64 + lane];
+        f32_store_piece<CS>(o, p, sum * inv);
     }
-    if (wave == 0 && g4 == 0) {
+    if (wave == 0 && g4 == 0 && part == 0) {
 #pragma clang fp contract(off)    // the rounded product, as in f32_prob
         a.lse[((int64_t)t.b * a.H + t.h) * a.S + i] = top * a.scale + __builtin_amdgcn_logf(total) * kLn2;
     }
 }
 
 // Adds up the accumulators of the eight waves and writes mul times them: out points at the lane's row.
-template <int D>
-__device__ __forceinline__ void f32_combine(LDS_AS unsigned char *lds, const f32x4 (&acc)[D / 16], float *out, bool live, float mul,
+template <int D, int CS, bool kFirst>
+__device__ __forceinline__ void f32_combine(LDS_AS unsigned char *lds, const f32x4 (&acc)[D / 16 / CS], float *out, bool live, float mul,
                                             int wave, int lane)
 {
     using Shape = F32Shape<D>;
-    constexpr int NP = Shape::kPieces, KS = kF32Waves;
+    constexpr int NP = Shape::kPieces / CS, KS = kF32Waves;
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
-    __syncthreads();              // every wave has left what lies there
+    if (!kFirst) __syncthreads(); // every wave has read the sum before
 #pragma unroll
-    for (int p = 0; p < NP; ++p) pieces[(wave * NP + p) * 64 + lane] = f32_piece<D>(acc, p);
+    for (int p = 0; p < NP; ++p) pieces[(wave * Shape::kSet + p) * 64 + lane] = f32_piece<D, CS>(acc, p);
     __syncthreads();
     for (int p = wave; p < NP; p += KS) {
         f32x4 sum = kZero4;
 #pragma unroll
-        for (int g = 0; g < KS; ++g) sum += pieces[(g * NP + p) * 64 + lane];
-        if (live) *reinterpret_cast<f32x4 *>(out + 64 * (p >> 2) + 4 * (p & 3)) = sum * mul;
+        for (int g = 0; g < KS; ++g) sum += pieces[(g * Shape::kSet + p) * 64 + lane];
+        if (live) f32_store_piece<CS>(out, p, sum * mul);
     }
 }
 
 // dQ_i = scale * sum_{j<=i} dS_ij k_j, dS_ij = P_ij (dO_i.v_j - D_i), P_ij = exp(s_ij - LSE_i); rows = queries
-template <int D, bool FAR>
-__device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id, bool longest_first)
+template <int D, bool FAR, int CS>
+__device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t, int part)
 {
     using Shape = F32Shape<D>;
     constexpr int KS = kF32Waves;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const PairId t = decode_block(a, id, (a.S + kT - 1) / kT, kLongestFirst, longest_first);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh, stat = ((int64_t)t.b * a.H + t.h) * a.S;
     const float *k = static_cast<const float *>(a.k) + base, *v = static_cast<const float *>(a.v) + base;
-    const int64_t row0 = t.first * kT, i = row0 + l16, iq = i < a.S ? i : a.S - 1;
-    const int ntiles = (int)((min(row0 + kT, a.S) - 1) / kT) + 1;
+    const int64_t i = (int64_t)t.tile * kT + l16, iq = i < a.S ? i : a.S - 1;
+    const int ntiles = t.tile + 1;                    // the last one is the diagonal
     LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
@@ -378,20 +422,20 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
         fill_k(wave);
         fill_v(wave);
     }
-    const F32Addr ad = f32_addr<D>(ring, l16, g4);
-    f32x4 q[D / 16], go[D / 16], acc[D / 16];
+    const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
+    f32x4 q[D / 16], go[D / 16], acc[D / 16 / CS];
     f32_load_row<D>(q, static_cast<const float *>(a.q) + base + iq * a.ss, g4);
     f32_load_row<D>(go, static_cast<const float *>(a.d_o) + base + iq * a.ss, g4);
     const float lse = a.lse[stat + iq], nd = -a.delta[stat + iq];
 #pragma unroll
-    for (int n = 0; n < D / 16; ++n) acc[n] = kZero4;
+    for (int n = 0; n < D / 16 / CS; ++n) acc[n] = kZero4;
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
         wait_fills();
         f32x4 s, dp = {nd, nd, nd, nd};               // keys 4*g4 + r x query l16
         f32_two_scores<D>(s, dp, ad, q, go);
         if (more) fill_v(jt + KS);                    // V is used up
-        F32Outer<D, 0> kds(ad);
+        F32Outer<D, 0, CS> kds(ad);
         if (jt == ntiles - 1) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -403,22 +447,21 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
         kds.run(acc, ds);                             // dQ^T += K^T dS^T
         if (more) fill_k(jt + KS);
     }
-    f32_combine<D>(lds, acc, static_cast<float *>(a.dq) + base + iq * a.ss + 16 * g4, i < a.S, a.scale, wave, lane);
+    f32_combine<D, CS, true>(lds, acc, static_cast<float *>(a.dq) + base + iq * a.ss + 16 * g4 + 4 / CS * part, i < a.S, a.scale, wave, lane);
 }
 
 // dV_j = sum_{i>=j} P_ij dO_i,  dK_j = scale * sum_{i>=j} dS_ij q_i; rows = keys, K and V rows in registers
-template <int D, bool FAR>
-__device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, uint32_t id)
+template <int D, bool FAR, int CS>
+__device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t, int part)
 {
     using Shape = F32Shape<D>;
     constexpr int QS = kF32Waves;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const PairId t = decode_block(a, id, (a.S + kT - 1) / kT, kLongestFirst, false);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh, stat = ((int64_t)t.b * a.H + t.h) * a.S;
     const float *q = static_cast<const float *>(a.q) + base, *g = static_cast<const float *>(a.d_o) + base;
-    const int64_t col0 = t.first * kT, j = col0 + l16, jk = j < a.S ? j : a.S - 1;
-    const int it0 = (int)(col0 / kT), ntiles = (int)((a.S + kT - 1) / kT);
+    const int64_t col0 = (int64_t)t.tile * kT, j = col0 + l16, jk = j < a.S ? j : a.S - 1;
+    const int it0 = t.tile, ntiles = (int)((a.S + kT - 1) / kT);
     LDS_AS unsigned char *ring = lds + wave * Shape::kStage;
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_q = [&](int it) { fill(ring, q, a.ss, (int64_t)it * kT, a.S, lane); };
@@ -431,18 +474,18 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
             d[r] = row < a.S ? a.delta[stat + row] : 0.f;
         }
     };
-    const F32Addr ad = f32_addr<D>(ring, l16, g4);
+    const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 lse_n = kZero4, dl_n = kZero4;
     if (it0 + wave < ntiles) {
         fill_q(it0 + wave);
         fill_g(it0 + wave);
         load_stats(it0 + wave, lse_n, dl_n);
     }
-    f32x4 kr[D / 16], vr[D / 16], dk[D / 16], dv[D / 16];
+    f32x4 kr[D / 16], vr[D / 16], dk[D / 16 / CS], dv[D / 16 / CS];
     f32_load_row<D>(kr, static_cast<const float *>(a.k) + base + jk * a.ss, g4);
     f32_load_row<D>(vr, static_cast<const float *>(a.v) + base + jk * a.ss, g4);
 #pragma unroll
-    for (int n = 0; n < D / 16; ++n) dk[n] = dv[n] = kZero4;
+    for (int n = 0; n < D / 16 / CS; ++n) dk[n] = dv[n] = kZero4;
     for (int it = it0 + wave; it < ntiles; it += QS) {
         const bool more = it + QS < ntiles;
         wait_fills();
@@ -452,7 +495,7 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
 #pragma unroll
         for (int r = 0; r < 4; ++r) dp[r] = -dl[r];
         f32_two_scores<D>(s, dp, ad, kr, vr);
-        F32Outer<D, Shape::kTile> gp(ad);
+        F32Outer<D, Shape::kTile, CS> gp(ad);
         if (it == it0) {         // query 4*g4 + r of the tile sees key l16 iff it is >= l16
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -471,26 +514,32 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
         }
         gp.run(dv, p);                                // dV^T += dO^T P
         if (more) fill_g(it + QS);                    // dO is used up
-        F32Outer<D, 0> qds(ad);
+        F32Outer<D, 0, CS> qds(ad);
         qds.run(dk, ds);                              // dK^T += Q^T dS
         if (more) fill_q(it + QS);
     }
-    f32_combine<D>(lds, dv, static_cast<float *>(a.dv) + base + jk * a.ss + 16 * g4, j < a.S, 1.f, wave, lane);
-    f32_combine<D>(lds, dk, static_cast<float *>(a.dk) + base + jk * a.ss + 16 * g4, j < a.S, a.scale, wave, lane);
+    f32_combine<D, CS, true>(lds, dv, static_cast<float *>(a.dv) + base + jk * a.ss + 16 * g4 + 4 / CS * part, j < a.S, 1.f, wave, lane);
+    f32_combine<D, CS, false>(lds, dk, static_cast<float *>(a.dk) + base + jk * a.ss + 16 * g4 + 4 / CS * part, j < a.S, a.scale, wave, lane);
 }
 
-// One launch for the gradients asked for: first the dkdv_blocks key-stationary workgroups, then the query-stationary ones.  Longest
-// first, except where all of them are resident at once, two per unit (head dim 64): then a unit gets the key tile
+// One launch for the gradients asked for: first the key-stationary workgroups (key_ranks tiles of every head), then the query-stationary
+// ones.  Longest first, except where all of them are resident at once, two per unit (head dim 64): then a unit gets the key tile
 // of a rank and the query tile of the same rank, and the query tiles go shortest first to even that out
 // (S = 2000, H = 2: 66 us both longest first).
-template <int D, bool FAR>
-__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t dkdv_blocks)
+template <int D, bool FAR, int CS>
+__global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t key_ranks, Divisor heads, Divisor H)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D>::kRing];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     const bool resident = D == 64 && gridDim.x <= 2 * kXcds * kChunk;
-    if (blockIdx.x < dkdv_blocks) f32_dkdv_rows<D, FAR>(a, lds, blockIdx.x);
-    else f32_dq_rows<D, FAR>(a, lds, blockIdx.x - dkdv_blocks, !resident);
+    const uint32_t key_blocks = key_ranks * heads.d;
+    if (blockIdx.x < key_blocks) {
+        const auto [rank, hbp] = heads(blockIdx.x);
+        f32_dkdv_rows<D, FAR, CS>(a, lds, head_of(hbp / CS, (int)rank, H), (int)(hbp % CS));
+    } else {
+        const auto [rank, hbp] = heads(blockIdx.x - key_blocks);
+        f32_dq_rows<D, FAR, CS>(a, lds, head_of(hbp / CS, resident ? (int)rank : (int)((a.S + kT - 1) / kT) - 1 - (int)rank, H), (int)(hbp % CS));
+    }
 }
 
 // D_i = sum_c dO_ic O_ic.  16 lanes per row, 16 rows per 256-thread workgroup.
@@ -528,17 +577,33 @@ hipError_t launch_fwd_f32(const AttnArgs &a, hipStream_t st)
     const int64_t blocks = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst);
     if (blocks > kMaxBlocks)
         return launch_fewer_heads(a, sizeof(float), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_fwd_f32<D, FAR>(part, st); });
-    return launch_blocks(attn_fwd_f32_kernel<D, FAR>, blocks, st, a);
+    const int64_t heads = (int64_t)a.H * a.B;
+    auto launch = [&](auto kernel, int parts) { return launch_blocks(kernel, blocks * parts, st, a, Divisor(heads * parts), Divisor(a.H)); };
+    if constexpr (!FAR) {
+        const int parts = a.o_out == a.q ? 1 : column_parts(blocks);         // in place of Q: another part may not have read it yet
+        if (parts == 4) return launch(attn_fwd_f32_kernel<D, FAR, 4>, 4);
+        if (parts == 2) return launch(attn_fwd_f32_kernel<D, FAR, 2>, 2);
+    }
+    return launch(attn_fwd_f32_kernel<D, FAR, 1>, 1);
 }
 
 // dkdv, dq: which of the two to launch
 template <int D, bool FAR>
 hipError_t launch_bwd_f32(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 {
-    const int64_t n = order_grid((a.S + kT - 1) / kT, (int64_t)a.H * a.B, kLongestFirst), blocks = n * (dkdv + dq);
+    const int64_t heads = (int64_t)a.H * a.B, tiles = (a.S + kT - 1) / kT, blocks = tiles * heads * (dkdv + dq);
     if (blocks > kMaxBlocks)
         return launch_fewer_heads(a, sizeof(float), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_bwd_f32<D, FAR>(part, dkdv, dq, st); });
-    return launch_blocks(attn_bwd_f32_kernel<D, FAR>, blocks, st, a, dkdv ? (uint32_t)n : 0u);
+    auto launch = [&](auto kernel, int parts) {
+        return launch_blocks(kernel, blocks * parts, st, a, dkdv ? (uint32_t)tiles : 0u, Divisor(heads * parts), Divisor(a.H));
+    };
+    if constexpr (!FAR) {
+        // a dQ that takes the place of Q or dO is not split: another part may not have read them yet
+        const int parts = dq_in_place(a) ? 1 : column_parts(2 * tiles * heads);
+        if (parts == 4) return launch(attn_bwd_f32_kernel<D, FAR, 4>, 4);
+        if (parts == 2) return launch(attn_bwd_f32_kernel<D, FAR, 2>, 2);
+    }
+    return launch(attn_bwd_f32_kernel<D, FAR, 1>, 1);
 }
 
 }  // namespace

@@ -103,6 +103,18 @@ constexpr JointSlot joint_slot(const JointOrder &o, uint32_t pos)
     return {false, m - keys};
 }
 
+// Launches of 16- or 32-row workgroups that leave units idle: a tile goes to so many workgroups, each of which forms the scores again
+// and its part of the output columns, as long as all of them find a unit.  What shrinks with the parts is the second half of a
+// step's contractions, the accumulators to clear and the sums through the LDS at the end; output bits do not change.  us in 1 : 2 : 4
+// parts, bf16 forward S = 32 H = 2 4.0 : 3.4 : 3.2, S = 640 H = 2 6.8 : 6.0 : 5.8, S = 2000 H = 1 12.0 : 11.0 : 11.0; bf16 backward with the D_i
+// launch S = 32 H = 2 8.4 : 7.2 : 6.6, S = 500 H = 2 11.1 : 9.6 : 9.2.  With more workgroups than units it loses: two parts of S = 1000 H = 4
+// backward 14.7 : 17.2, S = 2000 H = 4 forward 12.6 : 15.3.
+inline int column_parts(int64_t blocks)
+{
+    const int64_t units = kXcds * kChunk;
+    return blocks * 4 <= units ? 4 : blocks * 2 <= units ? 2 : 1;
+}
+
 // One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
 // 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
 // and after its sweep.

@@ -504,3 +504,17 @@ def test_fp32_rows_almost_too_far_for_a_buffer(d, ss):
 def test_bf16_rows_as_far_apart_as_accepted(S, heads):
     # the largest row stride that is not refused: a 64-row tile spans 2 GiB, in every shape of both directions
     _far_rows("bf16", S, heads, 128, 1 << 24)
+
+
+@pytest.mark.parametrize("B,S,H", [(1, 33, 1), (2, 255, 2), (1, 480, 4), (1, 1023, 2), (1, 1025, 2), (1, 2050, 1)])
+def test_bf16_columns_in_parts(oracle, B, S, H):
+    # launches that go out with the output columns in four, two and one parts, on both sides of either limit (64 and 128
+    # workgroups), forward and backward; fewer tiles than waves among them
+    _dense_case(oracle, B, S, H, 128, "bf16", 8100 + S)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,S,H", [(1, 17, 1), (2, 250, 2), (1, 513, 1), (1, 529, 2), (1, 1025, 1), (1, 2049, 1)])
+def test_fp32_columns_in_parts(oracle, B, S, H, d):
+    # the same for the 16-row workgroups of fp32
+    _dense_case(oracle, B, S, H, d, "f32", 8200 + S)
