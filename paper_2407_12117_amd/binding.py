@@ -77,6 +77,7 @@ class MemoError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def lib():
@@ -145,8 +146,23 @@ def lib():
     L.memo_layernorm_rows.restype = ctypes.c_int
     L.memo_linear_rows.argtypes = [vp, vp, vp, vp, i64, ctypes.c_int32, ctypes.c_int32, i64, i64, vp]
     L.memo_linear_rows.restype = ctypes.c_int
+    L.address = {name: ctypes.cast(getattr(L, name), vp).value for name in
+                 ("memo_attn_fwd", "memo_attn_bwd", "memo_attn_bwd_static", "memo_attn_bwd_workspace_bytes")}
     _lib = L
     return L
+
+
+def _marshal():
+    """The native marshalling of the attention calls; raises if it has not been built."""
+    global _native
+    if _native is None:
+        try:
+            from . import _marshal as native
+        except ImportError as e:
+            raise RuntimeError("paper_2407_12117_amd/_marshal.so is missing: build it with "
+                               "`python -c 'import __graft_entry__ as g; g.build()'`") from e
+        _native = native
+    return _native
 
 
 def status_str(status):
@@ -189,8 +205,8 @@ def _stream_obj(stream):
 _DTYPE_CODES = {torch.float32: MEMO_F32, torch.bfloat16: MEMO_BF16}
 
 
-# make_desc and _same_layout run on every call of a loop whose kernels take some ten microseconds: each property of a
-# tensor is asked for once (S = 640 forward + static backward: 26.4 us of host time a pass, now 18.6, see _stream_ptr too).
+# make_desc and _same_layout serve the calls that the native marshalling (csrc/marshal.cpp) does not take: each property of a
+# tensor is asked for once.
 def make_desc(q, scale, causal=1, flags=0):
     """Descriptor for a [B,S,H,d] tensor (any strides with contiguous last dim)."""
     stride = q.stride()
@@ -214,6 +230,9 @@ def _same_layout(ref, *others):
 
 def memo_attn_fwd(q, k, v, scale, o=None, lse=None, stream=None):
     """o, lse = causal softmax attention of q,k,v [B,S,H,d]; lse is [B,H,S] fp32."""
+    done = _marshal().attn_fwd(lib().address["memo_attn_fwd"], _stream_ptr, q, k, v, scale, o, lse, stream)
+    if done is not None:
+        return done if type(done) is tuple else _check(done, "memo_attn_fwd")
     B, S, H, d = q.shape
     if o is None:
         o = torch.empty_like(q)
@@ -238,6 +257,12 @@ def memo_attn_bwd(q, k, v, o, lse, d_o, scale, dq=None, dk=None, dv=None, worksp
                   stream=None, stage_events=None):
     """dq, dk, dv for dL/dO = d_o.  `workspace`: uint8 device tensor (allocated if None).
     stage_events: optional 4 torch.cuda.Event(enable_timing=True), passed to memo_attn_bwd_staged."""
+    if stage_events is None:
+        at = lib().address
+        done = _marshal().attn_bwd(at["memo_attn_bwd"], at["memo_attn_bwd_workspace_bytes"], _stream_ptr, q, k, v, o, lse, d_o, scale,
+                                   dq, dk, dv, workspace, stream)
+        if done is not None:
+            return done if type(done) is tuple else _check(done, "memo_attn_bwd")
     if dq is None:
         dq = torch.empty_like(q)
     if dk is None:
@@ -267,6 +292,9 @@ def memo_attn_bwd(q, k, v, o, lse, d_o, scale, dq=None, dk=None, dv=None, worksp
 def memo_attn_bwd_static(q, k, v, o, lse, d_o, scale, dq, dk, dv, stream=None):
     """memo_attn_bwd without a workspace and without any allocation: the caller passes every
     output; the library keeps D_i in its static device array (B*H*S <= 4 Mi rows)."""
+    done = _marshal().attn_bwd(lib().address["memo_attn_bwd_static"], None, _stream_ptr, q, k, v, o, lse, d_o, scale, dq, dk, dv, None, stream)
+    if done is not None:
+        return done if type(done) is tuple else _check(done, "memo_attn_bwd_static")
     _same_layout(q, k, v, o, d_o, dq, dk, dv)
     desc = make_desc(q, scale)
     _check(lib().memo_attn_bwd_static(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(),

@@ -10,6 +10,7 @@ LIB = os.path.join(HERE, "libmemo.so")
 # measurement aids of bench.py (an MFMA-only probe, an atomic-add probe): a library of their own, not part of libmemo
 BENCH_AIDS_SRC = [os.path.join(HERE, "bench_aids", "probe_mfma.hip"), os.path.join(HERE, "bench_aids", "atomic_add.hip")]
 BENCH_AIDS_LIB = os.path.join(HERE, "bench_aids", "libmemo_bench_aids.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 # source -> extra flags.  Every file keeps IEEE NaN semantics: a NaN or Inf in an input must reach
 # the outputs that depend on it (a training loop detects divergence that way).
 SOURCES = {
@@ -34,7 +35,7 @@ def _run(cmd, verbose):
     # the host pass warns that it does not know the packed-fp32 feature: harmless, filtered
     err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(cmd[0] + " failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
 
@@ -48,7 +49,22 @@ def build(verbose=False, extra=()):
         _run([hipcc] + FLAGS + flags + list(extra) + ["-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, verbose)
+    build_marshal(verbose)
     return LIB
+
+
+def build_marshal(verbose=False):
+    """The Python extension beside libmemo.so (csrc/marshal.cpp): host code against torch's headers, no HIP in it."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for path in include:
+        cmd += ["-isystem", path]
+    _run(cmd + [os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], verbose)
+    return MARSHAL
 
 
 def build_bench_aids(verbose=False):

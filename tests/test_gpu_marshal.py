@@ -1,0 +1,59 @@
+"""The native marshalling of the attention calls (csrc/marshal.cpp) against the Python code beside it: same outputs, same errors."""
+import pytest
+import torch
+
+from paper_2407_12117_amd import binding as mb
+from paper_2407_12117_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+class Wrapped(torch.Tensor):
+    """A subclass: the native code leaves it to Python."""
+
+
+def _calls(q, k, v, g, scale, as_given, lse=None):
+    o, lse = mb.memo_attn_fwd(q, k, v, scale, o=torch.empty_like(q) if as_given else None, lse=lse)
+    grads = [torch.empty_like(q) for _ in range(3)] if as_given else [None] * 3
+    ws = torch.empty(mb.memo_attn_bwd_workspace_bytes(q, scale), dtype=torch.uint8, device="cuda") if as_given else None
+    out = (o, lse) + mb.memo_attn_bwd(q, k, v, o, lse, g, scale, *grads, workspace=ws)
+    return out + mb.memo_attn_bwd_static(q, k, v, o, lse, g, scale, *(torch.empty_like(q) for _ in range(3)))
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+@pytest.mark.parametrize("as_given", [False, True])
+@pytest.mark.parametrize("side_stream", [False, True])
+def test_native_and_python_marshalling_agree(dtype, d, as_given, side_stream):
+    scale = synth.default_scale(d)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(2, 75, 3, d, dtype, 5))
+    torch.cuda.synchronize()
+    taken = mb._marshal().attn_fwd(mb.lib().address["memo_attn_fwd"], mb._stream_ptr, q, k, v, scale, None, None, None)
+    assert type(taken) is tuple                       # plain device tensors are taken
+    assert mb._marshal().attn_fwd(mb.lib().address["memo_attn_fwd"], mb._stream_ptr, q.as_subclass(Wrapped), k, v, scale, None, None, None) is None
+    with torch.cuda.stream(torch.cuda.Stream() if side_stream else torch.cuda.current_stream()):
+        native = _calls(q, k, v, g, scale, as_given)
+        plain = _calls(*(t.as_subclass(Wrapped) for t in (q, k, v, g)), scale, as_given)
+    torch.cuda.synchronize()
+    for x, y in zip(native, plain):
+        assert x.shape == y.shape and x.stride() == y.stride() and x.dtype == y.dtype and torch.equal(x, y.as_subclass(torch.Tensor))
+
+
+def test_errors_are_those_of_the_python_code():
+    q = torch.zeros(1, 40, 2, 128, dtype=torch.bfloat16, device="cuda")
+    lse, scale = torch.zeros(1, 2, 40, device="cuda"), 0.1
+    for bad in (q[:, :32], q.float(), q.cpu(), q.transpose(1, 2).contiguous().transpose(1, 2)):
+        with pytest.raises(ValueError, match="share shape|one device"):
+            mb.memo_attn_fwd(q, bad, q, scale)
+        with pytest.raises(ValueError, match="share shape|one device"):
+            mb.memo_attn_bwd_static(q, q, q, q, lse, q, scale, q, bad, q)
+    with pytest.raises(ValueError, match="lse must be"):
+        mb.memo_attn_fwd(q, q, q, scale, o=torch.empty_like(q), lse=lse[:, :, :39])
+    with pytest.raises(ValueError, match="unsupported dtype"):
+        mb.memo_attn_fwd(*(q.half(),) * 3, scale)
+    for f32_only, s in ((torch.zeros(1, 8, 1, 96, device="cuda"), scale), (q, -1.0)):
+        with pytest.raises(mb.MemoError):
+            mb.memo_attn_fwd(f32_only, f32_only, f32_only, s)
+    with pytest.raises(mb.MemoError):                 # a workspace that is too small
+        mb.memo_attn_bwd(q, q, q, q, lse, q, scale, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+    with pytest.raises(AttributeError):
+        mb.memo_attn_fwd(None, q, q, scale)
