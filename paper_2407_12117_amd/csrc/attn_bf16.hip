@@ -123,6 +123,17 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     auto fill_v = [&](int off, int jt) {
         toff.fill(lds + grp * kGroup + off + kTile, v, a.ss, (int64_t)jt * kBk, a.S, wq);
     };
+    // Key groups that need the same Q rows bring them in once, as whole rows, in the place of the buffers that the second tiles take: to each
+    // wave's registers straight from memory, 32 bytes of a row at a time, they cost a unit 5000 cycles.
+    constexpr bool kStaged = KS > 1;
+    constexpr int kBlocks = kStage / (32 * 256);      // 32-row blocks in one such buffer
+    static_assert(!kStaged || KS * kBlocks >= QG, "room for the Q rows");
+    auto staged = [&](int block) { return lds + block / kBlocks * kGroup + kStage + block % kBlocks * 32 * 256; };
+    if constexpr (kStaged) {
+        const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzA, 32>(a.ss, wave, lane);
+#pragma unroll
+        for (int blk = 0; blk < QG; ++blk) qoff.fill(staged(blk), q, a.ss, row0 + 32 * blk, a.S, wave);
+    }
     if (jfirst < ntiles) {
         fill_k(0, jfirst);
         fill_v(0, jfirst);
@@ -130,7 +141,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
 
     // Q^T as B operand: lane = query row i, 8 head-dim values per 16-wide chunk
     bf16x8 qB[8];
-    {
+    if constexpr (!kStaged) {
         const int64_t iq = i < a.S ? i : a.S - 1;     // rows past S are computed and never stored
 #pragma unroll
         for (int kc = 0; kc < 8; ++kc)
@@ -145,6 +156,15 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     float m = -INFINITY, mc = -INFINITY, lsum = 0.f;   // running max of raw dots (and times c), running sum
     const int wave_first_tile_masked = min((int)((i0w + 31) / kBk) + 1, ntiles);   // tiles >= this are fully masked
     const int wave_first_diag = (int)(i0w / kBk);                     // tiles >= this need the mask
+
+    if constexpr (kStaged) {
+        wait_fills();
+        __syncthreads();          // the Q rows are complete; the first step's barrier is what their place waits for
+        static_for<0, 8>([&](auto n) {
+            lds_issue_b128<0>(qB[decltype(n)::value], (uint32_t)(uintptr_t)staged(wq) + (uint32_t)(la.row_op[0] ^ (decltype(n)::value << 5)));
+        });
+        static_for<0, 8>([&](auto n) { lds_wait<0>(qB[decltype(n)::value]); });
+    }
 
     // One key/value tile.  BUF is a compile-time buffer index, so every LDS address below is
     // a per-lane register plus an immediate offset.

@@ -109,6 +109,20 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
         fill_tile_at<SwzB>(dst, toff, k, a.ss, (int64_t)jt * kBk, a.S, wq, lane);
         fill_tile_at<SwzB>(dst + kTile, toff, v, a.ss, (int64_t)jt * kBk, a.S, wq, lane);
     };
+    // Workgroups whose key groups all need the same Q and dO rows bring them in once, as whole rows, in the place of the buffers that the
+    // second tiles take: to each wave's registers straight from memory, 64 bytes of a row at a time, they cost a unit 5000 cycles.
+    constexpr bool kStaged = QG < 8;
+    constexpr int kBlocks = kStage / (32 * 256);      // 32-row blocks in one such buffer
+    static_assert(!kStaged || KS * kBlocks >= 2 * QG, "room for the Q and dO rows");
+    auto staged = [&](int block) { return lds + block / kBlocks * kGroup + kStage + block % kBlocks * 32 * 256; };
+    if constexpr (kStaged) {
+        const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzB, 32>(a.ss, wave, lane);
+#pragma unroll
+        for (int blk = 0; blk < QG; ++blk) {
+            qoff.fill(staged(2 * blk), q, a.ss, row0 + 32 * blk, a.S, wave);
+            qoff.fill(staged(2 * blk + 1), g, a.ss, row0 + 32 * blk, a.S, wave);
+        }
+    }
     if (jfirst < ntiles) fill(0, jfirst);
 
     // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
@@ -120,10 +134,12 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     for (int qt = 0; qt < 2; ++qt) {
         const int64_t i = i0w + 16 * qt + l16;
         iq[qt] = i < a.S ? i : a.S - 1;               // rows past S are computed and never stored
+        if constexpr (!kStaged) {
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            qB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq[qt] * a.ss + 32 * kk + 8 * g4));
-            gB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(g + iq[qt] * a.ss + 32 * kk + 8 * g4));
+            for (int kk = 0; kk < 4; ++kk) {
+                qB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq[qt] * a.ss + 32 * kk + 8 * g4));
+                gB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(g + iq[qt] * a.ss + 32 * kk + 8 * g4));
+            }
         }
         lse2[qt] = a.lse[stat + iq[qt]] * kLog2e;
         const float nd = -a.delta[stat + iq[qt]];
@@ -136,6 +152,20 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
         for (int qt = 0; qt < 2; ++qt) accQ[dt][qt] = kZero4;
     const int wave_first_tile_masked = min((int)((i0w + 31) / kBk) + 1, ntiles);   // tiles >= this are fully masked
     const int wave_first_diag = (int)(i0w / kBk);                     // tiles >= this need the mask
+    if constexpr (kStaged) {
+        wait_fills();
+        __syncthreads();          // the Q and dO rows are complete; the first step's barrier is what their place waits for
+        const uint32_t at = ad.row16[0] - (uint32_t)(uintptr_t)(lds + grp * kGroup);
+        static_for<0, 8>([&](auto n) {
+            constexpr int qt = decltype(n)::value / 4, kk = decltype(n)::value % 4;
+            lds_issue_b128<4096 * qt>(qB[qt][kk], (uint32_t)(uintptr_t)staged(2 * wq) + (at ^ (kk << 6)));
+            lds_issue_b128<4096 * qt>(gB[qt][kk], (uint32_t)(uintptr_t)staged(2 * wq + 1) + (at ^ (kk << 6)));
+        });
+        static_for<0, 8>([&](auto n) {
+            lds_wait<0>(qB[decltype(n)::value / 4][decltype(n)::value % 4]);
+            lds_wait<0>(gB[decltype(n)::value / 4][decltype(n)::value % 4]);
+        });
+    }
 
     auto tile_step = [&](auto bufc, int jt) {
         constexpr int BUF = decltype(bufc)::value;
