@@ -6,7 +6,7 @@
 // What bounds it: the fp32 matrix rate, 256 flops per cycle and compute unit (157 TFLOP/s), the same as the
 // vector units'; but one MFMA instruction does 32 cycles of that work from two registers, where the
 // vector form needs an LDS read per multiply-add and lane.  An earlier VALU version of these kernels ran at 5 to
-// 7 TFLOP/s, bound by its scalar LDS reads; these reach 118 (forward) and 117 (backward, of its seven contractions) at
+// 7 TFLOP/s, bound by its scalar LDS reads; these reach 116 (forward) and 122 (backward, of its seven contractions) at
 // S = 5000, B = 2, H = 4, d = 128.  Where units would be idle a tile's output columns go to two or four workgroups, which halves or quarters
 // the second contractions of the longest tile, the one that such a launch takes (us, with the D_i launch: S = 1024 H = 1 d = 64 forward
 // 12.9 -> 10.8, backward 26.8 -> 23.0; d = 128 21.5 -> 17.9 and 43.1 -> 37.2).
@@ -71,11 +71,12 @@ struct F32Fill {
         row_off = (uint32_t)row * (uint32_t)ss * 4;
         piece_off = (uint32_t)(pos ^ SwzB::f(row)) * 16;
     }
-    __device__ __forceinline__ void operator()(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane) const
+    template <int kCount>         // instructions first ..
+    __device__ __forceinline__ void some(int first, LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane) const
     {
         if constexpr (FAR) {
 #pragma unroll
-            for (int n = 0; n < kInstr; ++n) {
+            for (int n = first; n < first + kCount; ++n) {
                 const int row = kRows * n + lane / (D / 4), piece = lane % (D / 4) ^ SwzB::f(row);
                 const int64_t rg = r0 + row < S ? r0 + row : S - 1;
                 __builtin_amdgcn_global_load_lds((const GLB_AS void *)(src + rg * ss + piece * 4),
@@ -87,12 +88,25 @@ struct F32Fill {
             const uint32_t bytes = rows > 0 ? (uint32_t)(rows - 1) * (uint32_t)ss * 4 + D * 4 : 0;
             const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src + r0 * ss), 0, bytes, 0x00020000);
 #pragma unroll
-            for (int n = 0; n < kInstr; ++n)
+            for (int n = first; n < first + kCount; ++n)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (LDS_AS void *)(tile + n * 1024), 16,
                                                          row_off + (piece_off ^ (uint32_t)(SwzB::f(kRows * n) * 16)) +
                                                              (uint32_t)(kRows * n) * (uint32_t)ss * 4, 0, 0, 0);
 #endif
         }
+    }
+    __device__ __forceinline__ void operator()(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane) const
+    {
+        some<kInstr>(0, tile, src, ss, r0, S, lane);
+    }
+    // The rows that all waves of a workgroup need, brought in once by all of them: a wave issues instruction `wave`, if there is one.  With
+    // each wave loading them straight to its registers, 64 bytes of a row at a time and behind the fills of its own tiles, a workgroup's
+    // start was bound by 8 times those bytes through the unit's 64 B per cycle, and no wave began before its second tile had
+    // landed; the row pointers also cost registers (head dim 64 backward: 5 spilled, now none).  Forward and backward, us, before -> now:
+    // S = 1024 H = 1 d = 64 33.4 -> 32.1, S = 3000 H = 4 d = 128 388 -> 372 (workgroups of many tiles gain least: S = 20000 H = 2 d = 128 1 %).
+    __device__ __forceinline__ void shared(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane, int wave) const
+    {
+        if (wave < kInstr) some<1>(wave, tile, src, ss, r0, S, lane);
     }
 };
 
@@ -127,11 +141,29 @@ __device__ __forceinline__ float f32_prob(float s, float scale, float lse)
     return __builtin_amdgcn_exp2f((s * scale - lse) * kLog2e);
 }
 
-template <int D>
-__device__ __forceinline__ void f32_load_row(f32x4 (&dst)[D / 16], const float *row, int g4)
+// A lane's row of a shared tile that lies `off` bytes from the buffer that ad is for: floats 16c + 4*g4 ..
+template <int D, int OFF = 0>
+__device__ __forceinline__ void f32_issue_row(f32x4 (&dst)[D / 16], const F32Addr &ad, uint32_t off)
 {
-#pragma unroll
-    for (int c = 0; c < D / 16; ++c) dst[c] = *reinterpret_cast<const f32x4 *>(row + 16 * c + 4 * g4);
+    static_for<0, D / 16>([&](auto n) {
+        constexpr int c = decltype(n)::value;
+        lds_issue_b128<OFF + 256 * (c / 4)>(dst[c], ad.row[c % 4] + off);
+    });
+}
+template <int D>
+__device__ __forceinline__ void f32_wait_row(f32x4 (&dst)[D / 16])
+{
+    static_for<0, D / 16>([&](auto n) { lds_wait<0>(dst[decltype(n)::value]); });
+}
+
+// The end of the shared fills: `queued` says that this wave has queued its own first two tiles behind them.
+template <int D>
+__device__ __forceinline__ void f32_shared_rows_complete(bool queued)
+{
+    if (queued) wait_fills_but<2 * F32Shape<D>::kFills>();
+    else wait_fills();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 constexpr int kDepth = 3;         // operand reads in flight ahead of their MFMAs
@@ -266,8 +298,10 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
 {
     using Shape = F32Shape<D>;
     constexpr int KS = kF32Waves, NP = Shape::kPieces / CS;
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[Shape::kRing + kF32Waves * 16 * 8];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, then (maximum, sum) per wave and row
+    constexpr int kStats = Shape::kRing + Shape::kTile;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kF32Waves * 16 * 8];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, the Q rows, (maximum, sum) per wave and row
+    load_args_at_once(a);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const auto [rank, hbp] = heads(blockIdx.x);       // CS parts of a head beside each other
@@ -282,15 +316,19 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
     auto fill_v = [&](int jt) { fill(ring + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, lane); };
+    fill.shared(lds + Shape::kRing, static_cast<const float *>(a.q) + base, a.ss, row0, a.S, lane, wave);
     if (wave < ntiles) {
         fill_k(wave);
         fill_v(wave);
     }
+    __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 q[D / 16], acc[D / 16 / CS];
-    f32_load_row<D>(q, static_cast<const float *>(a.q) + base + (i < a.S ? i : a.S - 1) * a.ss, g4);
 #pragma unroll
     for (int n = 0; n < D / 16 / CS; ++n) acc[n] = kZero4;
+    f32_shared_rows_complete<D>(wave < ntiles);
+    f32_issue_row<D>(q, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));       // rows past S are computed and never stored
+    f32_wait_row<D>(q);
     float m = -INFINITY, lsum = 0.f;                  // running maximum and sum of this lane's keys
 
     for (int jt = wave; jt < ntiles; jt += KS) {
@@ -350,7 +388,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     lsum += __shfl_xor(lsum, 32);
 
     LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
-    LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + Shape::kRing);
+    LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kStats);
 #pragma unroll
     for (int p = 0; p < NP; ++p) pieces[(wave * Shape::kSet + p) * 64 + lane] = f32_piece<D, CS>(acc, p);
     if (g4 == 0) stats[wave * 16 + l16] = f32x2{m, lsum};
@@ -418,17 +456,23 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
     auto fill_v = [&](int jt) { fill(ring + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, lane); };
+    const float lse = a.lse[stat + iq], nd = -a.delta[stat + iq];
+    fill.shared(lds + Shape::kRing, static_cast<const float *>(a.q) + base, a.ss, (int64_t)t.tile * kT, a.S, lane, wave);
+    fill.shared(lds + Shape::kRing + Shape::kTile, static_cast<const float *>(a.d_o) + base, a.ss, (int64_t)t.tile * kT, a.S, lane, wave);
     if (wave < ntiles) {
         fill_k(wave);
         fill_v(wave);
     }
+    __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 q[D / 16], go[D / 16], acc[D / 16 / CS];
-    f32_load_row<D>(q, static_cast<const float *>(a.q) + base + iq * a.ss, g4);
-    f32_load_row<D>(go, static_cast<const float *>(a.d_o) + base + iq * a.ss, g4);
-    const float lse = a.lse[stat + iq], nd = -a.delta[stat + iq];
 #pragma unroll
     for (int n = 0; n < D / 16 / CS; ++n) acc[n] = kZero4;
+    f32_shared_rows_complete<D>(wave < ntiles);
+    f32_issue_row<D>(q, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+    f32_issue_row<D, Shape::kTile>(go, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+    f32_wait_row<D>(q);
+    f32_wait_row<D>(go);
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
         wait_fills();
@@ -474,18 +518,24 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
             d[r] = row < a.S ? a.delta[stat + row] : 0.f;
         }
     };
-    const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 lse_n = kZero4, dl_n = kZero4;
+    if (it0 + wave < ntiles) load_stats(it0 + wave, lse_n, dl_n);
+    fill.shared(lds + Shape::kRing, static_cast<const float *>(a.k) + base, a.ss, col0, a.S, lane, wave);
+    fill.shared(lds + Shape::kRing + Shape::kTile, static_cast<const float *>(a.v) + base, a.ss, col0, a.S, lane, wave);
     if (it0 + wave < ntiles) {
         fill_q(it0 + wave);
         fill_g(it0 + wave);
-        load_stats(it0 + wave, lse_n, dl_n);
     }
+    __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
+    const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 kr[D / 16], vr[D / 16], dk[D / 16 / CS], dv[D / 16 / CS];
-    f32_load_row<D>(kr, static_cast<const float *>(a.k) + base + jk * a.ss, g4);
-    f32_load_row<D>(vr, static_cast<const float *>(a.v) + base + jk * a.ss, g4);
 #pragma unroll
     for (int n = 0; n < D / 16 / CS; ++n) dk[n] = dv[n] = kZero4;
+    f32_shared_rows_complete<D>(it0 + wave < ntiles);
+    f32_issue_row<D>(kr, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+    f32_issue_row<D, Shape::kTile>(vr, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+    f32_wait_row<D>(kr);
+    f32_wait_row<D>(vr);
     for (int it = it0 + wave; it < ntiles; it += QS) {
         const bool more = it + QS < ntiles;
         wait_fills();
@@ -529,8 +579,10 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
 template <int D, bool FAR, int CS>
 __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t key_ranks, Divisor heads, Divisor H)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D>::kRing];
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D>::kRing + 2 * F32Shape<D>::kTile];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave] two tiles, then the two rows that all waves need
+    load_args_at_once(a);
+    asm volatile("" ::"s"(a.d_o), "s"(a.delta));
     const bool resident = D == 64 && gridDim.x <= 2 * kXcds * kChunk;
     const uint32_t key_blocks = key_ranks * heads.d;
     if (blockIdx.x < key_blocks) {

@@ -518,3 +518,11 @@ def test_bf16_columns_in_parts(oracle, B, S, H):
 def test_fp32_columns_in_parts(oracle, B, S, H, d):
     # the same for the 16-row workgroups of fp32
     _dense_case(oracle, B, S, H, d, "f32", 8200 + S)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,S,H", [(1, 1, 1), (1, 15, 2), (1, 15, 270), (2, 19, 70), (1, 129, 3)])
+def test_fp32_rows_that_all_waves_share(oracle, B, S, H, d):
+    # one to nine tiles of 16 rows, ragged last ones: waves that bring in rows for the others and have no tile of their own, with
+    # the columns in four parts, in two and in one
+    _dense_case(oracle, B, S, H, d, "f32", 8300 + S)
