@@ -104,6 +104,8 @@ struct F32Fill {
     // start was bound by 8 times those bytes through the unit's 64 B per cycle, and no wave began before its second tile had
     // landed; the row pointers also cost registers (head dim 64 backward: 5 spilled, now none).  Forward and backward, us, before -> now:
     // S = 1024 H = 1 d = 64 33.4 -> 32.1, S = 3000 H = 4 d = 128 388 -> 372 (workgroups of many tiles gain least: S = 20000 H = 2 d = 128 1 %).
+    // Head dim 64, where another workgroup of the unit can cover a start, pays the barrier: backward S = 1500 H = 2 43.4 -> 41.2, 2000 H = 3
+    // 64.1 -> 60.7, 4000 H = 3 206.4 -> 206.5, but 12000 H = 2 1088 -> 1098; forward 2000 H = 2 22.3 -> 22.6, H = 3 26.9 -> 26.6, 12000 H = 2 314 -> 315.5.
     __device__ __forceinline__ void shared(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane, int wave) const
     {
         if (wave < kInstr) some<1>(wave, tile, src, ss, r0, S, lane);
