@@ -104,8 +104,8 @@ struct F32Fill {
     // start was bound by 8 times those bytes through the unit's 64 B per cycle, and no wave began before its second tile had
     // landed; the row pointers also cost registers (head dim 64 backward: 5 spilled, now none).  Forward and backward, us, before -> now:
     // S = 1024 H = 1 d = 64 33.4 -> 32.1, S = 3000 H = 4 d = 128 388 -> 372 (workgroups of many tiles gain least: S = 20000 H = 2 d = 128 1 %).
-    // Head dim 64, where another workgroup of the unit can cover a start, pays the barrier: backward S = 1500 H = 2 43.4 -> 41.2, 2000 H = 3
-    // 64.1 -> 60.7, 4000 H = 3 206.4 -> 206.5, but 12000 H = 2 1088 -> 1098; forward 2000 H = 2 22.3 -> 22.6, H = 3 26.9 -> 26.6, 12000 H = 2 314 -> 315.5.
+    // Head dim 64, where another workgroup of the unit can cover a start, does without where that is faster (f32_fwd_shares_rows and
+    // f32_bwd_shares_rows, launch_plan.h).
     __device__ __forceinline__ void shared(LDS_AS unsigned char *tile, const float *src, int64_t ss, int64_t r0, int64_t S, int lane, int wave) const
     {
         if (wave < kInstr) some<1>(wave, tile, src, ss, r0, S, lane);
@@ -156,6 +156,14 @@ template <int D>
 __device__ __forceinline__ void f32_wait_row(f32x4 (&dst)[D / 16])
 {
     static_for<0, D / 16>([&](auto n) { lds_wait<0>(dst[decltype(n)::value]); });
+}
+
+// The same row straight from memory to the registers of each wave.
+template <int D>
+__device__ __forceinline__ void f32_load_row(f32x4 (&dst)[D / 16], const float *row, int g4)
+{
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) dst[c] = *reinterpret_cast<const f32x4 *>(row + 16 * c + 4 * g4);
 }
 
 // The end of the shared fills: `queued` says that this wave has queued its own first two tiles behind them.
@@ -295,7 +303,7 @@ __device__ __forceinline__ void f32_store_piece(float *out, int p, const f32x4 &
     }
 }
 
-template <int D, bool FAR, int CS>
+template <int D, bool FAR, int CS, bool SHARED>
 __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(AttnArgs a, Divisor heads, Divisor H)
 {
     using Shape = F32Shape<D>;
@@ -303,7 +311,7 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     constexpr int kStats = Shape::kRing + Shape::kTile;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kStats + kF32Waves * 16 * 8];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave][K|V] tiles, the Q rows, (maximum, sum) per wave and row
-    load_args_at_once(a);
+    if constexpr (SHARED) load_args_at_once(a);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const auto [rank, hbp] = heads(blockIdx.x);       // CS parts of a head beside each other
@@ -318,19 +326,22 @@ __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_fwd_f32_kernel(Att
     const F32Fill<D, FAR> fill(a.ss, lane);
     auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
     auto fill_v = [&](int jt) { fill(ring + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, lane); };
-    fill.shared(lds + Shape::kRing, static_cast<const float *>(a.q) + base, a.ss, row0, a.S, lane, wave);
+    if constexpr (SHARED) fill.shared(lds + Shape::kRing, static_cast<const float *>(a.q) + base, a.ss, row0, a.S, lane, wave);
     if (wave < ntiles) {
         fill_k(wave);
         fill_v(wave);
     }
     __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
-    f32x4 q[D / 16], acc[D / 16 / CS];
+    f32x4 q[D / 16], acc[D / 16 / CS];                // rows past S are computed and never stored
+    if constexpr (!SHARED) f32_load_row<D>(q, static_cast<const float *>(a.q) + base + (i < a.S ? i : a.S - 1) * a.ss, g4);
 #pragma unroll
     for (int n = 0; n < D / 16 / CS; ++n) acc[n] = kZero4;
-    f32_shared_rows_complete<D>(wave < ntiles);
-    f32_issue_row<D>(q, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));       // rows past S are computed and never stored
-    f32_wait_row<D>(q);
+    if constexpr (SHARED) {
+        f32_shared_rows_complete<D>(wave < ntiles);
+        f32_issue_row<D>(q, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+        f32_wait_row<D>(q);
+    }
     float m = -INFINITY, lsum = 0.f;                  // running maximum and sum of this lane's keys
 
     for (int jt = wave; jt < ntiles; jt += KS) {
@@ -443,7 +454,7 @@ __device__ __forceinline__ void f32_combine(LDS_AS unsigned char *lds, const f32
 }
 
 // dQ_i = scale * sum_{j<=i} dS_ij k_j, dS_ij = P_ij (dO_i.v_j - D_i), P_ij = exp(s_ij - LSE_i); rows = queries
-template <int D, bool FAR, int CS>
+template <int D, bool FAR, int CS, bool SHARED>
 __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t, int part)
 {
     using Shape = F32Shape<D>;
@@ -459,8 +470,10 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     auto fill_k = [&](int jt) { fill(ring, k, a.ss, (int64_t)jt * kT, a.S, lane); };
     auto fill_v = [&](int jt) { fill(ring + Shape::kTile, v, a.ss, (int64_t)jt * kT, a.S, lane); };
     const float lse = a.lse[stat + iq], nd = -a.delta[stat + iq];
-    fill.shared(lds + Shape::kRing, static_cast<const float *>(a.q) + base, a.ss, (int64_t)t.tile * kT, a.S, lane, wave);
-    fill.shared(lds + Shape::kRing + Shape::kTile, static_cast<const float *>(a.d_o) + base, a.ss, (int64_t)t.tile * kT, a.S, lane, wave);
+    if constexpr (SHARED) {
+        fill.shared(lds + Shape::kRing, static_cast<const float *>(a.q) + base, a.ss, (int64_t)t.tile * kT, a.S, lane, wave);
+        fill.shared(lds + Shape::kRing + Shape::kTile, static_cast<const float *>(a.d_o) + base, a.ss, (int64_t)t.tile * kT, a.S, lane, wave);
+    }
     if (wave < ntiles) {
         fill_k(wave);
         fill_v(wave);
@@ -468,13 +481,19 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
     __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 q[D / 16], go[D / 16], acc[D / 16 / CS];
+    if constexpr (!SHARED) {
+        f32_load_row<D>(q, static_cast<const float *>(a.q) + base + iq * a.ss, g4);
+        f32_load_row<D>(go, static_cast<const float *>(a.d_o) + base + iq * a.ss, g4);
+    }
 #pragma unroll
     for (int n = 0; n < D / 16 / CS; ++n) acc[n] = kZero4;
-    f32_shared_rows_complete<D>(wave < ntiles);
-    f32_issue_row<D>(q, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
-    f32_issue_row<D, Shape::kTile>(go, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
-    f32_wait_row<D>(q);
-    f32_wait_row<D>(go);
+    if constexpr (SHARED) {
+        f32_shared_rows_complete<D>(wave < ntiles);
+        f32_issue_row<D>(q, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+        f32_issue_row<D, Shape::kTile>(go, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+        f32_wait_row<D>(q);
+        f32_wait_row<D>(go);
+    }
     for (int jt = wave; jt < ntiles; jt += KS) {
         const bool more = jt + KS < ntiles;
         wait_fills();
@@ -497,7 +516,7 @@ __device__ __forceinline__ void f32_dq_rows(const AttnArgs &a, LDS_AS unsigned c
 }
 
 // dV_j = sum_{i>=j} P_ij dO_i,  dK_j = scale * sum_{i>=j} dS_ij q_i; rows = keys, K and V rows in registers
-template <int D, bool FAR, int CS>
+template <int D, bool FAR, int CS, bool SHARED>
 __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const TileId t, int part)
 {
     using Shape = F32Shape<D>;
@@ -522,8 +541,10 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
     };
     f32x4 lse_n = kZero4, dl_n = kZero4;
     if (it0 + wave < ntiles) load_stats(it0 + wave, lse_n, dl_n);
-    fill.shared(lds + Shape::kRing, static_cast<const float *>(a.k) + base, a.ss, col0, a.S, lane, wave);
-    fill.shared(lds + Shape::kRing + Shape::kTile, static_cast<const float *>(a.v) + base, a.ss, col0, a.S, lane, wave);
+    if constexpr (SHARED) {
+        fill.shared(lds + Shape::kRing, static_cast<const float *>(a.k) + base, a.ss, col0, a.S, lane, wave);
+        fill.shared(lds + Shape::kRing + Shape::kTile, static_cast<const float *>(a.v) + base, a.ss, col0, a.S, lane, wave);
+    }
     if (it0 + wave < ntiles) {
         fill_q(it0 + wave);
         fill_g(it0 + wave);
@@ -531,13 +552,19 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
     __builtin_amdgcn_sched_barrier(0);                // addresses and accumulators are set up while the loads are on their way
     const F32Addr ad = f32_addr<D, CS>(ring, l16, g4, part);
     f32x4 kr[D / 16], vr[D / 16], dk[D / 16 / CS], dv[D / 16 / CS];
+    if constexpr (!SHARED) {
+        f32_load_row<D>(kr, static_cast<const float *>(a.k) + base + jk * a.ss, g4);
+        f32_load_row<D>(vr, static_cast<const float *>(a.v) + base + jk * a.ss, g4);
+    }
 #pragma unroll
     for (int n = 0; n < D / 16 / CS; ++n) dk[n] = dv[n] = kZero4;
-    f32_shared_rows_complete<D>(it0 + wave < ntiles);
-    f32_issue_row<D>(kr, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
-    f32_issue_row<D, Shape::kTile>(vr, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
-    f32_wait_row<D>(kr);
-    f32_wait_row<D>(vr);
+    if constexpr (SHARED) {
+        f32_shared_rows_complete<D>(it0 + wave < ntiles);
+        f32_issue_row<D>(kr, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+        f32_issue_row<D, Shape::kTile>(vr, ad, (uint32_t)(Shape::kRing - wave * Shape::kStage));
+        f32_wait_row<D>(kr);
+        f32_wait_row<D>(vr);
+    }
     for (int it = it0 + wave; it < ntiles; it += QS) {
         const bool more = it + QS < ntiles;
         wait_fills();
@@ -578,21 +605,23 @@ __device__ __forceinline__ void f32_dkdv_rows(const AttnArgs &a, LDS_AS unsigned
 // ones.  Longest first, except where all of them are resident at once, two per unit (head dim 64): then a unit gets the key tile
 // of a rank and the query tile of the same rank, and the query tiles go shortest first to even that out
 // (S = 2000, H = 2: 66 us both longest first).
-template <int D, bool FAR, int CS>
+template <int D, bool FAR, int CS, bool SHARED>
 __global__ __launch_bounds__(512, kWavesPerSimd<D>) void attn_bwd_f32_kernel(AttnArgs a, uint32_t key_ranks, Divisor heads, Divisor H)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[F32Shape<D>::kRing + 2 * F32Shape<D>::kTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;     // [wave] two tiles, then the two rows that all waves need
-    load_args_at_once(a);
-    asm volatile("" ::"s"(a.d_o), "s"(a.delta));
+    if constexpr (SHARED) {
+        load_args_at_once(a);
+        asm volatile("" ::"s"(a.d_o), "s"(a.delta));
+    }
     const bool resident = D == 64 && gridDim.x <= 2 * kXcds * kChunk;
     const uint32_t key_blocks = key_ranks * heads.d;
     if (blockIdx.x < key_blocks) {
         const auto [rank, hbp] = heads(blockIdx.x);
-        f32_dkdv_rows<D, FAR, CS>(a, lds, head_of(hbp / CS, (int)rank, H), (int)(hbp % CS));
+        f32_dkdv_rows<D, FAR, CS, SHARED>(a, lds, head_of(hbp / CS, (int)rank, H), (int)(hbp % CS));
     } else {
         const auto [rank, hbp] = heads(blockIdx.x - key_blocks);
-        f32_dq_rows<D, FAR, CS>(a, lds, head_of(hbp / CS, resident ? (int)rank : (int)((a.S + kT - 1) / kT) - 1 - (int)rank, H), (int)(hbp % CS));
+        f32_dq_rows<D, FAR, CS, SHARED>(a, lds, head_of(hbp / CS, resident ? (int)rank : (int)((a.S + kT - 1) / kT) - 1 - (int)rank, H), (int)(hbp % CS));
     }
 }
 
@@ -663,10 +692,12 @@ hipError_t launch_fwd_f32(const AttnArgs &a, hipStream_t st)
     auto launch = [&](auto kernel, int parts) { return launch_blocks(kernel, blocks * parts, st, a, Divisor(heads * parts), Divisor(a.H)); };
     if constexpr (!FAR) {
         const int parts = a.o_out == a.q ? 1 : column_parts(blocks);         // in place of Q: another part may not have read it yet
-        if (parts == 4) return launch(attn_fwd_f32_kernel<D, FAR, 4>, 4);
-        if (parts == 2) return launch(attn_fwd_f32_kernel<D, FAR, 2>, 2);
+        if (parts == 4) return launch(attn_fwd_f32_kernel<D, FAR, 4, true>, 4);
+        if (parts == 2) return launch(attn_fwd_f32_kernel<D, FAR, 2, true>, 2);
+        if constexpr (D == 64)
+            if (!f32_fwd_shares_rows(blocks / heads, heads)) return launch(attn_fwd_f32_kernel<D, FAR, 1, false>, 1);
     }
-    return launch(attn_fwd_f32_kernel<D, FAR, 1>, 1);
+    return launch(attn_fwd_f32_kernel<D, FAR, 1, true>, 1);
 }
 
 // dkdv, dq: which of the two to launch
@@ -682,10 +713,12 @@ hipError_t launch_bwd_f32(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
     if constexpr (!FAR) {
         // a dQ that takes the place of Q or dO is not split: another part may not have read them yet
         const int parts = dq_in_place(a) ? 1 : column_parts(2 * tiles * heads);
-        if (parts == 4) return launch(attn_bwd_f32_kernel<D, FAR, 4>, 4);
-        if (parts == 2) return launch(attn_bwd_f32_kernel<D, FAR, 2>, 2);
+        if (parts == 4) return launch(attn_bwd_f32_kernel<D, FAR, 4, true>, 4);
+        if (parts == 2) return launch(attn_bwd_f32_kernel<D, FAR, 2, true>, 2);
+        if constexpr (D == 64)
+            if (!f32_bwd_shares_rows(tiles)) return launch(attn_bwd_f32_kernel<D, FAR, 1, false>, 1);
     }
-    return launch(attn_bwd_f32_kernel<D, FAR, 1>, 1);
+    return launch(attn_bwd_f32_kernel<D, FAR, 1, true>, 1);
 }
 
 }  // namespace

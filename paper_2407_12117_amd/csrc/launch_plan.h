@@ -115,6 +115,17 @@ inline int column_parts(int64_t blocks)
     return blocks * 4 <= units ? 4 : blocks * 2 <= units ? 2 : 1;
 }
 
+// fp32, head dim 64, launches in one part: whether the rows that all waves of a workgroup need are brought in once (F32Fill::shared) or
+// by each wave for itself.  Sharing them puts a barrier in front of the sweep.  us, each wave for itself : shared.
+// Forward: a unit with one workgroup has nothing to do before the barrier (S = 2000 H = 2 22.20 : 22.48, S = 4000 H = 1 40.37 : 40.94); from the
+// second workgroup of a unit on sharing is ahead (S = 1500 H = 3 19.23 : 19.06, S = 4000 H = 3 64.30 : 63.79), and over long sweeps, where the
+// starts are a small part, behind again (S = 5000 H = 2 70.5 : 71.2, H = 4 116.4 : 117.8, S = 10000 H = 1 136.1 : 137.1).
+// Backward: ahead by 1 us and more per round of workgroups (S = 300 B = 16 H = 4 45.5 : 41.0, S = 2000 H = 3 64.2 : 61.5, S = 5000 H = 1 138.8 : 137.2),
+// but its loop, which holds other registers, is 1 to 2 % slower (S = 6000 H = 2 302.9 : 304.7, S = 8000 H = 1 266.0 : 270.1, S = 12000 H = 2 1104 : 1114,
+// S = 30000 H = 1 3338 : 3398).  The lines lie where the two meet; S = 6000 H = 1 (175.3 : 171.3) is on the wrong side of its.
+inline bool f32_fwd_shares_rows(int64_t tiles, int64_t heads) { return tiles * heads > kXcds * kChunk && tiles <= 256; }
+inline bool f32_bwd_shares_rows(int64_t tiles) { return tiles <= 320; }
+
 // One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
 // 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
 // and after its sweep.

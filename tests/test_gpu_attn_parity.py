@@ -526,3 +526,10 @@ def test_fp32_rows_that_all_waves_share(oracle, B, S, H, d):
     # one to nine tiles of 16 rows, ragged last ones: waves that bring in rows for the others and have no tile of their own, with
     # the columns in four parts, in two and in one
     _dense_case(oracle, B, S, H, d, "f32", 8300 + S)
+
+
+@pytest.mark.parametrize("S,H", [(257, 14), (257, 16), (2033, 2), (2049, 2), (4097, 1), (5120, 1), (5121, 1), (6003, 1)])
+def test_fp32_rows_shared_and_not(oracle, S, H):
+    # head dim 64 in one part, on both sides of the lengths and numbers of workgroups from which each wave brings in the workgroup's
+    # rows for itself, forward and backward
+    _dense_case(oracle, 1, S, H, 64, "f32", 8400 + S)

@@ -74,6 +74,18 @@ def test_division_by_a_launch_constant(plans):
         assert plans([("divide", x, d) for x in xs]) == [divmod(x, d) for x in xs]
 
 
+# fp32 at head dim 64: the sizes at which shared rows were measured slower than none by more than the runs differ
+def test_fp32_rows_are_shared_only_where_that_is_not_slower(plans):
+    forward = [(1700, 2), (2000, 2), (2500, 1), (3000, 1), (4000, 1), (5000, 2), (5000, 4), (10000, 1)]
+    assert [p[0] for p in plans([("f32rows", S, h) for S, h in forward])] == [0] * len(forward)
+    backward = [(6000, 2), (7000, 4), (8000, 1), (8000, 4), (10000, 3), (12000, 2), (16000, 1), (20000, 2), (30000, 1)]
+    assert [p[1] for p in plans([("f32rows", S, h) for S, h in backward])] == [0] * len(backward)
+    # and faster
+    forward, backward = [(1500, 3), (2000, 3), (4000, 3), (3000, 4)], [(200, 64), (300, 64), (1024, 4), (2000, 3), (3000, 2), (5000, 1)]
+    assert [p[0] for p in plans([("f32rows", S, h) for S, h in forward])] == [1] * len(forward)
+    assert [p[1] for p in plans([("f32rows", S, h) for S, h in backward])] == [1] * len(backward)
+
+
 def test_projection_buffers_stay_inside_the_matrix(plans):
     # every tile a workgroup may name: its own, and the ones behind its last, whose buffers are empty
     for begin, end, tile_rows in ((0, 1, 64), (0, 64, 64), (130, 40001, 256), (7, 5000, 192), (4096, 4100, 128)):
