@@ -228,6 +228,27 @@ def _same_layout(ref, *others):
             raise ValueError("tensors must live on one device")
 
 
+def _reachable(t, q):
+    """Whether the kernels that work q can reach t: on q's device, or in pinned host memory."""
+    return t.device == q.device or t.is_pinned()
+
+
+def _check_lse(lse, q, desc):
+    rows = desc.B * desc.H * desc.S
+    if lse.dtype != torch.float32 or not lse.is_contiguous() or not (lse.numel() == rows or lse.dim() == 1 and lse.numel() > rows):
+        raise ValueError("lse must be contiguous fp32 [B,H,S]")
+    if not _reachable(lse, q):
+        raise ValueError("tensors must live on one device")
+
+
+def _check_workspace(workspace, q):
+    # its number of elements is passed on as its size in bytes
+    if workspace.untyped_storage().nbytes() - workspace.storage_offset() * workspace.element_size() < workspace.numel():
+        raise ValueError("workspace must be a uint8 tensor whose elements lie one behind the other")
+    if not _reachable(workspace, q):
+        raise ValueError("tensors must live on one device")
+
+
 def memo_attn_fwd(q, k, v, scale, o=None, lse=None, stream=None):
     """o, lse = causal softmax attention of q,k,v [B,S,H,d]; lse is [B,H,S] fp32."""
     done = _marshal().attn_fwd(lib().address["memo_attn_fwd"], _stream_ptr, q, k, v, scale, o, lse, stream)
@@ -241,6 +262,8 @@ def memo_attn_fwd(q, k, v, scale, o=None, lse=None, stream=None):
     _same_layout(q, k, v, o)
     if lse.dtype != torch.float32 or not lse.is_contiguous() or tuple(lse.shape) != (B, H, S):
         raise ValueError("lse must be contiguous fp32 [B,H,S]")
+    if not _reachable(lse, q):
+        raise ValueError("tensors must live on one device")
     desc = make_desc(q, scale)
     st = lib().memo_attn_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                              o.data_ptr(), lse.data_ptr(), _stream_ptr(stream))
@@ -271,9 +294,12 @@ def memo_attn_bwd(q, k, v, o, lse, d_o, scale, dq=None, dk=None, dv=None, worksp
         dv = torch.empty_like(q)
     _same_layout(q, k, v, o, d_o, dq, dk, dv)
     desc = make_desc(q, scale)
+    _check_lse(lse, q, desc)
     if workspace is None:
         need = int(lib().memo_attn_bwd_workspace_bytes(ctypes.byref(desc)))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+    else:
+        _check_workspace(workspace, q)
     args = (ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(),
             o.data_ptr(), lse.data_ptr(), d_o.data_ptr(),
             dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
@@ -297,6 +323,7 @@ def memo_attn_bwd_static(q, k, v, o, lse, d_o, scale, dq, dk, dv, stream=None):
         return done if type(done) is tuple else _check(done, "memo_attn_bwd_static")
     _same_layout(q, k, v, o, d_o, dq, dk, dv)
     desc = make_desc(q, scale)
+    _check_lse(lse, q, desc)
     _check(lib().memo_attn_bwd_static(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                       o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), dq.data_ptr(),
                                       dk.data_ptr(), dv.data_ptr(), _stream_ptr(stream)),

@@ -70,6 +70,19 @@ bool describe(const at::Tensor &q, PyObject *scale, memo_attn_desc *d)
     return true;
 }
 
+// The logsumexp of the problem `d` on q's device.
+bool holds_lse(const at::Tensor &lse, const at::Tensor &q, const memo_attn_desc &d)
+{
+    return lse.scalar_type() == at::kFloat && lse.is_contiguous() && lse.device() == q.device() && lse.numel() == (int64_t)d.B * d.H * d.S;
+}
+
+// A workspace on q's device with as many bytes behind its first element as it has elements, which is the size it is passed on with.
+bool holds_bytes(const at::Tensor &t, const at::Tensor &q)
+{
+    return t.device() == q.device() && t.scalar_type() == at::kByte && t.is_contiguous() &&
+           (int64_t)t.storage().nbytes() - t.storage_offset() >= t.numel();
+}
+
 template <typename Fn>
 Fn address(PyObject *obj)
 {
@@ -105,8 +118,7 @@ PyObject *attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     if ((a[6] != Py_None && !given_o) || (a[7] != Py_None && !given_lse)) Py_RETURN_NONE;
     const at::Tensor o = given_o ? *given_o : at::empty_like(*q);
     const at::Tensor lse = given_lse ? *given_lse : at::empty({desc.B, desc.H, desc.S}, q->options().dtype(at::kFloat));
-    if (!same_layout(*q, {&o}) || lse.scalar_type() != at::kFloat || !lse.is_contiguous() || lse.dim() != 3 || lse.size(0) != desc.B ||
-        lse.size(1) != desc.H || lse.size(2) != desc.S)
+    if (!same_layout(*q, {&o}) || !holds_lse(lse, *q, desc) || lse.dim() != 3 || lse.size(0) != desc.B || lse.size(1) != desc.H)
         Py_RETURN_NONE;
     void *stream = nullptr;
     if (!stream_handle(a[1], a[8], &stream)) return nullptr;
@@ -132,7 +144,7 @@ PyObject *attn_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (n != 15 || intercepted()) Py_RETURN_NONE;
     const at::Tensor *q = plain(a[3]), *k = plain(a[4]), *v = plain(a[5]), *o = plain(a[6]), *lse = plain(a[7]), *g = plain(a[8]);
     memo_attn_desc desc;
-    if (!q || !lse || !same_layout(*q, {k, v, o, g}) || !describe(*q, a[9], &desc)) Py_RETURN_NONE;
+    if (!q || !lse || !same_layout(*q, {k, v, o, g}) || !describe(*q, a[9], &desc) || !holds_lse(*lse, *q, desc)) Py_RETURN_NONE;
     const bool is_static = a[1] == Py_None;
     at::Tensor out[3], workspace;
     for (int i = 0; i < 3; ++i) {
@@ -143,7 +155,7 @@ PyObject *attn_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (!same_layout(*q, {&out[0], &out[1], &out[2]})) Py_RETURN_NONE;
     if (!is_static) {
         const at::Tensor *t = a[13] == Py_None ? nullptr : plain(a[13]);
-        if (!t && a[13] != Py_None) Py_RETURN_NONE;
+        if (a[13] != Py_None && (!t || !holds_bytes(*t, *q))) Py_RETURN_NONE;
         workspace = t ? *t : at::empty({(int64_t)std::max<size_t>(address<BytesFn>(a[1])(&desc), 256)}, q->options().dtype(at::kByte));
     }
     void *stream = nullptr;

@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2407_12117_amd import binding as mb
 
@@ -112,6 +113,30 @@ def test_attention_rejects_null_and_misaligned_pointers():
     assert L.memo_attn_bwd(ctypes.byref(d), *args, None, 0, None) == mb.MEMO_ERR_WORKSPACE
     assert L.memo_attn_bwd(ctypes.byref(d), *args, ok, need - 1, None) == mb.MEMO_ERR_WORKSPACE
     assert L.memo_attn_bwd(ctypes.byref(d), *args, ctypes.c_void_p(4100), need, None) == mb.MEMO_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("bad", ["short", "bf16", "strided", "wide"])
+def test_backward_rejects_an_lse_that_is_not_the_forwards(static, bad):
+    q = torch.zeros(2, 40, 3, 128, dtype=torch.bfloat16)
+    lse = {"short": torch.zeros(2, 3, 39), "bf16": torch.zeros(2, 3, 40, dtype=torch.bfloat16), "strided": torch.zeros(2, 3, 80)[:, :, ::2],
+           "wide": torch.zeros(2, 3, 41)}[bad]
+    with pytest.raises(ValueError, match="lse must be"):
+        if static:
+            mb.memo_attn_bwd_static(q, q, q, q, lse, q, 0.1, *(torch.empty_like(q) for _ in range(3)))
+        else:
+            mb.memo_attn_bwd(q, q, q, q, lse, q, 0.1)
+
+
+@pytest.mark.parametrize("rows,step", [(1, 0), (2, 1)])
+def test_backward_rejects_a_workspace_with_fewer_bytes_than_elements(rows, step):
+    # one byte expanded; rows that are the same bytes
+    q, lse = torch.zeros(1, 40, 2, 128, dtype=torch.bfloat16), torch.zeros(1, 2, 40)
+    need = mb.memo_attn_bwd_workspace_bytes(q, 0.1)
+    workspace = torch.as_strided(torch.zeros(max(1, need // 2 * step), dtype=torch.uint8), (rows, need // rows), (0, step))
+    assert workspace.numel() == need
+    with pytest.raises(ValueError, match="workspace must be"):
+        mb.memo_attn_bwd(q, q, q, q, lse, q, 0.1, workspace=workspace)
 
 
 def test_swap_rejects_before_any_copy():

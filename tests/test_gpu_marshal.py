@@ -57,3 +57,34 @@ def test_errors_are_those_of_the_python_code():
         mb.memo_attn_bwd(q, q, q, q, lse, q, scale, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
     with pytest.raises(AttributeError):
         mb.memo_attn_fwd(None, q, q, scale)
+
+
+def test_buffers_that_are_too_small_are_refused_on_the_host():
+    q = torch.zeros(1, 40, 2, 128, dtype=torch.bfloat16, device="cuda")
+    lse, scale, out = torch.zeros(1, 2, 40, device="cuda"), 0.1, [torch.empty_like(q) for _ in range(3)]
+    for bad, text in ((lse[:, :, :39], "lse must be"), (lse[:, :, :39].contiguous(), "lse must be"), (lse.bfloat16(), "lse must be"), (lse.cpu(), "one device")):
+        for call in (lambda: mb.memo_attn_bwd(q, q, q, q, bad, q, scale), lambda: mb.memo_attn_bwd_static(q, q, q, q, bad, q, scale, *out)):
+            with pytest.raises(ValueError, match=text):
+                call()
+    with pytest.raises(ValueError, match="one device"):
+        mb.memo_attn_fwd(q, q, q, scale, lse=lse.cpu())
+    need = mb.memo_attn_bwd_workspace_bytes(q, scale)
+    few = torch.zeros(1, dtype=torch.uint8, device="cuda")
+    for bad, text in ((few.expand(need), "workspace must be"), (torch.zeros(need, dtype=torch.uint8), "one device")):
+        with pytest.raises(ValueError, match=text):
+            mb.memo_attn_bwd(q, q, q, q, lse, q, scale, workspace=bad)
+
+
+def test_buffers_of_other_forms_are_still_taken():
+    # an lse without its shape, a longer one, a workspace that is a view, of another type or with gaps: enough memory in every case
+    scale = synth.default_scale(64)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(1, 75, 2, 64, "f32", 6))
+    o, lse = mb.memo_attn_fwd(q, k, v, scale)
+    want = mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+    need = mb.memo_attn_bwd_workspace_bytes(q, scale)
+    longer = torch.cat([lse.flatten(), torch.full((7,), float("nan"), device="cuda")])
+    room = torch.zeros(4 * need, dtype=torch.uint8, device="cuda")
+    for some_lse, workspace in ((lse.view(2, 75), None), (lse.flatten(), room), (longer, room[256:]), (lse, room[::2]), (lse, room.view(torch.float32)),
+                                (lse.cpu().pin_memory(), room.view(2, -1)), (lse, torch.zeros(need, dtype=torch.uint8, pin_memory=True))):
+        for x, y in zip(mb.memo_attn_bwd(q, k, v, o, some_lse, g, scale, workspace=workspace), want):
+            assert torch.equal(x, y)
