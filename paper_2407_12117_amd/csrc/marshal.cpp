@@ -89,6 +89,25 @@ Fn address(PyObject *obj)
     return reinterpret_cast<Fn>(PyLong_AsVoidPtr(obj));
 }
 
+// Outputs and workspaces are allocated without the interpreter's lock, as torch's own functions do: the allocator may have to wait for the
+// device.
+struct OthersMayRun {
+    PyThreadState *const state = PyEval_SaveThread();
+    ~OthersMayRun() { PyEval_RestoreThread(state); }
+};
+
+at::Tensor new_like(at::Tensor like)     // a copy: nothing that another thread does to the Python object takes it away
+{
+    const OthersMayRun here;
+    return at::empty_like(like);
+}
+
+at::Tensor new_tensor(at::IntArrayRef sizes, const at::TensorOptions &options)
+{
+    const OthersMayRun here;
+    return at::empty(sizes, options);
+}
+
 // The stream's handle, as the binding finds it (find(stream)): after the checks, so that their errors come first.  false: an error is set.
 bool stream_handle(PyObject *find, PyObject *stream, void **out)
 {
@@ -116,8 +135,8 @@ PyObject *attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (!q || !same_layout(*q, {k, v}) || !describe(*q, a[5], &desc)) Py_RETURN_NONE;
     const at::Tensor *given_o = a[6] == Py_None ? nullptr : plain(a[6]), *given_lse = a[7] == Py_None ? nullptr : plain(a[7]);
     if ((a[6] != Py_None && !given_o) || (a[7] != Py_None && !given_lse)) Py_RETURN_NONE;
-    const at::Tensor o = given_o ? *given_o : at::empty_like(*q);
-    const at::Tensor lse = given_lse ? *given_lse : at::empty({desc.B, desc.H, desc.S}, q->options().dtype(at::kFloat));
+    const at::Tensor o = given_o ? *given_o : new_like(*q);
+    const at::Tensor lse = given_lse ? *given_lse : new_tensor({desc.B, desc.H, desc.S}, q->options().dtype(at::kFloat));
     if (!same_layout(*q, {&o}) || !holds_lse(lse, *q, desc) || lse.dim() != 3 || lse.size(0) != desc.B || lse.size(1) != desc.H)
         Py_RETURN_NONE;
     void *stream = nullptr;
@@ -150,13 +169,13 @@ PyObject *attn_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     for (int i = 0; i < 3; ++i) {
         const at::Tensor *t = a[10 + i] == Py_None ? nullptr : plain(a[10 + i]);
         if (!t && (a[10 + i] != Py_None || is_static)) Py_RETURN_NONE;
-        out[i] = t ? *t : at::empty_like(*q);
+        out[i] = t ? *t : new_like(*q);
     }
     if (!same_layout(*q, {&out[0], &out[1], &out[2]})) Py_RETURN_NONE;
     if (!is_static) {
         const at::Tensor *t = a[13] == Py_None ? nullptr : plain(a[13]);
         if (a[13] != Py_None && (!t || !holds_bytes(*t, *q))) Py_RETURN_NONE;
-        workspace = t ? *t : at::empty({(int64_t)std::max<size_t>(address<BytesFn>(a[1])(&desc), 256)}, q->options().dtype(at::kByte));
+        workspace = t ? *t : new_tensor({(int64_t)std::max<size_t>(address<BytesFn>(a[1])(&desc), 256)}, q->options().dtype(at::kByte));
     }
     void *stream = nullptr;
     if (!stream_handle(a[2], a[14], &stream)) return nullptr;

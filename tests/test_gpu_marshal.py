@@ -1,4 +1,7 @@
 """The native marshalling of the attention calls (csrc/marshal.cpp) against the Python code beside it: same outputs, same errors."""
+import threading
+import time
+
 import pytest
 import torch
 
@@ -88,3 +91,52 @@ def test_buffers_of_other_forms_are_still_taken():
                                 (lse.cpu().pin_memory(), room.view(2, -1)), (lse, torch.zeros(need, dtype=torch.uint8, pin_memory=True))):
         for x, y in zip(mb.memo_attn_bwd(q, k, v, o, some_lse, g, scale, workspace=workspace), want):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_other_threads_run_while_an_output_is_allocated(backward):
+    # the allocator gives segments back to the device first, which waits for the work that is queued
+    q = torch.zeros(64, 4096, 16, 128, dtype=torch.bfloat16, device="cuda")     # 1 GiB
+    scale = synth.default_scale(128)
+    o, lse = mb.memo_attn_fwd(q, q, q, scale)
+    busy = torch.zeros(1, 131072, 4, 128, dtype=torch.bfloat16, device="cuda")
+    busy_o, busy_lse = mb.memo_attn_fwd(busy, busy, busy, scale)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    outs = [torch.empty_like(q) for _ in range(2)]
+    parts = [torch.empty(600 << 20, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    room = torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory
+    del parts
+    gaps, stop = [0.0], threading.Event()
+
+    def watch():
+        last = time.perf_counter()
+        while not stop.is_set():
+            time.sleep(0.001)
+            now = time.perf_counter()
+            gaps.append(now - last)
+            last = now
+
+    watcher = threading.Thread(target=watch)
+    try:
+        torch.cuda.set_per_process_memory_fraction(room)
+        for _ in range(40):
+            mb.memo_attn_fwd(busy, busy, busy, scale, o=busy_o, lse=busy_lse)
+        watcher.start()
+        time.sleep(0.02)
+        begin = time.perf_counter()
+        if backward:
+            workspace = busy_o.view(torch.uint8).flatten()[:mb.memo_attn_bwd_workspace_bytes(q, scale)]
+            mb.memo_attn_bwd(q, q, q, o, lse, q, scale, dk=outs[0], dv=outs[1], workspace=workspace)
+        else:
+            mb.memo_attn_fwd(q, q, q, scale, lse=lse)
+        took = time.perf_counter() - begin
+    finally:
+        stop.set()
+        if watcher.ident:
+            watcher.join()
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    print(f"allocation took {took:.3f} s, the other thread's longest gap was {max(gaps):.3f} s", flush=True)
+    assert took > 0.1                                 # it did wait
+    assert max(gaps) < 0.3 * took
