@@ -108,14 +108,21 @@ at::Tensor new_tensor(at::IntArrayRef sizes, const at::TensorOptions &options)
     return at::empty(sizes, options);
 }
 
-// The stream's handle, as the binding finds it (find(stream)): after the checks, so that their errors come first.  false: an error is set.
-bool stream_handle(PyObject *find, PyObject *stream, void **out)
+// The stream's handle, as the binding finds it (find(stream)): after the checks, so that their errors come first.
+// kOther: no integer that fits a pointer; the Python code takes what ctypes takes (None, a c_void_p ..).
+enum Handle { kFound, kOther, kFailed };
+Handle stream_handle(PyObject *find, PyObject *stream, void **out)
 {
     PyObject *handle = PyObject_CallOneArg(find, stream);
-    if (!handle) return false;
-    *out = PyLong_AsVoidPtr(handle);
+    if (!handle) return kFailed;
+    Handle found = kOther;
+    if (PyLong_Check(handle)) {
+        *out = PyLong_AsVoidPtr(handle);
+        if (PyErr_Occurred()) PyErr_Clear();
+        else found = kFound;
+    }
     Py_DECREF(handle);
-    return !PyErr_Occurred();
+    return found;
 }
 
 PyObject *wrap(PyObject *given, const at::Tensor &t)
@@ -140,7 +147,9 @@ PyObject *attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (!same_layout(*q, {&o}) || !holds_lse(lse, *q, desc) || lse.dim() != 3 || lse.size(0) != desc.B || lse.size(1) != desc.H)
         Py_RETURN_NONE;
     void *stream = nullptr;
-    if (!stream_handle(a[1], a[8], &stream)) return nullptr;
+    const Handle found = stream_handle(a[1], a[8], &stream);
+    if (found == kFailed) return nullptr;
+    if (found == kOther) Py_RETURN_NONE;
     const FwdFn fn = address<FwdFn>(a[0]);
     const void *qp = q->data_ptr(), *kp = k->data_ptr(), *vp = v->data_ptr();
     void *op = o.data_ptr();
@@ -178,7 +187,9 @@ PyObject *attn_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
         workspace = t ? *t : new_tensor({(int64_t)std::max<size_t>(address<BytesFn>(a[1])(&desc), 256)}, q->options().dtype(at::kByte));
     }
     void *stream = nullptr;
-    if (!stream_handle(a[2], a[14], &stream)) return nullptr;
+    const Handle found = stream_handle(a[2], a[14], &stream);
+    if (found == kFailed) return nullptr;
+    if (found == kOther) Py_RETURN_NONE;
     const void *qp = q->data_ptr(), *kp = k->data_ptr(), *vp = v->data_ptr(), *op = o->data_ptr(), *gp = g->data_ptr();
     const float *lp = static_cast<const float *>(lse->data_ptr());
     void *dq = out[0].data_ptr(), *dk = out[1].data_ptr(), *dv = out[2].data_ptr(), *ws = is_static ? nullptr : workspace.data_ptr();

@@ -1,4 +1,5 @@
 """The native marshalling of the attention calls (csrc/marshal.cpp) against the Python code beside it: same outputs, same errors."""
+import ctypes
 import threading
 import time
 
@@ -91,6 +92,25 @@ def test_buffers_of_other_forms_are_still_taken():
                                 (lse.cpu().pin_memory(), room.view(2, -1)), (lse, torch.zeros(need, dtype=torch.uint8, pin_memory=True))):
         for x, y in zip(mb.memo_attn_bwd(q, k, v, o, some_lse, g, scale, workspace=workspace), want):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("handle", [None, 0, False, ctypes.c_void_p(None), ctypes.c_void_p(0), 1 << 64])
+def test_stream_handles_that_ctypes_takes(handle):
+    # the default stream in the forms in which a caller's own stream object may hold it
+    class Stream:
+        cuda_stream = handle
+
+    scale = synth.default_scale(64)
+    q, k, v, g = (t.cuda() for t in synth.attn_inputs(1, 75, 2, 64, "f32", 7))
+    torch.cuda.synchronize()
+    got = mb.memo_attn_fwd(q, k, v, scale, stream=Stream())
+    got += mb.memo_attn_bwd(q, k, v, *got, g, scale, stream=Stream())
+    got += mb.memo_attn_bwd_static(q, k, v, got[0], got[1], g, scale, *(torch.empty_like(q) for _ in range(3)), stream=Stream())
+    torch.cuda.synchronize()
+    want = mb.memo_attn_fwd(q, k, v, scale)
+    grads = mb.memo_attn_bwd(q, k, v, *want, g, scale)
+    for x, y in zip(got, want + grads + grads):
+        assert torch.equal(x, y)
 
 
 @pytest.mark.parametrize("backward", [False, True])
