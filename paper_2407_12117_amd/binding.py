@@ -11,6 +11,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmemo.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 MEMO_OK = 0
 MEMO_ERR_INVALID_ARG = 1
@@ -153,14 +154,14 @@ def lib():
 
 
 def _marshal():
-    """The native marshalling of the attention calls; raises if it has not been built."""
+    """The native marshalling of the attention calls; raises if it has not been built, or not for this Python and torch."""
     global _native
     if _native is None:
         try:
             from . import _marshal as native
         except ImportError as e:
-            raise RuntimeError("paper_2407_12117_amd/_marshal.so is missing: build it with "
-                               "`python -c 'import __graft_entry__ as g; g.build()'`") from e
+            state = f"cannot be loaded ({e})" if os.path.exists(MARSHAL_PATH) else "is missing"
+            raise RuntimeError(f"{MARSHAL_PATH} {state}: build it with `python -c 'import __graft_entry__ as g; g.build()'`") from e
         _native = native
     return _native
 

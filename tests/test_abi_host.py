@@ -4,6 +4,7 @@ swap plan, alpha) is bit-identical to the oracle's."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 import torch
@@ -26,6 +27,41 @@ def test_library_exports_every_declared_symbol():
     assert set(names) == set(mb.EXPORTS)
     for n in names:
         assert hasattr(L, n), n
+
+
+def test_native_marshalling_says_why_it_cannot_be_loaded(monkeypatch, tmp_path):
+    import paper_2407_12117_amd as package
+    mb._marshal()
+    monkeypatch.setattr(mb, "_native", None)
+    monkeypatch.delattr(package, "_marshal")
+    monkeypatch.delitem(sys.modules, package.__name__ + "._marshal")
+
+    class Broken:
+        @staticmethod
+        def find_spec(name, path=None, target=None):
+            if name == package.__name__ + "._marshal":
+                raise ImportError("undefined symbol: some_symbol")
+
+    monkeypatch.setattr(sys, "meta_path", [Broken] + sys.meta_path)
+    with pytest.raises(RuntimeError, match="cannot be loaded .undefined symbol: some_symbol"):
+        mb._marshal()
+    monkeypatch.setattr(mb, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    with pytest.raises(RuntimeError, match="is missing"):
+        mb._marshal()
+
+
+def test_build_loads_both_libraries(monkeypatch):
+    # a library that compiles and cannot be loaded fails the build, not the first call
+    import __graft_entry__ as entry
+    from oracle import memo_oracle
+    from paper_2407_12117_amd import build as memo_build
+    loaded = []
+    for module, name in ((memo_build, "build"), (memo_build, "build_bench_aids"), (memo_oracle, "build")):
+        monkeypatch.setattr(module, name, lambda **_: None)
+    monkeypatch.setattr(mb, "lib", lambda: loaded.append("libmemo"))
+    monkeypatch.setattr(mb, "_marshal", lambda: loaded.append("_marshal"))
+    entry.build()
+    assert sorted(loaded) == ["_marshal", "libmemo"]
 
 
 def test_status_strings():
