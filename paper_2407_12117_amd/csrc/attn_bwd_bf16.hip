@@ -571,23 +571,25 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, 
     dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, [&](int64_t nkt) { return decode_block(a, blockIdx.x, nkt, order, false); });
 }
 
-// both gradients in one launch, longest tiles of either kind first (JointOrder)
+// both gradients in one launch (joint_slot)
 template <int KG, int QG, int T>
-__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, JointOrder order, Divisor heads, Divisor H)
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_bf16_kernel(AttnArgs a, uint32_t key_tiles, Divisor heads, Divisor H)
 {
     constexpr int kLds = DkdvShape<KG>::kLds > DqShape<QG, T>::kLds ? DkdvShape<KG>::kLds : DqShape<QG, T>::kLds;
     static_assert(KG == QG, "a position stands for a key tile or a query tile of as many rows");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     const auto [pos, hb] = heads(blockIdx.x);
-    const JointSlot slot = joint_slot(order, pos);
+    const JointSlot slot = joint_slot(key_tiles, pos);
     const auto [b, h] = H(hb);
     const PairId t = {(int64_t)slot.rank, -1, (int)h, (int)b};
     if (slot.key) dkdv_rows<KG>(a, lds, [&](int64_t) { return t; });
     else dq_rows<QG, T>(a, lds, [&](int64_t nqt) { return PairId{nqt - 1 - t.first, -1, t.h, t.b}; });
 }
 
-// the same of 256 rows, whose launches are all beyond two rounds: first the key tiles, then the query tiles
+// the same of 256 rows, with the workgroup id decoded as in the launches of one gradient: a tile found by Divisor moved the
+// loops by half to one per cent (S = 90000 H = 4 23280 : 23516 us).  In the shorter launches above that costs as much where they last longest (64 rows,
+// S = 3001 H = 4 46.2 : 46.6) and gains 1 to 2 % where they are short (S = 334 H = 24 14.5 : 14.2, S = 1657 H = 8 29.5 : 29.2), half a per cent on average.
 __global__ __launch_bounds__(512, 2) void attn_bwd_both_long_bf16_kernel(AttnArgs a, uint32_t dkdv_blocks)
 {
     constexpr int kLds = DkdvShape<8>::kLds > DqShape<8, 64>::kLds ? DkdvShape<8>::kLds : DqShape<8, 64>::kLds;
@@ -931,7 +933,7 @@ __device__ __forceinline__ void dq_own_rows(const AttnArgs &a, LDS_AS unsigned c
 }
 
 template <int CS>
-__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, JointOrder order, Divisor heads, Divisor H)
+__global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, uint32_t key_tiles, Divisor heads, Divisor H)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kOwnRing + 2 * kOwnTile];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
@@ -939,7 +941,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_own_bf16_kernel(AttnArgs a, J
     asm volatile("" ::"s"(a.d_o), "s"(a.delta));
     const auto [pos, hbp] = heads(blockIdx.x);        // CS parts of a head beside each other
     const int part = (int)(hbp % CS);
-    const JointSlot slot = joint_slot(order, pos);
+    const JointSlot slot = joint_slot(key_tiles, pos);
     const TileId t = head_of(hbp / CS, slot.key ? (int)slot.rank : (int)((a.S + 31) / 32) - 1 - (int)slot.rank, H);
     if (slot.key) dkdv_own_rows<CS>(a, lds, t, part);
     else dq_own_rows<CS>(a, lds, t, part);
@@ -966,9 +968,8 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
         e = launch_main(a, true, false, st);
         return e == hipSuccess ? launch_main(a, false, true, st) : e;
     }
-    const JointOrder order(dkdv ? tiles : 0, dq ? tiles : 0, heads);
     auto launch = [&](auto kernel, int parts = 1) {
-        return launch_blocks(kernel, (dkdv + dq) * tiles * heads * parts, st, a, order, Divisor(heads * parts), Divisor(a.H));
+        return launch_blocks(kernel, (dkdv + dq) * tiles * heads * parts, st, a, dkdv ? (uint32_t)tiles : 0u, Divisor(heads * parts), Divisor(a.H));
     };
     switch (p.rows) {
     case 32:

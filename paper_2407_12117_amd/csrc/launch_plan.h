@@ -72,35 +72,17 @@ struct Divisor {
     }
 };
 
-// The order of one launch that works key tiles (dK/dV) and query tiles (dQ), longest first over both kinds: a query tile takes
-// `ratio` of the time of the key tile of the same length, so the longest 1 - ratio of the key tiles lead and the others are
-// spread evenly among the query tiles.  Position p stands for one tile of every head.
-// In launches of up to two rounds, whose second round is what the units with the shorter first tiles can take; with all key tiles
-// in front these end early beside the longest ones (us, key tiles in front : spread by a ratio of 0.8, which matters little: 64 rows, S = 2000
-// with 6 heads 36.4 : 34.6, S = 3000 H = 4 44.6 : 44.7, S = 4000 H = 4 67.0 : 67.0; 128 rows, S = 8192 H = 4 223 : 217).  Beyond that the key tiles in front
-// fill the end with short query tiles anyhow, and units that work tiles of one kind share what they stream: S = 5000 H = 5 125 : 131,
-// S = 12000 H = 5 554 : 571, S = 16461 H = 4 791 : 801, S = 90000 H = 4 22307 : 22762.
-struct JointOrder {
-    uint32_t lead, spread;        // key tiles in front, and among the query tiles
-    Divisor mixed;                // spread + query tiles
-
-    JointOrder(int64_t keys, int64_t queries, int64_t heads)
-        : lead((uint32_t)keys), spread(0), mixed(std::max<int64_t>(queries, 1))
-    {
-        if (queries == 0 || (keys + queries) * heads > 2 * kXcds * kChunk) return;
-        const int64_t behind = keys * 4 / 5;
-        lead = (uint32_t)(keys - behind);
-        spread = (uint32_t)behind;
-        mixed = Divisor(behind + queries);
-    }
-};
+// The order of one launch that works key tiles (dK/dV) and query tiles (dQ): all key tiles, longest first, and then all query tiles, longest
+// first.  Position p stands for one tile of every head.  The key tiles take longer, their starts and ends most of all, the short query tiles
+// fill the end, and units that work tiles of one kind share what they stream.  Key tiles shorter than the longest query tile spread among the query
+// tiles instead, in launches of one to two rounds of workgroups: 134 sizes of 1 to 32 heads 2.2 % slower on average, us in front : spread,
+// S = 825 H = 16 21.2 : 23.3, S = 1017 H = 32 44.7 : 48.5, S = 675 H = 6 13.3 : 14.4, S = 2041 H = 4 26.0 : 27.5, S = 1998 H = 6 33.4 : 34.0; the other way
+// round where the key tiles nearly fill the first round, with up to five heads: S = 2962 H = 5 52.4 : 50.5, S = 8185 H = 1 74.0 : 71.7.  With fewer of
+// them spread it is 0.5 % slower or more.  Beyond two rounds: S = 5000 H = 5 125 : 131, S = 12000 H = 5 554 : 571, S = 90000 H = 4 22307 : 22762.
 struct JointSlot { bool key; uint32_t rank; };      // rank 0: the longest tile of its kind
-constexpr JointSlot joint_slot(const JointOrder &o, uint32_t pos)
+constexpr JointSlot joint_slot(uint32_t key_tiles, uint32_t pos)
 {
-    if (pos < o.lead) return {true, pos};
-    const uint32_t m = pos - o.lead, keys = o.mixed(m * o.spread).quot;
-    if (o.mixed((m + 1) * o.spread).quot > keys) return {true, o.lead + keys};
-    return {false, m - keys};
+    return pos < key_tiles ? JointSlot{true, pos} : JointSlot{false, pos - key_tiles};
 }
 
 // Launches of 16- or 32-row workgroups that leave units idle: a tile goes to so many workgroups, each of which forms the scores again

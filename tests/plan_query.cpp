@@ -32,9 +32,8 @@ int main()
             const memo::Division r = memo::Divisor(b)((uint32_t)a);
             std::printf("%u %u\n", r.quot, r.rem);
         } else if (!std::strcmp(what, "joint") && std::scanf("%lld", &c) == 1) {
-            const memo::JointOrder o(a, b, c);
             for (uint32_t pos = 0; pos < a + b; ++pos) {
-                const memo::JointSlot s = memo::joint_slot(o, pos);
+                const memo::JointSlot s = memo::joint_slot((uint32_t)a, pos);
                 std::printf("%d ", s.key ? (int)s.rank : -1 - (int)s.rank);
             }
             std::printf("\n");

@@ -67,6 +67,12 @@ def test_joint_order_works_every_tile_once_and_longest_first(plans, tiles, heads
         assert [-1 - r for r in order if r < 0] == list(range(queries))
 
 
+# launches of one to two rounds of workgroups, where key tiles spread among the query tiles were measured slower, and one beyond
+@pytest.mark.parametrize("tiles,heads", [(13, 16), (14, 12), (9, 24), (8, 32), (22, 6), (64, 4), (64, 2), (32, 8), (65, 4)])
+def test_joint_launch_works_the_key_tiles_first(plans, tiles, heads):
+    assert plans([("joint", tiles, tiles, heads)])[0] == tuple(range(tiles)) + tuple(-1 - r for r in range(tiles))
+
+
 def test_division_by_a_launch_constant(plans):
     top = (1 << 32) - 1
     for d in (1, 2, 3, 5, 7, 40, 65535, 65536, 1000003, (1 << 26) - 1, (1 << 31) + 1, top):
