@@ -35,7 +35,7 @@ namespace {
 
 // ============================================================================ forward
 // Workgroup: kFwdWaves waves as QG query groups (32 rows each) x KS = 8 / QG key groups; key group g
-// takes the key tiles g, g + KS, ... of T rows through its own double-buffered LDS ring, filled
+// takes the key tiles g, g + KS, ... of 64 rows through its own double-buffered LDS ring, filled
 // asynchronously (one barrier per step), and the groups of a row are combined at the end.
 //   QG = 8: 256 rows, no split.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
 //           each MFMA pays for: the best rate on a full chip (1216 TFLOP/s at S = 128K, H = 4).
@@ -76,11 +76,11 @@ __device__ __forceinline__ void lds_wait(KqSlot<2> &x)
     asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(x.k), "+v"(x.q[0]), "+v"(x.q[1]) : "n"(N));
 }
 
-template <int QG, int T>
+template <int QG>
 __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int fold)
 {
-    constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = T, JB = T / 32;
-    constexpr int kTile = T * 256;              // bytes of one K or V tile
+    constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = 64, JB = kBk / 32;
+    constexpr int kTile = kBk * 256;            // bytes of one K or V tile
     constexpr int kStage = 2 * kTile, kGroup = 2 * kStage, kRing = KS * kGroup;
     constexpr int kMerge = KS > 1 ? 8 * 32 * 8 : 0;             // (maximum, sum) of every row of every wave
     static_assert(KS == 1 || kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
     const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
     if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
-    const TileOffsets<QG, T> toff = make_tile_offsets<QG, SwzA, T>(a.ss, wq, lane);
+    const TileOffsets<QG, kBk> toff = make_tile_offsets<QG, SwzA, kBk>(a.ss, wq, lane);
     auto fill_k = [&](int off, int jt) {
         toff.fill(lds + grp * kGroup + off, k, a.ss, (int64_t)jt * kBk, a.S, wq);
     };
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
         }
         if (jt >= wave_first_tile_masked) return;         // every key of this tile is masked for this wave
 
-        // S^T tile: rows = T keys (JB blocks of 32), cols = this wave's 32 queries.
+        // S^T tile: rows = 64 keys (JB = 2 blocks of 32), cols = this wave's 32 queries.
         // item n = (jb = n%JB, kc = n/JB): one row operand of K, read 2 MFMAs ahead; two key blocks
         // alternate, so that no MFMA accumulates onto the result of the one issued right before it
         f32x16 s[JB];
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
                 for (int e = 3; e < 15; e += 2) mb[jb] = fmaxf(fmaxf(mb[jb], s[jb][e]), s[jb][e + 1]);
                 mb[jb] = fmaxf(mb[jb], s[jb][15]);
             }
-            const float mt = max_across_halves(JB == 2 ? fmaxf(mb[0], mb[JB - 1]) : mb[0]);
+            const float mt = max_across_halves(fmaxf(mb[0], mb[1]));
             const float m_new = finite_max(m, mt);
             const float corr = __builtin_amdgcn_exp2f((m - m_new) * c);
             m = m_new;
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const TileId t = decode_tile(blockIdx.x, (int)((a.S + kBq - 1) / kBq), heads, H, true);
+    const TileId t = decode_tile(blockIdx.x, (int)((a.S + kBq - 1) / kBq), heads, H);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
     const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
@@ -717,8 +717,8 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
                                                                               : launch(attn_fwd_bf16_short_kernel<1>);
     }
     case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
-    case 128: return launch_blocks(attn_fwd_bf16_kernel<4, 64>, blocks, st, a, order);
-    default: return launch_blocks(attn_fwd_bf16_kernel<8, 64>, blocks, st, a, order);
+    case 128: return launch_blocks(attn_fwd_bf16_kernel<4>, blocks, st, a, order);
+    default: return launch_blocks(attn_fwd_bf16_kernel<8>, blocks, st, a, order);
     }
 }
 

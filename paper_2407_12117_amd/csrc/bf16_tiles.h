@@ -209,17 +209,17 @@ __device__ __forceinline__ void load_args_at_once(const AttnArgs &a)
     asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.S), "s"(a.sb), "s"(a.ss), "s"(a.sh), "s"(a.lse), "s"(a.scale), "s"(a.H));
 }
 
-// Longest-first work of one tile per workgroup, without the divisions of decode_block.
+// Longest-first work of one tile per workgroup, the last tile being the longest, without the divisions of decode_block.
 struct TileId { int tile, h, b; };
 __device__ __forceinline__ TileId head_of(uint32_t hb, int tile, Divisor H)
 {
     const auto [b, h] = H(hb);
     return {tile, (int)h, (int)b};
 }
-__device__ __forceinline__ TileId decode_tile(uint32_t id, int ntiles, Divisor heads, Divisor H, bool last_is_longest)
+__device__ __forceinline__ TileId decode_tile(uint32_t id, int ntiles, Divisor heads, Divisor H)
 {
     const auto [rank, hb] = heads(id);
-    return head_of(hb, last_is_longest ? ntiles - 1 - (int)rank : (int)rank, H);
+    return head_of(hb, ntiles - 1 - (int)rank, H);
 }
 
 // ---- asynchronous tile fill: global -> LDS without passing through registers -------------
