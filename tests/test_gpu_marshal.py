@@ -5,6 +5,8 @@ import time
 
 import pytest
 import torch
+from torch.overrides import TorchFunctionMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from paper_2407_12117_amd import binding as mb
 from paper_2407_12117_amd import synth
@@ -92,6 +94,93 @@ def test_buffers_of_other_forms_are_still_taken():
                                 (lse.cpu().pin_memory(), room.view(2, -1)), (lse, torch.zeros(need, dtype=torch.uint8, pin_memory=True))):
         for x, y in zip(mb.memo_attn_bwd(q, k, v, o, some_lse, g, scale, workspace=workspace), want):
             assert torch.equal(x, y)
+
+
+def _native(q, k, v, g, scale):
+    """What the native code alone makes of a forward and a backward: their outputs, or None where it leaves a call to Python."""
+    at, native = mb.lib().address, mb._marshal()
+    fwd = native.attn_fwd(at["memo_attn_fwd"], mb._stream_ptr, q, k, v, scale, None, None, None)
+    o, lse = fwd if fwd is not None else (torch.empty_like(q), torch.empty(q.shape[0], q.shape[2], q.shape[1], device=q.device))
+    return fwd, native.attn_bwd(at["memo_attn_bwd"], at["memo_attn_bwd_workspace_bytes"], mb._stream_ptr, q, k, v, o, lse, g, scale, None, None, None, None, None)
+
+
+def _case(seed):
+    return [t.cuda() for t in synth.attn_inputs(1, 75, 2, 64, "f32", seed)] + [synth.default_scale(64)]
+
+
+def test_tensors_that_require_grad_and_inference_tensors_are_taken():
+    q, k, v, g, scale = _case(8)
+    want = [t for part in _native(q, k, v, g, scale) for t in part]
+    for t in (q, k, v, g):
+        t.requires_grad_()
+    got = [t for part in _native(q, k, v, g, scale) for t in part]
+    assert all(torch.equal(x, y) and not x.requires_grad for x, y in zip(got, want))
+    with torch.inference_mode():
+        q, k, v, g = (t.clone() for t in (q, k, v, g))
+        got = [t for part in _native(q, k, v, g, scale) for t in part]
+        assert all(torch.equal(x, y) and x.is_inference() for x, y in zip(got, want))
+
+
+def test_modes_that_intercept_calls_see_the_python_code():
+    class Dispatch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            seen.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    class Function(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(getattr(func, "__name__", str(func)))
+            return func(*args, **(kwargs or {}))
+
+    q, k, v, g, scale = _case(9)
+    o, lse = mb.memo_attn_fwd(q, k, v, scale)
+    want = (o, lse) + mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+    for mode in (Dispatch, Function):
+        seen = []
+        with mode():
+            assert _native(q, k, v, g, scale) == (None, None)
+            seen.clear()
+            o, lse = mb.memo_attn_fwd(q, k, v, scale)
+            got = (o, lse) + mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+        assert sum("empty" in name for name in seen) >= 4        # the outputs are allocated where the mode sees it
+        assert all(torch.equal(x, y) for x, y in zip(got, want))
+
+
+def test_functorch_wrappers_are_left_to_python():
+    q, k, v, g, scale = _case(10)
+
+    def batched(x):
+        left.append(_native(x, x, x, x, scale))
+        with pytest.raises(RuntimeError):             # a wrapper has no memory of its own
+            mb.memo_attn_fwd(x, x, x, scale)
+        return x
+
+    left = []
+    torch.func.vmap(batched)(torch.stack((q, k)))
+    torch.func.grad(lambda x: batched(x).sum())(q)
+    assert left == [(None, None)] * 2
+
+
+def test_calls_under_graph_capture():
+    # outputs and workspace from the graph's pool; replayed on new inputs with eager work between
+    q, k, v, g, scale = _case(11)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        mb.memo_attn_bwd(q, k, v, *mb.memo_attn_fwd(q, k, v, scale), g, scale)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        o, lse = mb.memo_attn_fwd(q, k, v, scale)
+        got = (o, lse) + mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+    for seed in (12, 13, 14):
+        for t, new in zip((q, k, v, g), _case(seed)):
+            t.copy_(new)
+        o, lse = mb.memo_attn_fwd(q, k, v, scale)
+        want = (o, lse) + mb.memo_attn_bwd(q, k, v, o, lse, g, scale)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(got, want))
 
 
 @pytest.mark.parametrize("handle", [None, 0, False, ctypes.c_void_p(None), ctypes.c_void_p(0), 1 << 64])
