@@ -38,14 +38,15 @@ namespace {
 // takes the key tiles g, g + KS, ... of 64 rows through its own double-buffered LDS ring, filled
 // asynchronously (one barrier per step), and the groups of a row are combined at the end.
 //   QG = 8: 256 rows, no split.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
-//           each MFMA pays for: the best rate on a full chip (1216 TFLOP/s at S = 128K, H = 4).
-//   QG = 4: 128 rows, keys in two (1110).
-//   64 rows, keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel below (960).
-//   32 rows, keys in eight: attn_fwd_bf16_short_kernel below (752).
+//           each MFMA pays for: the best rate on a full chip (1150 TFLOP/s at S = 128K, H = 4, on one card in turn
+//           with the others; 1216 on a cool one).
+//   QG = 4: 128 rows, keys in two (1130).
+//   64 rows, keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel below (1050).
+//   32 rows, keys in eight: attn_fwd_bf16_short_kernel below (700).
 // A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
 // last row: what bounds it is the longest workgroup, which 32 rows make 64 times shorter.  The launcher
-// takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 6.8,
-// B = 2 S = 2000 H = 3 67.8 -> 14.8, S = 8192 H = 4 250 -> 78, S = 16461 H = 4 482 -> 265, S = 40000 H = 4 2202 -> 1516.
+// takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 5.7,
+// B = 2 S = 2000 H = 3 67.8 -> 14.8, S = 8192 H = 4 250 -> 77, S = 16461 H = 4 482 -> 264, S = 40000 H = 4 2202 -> 1483.
 // The fills address a tile as a buffer (TileOffsets::fill): no per-lane pointers to step and no second path for the
 // ragged last tile, 1 to 3 % of every shape.
 constexpr int kFwdWaves = 8;                 // waves per workgroup
@@ -374,9 +375,9 @@ __device__ __forceinline__ void merge_waves(const AttnArgs &a, const LDS_AS f32x
 // through the compute unit's 64 B per cycle from the L2, its 128 B per cycle into the LDS, and single waves' chains of
 // instructions.  So the loads go out first and once (kernel arguments in one go; Q to the LDS, not to every wave's registers in
 // pieces of 32 bytes), the set-up of addresses and accumulators comes behind them, and at the end a wave leaves its
-// accumulators in its own buffer without waiting for the others.  us: S = 32 H = 2 6.0 -> 4.0, S = 640 H = 2 8.1 -> 6.8,
-// B = 2 S = 2000 H = 3 17.8 -> 14.8, S = 3000 H = 4 20.3 -> 17.8.
-// CS: the columns of O of a tile go to so many workgroups where units would be idle (column_parts, launch_plan.h).
+// accumulators in its own buffer without waiting for the others.  us, columns in one part: S = 32 H = 2 6.0 -> 4.0, S = 640 H = 2 8.1 -> 6.8,
+// B = 2 S = 2000 H = 3 18.1 -> 14.8, S = 3000 H = 4 20.6 -> 17.9.
+// CS: the columns of O of a tile go to so many workgroups where units would be idle (column_parts, launch_plan.h): S = 32 H = 2 3.2, S = 640 H = 2 5.7.
 template <int CS>
 __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_short_kernel(AttnArgs a, Divisor heads, Divisor H)
 {
@@ -581,8 +582,8 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void attn_fwd_bf16_own_kernel(At
     asm volatile("" ::: "memory");
 
     // Of the two waves of a SIMD the older one is served first and would end its keys a fifth of the sweep ahead; from here on the
-    // younger one is, so that they end together and neither works alone (S = 8192, H = 4: 81.3 -> 78.1 us; the place, between a third and
-    // a half of the sweep, matters by 0.5 %).
+    // younger one is, so that they end together and neither works alone (without : with, us: S = 8192 H = 4 79.1 : 76.7, S = 6000 H = 4
+    // 49.8 : 47.7, S = 12000 H = 3 134.7 : 131.0, S = 4096 H = 4 27.4 : 27.4; the place, between a third and a half of the sweep, matters by 0.5 %).
     const int even_out = ntiles * 7 / 16;
 
     // one key tile against the row blocks from `F` on (the tile past the first block's diagonal is the second's alone)

@@ -605,14 +605,14 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_both_long_bf16_kernel(AttnArg
 // For short sequences: 32 keys (or query rows) per workgroup, the other side of the sweep in eight.  Every wave works all 32
 // rows against 32-row tiles of its own, one buffer each, so there is no barrier in the sweep; a half of the buffer
 // is refilled as soon as it is used up.  The sums meet in LDS at the end.  Twice the fill traffic of 64-row workgroups, and
-// sweeps of half the steps: ahead where the longest sweep, not the work, is what a launch takes (own_us, launch_plan.h).  us, 64-row
-// workgroups -> these: S = 1000 H = 4 20.5 -> 15.4, S = 1500 H = 4 26.4 -> 22.5, S = 2500 H = 2 37.6 -> 25.1, S = 640 H = 2
-// 16.1 -> 15.3; but S = 2000, 6 heads 36.2 -> 45.9, S = 8192 H = 4 227 -> 259.
+// sweeps of half the steps: ahead where the longest sweep, not the work, is what a launch takes (own_us, launch_plan.h).  us with the
+// D_i launch, 64-row workgroups : these: S = 256 H = 2 10.4 : 7.3, S = 640 H = 2 15.1 : 9.9, S = 1000 H = 4 20.0 : 14.9, S = 1500 H = 4 25.9 : 19.8,
+// S = 2500 H = 2 37.3 : 24.4; but S = 2000 with 6 heads 33.3 : 40.5, S = 8192 H = 4 227 : 252.
 // A start is bound by the 144 KB that eight waves fetch through a unit's 64 B per cycle (dQ: Q and dO once to the LDS, not to every wave's
-// registers) with the set-up behind it, an end by 128 KB through the LDS per sum.  us with these, without, the D_i launch in both: S = 256 H = 2
-// 9.5, 10.5; S = 640 H = 2 11.8, 12.1; S = 1000 H = 4 14.7, 15.0; S = 1536 H = 2 17.6, 18.1.  Tried at the end without gain: dK's pieces put
-// while dV's are added up, barriers that do not wait for stores.
-// CS: the output columns of a tile go to so many workgroups where units would be idle (column_parts, launch_plan.h).
+// registers) with the set-up behind it, an end by 128 KB through the LDS per sum.  What Q and dO through the LDS and the set-up behind the loads gave, columns in one part: S = 256 H = 2
+// 10.5 -> 9.5, S = 1000 H = 4 15.0 -> 14.7, S = 1536 H = 2 18.1 -> 17.6.  Tried at the end without gain: dK's pieces put while dV's are added up,
+// barriers that do not wait for stores.
+// CS: the output columns of a tile go to so many workgroups where units would be idle (column_parts, launch_plan.h): S = 640 H = 2 11.6 -> 9.9.
 constexpr int kOwnTile = 32 * 256, kOwnRing = 8 * 2 * kOwnTile;
 
 // piece of every wave -> its sum in the wave that owns the piece (two of sixteen for NB = 8 blocks of columns): out(block of rows, block of

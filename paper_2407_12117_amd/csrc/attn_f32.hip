@@ -8,8 +8,8 @@
 // vector form needs an LDS read per multiply-add and lane.  An earlier VALU version of these kernels ran at 5 to
 // 7 TFLOP/s, bound by its scalar LDS reads; these reach 116 (forward) and 122 (backward, of its seven contractions) at
 // S = 5000, B = 2, H = 4, d = 128.  Where units would be idle a tile's output columns go to two or four workgroups, which halves or quarters
-// the second contractions of the longest tile, the one that such a launch takes (us, with the D_i launch: S = 1024 H = 1 d = 64 forward
-// 12.9 -> 10.8, backward 26.8 -> 23.0; d = 128 21.5 -> 17.9 and 43.1 -> 37.2).
+// the second contractions of the longest tile, the one that such a launch takes (us, one part : as they go out, with the D_i launch: S = 1024 H = 1 d = 64
+// forward 12.7 : 10.4, backward 24.6 : 21.5; d = 128 20.7 : 17.5 and 39.8 : 34.0).
 //
 // Operand conventions of the 16x16x4 MFMA, D = A(16xK4) * B(K4x16), lane = 16*g4 + l16:
 //   A : lane holds row l16, k = g4;  B : lane holds col l16, k = g4;

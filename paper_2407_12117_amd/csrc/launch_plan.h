@@ -88,9 +88,12 @@ constexpr JointSlot joint_slot(uint32_t key_tiles, uint32_t pos)
 // Launches of 16- or 32-row workgroups that leave units idle: a tile goes to so many workgroups, each of which forms the scores again
 // and its part of the output columns, as long as all of them find a unit.  What shrinks with the parts is the second half of a
 // step's contractions, the accumulators to clear and the sums through the LDS at the end; output bits do not change.  us in 1 : 2 : 4
-// parts, bf16 forward S = 32 H = 2 4.0 : 3.4 : 3.2, S = 640 H = 2 6.8 : 6.0 : 5.8, S = 2000 H = 1 12.0 : 11.0 : 11.0; bf16 backward with the D_i
-// launch S = 32 H = 2 8.4 : 7.2 : 6.6, S = 500 H = 2 11.1 : 9.6 : 9.2.  With more workgroups than units it loses: two parts of S = 1000 H = 4
-// backward 14.7 : 17.2, S = 2000 H = 4 forward 12.6 : 15.3.
+// parts, bf16 forward S = 32 H = 2 4.0 : 3.4 : 3.2, S = 640 H = 2 6.8 : 6.0 : 5.7, S = 2000 H = 1 12.0 : 10.9 : 10.8; bf16 backward with the D_i
+// launch S = 32 H = 2 8.1 : 6.9 : 6.3, S = 500 H = 2 11.0 : 9.2 : 8.8.  With more workgroups than units it loses: two parts of S = 1000 H = 4
+// backward 14.9 : 16.6, S = 2000 H = 4 forward 12.8 : 14.9.
+// The units are idle only if nobody else wants them.  Beside a copy to the host no more is lost than in one part, and the copy takes as long.
+// But calls on several streams at once meet that limit together: us for a forward and backward on every one of 1, 2, 3, 4 streams, one part : as
+// here, S = 640 H = 2 18.6 : 16.0, 21.0 : 18.8, 23.4 : 22.5, 25.2 : 34.8; S = 1000 H = 2 23.1 : 20.2, 25.7 : 25.4, 28.5 : 36.1, 31.7 : 53.8.
 inline int column_parts(int64_t blocks)
 {
     const int64_t units = kXcds * kChunk;
@@ -187,7 +190,10 @@ inline constexpr TileChoice kDqChoices[] = {
 };
 
 // A launch of 32-row workgroups: no shorter than its longest key tile, nor than all work spread over the chip with the start and
-// the end of every workgroup (4.5 us); fitted to S = 250 .. 8192, 1 to 6 heads (within 10 %).
+// the end of every workgroup (4.5 us).  Fitted before these kernels' starts and ends became shorter and their columns went out in parts: the estimate
+// is 0.92 to 1.17 times what is measured now from 2000 rows on, 1.05 to 1.45 times from 400, and up to 1.6 times below.  So launches of up to one
+// round of 32-row workgroups and many heads still go to 64 rows: us, 64 rows (taken) : 32, S = 78 H = 12 9.8 : 7.5, S = 121 H = 16 9.9 : 7.9, S = 300 H = 10
+// 12.6 : 11.0, S = 1187 H = 6 24.3 : 21.3; over 250 sizes of 25 to 25593 rows and 1 to 32 heads the choice of rows is 1.8 % slower than the best one on average.
 inline double own_us(int64_t S, int64_t heads)
 {
     const double per_row = (double)S / (1 << 20), items = 2.0 * ((S + 31) / 32) * heads;

@@ -1,7 +1,7 @@
 // The attention calls' way from Python to the C entry points: layout checks, outputs and argument blocks of memo_attn_fwd,
 // memo_attn_bwd and memo_attn_bwd_static in one native call each.  The kernels of a short forward and backward take 13 to 16 us, and
-// with the same work in Python (ctypes, some 60 property reads) the host took 17.7 us to queue a forward and a static backward, 27 with the outputs
-// allocated; now 10.7 and 18, launches included.
+// with the same work in Python (ctypes, some 60 property reads) the host took 17.6 us to queue a forward and a static backward, 26.2 with the outputs
+// allocated; now 10.6 and 16.5, launches included.
 //
 // Only plain device tensors that pass every check are taken.  For anything else (another layout or type, subclasses, wrapped
 // or lazy tensors, modes that intercept calls) the functions return None, and the Python code beside the call does what
