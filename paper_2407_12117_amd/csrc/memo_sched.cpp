@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/memo.h"
+#include "memo_kernels.h"
 
 namespace {
 
@@ -164,8 +165,8 @@ memo_status memo_sched_forward_end(memo_sched *s, int32_t layer)
         char *slot = s->host + static_cast<size_t>(layer) * s->host_bytes;
         for (const memo_tensor_slot &t : s->slots) {
             if (t.bytes_swapped == 0) continue;
-            if (hipMemcpyAsync(slot + t.host_offset, buf + t.dev_offset, t.bytes_swapped,
-                               hipMemcpyDeviceToHost, s->offload) != hipSuccess)
+            if (memo::copy_swapped(slot + t.host_offset, buf + t.dev_offset, t.bytes_swapped,
+                                   hipMemcpyDeviceToHost, s->offload) != hipSuccess)
                 return fail(s);
         }
         if (hipEventRecord(s->offloaded[layer], s->offload) != hipSuccess) return fail(s);
@@ -199,8 +200,8 @@ memo_status memo_sched_backward_end(memo_sched *s, int32_t layer)
         const char *slot = s->host + static_cast<size_t>(j) * s->host_bytes;
         for (const memo_tensor_slot &t : s->slots) {
             if (t.bytes_swapped == 0) continue;
-            if (hipMemcpyAsync(buf + t.dev_offset, slot + t.host_offset, t.bytes_swapped,
-                               hipMemcpyHostToDevice, s->prefetch) != hipSuccess)
+            if (memo::copy_swapped(buf + t.dev_offset, slot + t.host_offset, t.bytes_swapped,
+                                   hipMemcpyHostToDevice, s->prefetch) != hipSuccess)
                 return fail(s);
         }
         if (hipEventRecord(s->fetched[j], s->prefetch) != hipSuccess) return fail(s);
