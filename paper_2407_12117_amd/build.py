@@ -19,6 +19,7 @@ SOURCES = {
     "memo_dsa.cpp": [],
     "attn_f32.hip": [],
     "attn_bf16.hip": [],
+    "attn_fwd_long_bf16.hip": [],
     "attn_bwd_bf16.hip": [],
     "attn_bwd_static.hip": [],
     "recompute_bf16.hip": [],

@@ -34,15 +34,15 @@ namespace memo {
 namespace {
 
 // ============================================================================ forward
-// Workgroup: kFwdWaves waves as QG query groups (32 rows each) x KS = 8 / QG key groups; key group g
-// takes the key tiles g, g + KS, ... of 64 rows through its own double-buffered LDS ring, filled
-// asynchronously (one barrier per step), and the groups of a row are combined at the end.
-//   QG = 8: 256 rows, no split.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
-//           each MFMA pays for: the best rate on a full chip (1150 TFLOP/s at S = 128K, H = 4, on one card in turn
-//           with the others; 1216 on a cool one).
-//   QG = 4: 128 rows, keys in two (1130).
-//   64 rows, keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel below (1050).
-//   32 rows, keys in eight: attn_fwd_bf16_short_kernel below (700).
+// Workgroups, by owned rows:
+//   256 rows: attn_fwd_long_bf16.hip, four waves of 64 rows.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
+//        each MFMA pays for, and the fewer LDS reads per MFMA with more rows in a wave: the best rate on a full chip.
+//   128: attn_fwd_bf16_kernel, eight waves as four query groups (32 rows each) x two key groups; key group g
+//        takes the key tiles g, g + 2, ... of 64 rows through its own double-buffered LDS ring, filled
+//        asynchronously (one barrier per step), and the groups of a row are combined at the end.
+//   64: keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel.
+//   32: keys in eight: attn_fwd_bf16_short_kernel.
+// TFLOP/s at S = 128K, H = 4: 1312, 1130, 1050, 700.
 // A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
 // last row: what bounds it is the longest workgroup, which 32 rows make 64 times shorter.  The launcher
 // takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 5.7,
@@ -50,16 +50,6 @@ namespace {
 // The fills address a tile as a buffer (TileOffsets::fill): no per-lane pointers to step and no second path for the
 // ragged last tile, 1 to 3 % of every shape.
 constexpr int kFwdWaves = 8;                 // waves per workgroup
-// A lane's 32 exponentials of a tile may sum to this much before the running maximum is brought up to
-// date: 2^40 per tile leaves the row sum over 2^20 keys and the output accumulators far inside fp32.
-constexpr float kRescaleAbove = 1099511627776.f;
-
-// The running maximum of a wave that has met keys, never below the lowest finite value: a row may see nothing but scores of
-// -inf in a wave's tile (masked keys), and -inf - -inf is NaN.  Times c it stays above -2^31, where the rounding of the
-// product moves an exponent by up to 2^6, which fp32 holds; scores further down weigh zero against any key that is not masked.
-__device__ __forceinline__ float finite_max(float m, float tile_max) { return fmaxf(fmaxf(m, tile_max), -3.402823466e38f); }
-__device__ __forceinline__ float scaled_max(float m, float c) { return fmaxf(m * c, -2147483648.f); }
-
 // a K operand and the Q operands of one or two row blocks
 template <int NQ> struct KqSlot { bf16x8 k, q[NQ]; };
 
@@ -77,14 +67,13 @@ __device__ __forceinline__ void lds_wait(KqSlot<2> &x)
     asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(x.k), "+v"(x.q[0]), "+v"(x.q[1]) : "n"(N));
 }
 
-template <int QG>
-__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int fold)
+__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a)
 {
-    constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = 64, JB = kBk / 32;
+    constexpr int QG = 4, KS = kFwdWaves / QG, kBq = 32 * QG, kBk = 64, JB = kBk / 32;
     constexpr int kTile = kBk * 256;            // bytes of one K or V tile
     constexpr int kStage = 2 * kTile, kGroup = 2 * kStage, kRing = KS * kGroup;
-    constexpr int kMerge = KS > 1 ? 8 * 32 * 8 : 0;             // (maximum, sum) of every row of every wave
-    static_assert(KS == 1 || kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
+    constexpr int kMerge = 8 * 32 * 8;             // (maximum, sum) of every row of every wave
+    static_assert(kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kRing + kMerge];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [key group][buf][K|V] tiles
 
@@ -93,9 +82,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const LaneAddr la = make_lane_addr(lane);
     const int wq = wave % QG, grp = wave / QG;  // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const int order = tile_order(kBq, fold);
-    const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
-    if (t.first < 0) return;
+    const PairId t = decode_block(a, blockIdx.x, nqt, kLongestFirst, true);
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
@@ -106,17 +93,10 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const uint32_t (&row_addr)[8] = ad.row;
     const uint32_t (&tr_addr)[4][2] = ad.tr;
 
-    // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
-    // (online softmax takes the key tiles in any order)
-    for (int pass = 0; pass < (QG == 8 ? 2 : 1); ++pass) {
-    const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
-    if (tile < 0) break;
-    const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq, i = i0w + l32;
+    const int64_t row0 = t.first * kBq, i0w = row0 + 32 * wq, i = i0w + l32;
     const int64_t last_row = min(row0 + kBq, a.S) - 1;
     const int ntiles = (int)(last_row / kBk) + 1, nsteps = (ntiles + KS - 1) / KS;
-    // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
-    const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
-    if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
+    // step n of a key group works tile KS * n + grp
     const TileOffsets<QG, kBk> toff = make_tile_offsets<QG, SwzA, kBk>(a.ss, wq, lane);
     auto fill_k = [&](int off, int jt) {
         toff.fill(lds + grp * kGroup + off, k, a.ss, (int64_t)jt * kBk, a.S, wq);
@@ -126,29 +106,19 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     };
     // Key groups that need the same Q rows bring them in once, as whole rows, in the place of the buffers that the second tiles take: to each
     // wave's registers straight from memory, 32 bytes of a row at a time, they cost a unit 5000 cycles.
-    constexpr bool kStaged = KS > 1;
     constexpr int kBlocks = kStage / (32 * 256);      // 32-row blocks in one such buffer
-    static_assert(!kStaged || KS * kBlocks >= QG, "room for the Q rows");
+    static_assert(KS * kBlocks >= QG, "room for the Q rows");
     auto staged = [&](int block) { return lds + block / kBlocks * kGroup + kStage + block % kBlocks * 32 * 256; };
-    if constexpr (kStaged) {
-        const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzA, 32>(a.ss, wave, lane);
+    const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzA, 32>(a.ss, wave, lane);
 #pragma unroll
-        for (int blk = 0; blk < QG; ++blk) qoff.fill(staged(blk), q, a.ss, row0 + 32 * blk, a.S, wave);
-    }
-    if (jfirst < ntiles) {
-        fill_k(0, jfirst);
-        fill_v(0, jfirst);
+    for (int blk = 0; blk < QG; ++blk) qoff.fill(staged(blk), q, a.ss, row0 + 32 * blk, a.S, wave);
+    if (grp < ntiles) {
+        fill_k(0, grp);
+        fill_v(0, grp);
     }
 
     // Q^T as B operand: lane = query row i, 8 head-dim values per 16-wide chunk
     bf16x8 qB[8];
-    if constexpr (!kStaged) {
-        const int64_t iq = i < a.S ? i : a.S - 1;     // rows past S are computed and never stored
-#pragma unroll
-        for (int kc = 0; kc < 8; ++kc)
-            qB[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq * a.ss + 16 * kc + 8 * half));
-    }
-
     f32x16 accO[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
@@ -158,14 +128,12 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const int wave_first_tile_masked = min((int)((i0w + 31) / kBk) + 1, ntiles);   // tiles >= this are fully masked
     const int wave_first_diag = (int)(i0w / kBk);                     // tiles >= this need the mask
 
-    if constexpr (kStaged) {
-        wait_fills();
-        __syncthreads();          // the Q rows are complete; the first step's barrier is what their place waits for
-        static_for<0, 8>([&](auto n) {
-            lds_issue_b128<0>(qB[decltype(n)::value], (uint32_t)(uintptr_t)staged(wq) + (uint32_t)(la.row_op[0] ^ (decltype(n)::value << 5)));
-        });
-        static_for<0, 8>([&](auto n) { lds_wait<0>(qB[decltype(n)::value]); });
-    }
+    wait_fills();
+    __syncthreads();              // the Q rows are complete; the first step's barrier is what their place waits for
+    static_for<0, 8>([&](auto n) {
+        lds_issue_b128<0>(qB[decltype(n)::value], (uint32_t)(uintptr_t)staged(wq) + (uint32_t)(la.row_op[0] ^ (decltype(n)::value << 5)));
+    });
+    static_for<0, 8>([&](auto n) { lds_wait<0>(qB[decltype(n)::value]); });
 
     // One key/value tile.  BUF is a compile-time buffer index, so every LDS address below is
     // a per-lane register plus an immediate offset.
@@ -173,10 +141,10 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
         constexpr int BUF = decltype(bufc)::value;
         constexpr int kOff = BUF * kStage, vOff = kOff + kTile;
         constexpr int nOff = (BUF ^ 1) * kStage;
-        const int jn = jt + jstep;
+        const int jn = jt + KS;
         wait_fills();
         __syncthreads();          // tile jt is complete; nobody still reads the other buffer
-        if (jn >= 0 && jn < ntiles) {
+        if (jn < ntiles) {
             fill_k(nOff, jn);
             fill_v(nOff, jn);
         }
@@ -271,61 +239,53 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     };
 
     for (int n = 0; n < nsteps; n += 2) {
-        tile_step(IntC<0>{}, jfirst + jstep * n);
-        if (n + 1 < nsteps) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
+        tile_step(IntC<0>{}, grp + KS * n);
+        if (n + 1 < nsteps) tile_step(IntC<1>{}, grp + KS * (n + 1));
     }
 
     const float ltot = add_across_halves(lsum);
     __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
     float *lse = a.lse + ((int64_t)t.b * a.H + t.h) * a.S + i;
-    if constexpr (KS == 1) {
-        if (i < a.S) {
-            store_acc_T(o, accO, 1.f / ltot, half);
-            if (half == 0) *lse = (mc + __builtin_amdgcn_logf(ltot)) * kLn2;
-        }
-    } else {
-        // The key groups of a row meet in LDS: every wave leaves its accumulators, (c m) and row sums; each
-        // then combines 16/KS of the sixteen 4-value pieces of its rows over the groups.  A group that had
-        // no tile has m = -inf and weighs exactly zero.
-        LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
-        LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kRing);
-        __syncthreads();          // every wave has left the last LDS buffer
+    // The key groups of a row meet in LDS: every wave leaves its accumulators, (c m) and row sums; each
+    // then combines 16/KS of the sixteen 4-value pieces of its rows over the groups.  A group that had
+    // no tile has m = -inf and weighs exactly zero.
+    LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+    LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kRing);
+    __syncthreads();          // every wave has left the last LDS buffer
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-            pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
-                                                        accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
-        if (half == 0) stats[wave * 32 + l32] = f32x2{mc, ltot};
-        __syncthreads();
-        float top = -INFINITY, total = 0.f, weight[KS];
-        f32x2 st[KS];
+    for (int e = 0; e < 16; ++e)
+        pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
+                                                    accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
+    if (half == 0) stats[wave * 32 + l32] = f32x2{mc, ltot};
+    __syncthreads();
+    float top = -INFINITY, total = 0.f, weight[KS];
+    f32x2 st[KS];
 #pragma unroll
-        for (int g = 0; g < KS; ++g) {
-            st[g] = stats[(g * QG + wq) * 32 + l32];
-            top = fmaxf(top, st[g][0]);
-        }
-#pragma unroll
-        for (int g = 0; g < KS; ++g) {
-            weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
-            total += weight[g] * st[g][1];
-        }
-        if (i < a.S) {
-            const float inv = 1.f / total;
-#pragma unroll
-            for (int n = 0; n < 16 / KS; ++n) {
-                const int e = grp * (16 / KS) + n;
-                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int g = 0; g < KS; ++g) {
-                    const f32x4 x = pieces[((g * QG + wq) * 16 + e) * 64 + lane];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
-                }
-                store4(o + 8 * e + 4 * half, sum, inv);
-            }
-            if (grp == 0 && half == 0) *lse = (top + __builtin_amdgcn_logf(total)) * kLn2;
-        }
+    for (int g = 0; g < KS; ++g) {
+        st[g] = stats[(g * QG + wq) * 32 + l32];
+        top = fmaxf(top, st[g][0]);
     }
-    }   // pass
+#pragma unroll
+    for (int g = 0; g < KS; ++g) {
+        weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
+        total += weight[g] * st[g][1];
+    }
+    if (i < a.S) {
+        const float inv = 1.f / total;
+#pragma unroll
+        for (int n = 0; n < 16 / KS; ++n) {
+            const int e = grp * (16 / KS) + n;
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int g = 0; g < KS; ++g) {
+                const f32x4 x = pieces[((g * QG + wq) * 16 + e) * 64 + lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
+            }
+            store4(o + 8 * e + 4 * half, sum, inv);
+        }
+        if (grp == 0 && half == 0) *lse = (top + __builtin_amdgcn_logf(total)) * kLn2;
+    }
 }
 
 // The end of the kernels whose eight waves share out the keys of 32 rows: every wave has left its accumulators as sixteen
@@ -718,8 +678,8 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
                                                                               : launch(attn_fwd_bf16_short_kernel<1>);
     }
     case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
-    case 128: return launch_blocks(attn_fwd_bf16_kernel<4>, blocks, st, a, order);
-    default: return launch_blocks(attn_fwd_bf16_kernel<8>, blocks, st, a, order);
+    case 128: return launch_blocks(attn_fwd_bf16_kernel, blocks, st, a);
+    default: return launch_attn_fwd_bf16_long(a, order, blocks, st);
     }
 }
 

@@ -167,12 +167,13 @@ __device__ __forceinline__ void store_acc_T(__bf16 *out_row, const f32x16 (&acc)
 // a workgroup's work (launch_plan.h)
 struct PairId { int64_t first, second; int h, b; };   // first < 0: nothing to do; second < 0: one tile only
 
-// Launches `blocks` workgroups of 512 threads.
-template <typename... P, typename... A>
+// Launches `blocks` workgroups of THREADS threads.
+template <int THREADS = kThreads, typename... P, typename... A>
 hipError_t launch_blocks(void (*kernel)(P...), int64_t blocks, hipStream_t st, const A &...args)
 {
     if (blocks > kMaxBlocks) return hipErrorInvalidValue;
-    kernel<<<dim3((unsigned)blocks), kThreads, 0, st>>>(args...);
+    static_assert(THREADS <= kThreads, "kMaxBlocks");
+    kernel<<<dim3((unsigned)blocks), THREADS, 0, st>>>(args...);
     return hipGetLastError();
 }
 
@@ -238,12 +239,23 @@ struct TileOffsets {
     __device__ __forceinline__ void fill(LDS_AS unsigned char *tile, const __bf16 *src, int64_t ss, int64_t r0, int64_t end, int wave) const
     {
 #ifdef __HIP_DEVICE_COMPILE__      // the host pass does not know the 16-byte form of the builtin
+        const __amdgpu_buffer_rsrc_t rsrc = buffer(src, ss, r0, end);
+#pragma unroll
+        for (int n = 0; n < kInstr; ++n) part(tile, rsrc, n, wave);
+#endif
+    }
+
+    // The two halves of it: the buffer, and instruction n.
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const __bf16 *src, int64_t ss, int64_t r0, int64_t end) const
+    {
         const int rows = (int)max((int64_t)0, min((int64_t)ROWS, end - r0));
         const uint32_t bytes = rows > 0 ? (uint32_t)(rows - 1) * (uint32_t)ss * 2 + 256 : 0;
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(src + r0 * ss), 0, bytes, 0x00020000);
-#pragma unroll
-        for (int n = 0; n < kInstr; ++n)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (LDS_AS void *)(tile + (kInstr * wave + n) * 1024), 16, off[n], 0, 0, 0);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(src + r0 * ss), 0, bytes, 0x00020000);
+    }
+    __device__ __forceinline__ void part(LDS_AS unsigned char *tile, __amdgpu_buffer_rsrc_t rsrc, int n, int wave) const
+    {
+#ifdef __HIP_DEVICE_COMPILE__
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (LDS_AS void *)(tile + (kInstr * wave + n) * 1024), 16, off[n], 0, 0, 0);
 #endif
     }
 };
@@ -358,11 +370,17 @@ __device__ __forceinline__ void lds_issue_b128(V16 &dst, uint32_t addr)
 }
 
 template <int OFF>
-__device__ __forceinline__ void lds_issue_tr(TrSlot &dst, uint32_t addr_lo, uint32_t addr_hi)
+__device__ __forceinline__ void lds_issue_tr_half(s16x4 &dst, uint32_t addr)
 {
     static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst.lo) : "v"(addr_lo), "n"(OFF) : "memory");
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst.hi) : "v"(addr_hi), "n"(OFF) : "memory");
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
+}
+
+template <int OFF>
+__device__ __forceinline__ void lds_issue_tr(TrSlot &dst, uint32_t addr_lo, uint32_t addr_hi)
+{
+    lds_issue_tr_half<OFF>(dst.lo, addr_lo);
+    lds_issue_tr_half<OFF>(dst.hi, addr_hi);
 }
 
 // the two halves from one address register: rows +0 and +16 of a 32-row chunk (16x16x32 kernels)
@@ -427,6 +445,16 @@ __device__ __forceinline__ void lds_pipeline_body(Slot (&ring)[DEPTH + 1], Issue
 __device__ __forceinline__ void wait_fills() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 template <int N>
 __device__ __forceinline__ void wait_fills_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// Forward: a lane's 32 exponentials of a tile may sum to this much before the running maximum is brought up to
+// date: 2^40 per tile leaves the row sum over 2^20 keys and the output accumulators far inside fp32.
+constexpr float kRescaleAbove = 1099511627776.f;
+
+// The running maximum of a wave that has met keys, never below the lowest finite value: a row may see nothing but scores of
+// -inf in a wave's tile (masked keys), and -inf - -inf is NaN.  Times c it stays above -2^31, where the rounding of the
+// product moves an exponent by up to 2^6, which fp32 holds; scores further down weigh zero against any key that is not masked.
+__device__ __forceinline__ float finite_max(float m, float tile_max) { return fmaxf(fmaxf(m, tile_max), -3.402823466e38f); }
+__device__ __forceinline__ float scaled_max(float m, float c) { return fmaxf(m * c, -2147483648.f); }
 
 // v_permlane32_swap exchanges lanes 32..63 of its first operand with lanes 0..31 of its second:
 // fed two copies of x it leaves {x.lo, x.lo} and {x.hi, x.hi}.  The two results are copied to

@@ -91,6 +91,7 @@ hipError_t launch_attn_bwd_f32(const AttnArgs &a, hipStream_t st);
 
 // bf16 path (bf16 MFMA contractions, fp32 accumulation and softmax), d = 128
 hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st);
+hipError_t launch_attn_fwd_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st);      // 256-row workgroups
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st);
 
 // D_i = sum_c dO_ic * O_ic for either dtype (is_bf16 selects the element type)
