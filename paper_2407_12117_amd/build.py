@@ -21,6 +21,7 @@ SOURCES = {
     "attn_bf16.hip": [],
     "attn_fwd_long_bf16.hip": [],
     "attn_bwd_bf16.hip": [],
+    "attn_bwd_long_bf16.hip": [],
     "attn_bwd_static.hip": [],
     "recompute_bf16.hip": [],
 }

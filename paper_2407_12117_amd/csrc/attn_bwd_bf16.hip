@@ -274,6 +274,8 @@ __global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArg
 }
 
 // ============================================================================ backward: dK, dV
+// Launches of dK and dV alone take 256 keys in four waves (attn_bwd_long_bf16.hip); this is for joint ones, which share their workgroups'
+// shape with dQ.
 // Workgroup (KG = 8): 8 waves, 256 key rows whose K and V stay in LDS for the workgroup's lifetime (128 KB);
 // queries streamed in tiles of 32 through a double-buffered ring (Q and dO rows, 16 KB per stage,
 // one barrier per tile): LDS is full to the byte (160 KB).  The bytes streamed per (query, key) pair
@@ -323,8 +325,7 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = wave % KG, grp = wave / KG;        // key block, query group
     const int64_t nkt = (a.S + kBwdBk - 1) / kBwdBk;
-    const PairId t = find(nkt);                       // key tile p (long) and key tile nkt-1-p (short)
-    if (t.first < 0) return;
+    const PairId t = find(nkt);                       // one key tile
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
     const __bf16 *g = static_cast<const __bf16 *>(a.d_o) + base;
@@ -339,19 +340,13 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
     LDS_AS unsigned char *ring_base = lds + grp * Shape::kGroup;
     const LdsAddr16 ad = make_lds_addr16(ring_base, lane);
 
-    // The long tile walks the query tiles downwards from the last one to its diagonal, the short tile
-    // upwards from its diagonal to the last one (the sums take the query tiles in any order): the
-    // workgroups of a chunk, which share an XCD and its L2, then read the same Q/dO rows at about the
-    // same time in both sweeps (launch_plan.h, folded order).
-    for (int pass = 0; pass < 2; ++pass) {
-    const int64_t tile = pass == 0 ? t.first : t.second;
-    if (tile < 0) break;
-    const int dir = pass == 0 ? -1 : 1;
-    const int64_t col0 = tile * kBwdBk, j0w = col0 + 32 * wk;
+    // The tile walks the query tiles downwards from the last one to its diagonal: the workgroups of an XCD then read the same
+    // Q/dO rows at about the same time.
+    const int dir = -1;
+    const int64_t col0 = t.first * kBwdBk, j0w = col0 + 32 * wk;
     const int it0 = (int)(col0 / kBq);                // the tile's first query tile (its diagonal)
     // the sweep's query tiles it_first, it_first + dir, ...: query group grp takes the positions grp, grp + QS, ...
-    const int it_first = dir > 0 ? it0 : nit - 1, npos = nit - it0, nsteps = (npos + QS - 1) / QS;
-    if (pass) __syncthreads();    // every wave has left the first tile's K, V and ring
+    const int it_first = nit - 1, npos = nit - it0, nsteps = (npos + QS - 1) / QS;
     {   // resident K and V rows (rows past S repeat row S-1, never stored): 32-row pieces, 8 waves x 4 rows
         const __bf16 *kp = static_cast<const __bf16 *>(a.k) + base;
         const __bf16 *vp = static_cast<const __bf16 *>(a.v) + base;
@@ -562,13 +557,6 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
         combine(accV, dv, 1.f);
         combine(accK, dk, a.scale);
     }
-    }   // pass
-}
-
-__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a, int order)
-{
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[DkdvShape<8>::kLds];
-    dkdv_rows<8>(a, (LDS_AS unsigned char *)smem, [&](int64_t nkt) { return decode_block(a, blockIdx.x, nkt, order, false); });
 }
 
 // both gradients in one launch (joint_slot)
@@ -960,7 +948,7 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
         return launch_fewer_heads(a, sizeof(__bf16), most, kMaxBlocks, [&](const AttnArgs &part) { return launch_main(part, dkdv, dq, st); });
     hipError_t e = hipSuccess;
     if (!joint) {
-        if (dkdv) e = launch_blocks(attn_bwd_dkdv_bf16_kernel, nk, st, a, p.k_order);
+        if (dkdv) e = launch_attn_bwd_dkdv_bf16_long(a, p.k_order, nk, st);
         if (dq && e == hipSuccess) e = launch_blocks(attn_bwd_dq_bf16_kernel, nq, st, a, p.q_order);
         return e;
     }
