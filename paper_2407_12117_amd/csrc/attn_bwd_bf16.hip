@@ -50,6 +50,7 @@ __device__ __forceinline__ f32x4 sum_pieces(const LDS_AS f32x4 *pieces, int m, i
 }
 
 // ============================================================================ backward: dQ
+// Launches of dQ alone take 256 rows in four waves (attn_bwd_long_bf16.hip); this is for joint launches.
 // Workgroup: 8 waves, 32 query rows per wave (two blocks of 16); keys/values streamed in tiles
 // of 64 through a double-buffered LDS ring filled asynchronously (one barrier per tile).
 //   S^T = K Q^T, dP^T = V dO^T - D   (A = K / V rows from LDS, B = Q^T / dO^T from registers)
@@ -81,8 +82,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wq = wave % QG, grp = wave / QG;        // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const PairId t = find(nqt);
-    if (t.first < 0) return;
+    const PairId t = find(nqt);                       // one query tile
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
@@ -92,16 +92,10 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
     const LdsAddr16 ad = make_lds_addr16(lds + grp * kGroup, lane);
     const float c = a.scale * kLog2e;
 
-    // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
-    for (int pass = 0; pass < (QG == 8 ? 2 : 1); ++pass) {
-    const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
-    if (tile < 0) break;
-    const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq;
+    const int64_t row0 = t.first * kBq, i0w = row0 + 32 * wq;
     const int64_t last_row = min(row0 + kBq, a.S) - 1;
     const int ntiles = (int)(last_row / kBk) + 1, nsteps = (ntiles + KS - 1) / KS;
-    // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
-    const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
-    if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
+    // step n of a key group works tile KS * n + grp
     // K and V rows have the same strides: one set of per-lane offsets serves both fills
     const TileOffsets<QG, T> toff = make_tile_offsets<QG, SwzB, T>(a.ss, wq, lane);
     auto fill = [&](int off, int jt) {
@@ -123,7 +117,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
             qoff.fill(staged(2 * blk + 1), g, a.ss, row0 + 32 * blk, a.S, wave);
         }
     }
-    if (jfirst < ntiles) fill(0, jfirst);
+    if (grp < ntiles) fill(0, grp);
 
     // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
     bf16x8 qB[2][4], gB[2][4];
@@ -173,8 +167,8 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
         constexpr int nOff = (BUF ^ 1) * kStage;
         wait_fills();
         __syncthreads();          // tile jt is complete; nobody still reads the other buffer
-        const int jn = jt + jstep;
-        if (jn >= 0 && jn < ntiles) fill(nOff, jn);
+        const int jn = jt + KS;
+        if (jn < ntiles) fill(nOff, jn);
         if (jt >= wave_first_tile_masked) return;
         const bool diag = jt >= wave_first_diag;
         static_for<0, T / 32>([&](auto hc) {
@@ -237,8 +231,8 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
         });
     };
     for (int n = 0; n < nsteps; n += 2) {
-        tile_step(IntC<0>{}, jfirst + jstep * n);
-        if (n + 1 < nsteps) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
+        tile_step(IntC<0>{}, grp + KS * n);
+        if (n + 1 < nsteps) tile_step(IntC<1>{}, grp + KS * (n + 1));
     }
     __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + (i0w + l16) * a.ss + 4 * g4;
     if constexpr (KS == 1) {
@@ -264,13 +258,6 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
             if (i0w + 16 * qt + l16 < a.S) store4(dq + 16 * qt * a.ss + 16 * dt, sum, a.scale);
         }
     }
-    }   // pass
-}
-
-__global__ __launch_bounds__(64 * kDqWaves) void attn_bwd_dq_bf16_kernel(AttnArgs a, int order)
-{
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<8, 64>::kLds];
-    dq_rows<8, 64>(a, (LDS_AS unsigned char *)smem, [&](int64_t nqt) { return decode_block(a, blockIdx.x, nqt, order, true); });
 }
 
 // ============================================================================ backward: dK, dV
@@ -949,7 +936,7 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
     hipError_t e = hipSuccess;
     if (!joint) {
         if (dkdv) e = launch_attn_bwd_dkdv_bf16_long(a, p.k_order, nk, st);
-        if (dq && e == hipSuccess) e = launch_blocks(attn_bwd_dq_bf16_kernel, nq, st, a, p.q_order);
+        if (dq && e == hipSuccess) e = launch_attn_bwd_dq_bf16_long(a, p.q_order, nq, st);
         return e;
     }
     if (dkdv && dq && !p.joint) {

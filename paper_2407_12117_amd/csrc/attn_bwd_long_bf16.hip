@@ -1,7 +1,7 @@
-// bf16 causal attention backward for gfx950 (CDNA4), head dim 128: dK and dV by workgroups of 256 keys, one per compute unit, for long
-// sequences (shorter ones, what is computed and the operand conventions: attn_bwd_bf16.hip).
+// bf16 causal attention backward for gfx950 (CDNA4), head dim 128: dK and dV by workgroups of 256 keys, dQ by workgroups of 256 rows, one
+// per compute unit, for long sequences (shorter ones, what is computed and the operand conventions: attn_bwd_bf16.hip).
 //
-// Four waves, one per SIMD, each with 64 key rows: all 256 accumulation registers hold its dV^T and dK^T, and a Q or dO operand read from
+// dK, dV.  Four waves, one per SIMD, each with 64 key rows: all 256 accumulation registers hold its dV^T and dK^T, and a Q or dO operand read from
 // LDS serves four key blocks of 16.  K and V of the 256 keys stay in LDS (128 KB), Q and dO come in tiles of 32 queries through
 // two places (32 KB).  A wave works a tile as 32 items of four MFMAs, in one stream that is ordered by hand, every MFMA first and its
 // share of the vector instructions behind it (as in attn_fwd_long_bf16.hip):
@@ -401,11 +401,295 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
     }   // pass
 }
 
+// ============================================================================ dQ
+// Four waves, one per SIMD, each with 64 query rows: accumulation registers hold its dQ^T, Q and dO (all 256 of them), and an operand of K,
+// V or K^T read from LDS serves four query blocks of 16.  K and V come in tiles of 64 keys through rings of three, with the barrier of a
+// step between its two blocks of 32 keys (as in attn_fwd_long_bf16.hip).  A block is worked as 24 items of four MFMAs, one operand each:
+//   items  0..7   S^T = K Q^T           keys 0..15, then 16..31
+//   items  8..15  dP^T = V dO^T - D     P = exp2(scale log2e S - LSE) behind the MFMAs of items 4..15
+//   items 16..23  dQ^T += K^T dS^T      of the block before; dS = P dP of this one behind them
+// Same bits as eight waves of 32 rows (attn_bwd_bf16.hip).  S = 128K, H = 4, same card in turn: 18.69 -> 17.5 to 18.05 ms (1411 -> 1462 to
+// 1508 TFLOP/s; all-zero inputs 1710 -> 1812).
+constexpr int kDqKeys = 64, kDqTile = kDqKeys * 256, kDqRing = 3 * kDqTile;
+
+template <int N>
+__device__ __forceinline__ void mfma_zero_a(f32x4 &d, const bf16x8 &x, const bf16x8 &y)                     // D = A B, B in accumulation registers
+{
+    if constexpr (N >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(x), "a"(y), "n"(N));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(x), "a"(y));
+}
+template <int N>
+__device__ __forceinline__ void mfma_from_a(f32x4 &d, const bf16x8 &x, const bf16x8 &y, const f32x4 &c)     // D = A B + C
+{
+    if constexpr (N >= 0) asm volatile("s_waitcnt lgkmcnt(%4)\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(x), "a"(y), "v"(c), "n"(N));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(x), "a"(y), "v"(c));
+}
+template <int N>
+__device__ __forceinline__ void mfma_on_a(f32x4 &d, const bf16x8 &x, const bf16x8 &y)                       // D = A B + D
+{
+    if constexpr (N >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(x), "a"(y), "n"(N));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(x), "a"(y));
+}
+__global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dq_bf16_long_kernel(AttnArgs a, int order)
+{
+    constexpr int kRows = 64 * kLongWaves;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kDqRing];    // K tile t at t % 3, V tile t behind them likewise
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t nqt = (a.S + kRows - 1) / kRows;
+    const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
+    if (t.first < 0) return;
+    const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
+    const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
+    const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
+    const __bf16 *v = static_cast<const __bf16 *>(a.v) + base;
+    const __bf16 *g = static_cast<const __bf16 *>(a.d_o) + base;
+    const int64_t stat = ((int64_t)t.b * a.H + t.h) * a.S;
+    const float c = a.scale * kLog2e;
+    using Fills = TileOffsets<kLongWaves, kDqKeys>;
+    const Fills toff = make_tile_offsets<kLongWaves, SwzB, kDqKeys>(a.ss, wave, lane);
+    static_assert(Fills::kInstr == 4, "fill_part deals out eight");
+    const LdsAddr16 ad = make_lds_addr16(lds, lane);
+
+    // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
+#pragma clang loop unroll(disable)
+    for (int pass = 0; pass < 2; ++pass) {
+        const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
+        if (tile < 0) break;
+        const int64_t row0 = tile * kRows, i0w = row0 + 64 * wave;
+        const int64_t last_row = min(row0 + kRows, a.S) - 1;
+        const int ntiles = (int)(last_row / kDqKeys) + 1;
+        // Tiles by their place in the sweep: this wave works [ua, ub], of which um holds its diagonal; one that has no rows works none.
+        const int diagonal = (int)(i0w / kDqKeys);
+        const bool live = i0w < a.S;
+        const int ua = !live ? ntiles : pass ? ntiles - 1 - diagonal : 0, ub = pass ? ntiles - 1 : diagonal, um = pass ? ua : ub;
+        if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffers
+
+        // Tile u of the sweep as two buffers, from pointers that move on a tile at a time; behind the last one they are empty.
+        const int64_t tile_bytes = (pass ? -1 : 1) * (int64_t)kDqKeys * a.ss * 2;
+        const int64_t first_key = pass ? (int64_t)(ntiles - 1) * kDqKeys : 0;
+        uint32_t full_bytes = (uint32_t)(kDqKeys - 1) * (uint32_t)a.ss * 2 + 256;
+        uint32_t last_bytes = (uint32_t)(min(a.S - (int64_t)(ntiles - 1) * kDqKeys, (int64_t)kDqKeys) - 1) * (uint32_t)a.ss * 2 + 256;
+        asm volatile("" : "+s"(full_bytes), "+s"(last_bytes));      // selected without branches
+        const int u_last = pass ? 0 : ntiles - 1;
+        const char *kp = reinterpret_cast<const char *>(k + first_key * a.ss), *vp = reinterpret_cast<const char *>(v + first_key * a.ss);
+        __amdgpu_buffer_rsrc_t kb, vb;
+        int to = -kDqTile;                         // the place of the tile that is filled
+        auto prepare = [&](int u) __attribute__((always_inline)) {
+            uint32_t bytes = u < ntiles ? full_bytes : 0;
+            bytes = u == u_last ? last_bytes : bytes;
+            kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kp), 0, bytes, 0x00020000);
+            vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(vp), 0, bytes, 0x00020000);
+            kp += tile_bytes;
+            vp += tile_bytes;
+            to = to == 2 * kDqTile ? 0 : to + kDqTile;
+        };
+        auto fill_part = [&](auto nc) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            toff.part(lds + to + n / Fills::kInstr * kDqRing, n / Fills::kInstr ? vb : kb, n % Fills::kInstr, wave);
+        };
+        prepare(0);
+        static_for<0, 8>(fill_part);
+        prepare(1);
+        static_for<0, 8>(fill_part);
+
+        // Q^T and dO^T as B operands: lane = query 16*qt + l16, 8 head-dim values per 32-wide k step
+        bf16x8 qB[4][4], gB[4][4];
+        float lse2[4];
+        f32x4 neg_d[4];               // -D_i in all four registers: dP^T starts from it
+#pragma unroll
+        for (int qt = 0; qt < 4; ++qt) {
+            const int64_t i = i0w + 16 * qt + l16, iq = i < a.S ? i : a.S - 1;      // rows past S are computed and never stored
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                qB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq * a.ss + 32 * kk + 8 * g4));
+                gB[qt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(g + iq * a.ss + 32 * kk + 8 * g4));
+            }
+            lse2[qt] = a.lse[stat + iq] * kLog2e;
+            const float nd = -a.delta[stat + iq];
+            neg_d[qt] = f32x4{nd, nd, nd, nd};
+        }
+        f32x4 accQ[8][4];             // dQ^T: [head-dim block of 16][query block]; lane = query, rows = head dim
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+            for (int qt = 0; qt < 4; ++qt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accQ[dt][qt][r] = 0.f;
+        uint32_t row[4], tr[8];       // LDS addresses in the K tile of the step; the V tile's are kDqRing further
+        int at = ua % 3 * kDqTile, way = 0;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) row[kk] = ad.row16[kk] + at;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) tr[dt] = ad.tr16[dt] + at;
+
+        f32x4 s[2][4], dp[2][4];      // [key block of 16][query block]
+        u32x4 dsB[2][4];              // [parity of the key block of 32][query block]
+        bf16x8 ka[4];
+        TrSlot kt[4];
+#pragma unroll
+        for (int qt = 0; qt < 4; ++qt) dsB[0][qt] = dsB[1][qt] = u32x4{0, 0, 0, 0};
+
+        // In the middle of step u: tile u + 1 is complete, and nobody reads tile u - 1 any more, whose place tile u + 2 takes from here on.
+        auto meet = [&](int u) __attribute__((always_inline)) {
+            wait_fills();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            prepare(u + 2);
+        };
+        auto idle = [&](int u) __attribute__((always_inline)) {        // a step in which this wave has no keys
+            meet(u);
+            static_for<0, 8>(fill_part);
+        };
+        // block X of a step (OUT: with dQ of the block before it); the reads of an item are queued three items ahead, from 24 on the next block's
+        constexpr int kAhead = 3;
+        auto block = [&](auto xc, auto outc, bool masked) __attribute__((always_inline)) {
+            constexpr int X = decltype(xc)::value, Y = X ^ 1;
+            constexpr bool OUT = decltype(outc)::value;
+            constexpr auto reads_of = [](int n) constexpr { return n >= 16 && n < 24 ? 2 : 1; };
+            auto read = [&](auto nc, auto pc) __attribute__((always_inline)) {
+                constexpr int n = decltype(nc)::value, P = decltype(pc)::value;
+                if constexpr (P >= reads_of(n)) {
+                } else if constexpr (n >= 16 && n < 24) {
+                    constexpr int off = (X == 0 ? 8192 : 0) + P * 4096;           // block 0 adds up block 1 of the tile before
+                    lds_issue_tr_half<off>(P ? kt[n % 4].hi : kt[n % 4].lo, tr[n % 8]);
+                    if constexpr (X == 0 && P == 1) tr[n % 8] += way;
+                } else {
+                    constexpr int XX = n < 24 ? X : Y, m = n % 24, isv = m / 8, kb16 = m % 8 / 4, kk = m % 4;
+                    lds_issue_b128<isv * kDqRing + XX * 8192 + kb16 * 4096>(ka[n % 4], row[kk]);
+                    if constexpr (X == 1 && n < 24 && isv && kb16) row[kk] += way;
+                }
+            };
+            // the element-wise chains: el = 16 (key block) + 4 qt + r
+            float x[2], ds[4];
+            auto exp_position = [&](auto ic) __attribute__((always_inline)) {      // P: fma of el i, exponential of i - 1
+                constexpr int i = decltype(ic)::value;
+                if constexpr (i >= 1) {
+                    constexpr int el = i - 1;
+                    s[el / 16][el / 4 % 4][el % 4] = __builtin_amdgcn_exp2f(x[el % 2]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (i < 32) x[i % 2] = fmaf(s[i / 16][i / 4 % 4][i % 4], c, -lse2[i / 4 % 4]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto ds_position = [&](auto ic) __attribute__((always_inline)) {       // dS: product of el i, rounding of i - 1
+                constexpr int i = decltype(ic)::value;
+                if constexpr (i >= 2 && i % 2 == 0) {
+                    constexpr int el = i - 1;
+                    const f32x2 two = {ds[(el - 1) % 4], ds[el % 4]};
+                    dsB[X][el / 4 % 4][el / 16 * 2 + el % 4 / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
+                    asm volatile("" : "+v"(dsB[X][el / 4 % 4][el / 16 * 2 + el % 4 / 2]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (i < 32) ds[i % 4] = s[i / 16][i / 4 % 4][i % 4] * dp[i / 16][i / 4 % 4][i % 4];
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            constexpr int kExpFrom = 16, kExpSpan = 46, kDsFrom = 64, kDsSpan = 30;      // in MFMAs of the block
+            auto item = [&](auto nc) __attribute__((always_inline)) {
+                constexpr int n = decltype(nc)::value;
+                constexpr auto behind = [](int i) constexpr { return !OUT && i >= 16 ? i + 8 : i; };       // without dQ the next block follows
+                constexpr int later = reads_of(behind(n + 1)) + reads_of(behind(n + 2)), ahead = behind(n + kAhead);
+                static_for<0, 4>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value, m = 4 * n + j, W = j == 0 ? later : kHere, kk = n % 4, kb16 = n % 8 / 4;
+                    if constexpr (n < 8) {
+                        if constexpr (kk == 0) mfma_zero_a<W>(s[kb16][j], ka[n % 4], qB[j][kk]);
+                        else mfma_on_a<W>(s[kb16][j], ka[n % 4], qB[j][kk]);
+                    } else if constexpr (n < 16) {
+                        if constexpr (kk == 0) mfma_from_a<W>(dp[kb16][j], ka[n % 4], gB[j][kk], neg_d[j]);
+                        else mfma_on_a<W>(dp[kb16][j], ka[n % 4], gB[j][kk]);
+                    } else {
+                        mfma_acc<W>(accQ[n % 8][j], tr_operand(kt[n % 4]), dsB[Y][j]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (j % 2 == 0) read(IntC<ahead>{}, IntC<j / 2>{});
+                    constexpr auto upto = [](int i, int span, int all) constexpr { return i <= 0 ? 0 : i >= span ? all : (i * all + span - 1) / span; };
+                    static_for<upto(m - kExpFrom, kExpSpan, 33), upto(m + 1 - kExpFrom, kExpSpan, 33)>(exp_position);
+                    if constexpr (OUT) static_for<upto(m - kDsFrom, kDsSpan, 33), upto(m + 1 - kDsFrom, kDsSpan, 33)>(ds_position);
+                    if constexpr (X == 1 && n < 8 && j == 3) fill_part(nc);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            auto mask = [&](auto hc) __attribute__((always_inline)) {              // keys beyond the query, in the diagonal tile
+                constexpr int H = decltype(hc)::value;
+                asm volatile("s_nop 15" : "+v"(s[H][0]), "+v"(s[H][1]), "+v"(s[H][2]), "+v"(s[H][3]));
+                int thr = l16 - 4 * g4;
+                asm volatile("" : "+v"(thr));
+#pragma unroll
+                for (int qt = 0; qt < 4; ++qt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (r > thr + 16 * qt - (32 * X + 16 * H)) s[H][qt][r] = -INFINITY;
+            };
+            if constexpr (!OUT) static_for<0, kAhead>([&](auto n) { read(n, IntC<0>{}); });
+            static_for<0, 4>(item);
+            if (masked) mask(IntC<0>{});
+            static_for<4, 8>(item);
+            if (masked) mask(IntC<1>{});
+            static_for<8, 16>(item);
+            if constexpr (OUT) {
+                static_for<16, 24>(item);
+            } else {
+                settle(dp);
+                static_for<0, 33>(ds_position);
+            }
+        };
+        using Yes = IntC<1>;
+        using No = IntC<0>;
+        wait_fills();
+        __syncthreads();
+        int u = 0;
+#pragma clang loop unroll(disable)
+        for (; u < ua; ++u) idle(u);
+        if (live) {
+            block(IntC<0>{}, No{}, u == um);
+            // the second half of step u; after the loop once more: with one copy and an exit in mid-loop the compiler spills Q
+            auto second = [&]() __attribute__((always_inline)) {
+                way = at == 2 * kDqTile ? -2 * kDqTile : kDqTile;
+                at += way;
+                meet(u);
+                block(IntC<1>{}, Yes{}, u == um);
+            };
+#pragma clang loop unroll(disable)
+            while (u < ub) {
+                second();
+                ++u;
+                block(IntC<0>{}, Yes{}, u == um);
+            }
+            second();
+            static_for<0, 8>([&](auto n) {        // dQ of the last block
+                constexpr int dt = decltype(n)::value;
+                lds_issue_tr_pair<8192>(kt[dt % 4], tr[dt]);
+                static_for<0, 4>([&](auto jc) { mfma_acc<decltype(jc)::value ? kHere : 0>(accQ[dt][decltype(jc)::value], tr_operand(kt[dt % 4]), dsB[1][decltype(jc)::value]); });
+            });
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) asm volatile("s_nop 15" : "+a"(accQ[dt][0]), "+a"(accQ[dt][1]), "+a"(accQ[dt][2]), "+a"(accQ[dt][3]));
+            ++u;
+        }
+#pragma clang loop unroll(disable)
+        for (; u < ntiles; ++u) idle(u);
+        wait_fills();
+
+        __bf16 *dq = static_cast<__bf16 *>(a.dq) + base + (i0w + l16) * a.ss + 4 * g4;
+#pragma unroll
+        for (int qt = 0; qt < 4; ++qt)
+            if (i0w + 16 * qt + l16 < a.S) {
+#pragma unroll
+                for (int dt = 0; dt < 8; ++dt) store4(dq + 16 * qt * a.ss + 16 * dt, accQ[dt][qt], a.scale);
+            }
+    }   // pass
+}
+
 }  // namespace
 
 hipError_t launch_attn_bwd_dkdv_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st)
 {
     return launch_blocks<64 * kLongWaves>(attn_bwd_dkdv_bf16_long_kernel, blocks, st, a, order);
+}
+
+hipError_t launch_attn_bwd_dq_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st)
+{
+    return launch_blocks<64 * kLongWaves>(attn_bwd_dq_bf16_long_kernel, blocks, st, a, order);
 }
 
 }  // namespace memo
