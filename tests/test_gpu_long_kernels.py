@@ -1,0 +1,106 @@
+"""The four-wave kernels of 256-row workgroups (csrc/attn_fwd_long_bf16.hip, csrc/attn_bwd_long_bf16.hip) where they can go wrong: waves without
+rows, of one row and of 63, one tile and several, both sweeps of a pair; a running maximum that is brought up to date in every tile, in
+either block of keys and either direction; infinities and NaN."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import shape_cases as shapes
+from gpu_util import LSE_MAX_ABS_BF16, assert_close, gpu_fwd_bwd, to_f64
+from paper_2407_12117_amd import binding as mb
+from paper_2407_12117_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SCALE = synth.default_scale(128)
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    from oracle import memo_oracle
+    memo_oracle.build()
+    return memo_oracle
+
+
+def _inputs(S, heads, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return [torch.randn((1, S, heads, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4)]
+
+
+def _check_forward(oracle, q, k, v, o, lse, heads):
+    for h in heads:
+        ro, rlse = oracle.attn_fwd(*(to_f64(t[:, :, h:h + 1]) for t in (q, k, v)), SCALE)
+        assert_close("O", to_f64(o[:, :, h:h + 1]), ro, "bf16")
+        # the bar of unit-scale scores, and fp32's share of larger ones (their products and sums are rounded at 2^-24 of their size)
+        bar = LSE_MAX_ABS_BF16 + 4e-6 * np.abs(rlse).max()
+        assert np.abs(to_f64(lse[:, h:h + 1]) - rlse).max() <= bar
+
+
+@pytest.mark.parametrize("S,heads", list(shapes.FWD_LONG_EDGES))
+def test_forward_edges(oracle, S, heads):
+    print(f"[case] long forward S={S} H={heads}", flush=True)
+    q, k, v, _ = _inputs(S, heads, S)
+    o, lse = mb.memo_attn_fwd(q, k, v, SCALE)
+    _check_forward(oracle, q, k, v, o, lse, (0, heads // 2, heads - 1))
+
+
+@pytest.mark.parametrize("S,heads", list(shapes.BWD_LONG_EDGES))
+def test_backward_edges(oracle, S, heads):
+    print(f"[case] long backward S={S} H={heads}", flush=True)
+    q, k, v, g = _inputs(S, heads, S)
+    got = gpu_fwd_bwd(q, k, v, g, SCALE)
+    for h in (0, heads - 1):
+        refs = oracle.attn_bwd(*(to_f64(t[:, :, h:h + 1]) for t in (q, k, v, g)), SCALE)
+        for name, x, r in zip(("dQ", "dK", "dV"), got[2:], refs):
+            assert_close(name, to_f64(x[:, :, h:h + 1]), r, "bf16", scaled=True)
+
+
+@pytest.mark.parametrize("log2_per_tile", [12.0, 500.0, -500.0])
+@pytest.mark.parametrize("S,heads", [(1025, 80), (1024, 160)])
+def test_forward_with_scores_climbing_along_the_keys(oracle, S, heads, log2_per_tile):
+    # every score moves with the key index by so many binary orders of magnitude per 64 keys (the first channel alone carries it)
+    print(f"[case] long forward climbing {log2_per_tile} S={S} H={heads}", flush=True)
+    q, k, v, _ = _inputs(S, heads, 5)
+    slope = log2_per_tile / 64.0 / (SCALE * math.log2(math.e))
+    q[..., 0] = 1.0
+    k[..., 0] = (slope * torch.arange(S, device="cuda", dtype=torch.float32))[None, :, None].to(torch.bfloat16)
+    o, lse = mb.memo_attn_fwd(q, k, v, SCALE)
+    _check_forward(oracle, q, k, v, o, lse, (0, heads - 1))
+
+
+def test_rows_that_depend_on_what_is_not_finite():
+    # what a key's rows reach: O and dQ of its queries and later ones, nothing before its 64-key tile
+    S, heads, h, j = 3905, 128, 3, 2000
+    print(f"[case] long kernels, NaN S={S} H={heads}", flush=True)
+    q, k, v, g = _inputs(S, heads, 9)
+    clean = gpu_fwd_bwd(q, k, v, g, SCALE)
+    v[0, j, h, 5] = math.nan
+    got = gpu_fwd_bwd(q, k, v, g, SCALE)
+    first = j // 64 * 64
+    assert torch.isnan(got[0][0, j:, h, 5]).all() and torch.isnan(got[2][0, j:, h]).all() and torch.isnan(got[3][0, j, h]).all()
+    for x, y in zip(clean, got):
+        other = torch.arange(heads, device="cuda") != h
+        rows = (0, slice(None), other) if x.dim() == 4 else (0, other)
+        assert torch.equal(x[rows], y[rows])
+    assert torch.equal(clean[0][0, :first, h], got[0][0, :first, h]) and torch.equal(clean[2][0, :first, h], got[2][0, :first, h])
+
+
+def test_masked_scores_of_minus_infinity(oracle):
+    # keys whose scores are all -inf weigh nothing, also where they are a wave's first tile
+    S, heads = 1025, 80
+    print(f"[case] long forward, -inf S={S} H={heads}", flush=True)
+    q, k, v, _ = _inputs(S, heads, 11)
+    q[..., 0] = q[..., 0].abs() + 0.5
+    hidden = torch.zeros(S, dtype=torch.bool, device="cuda")
+    hidden[1:200] = True
+    hidden[640:768] = True
+    k[0, hidden, :, 0] = -math.inf
+    o, lse = mb.memo_attn_fwd(q, k, v, SCALE)
+    kf = k.clone()
+    kf[0, hidden, :, 0] = -1e30
+    for h in (0, heads - 1):
+        ro, rlse = oracle.attn_fwd(*(to_f64(t[:, :, h:h + 1]) for t in (q, kf, v)), SCALE)
+        assert_close("O", to_f64(o[:, :, h:h + 1]), ro, "bf16")
+        assert np.abs(to_f64(lse[:, h:h + 1]) - rlse).max() <= LSE_MAX_ABS_BF16

@@ -116,3 +116,11 @@ def test_gpu_tests_get_the_shapes_they_are_written_for(plans):
     # every shape that there is has its case
     assert {rows for rows, _ in shapes.FWD_SHAPES.values()} == {32, 64, 128, 256}
     assert set(shapes.LINEAR_SHAPES.values()) == {(64, 64), (128, 64), (128, 128), (192, 128), (256, 128), (256, 256)}
+
+
+def test_the_edges_of_the_long_kernels_get_them(plans):
+    for (S, heads), order in shapes.FWD_LONG_EDGES.items():
+        assert plans([("fwd", S, heads)]) == [(256, order)]
+    for (S, heads), orders in shapes.BWD_LONG_EDGES.items():
+        assert plans([("bwd", S, heads)]) == [(256, 0) + orders]
+    assert plans([("fwd", 3905, 128)])[0][0] == 256
