@@ -966,7 +966,7 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 // of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch
 // fills the chip where neither kernel does alone (S = 2000, 6 heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups,
 // 207 as two launches of 256-row pairs) and lets the dQ tiles run in the tail of the dK/dV ones (S = 16461, H = 4:
-// 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us); two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 27.8 + 18.8 against 47.3 ms).
+// 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us); two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 25.0 + 17.8 against 47.3 ms).
 // A joint launch goes out in two parts, with the same bits, where dQ takes the place of Q or dO, which all key-stationary
 // workgroups read, and where an event between the stages is asked for.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)

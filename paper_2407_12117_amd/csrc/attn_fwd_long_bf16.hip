@@ -310,6 +310,13 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
                             for (int e = 3; e < 15; e += 2) mb = fmaxf(fmaxf(mb, se[b][e]), se[b][e + 1]);
                             mb = fmaxf(mb, se[b][15]);
+                            if constexpr (FIRST) {    // the maximum of a sweep's first tile, not of its first block alone: P of the largest score is 1, without rounding
+#pragma unroll
+                                for (int e = 0; e < 16; ++e) {
+                                    if (u == um && 8 * (e >> 2) + (e & 3) > l32 - 4 * half + 32 * (b - 1)) s[X][b][e] = -INFINITY;
+                                    mb = fmaxf(mb, s[X][b][e]);
+                                }
+                            }
                             const float m_new = finite_max(m[b], max_across_halves(mb));
                             const float corr = __builtin_amdgcn_exp2f((m[b] - m_new) * c);
                             m[b] = m_new;
