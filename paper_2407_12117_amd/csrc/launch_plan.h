@@ -172,8 +172,12 @@ constexpr int tile_order(int rows, int order) { return rows == 256 ? order : kLo
 // (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst; over 36 sizes of 2048 to
 // 400000 rows and 2 to 256 heads 0.3 % and, at S = 40000 with 5 heads (128 rows for 256), 4.6 %.  The worst are sizes
 // of less than a round of workgroups and a few heads (S = 3000, 16 heads: 64 rows for 128, 19 %).
+// The costs of 256 rows were then lowered for the four-wave kernel, which takes 106 and 108, only as far as the estimate of 128 rows
+// (up to 13 % too high in launches of little more than a round) allows: us, 128 rows : 256, S = 20000 H = 10 995 : 864,
+// 40000 H = 4 1486 : 1374, 40000 H = 5 2030 : 1700, 50000 H = 4 2280 : 2095, 90000 H = 2 3845 : 3440 now go to 256, 6000 H = 16 158 : 175,
+// 12000 H = 8 292 : 325, 25000 H = 4 611 : 656, 50000 H = 2 1214 : 1286 stay.
 inline constexpr TileChoice kFwdChoices[] = {
-    {256, kFolded, 115.5, 4.0}, {256, kLongestFirst, 117.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
+    {256, kFolded, 113.0, 4.0}, {256, kLongestFirst, 114.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
     {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
 };
 
