@@ -32,9 +32,9 @@ GIB = float(1 << 30)
 TRAFFIC_SOURCE = ("carried from profiles/attn_c5_counters.md (two rocprofv3 --pmc runs of this command), not read "
                   "in this run; it varies by tens of per cent between runs with the timing of the workgroups (how long the 32 workgroups of an XCD stay in step)")
 MEASURED_HBM_TRAFFIC_BYTES = {
-    "C5": {"attn_fwd_bf16_kernel": (1210.9 + 1.02) * GIB,
-           "attn_bwd_dkdv_bf16_kernel": (1253.5 + 2.00) * GIB,
-           "attn_bwd_dq_bf16_kernel": (2136.5 + 1.00) * GIB},
+    "C5": {"attn_fwd_bf16_long_kernel": (130.0 + 1.02) * GIB,
+           "attn_bwd_dkdv_bf16_long_kernel": (1516.0 + 2.00) * GIB,
+           "attn_bwd_dq_bf16_long_kernel": (131.0 + 1.00) * GIB},
 }
 
 
@@ -181,9 +181,9 @@ def run_workload(torch, mb, synth, name, steps, warmup, overlap=True, cpu=True, 
     # contractions each kernel executes (2*d flops per visible (i,j) pair and contraction):
     # forward 2 (QK^T, PV); dK/dV kernel 4 (QK^T, dO V^T, P^T dO, dS^T Q); dQ kernel 3
     kernels = {
-        "attn_fwd_bf16_kernel": (fwd_ms, 2.0 * pairs * d * H * B),
-        "attn_bwd_dkdv_bf16_kernel": (dkdv_ms, 4.0 * pairs * d * H * B),
-        "attn_bwd_dq_bf16_kernel": (dq_ms, 3.0 * pairs * d * H * B),
+        "attn_fwd_bf16_long_kernel": (fwd_ms, 2.0 * pairs * d * H * B),
+        "attn_bwd_dkdv_bf16_long_kernel": (dkdv_ms, 4.0 * pairs * d * H * B),
+        "attn_bwd_dq_bf16_long_kernel": (dq_ms, 3.0 * pairs * d * H * B),
     }
     dom = max(kernels, key=lambda n: kernels[n][0])
     dom_ms, dom_flop = kernels[dom]
@@ -195,8 +195,8 @@ def run_workload(torch, mb, synth, name, steps, warmup, overlap=True, cpu=True, 
                 "traffic_source": TRAFFIC_SOURCE if MEASURED_HBM_TRAFFIC_BYTES.get(name, {}).get(dom) else None,
                 # tensors each kernel must read or write once: fwd Q,K,V,O; dK/dV Q,K,V,dO,dK,dV;
                 # dQ Q,K,V,dO,dQ (the [B,H,S] statistics are 1/64 of a tensor and left out)
-                "algorithmic_hbm_bytes": {"attn_fwd_bf16_kernel": 4, "attn_bwd_dkdv_bf16_kernel": 6,
-                                          "attn_bwd_dq_bf16_kernel": 5}[dom] * B * S * H * d * 2,
+                "algorithmic_hbm_bytes": {"attn_fwd_bf16_long_kernel": 4, "attn_bwd_dkdv_bf16_long_kernel": 6,
+                                          "attn_bwd_dq_bf16_long_kernel": 5}[dom] * B * S * H * d * 2,
                 "avg_launch_ms": dom_ms,
                 "all_kernels": {n: {"avg_ms": ms, "TFLOP/s": fl / (ms * 1e-3) / 1e12,
                                     "frac": fl / (ms * 1e-3) / 1e12 / BF16_MFMA_PEAK_TFLOPS}
