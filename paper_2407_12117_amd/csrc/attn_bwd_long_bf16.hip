@@ -542,12 +542,13 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
             meet(u);
             static_for<0, 8>(fill_part);
         };
-        // block X of a step (OUT: with dQ of the block before it); the reads of an item are queued three items ahead, from 24 on the next block's
+        // block X of a step (OUT: with dQ of the block before it; LAST: no block follows); the reads of an item are queued three items ahead,
+        // from 24 on the next block's
         constexpr int kAhead = 3;
-        auto block = [&](auto xc, auto outc, bool masked) __attribute__((always_inline)) {
+        auto block = [&](auto xc, auto outc, auto lastc, bool masked) __attribute__((always_inline)) {
             constexpr int X = decltype(xc)::value, Y = X ^ 1;
-            constexpr bool OUT = decltype(outc)::value;
-            constexpr auto reads_of = [](int n) constexpr { return n >= 16 && n < 24 ? 2 : 1; };
+            constexpr bool OUT = decltype(outc)::value, LAST = decltype(lastc)::value;
+            constexpr auto reads_of = [](int n) constexpr { return n >= 24 ? (LAST ? 0 : 1) : n >= 16 ? 2 : 1; };
             auto read = [&](auto nc, auto pc) __attribute__((always_inline)) {
                 constexpr int n = decltype(nc)::value, P = decltype(pc)::value;
                 if constexpr (P >= reads_of(n)) {
@@ -642,21 +643,21 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
 #pragma clang loop unroll(disable)
         for (; u < ua; ++u) idle(u);
         if (live) {
-            block(IntC<0>{}, No{}, u == um);
+            block(IntC<0>{}, No{}, No{}, u == um);
             // the second half of step u; after the loop once more: with one copy and an exit in mid-loop the compiler spills Q
-            auto second = [&]() __attribute__((always_inline)) {
+            auto second = [&](auto lastc) __attribute__((always_inline)) {
                 way = at == 2 * kDqTile ? -2 * kDqTile : kDqTile;
                 at += way;
                 meet(u);
-                block(IntC<1>{}, Yes{}, u == um);
+                block(IntC<1>{}, Yes{}, lastc, u == um);
             };
 #pragma clang loop unroll(disable)
             while (u < ub) {
-                second();
+                second(No{});
                 ++u;
-                block(IntC<0>{}, Yes{}, u == um);
+                block(IntC<0>{}, Yes{}, No{}, u == um);
             }
-            second();
+            second(Yes{});
             static_for<0, 8>([&](auto n) {        // dQ of the last block
                 constexpr int dt = decltype(n)::value;
                 lds_issue_tr_pair<8192>(kt[dt % 4], tr[dt]);

@@ -348,7 +348,8 @@ __device__ __forceinline__ void fill_tile_at(LDS_AS unsigned char *tile, const T
 // read issued before the last N has completed; N counts only reads issued through these helpers
 // after the wanted one, so any other LDS traffic in between can only make a wait longer, never
 // too short.  The wait names the registers it guards as in/out operands, which orders it before
-// their first use.
+// their first use.  That holds on every path: a read whose result nobody uses leaves its registers free, to the compiler, while
+// the LDS still writes them, so none is queued for work that does not follow (tests/test_lds_reads.py walks the assembly).
 template <int N> struct IntC { static constexpr int value = N; };
 
 template <int I, int N, typename F>
