@@ -364,6 +364,8 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
             step(u, Yes{}, No{}, Yes{}, No{}, Yes{});
 #pragma clang loop unroll(disable)
             for (++u; u <= ub; ++u) step(u, Yes{}, Yes{}, Yes{}, Yes{}, No{});
+            // The reads queued ahead, of which the last step uses V's alone: K's keep their registers up to here (named in the text for the test).
+            asm volatile("s_waitcnt lgkmcnt(0) ; %0 %1" : "+v"(kr[0]), "+v"(kr[1]), "+v"(vr[0].lo), "+v"(vr[0].hi), "+v"(vr[1].lo), "+v"(vr[1].hi) :: "memory");
             step(u, No{}, Yes{}, No{}, Yes{}, No{});
             settle_output(acc);           // here: the compiler may move the accumulators before the waves meet again
             ++u;

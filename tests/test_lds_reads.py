@@ -15,7 +15,7 @@ import pytest
 
 from paper_2407_12117_amd import build as lib_build
 
-FILES = sorted(f for f in lib_build.SOURCES if f.endswith(".hip") and f != "attn_fwd_long_bf16.hip")
+FILES = sorted(f for f in lib_build.SOURCES if f.endswith(".hip"))
 REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 WRITES_NOTHING = ("ds_write", "ds_add_u32", "ds_add_f32", "buffer_store", "global_store", "flat_store", "scratch_store", "buffer_atomic", "global_atomic", "v_cmp", "v_readfirstlane",
                   "v_readlane", "s_", "buffer_wbl2", "buffer_inv")
@@ -46,7 +46,7 @@ class Instruction:
         self.regs = registers(args)
         to_lds = self.op.startswith("buffer_load") and args.endswith(" lds")
         self.writes = set() if to_lds or self.op.startswith(WRITES_NOTHING) else registers(first)
-        self.reads = registers(rest) if self.writes else self.regs
+        self.reads = registers(rest) if self.writes else set(self.regs)
         if self.op.startswith(("v_permlane", "v_swap")):
             self.writes = self.reads = self.regs
         elif self.op.startswith(("v_fmac", "v_mac", "v_dot2c", "v_pk_fmac")) or "d16_hi" in self.op or "dst_sel" in args or "_mov_b32_dpp" in self.op:
@@ -64,7 +64,7 @@ def kernels(assembly):
         if "#ASMSTART" in raw or "#ASMEND" in raw:
             in_asm = "#ASMSTART" in raw
             continue
-        text = " ".join(raw.split(";")[0].split())
+        text, _, comment = (" ".join(part.split()) for part in raw.partition(";"))
         if re.match(r"(\.Lfunc_end\w*|\.section)", text) and name:
             yield name, flow(lines)
             name, lines = None, []
@@ -76,6 +76,9 @@ def kernels(assembly):
                 lines.append(label)
         elif name and text and not text.startswith("."):
             lines.append(Instruction(number, text, in_asm))
+            if in_asm:                                 # registers that an asm takes without an instruction of its own using them
+                lines[-1].regs |= registers(comment)
+                lines[-1].reads |= registers(comment)
 
 
 def flow(lines):
@@ -209,6 +212,7 @@ READ = ";;#ASMSTART\nds_read_b128 v[4:7], v0\n;;#ASMEND\n"
     # read again in the loop, but not on the way out of it
     (".LBB0_1:\n" + READ + "s_cbranch_scc0 .LBB0_2\ns_waitcnt lgkmcnt(0)\nv_mfma_f32_4x4x1_16b_f32 a[0:3], v[4:5], v[6:7], 0\ns_branch .LBB0_1\n.LBB0_2:\ns_nop 0",
      "nothing reads any more"),
+    (READ + ";;#ASMSTART\ns_waitcnt lgkmcnt(0) ; v[4:7]\n;;#ASMEND", None),
     (".LBB0_1:\n" + READ + "s_waitcnt lgkmcnt(0)\ns_cbranch_scc0 .LBB0_2\nv_mfma_f32_4x4x1_16b_f32 a[0:3], v[4:5], v[6:7], 0\ns_branch .LBB0_1\n.LBB0_2:\ns_nop 0", None),
 ])
 def test_the_walk_finds_what_it_is_for(body, expect):
