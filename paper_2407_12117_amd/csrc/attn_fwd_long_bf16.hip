@@ -151,6 +151,9 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
             }
         }
         float m[2] = {-INFINITY, -INFINITY}, mc[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};   // as in attn_fwd_bf16_kernel
+        // Row sums of a tile: two chains over both of its key blocks, added to lsum once a tile, as in attn_fwd_bf16_kernel (once a block: rms error
+        // of the logsumexp 7.1e-7 for 6.3e-7 at 64K keys, 1.08e-6 for 8.5e-7 at 256K, and no faster); and what they were behind the first block.
+        float ps[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, ps_first[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
 
         uint32_t ka[8], va[4][2];                  // LDS addresses in the K tile of this step and in the V tile of the step before
         int kat = 0, vat = 0, kd = 0, vd = 0;      // places of these tiles, ways to the next ones
@@ -231,7 +234,13 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
                 // P = exp2(c S - c m) against the running maximum as it stands, its row sums, rounded to bf16 (attn_fwd_bf16_kernel), as a
                 // chain over positions 0..33: fma of element i, exponential of i - 1, sum and rounding of i - 2.  In this order: an
                 // exponential right before an MFMA costs 3 cycles of 45.
-                float ps[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, sum[2], x[3], y[4];
+                float sum[2], x[3], y[4];
+                if constexpr (EXP) {
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) (Y ? ps_first : ps)[b][i] = Y ? ps[b][i] : 0.f;
+                }
                 auto position = [&](auto ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(ic)::value;
                     if constexpr (i >= 2) {
@@ -326,7 +335,8 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
                             for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
                                 for (int e = 0; e < 16; ++e) acc[b][cb][e] *= corr;
-                            ps[b][0] = ps[b][1] = 0.f;
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) ps[b][i] = Y ? ps_first[b][i] * corr : 0.f;
 #pragma unroll
                             for (int e = 0; e < 16; e += 2) {
                                 const f32x2 two = {__builtin_amdgcn_exp2f(fmaf(se[b][e], c, -mc[b])), __builtin_amdgcn_exp2f(fmaf(se[b][e + 1], c, -mc[b]))};
@@ -338,8 +348,10 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
                         }
                         settle_output(acc);
                     }
+                    if constexpr (Y == 1) {
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) lsum[b] += sum[b];
+                        for (int b = 0; b < 2; ++b) lsum[b] += sum[b];
+                    }
                     asm volatile("s_nop 1" : "+v"(p[Y][0][0]), "+v"(p[Y][0][1]), "+v"(p[Y][1][0]), "+v"(p[Y][1][1]));
                 }
             });

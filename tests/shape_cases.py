@@ -37,3 +37,6 @@ FWD_LONG_EDGES = {(513, 128): FOLDED, (575, 160): LONGEST_FIRST, (576, 128): FOL
                   (1024, 160): LONGEST_FIRST, (1025, 80): FOLDED}
 BWD_LONG_EDGES = {(3841, 160): (FOLDED, FOLDED), (3903, 128): (FOLDED, FOLDED), (3904, 128): (FOLDED, FOLDED), (3905, 128): (FOLDED, FOLDED),
                   (4351, 96): (LONGEST_FIRST, LONGEST_FIRST), (4352, 96): (LONGEST_FIRST, LONGEST_FIRST), (5121, 160): (LONGEST_FIRST, FOLDED)}
+
+# row sums of a long sweep: (S, heads) -> order of the forward
+FWD_LONG_SUMS = {(16384, 16): FOLDED}

@@ -70,6 +70,24 @@ def test_forward_with_scores_climbing_along_the_keys(oracle, S, heads, log2_per_
     _check_forward(oracle, q, k, v, o, lse, (0, heads - 1))
 
 
+@pytest.mark.parametrize("S,heads", list(shapes.FWD_LONG_SUMS))
+def test_row_sums_grow_by_whole_tiles(S, heads):
+    # 64 keys of weight 1, all others of 2^-23.25: a lane sums half of a row's keys, 32 and then 0.42 ulp of that with every 32 keys.  Added up block
+    # by block all of it is lost (1.0e-7 of the sum per tile, 2.6e-5 at the end); by tiles of 64 keys 0.84 ulp becomes one: at most 0.17 ulp a tile, 2^-18 / 32 each.
+    print(f"[case] long forward, row sums S={S} H={heads}", flush=True)
+    q = torch.zeros((1, S, heads, 128), device="cuda", dtype=torch.bfloat16)
+    k = torch.zeros_like(q)
+    q[..., 0] = 1.0
+    k[:, 64:, :, 0] = -23.25
+    lse = to_f64(mb.memo_attn_fwd(q, k, torch.ones_like(q), math.log(2.0))[1])[0]
+    keys = np.arange(1, S + 1)
+    exact = np.log(np.minimum(keys, 64) + np.maximum(keys - 64, 0) * 2.0 ** -23.25)
+    # one ulp for the sums of a row's last tile, and two of the logsumexp, which is at most 4.2.  Rows of the lower half sweep downwards: their running maximum
+    # is that of the small weights, and the logsumexp is -23.25 ln 2 plus the logarithm of up to 2^30, an fp32 number of 2^-19 an ulp.
+    bar = (0.17 * keys / 64 + 1.0) * 2.0 ** -23 + np.where(keys > S // 2, 2.0 ** -20, 2.0 ** -18)
+    assert (np.abs(lse - exact) <= bar).all()
+
+
 def test_rows_that_depend_on_what_is_not_finite():
     # what a key's rows reach: O and dQ of its queries and later ones, nothing before its 64-key tile
     S, heads, h, j = 3905, 128, 3, 2000

@@ -119,7 +119,7 @@ def test_gpu_tests_get_the_shapes_they_are_written_for(plans):
 
 
 def test_the_edges_of_the_long_kernels_get_them(plans):
-    for (S, heads), order in shapes.FWD_LONG_EDGES.items():
+    for (S, heads), order in (shapes.FWD_LONG_EDGES | shapes.FWD_LONG_SUMS).items():
         assert plans([("fwd", S, heads)]) == [(256, order)]
     for (S, heads), orders in shapes.BWD_LONG_EDGES.items():
         assert plans([("bwd", S, heads)]) == [(256, 0) + orders]
