@@ -7,6 +7,7 @@
 // the code under test aborts the run; the checks below give those accesses something to do.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -30,6 +31,9 @@ namespace fake {
 int events_alive = 0;
 int copies = 0;
 int fail_copy_at = -1;      // the copy with this index fails
+int row_copies = 0;         // copies asked for as rows
+hipError_t rows_end = hipSuccess;        // what these end with: anything but success copies nothing
+hipError_t last = hipSuccess;            // the thread's last error
 int launches = 0;
 }  // namespace fake
 
@@ -71,7 +75,20 @@ hipError_t hipHostFree(void *p)
     std::free(p);
     return hipSuccess;
 }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipMemcpy2DAsync(void *dst, size_t dpitch, const void *src, size_t spitch, size_t width, size_t height, hipMemcpyKind, hipStream_t)
+{
+    ++fake::row_copies;
+    if (fake::rows_end != hipSuccess) return fake::last = fake::rows_end;
+    for (size_t r = 0; r < height; ++r) std::memcpy(static_cast<char *>(dst) + r * dpitch, static_cast<const char *>(src) + r * spitch, width);
+    return hipSuccess;
+}
+hipError_t hipPeekAtLastError(void) { return fake::last; }
+hipError_t hipGetLastError(void)
+{
+    const hipError_t e = fake::last;
+    fake::last = hipSuccess;
+    return e;
+}
 }
 
 namespace memo {
@@ -193,6 +210,41 @@ static void swap_both_sides()
     CHECK(memo_solve_alpha(1, 1, 14, 1, 1.0, 32, 1e9, &a) == MEMO_ERR_UNSUPPORTED);
     CHECK(memo_solve_alpha(1, 1, 14, 1e9, 1.0, 32, 1.0, &a) == MEMO_ERR_HOST_CAPACITY);
     CHECK(memo_solve_alpha(1, 1, 0, 1, 1.0, 32, 1.0, &a) == MEMO_ERR_INVALID_ARG);
+}
+
+// Blocks that are asked for as rows: what they leave to a linear copy, and what happens where they fail.
+static void swap_as_rows()
+{
+    const int64_t rb = 1001;
+    for (int64_t S : {261, 262, 1000})               // 256 KiB are 261.9 rows
+        for (int shift : {0, 16, 1}) {
+            const size_t n = (size_t)(S * rb);
+            std::vector<unsigned char> act(n + shift), host(n + shift), back(n + shift);
+            for (size_t i = 0; i < n; ++i) act[shift + i] = (unsigned char)(i * 131 + 7);
+            const bool rows = n >= 256 * 1024 && shift != 1;
+            auto out = [&] { return memo_swap_out(act.data() + shift, S, rb, 1.0, host.data() + shift, n, nullptr, nullptr, nullptr); };
+            auto in = [&] { return memo_swap_in(back.data() + shift, S, rb, 1.0, host.data() + shift, n, nullptr, nullptr, nullptr); };
+            fake::copies = fake::row_copies = 0;
+            CHECK(out() == MEMO_OK && in() == MEMO_OK && back == act);
+            CHECK(fake::row_copies == (rows ? 2 : 0) && fake::copies == 2);
+            if (!rows) continue;
+            // refused as rows: copied as one block, and no error of that is left behind
+            for (hipError_t refusal : {hipErrorInvalidValue, hipErrorNotSupported}) {
+                fake::rows_end = refusal;
+                std::fill(host.begin(), host.end(), 0);
+                CHECK(out() == MEMO_OK && host == act && fake::last == hipSuccess);
+                // an error that the caller has not read yet does not turn into none
+                fake::last = hipErrorInvalidDevice;
+                CHECK(out() == MEMO_OK && fake::last != hipSuccess);
+                fake::last = hipSuccess;
+            }
+            // any other failure is the call's own
+            fake::rows_end = hipErrorOutOfMemory;
+            std::fill(host.begin(), host.end(), 0);
+            fake::copies = 0;
+            CHECK(out() == MEMO_ERR_DEVICE && in() == MEMO_ERR_DEVICE && fake::copies == 0);
+            fake::rows_end = fake::last = hipSuccess;
+        }
 }
 
 static void attention_front_end()
@@ -334,6 +386,7 @@ int main()
 {
     oracle_attention();
     swap_both_sides();
+    swap_as_rows();
     attention_front_end();
     for (int n : {1, 2, 3, 5}) schedule(n, -1);
     for (int fail_at : {0, 1, 3, 6, 11, 12}) schedule(5, fail_at);
