@@ -31,8 +31,8 @@ struct AttnArgs {
 // 57 of the link (a layer's step of 32K tokens with 192 MiB each way, passes rotating over three pairs of streams: 11.4 to 15 ms for 7.2).
 // Asked for as rows of 4 KiB it takes the engine of its direction, from any stream, at the link's rate.  Both forms take as long by themselves: 64 KiB 10.5 us,
 // 1 MiB 27 us, 192 MiB 3.53 ms, 5 GiB 93.9 ms, for rows of 1 KiB to 16 MiB; rows of 256 bytes take 4.6 ms for 192 MiB, and a block of 4 KiB takes 9 us for 5.
-// Blocks below 256 KiB, the bytes behind the last row, and blocks off 16 bytes therefore stay linear, and so does what the runtime does not take as
-// rows.  Any other failure is the call's.
+// Blocks below 256 KiB, the bytes behind the last row, and blocks off 16 bytes therefore stay linear, and so do host memory that is not pinned (128 MiB out
+// 7.5 ms, as rows 235) and what the runtime does not take as rows.  Any other failure is the call's.
 inline hipError_t copy_swapped(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t st)
 {
     constexpr size_t kRow = 4096, kLeast = 256 * 1024;
@@ -40,10 +40,14 @@ inline hipError_t copy_swapped(void *dst, const void *src, size_t bytes, hipMemc
     size_t done = 0;
     if (aligned && bytes >= kLeast) {
         const hipError_t before = hipPeekAtLastError();
-        const hipError_t e = hipMemcpy2DAsync(dst, kRow, src, kRow, kRow, bytes / kRow, kind, st);
-        if (e == hipSuccess) done = bytes / kRow * kRow;
-        else if (e != hipErrorInvalidValue && e != hipErrorInvalidPitchValue && e != hipErrorNotSupported) return e;
-        else if (before == hipSuccess) (void)hipGetLastError();      // the refusal's own; an error that the caller has not read yet stays one
+        hipPointerAttribute_t host{};
+        hipError_t e = hipPointerGetAttributes(&host, kind == hipMemcpyDeviceToHost ? dst : src);
+        if (e == hipSuccess && host.type == hipMemoryTypeHost) {
+            e = hipMemcpy2DAsync(dst, kRow, src, kRow, kRow, bytes / kRow, kind, st);
+            if (e == hipSuccess) done = bytes / kRow * kRow;
+            else if (e != hipErrorInvalidValue && e != hipErrorInvalidPitchValue && e != hipErrorNotSupported) return e;
+        }
+        if (e != hipSuccess && before == hipSuccess) (void)hipGetLastError();    // the refusal's own; an error that the caller has not read yet stays one
     }
     if (done == bytes) return hipSuccess;
     return hipMemcpyAsync(static_cast<char *>(dst) + done, static_cast<const char *>(src) + done, bytes - done, kind, st);

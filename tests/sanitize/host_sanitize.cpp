@@ -34,6 +34,8 @@ int fail_copy_at = -1;      // the copy with this index fails
 int row_copies = 0;         // copies asked for as rows
 hipError_t rows_end = hipSuccess;        // what these end with: anything but success copies nothing
 hipError_t last = hipSuccess;            // the thread's last error
+const void *pageable = nullptr;          // host memory that is not pinned
+hipError_t unknown = hipSuccess;         // what asking for that memory's attributes ends with
 int launches = 0;
 }  // namespace fake
 
@@ -80,6 +82,12 @@ hipError_t hipMemcpy2DAsync(void *dst, size_t dpitch, const void *src, size_t sp
     ++fake::row_copies;
     if (fake::rows_end != hipSuccess) return fake::last = fake::rows_end;
     for (size_t r = 0; r < height; ++r) std::memcpy(static_cast<char *>(dst) + r * dpitch, static_cast<const char *>(src) + r * spitch, width);
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
+{
+    if (p == fake::pageable && fake::unknown != hipSuccess) return fake::last = fake::unknown;
+    a->type = p == fake::pageable ? hipMemoryTypeUnregistered : hipMemoryTypeHost;
     return hipSuccess;
 }
 hipError_t hipPeekAtLastError(void) { return fake::last; }
@@ -244,6 +252,18 @@ static void swap_as_rows()
             fake::copies = 0;
             CHECK(out() == MEMO_ERR_DEVICE && in() == MEMO_ERR_DEVICE && fake::copies == 0);
             fake::rows_end = fake::last = hipSuccess;
+            // host memory that is not pinned is never copied as rows
+            fake::pageable = host.data() + shift;
+            for (hipError_t unknown : {hipSuccess, hipErrorInvalidValue}) {
+                fake::unknown = unknown;
+                fake::row_copies = 0;
+                CHECK(out() == MEMO_OK && in() == MEMO_OK && fake::row_copies == 0 && back == act && fake::last == hipSuccess);
+                fake::last = hipErrorInvalidDevice;
+                CHECK(out() == MEMO_OK && in() == MEMO_OK && fake::last != hipSuccess);
+                fake::last = hipSuccess;
+            }
+            fake::pageable = nullptr;
+            fake::unknown = hipSuccess;
         }
 }
 

@@ -39,6 +39,21 @@ def test_bytes_come_back(rows, row_bytes, shift):
     assert torch.equal(back[shift:shift + n], act.view(-1)) and (back[shift + n:] == 0x5A).all() and (back[:shift] == 0x5A).all()
 
 
+def test_host_memory_that_is_not_pinned():
+    # the C entry points take it, as one block
+    print("[case] swap copy, host memory not pinned", flush=True)
+    rows, row_bytes = 100, 4 * KIB
+    act = _act(rows, row_bytes, 0, 4)
+    back = torch.zeros_like(act)
+    host = torch.zeros(rows * row_bytes, dtype=torch.uint8)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for call, dev in ((mb.lib().memo_swap_out, act), (mb.lib().memo_swap_in, back)):
+        assert call(dev.data_ptr(), rows, row_bytes, 1.0, host.data_ptr(), host.numel(), side.cuda_stream, None, None) == mb.MEMO_OK
+        side.synchronize()
+    assert torch.equal(host, act.cpu().view(-1)) and torch.equal(back, act)
+
+
 def test_pairs_of_streams_at_once():
     pairs = [(_act(4096, 8 * KIB, 0, s), torch.zeros(4096 * 8 * KIB, dtype=torch.uint8, pin_memory=True), torch.cuda.Stream(), torch.cuda.Stream())
              for s in range(3)]
