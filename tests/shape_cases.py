@@ -40,3 +40,6 @@ BWD_LONG_EDGES = {(3841, 160): (FOLDED, FOLDED), (3903, 128): (FOLDED, FOLDED), 
 
 # row sums of a long sweep: (S, heads) -> order of the forward
 FWD_LONG_SUMS = {(16384, 16): FOLDED}
+
+# batches in one packed buffer: (B, S, heads) -> orders of dK/dV and of dQ; the forward works 256 rows too
+LONG_LAYOUTS = {(2, 3905, 64): (FOLDED, FOLDED), (3, 4351, 32): (LONGEST_FIRST, LONGEST_FIRST)}

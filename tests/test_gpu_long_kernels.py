@@ -1,6 +1,6 @@
 """The four-wave kernels of 256-row workgroups (csrc/attn_fwd_long_bf16.hip, csrc/attn_bwd_long_bf16.hip) where they can go wrong: waves without
 rows, of one row and of 63, one tile and several, both sweeps of a pair; a running maximum that is brought up to date in every tile, in
-either block of keys and either direction; infinities and NaN."""
+either block of keys and either direction; rows apart, batches; infinities and NaN."""
 import math
 
 import numpy as np
@@ -55,6 +55,37 @@ def test_backward_edges(oracle, S, heads):
         refs = oracle.attn_bwd(*(to_f64(t[:, :, h:h + 1]) for t in (q, k, v, g)), SCALE)
         for name, x, r in zip(("dQ", "dK", "dV"), got[2:], refs):
             assert_close(name, to_f64(x[:, :, h:h + 1]), r, "bf16", scaled=True)
+
+
+def _bits_of_rows_apart(B, S, heads, views):
+    # the same bits as with contiguous tensors; views(): eight tensors of one layout, of which the last four are written
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    data = [torch.randn((B, S, heads, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    want = gpu_fwd_bwd(*data, SCALE)
+    q, k, v, g, o, dq, dk, dv = views
+    for dst, src in zip(views, data):
+        dst.copy_(src)
+    _, lse = mb.memo_attn_fwd(q, k, v, SCALE, o=o)
+    mb.memo_attn_bwd(q, k, v, o, lse, g, SCALE, dq=dq, dk=dk, dv=dv)
+    for x, y in zip((o, lse, dq, dk, dv), want):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("B,S,heads", list(shapes.LONG_LAYOUTS))
+def test_batches_in_packed_rows(B, S, heads):
+    # q, k, v and dO as slices of one [B, S, 5, H, d] buffer, the outputs as slices of another, whose last slot nobody writes
+    print(f"[case] long kernels, packed B={B} S={S} H={heads}", flush=True)
+    ins, outs = (torch.zeros((B, S, 5, heads, 128), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    _bits_of_rows_apart(B, S, heads, [t[:, :, n] for t in (ins, outs) for n in range(4)])
+    assert not outs[:, :, 4].any() and not ins[:, :, 4].any()
+
+
+def test_rows_far_apart():
+    # 2 MiB between rows: tiles of 64 rows that span 128 MiB, of tensors of 8 GiB
+    S, heads, ss = 3905, 128, 1 << 20
+    print(f"[case] long kernels, rows apart S={S} H={heads} stride {ss}", flush=True)
+    buf = torch.zeros((S - 1) * ss + 8 * heads * 128, device="cuda", dtype=torch.bfloat16)
+    _bits_of_rows_apart(1, S, heads, [torch.as_strided(buf, (1, S, heads, 128), (S * ss, ss, 128, 1), n * heads * 128) for n in range(8)])
 
 
 @pytest.mark.parametrize("log2_per_tile", [12.0, 500.0, -500.0])
@@ -122,3 +153,24 @@ def test_masked_scores_of_minus_infinity(oracle):
         ro, rlse = oracle.attn_fwd(*(to_f64(t[:, :, h:h + 1]) for t in (q, kf, v)), SCALE)
         assert_close("O", to_f64(o[:, :, h:h + 1]), ro, "bf16")
         assert np.abs(to_f64(lse[:, h:h + 1]) - rlse).max() <= LSE_MAX_ABS_BF16
+
+
+def test_backward_with_scores_of_minus_infinity(oracle):
+    # hidden keys get and give nothing: no gradient of their own, none in the others'.  The first channel of dQ, 0 times -inf, is left out
+    S, heads = 3905, 128
+    print(f"[case] long backward, -inf S={S} H={heads}", flush=True)
+    q, k, v, g = _inputs(S, heads, 13)
+    q[..., 0] = q[..., 0].abs() + 0.5
+    hidden = torch.zeros(S, dtype=torch.bool, device="cuda")
+    hidden[1:200] = True
+    hidden[1024:1280] = True
+    hidden[3900:] = True
+    k[0, hidden, :, 0] = -math.inf
+    _, _, dq, dk, dv = gpu_fwd_bwd(q, k, v, g, SCALE)
+    assert not dk[0, hidden].any() and not dv[0, hidden].any()
+    kf = k.clone()
+    kf[0, hidden, :, 0] = -1e30
+    for h in (0, heads - 1):
+        refs = oracle.attn_bwd(*(to_f64(t[:, :, h:h + 1]) for t in (q, kf, v, g)), SCALE)
+        for name, x, r, first in zip(("dQ", "dK", "dV"), (dq, dk, dv), refs, (1, 0, 0)):
+            assert_close(name, to_f64(x[:, :, h:h + 1, first:]), r[..., first:], "bf16", scaled=True)

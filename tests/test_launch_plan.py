@@ -123,4 +123,6 @@ def test_the_edges_of_the_long_kernels_get_them(plans):
         assert plans([("fwd", S, heads)]) == [(256, order)]
     for (S, heads), orders in shapes.BWD_LONG_EDGES.items():
         assert plans([("bwd", S, heads)]) == [(256, 0) + orders]
+    for (B, S, heads), orders in shapes.LONG_LAYOUTS.items():
+        assert plans([("bwd", S, B * heads)]) == [(256, 0) + orders] and plans([("fwd", S, B * heads)])[0][0] == 256
     assert plans([("fwd", 3905, 128)])[0][0] == 256
