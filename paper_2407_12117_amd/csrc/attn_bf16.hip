@@ -35,14 +35,15 @@ namespace {
 
 // ============================================================================ forward
 // Workgroups, by owned rows:
-//   256 rows: attn_fwd_long_bf16.hip, four waves of 64 rows.  The more rows share a K/V tile, the less fill traffic (L2 -> LDS)
-//        each MFMA pays for, and the fewer LDS reads per MFMA with more rows in a wave: the best rate on a full chip.
-//   128: attn_fwd_bf16_kernel, eight waves as four query groups (32 rows each) x two key groups; key group g
+//   256 rows, long sequences: attn_fwd_long_bf16.hip, four waves of 64 rows.  The more rows share a K/V tile, the less fill traffic
+//        (L2 -> LDS) each MFMA pays for, and the fewer LDS reads per MFMA with more rows in a wave: the best rate on a full chip.
+//   256 rows, shorter ones (launch_plan.h): attn_fwd_bf16_kernel<8>, eight waves of 32 rows, keys not split.  Its sweep starts and ends 3 to 4 us earlier.
+//   128: attn_fwd_bf16_kernel<4>, eight waves as four query groups (32 rows each) x two key groups; key group g
 //        takes the key tiles g, g + 2, ... of 64 rows through its own double-buffered LDS ring, filled
 //        asynchronously (one barrier per step), and the groups of a row are combined at the end.
 //   64: keys in eight, all rows in every wave: attn_fwd_bf16_own_kernel.
 //   32: keys in eight: attn_fwd_bf16_short_kernel.
-// TFLOP/s at S = 128K, H = 4: 1312, 1130, 1050, 700.
+// TFLOP/s at S = 128K, H = 4: 1312, 1208, 1130, 1050, 700.
 // A short sequence has too few 256-row tiles for 256 compute units, and a sweep is as long as its
 // last row: what bounds it is the longest workgroup, which 32 rows make 64 times shorter.  The launcher
 // takes the cheapest by estimate (launch_plan.h).  256-row pairs alone -> now, us: S = 640 H = 2 31.0 -> 5.7,
@@ -50,6 +51,7 @@ namespace {
 // The fills address a tile as a buffer (TileOffsets::fill): no per-lane pointers to step and no second path for the
 // ragged last tile, 1 to 3 % of every shape.
 constexpr int kFwdWaves = 8;                 // waves per workgroup
+
 // a K operand and the Q operands of one or two row blocks
 template <int NQ> struct KqSlot { bf16x8 k, q[NQ]; };
 
@@ -67,13 +69,14 @@ __device__ __forceinline__ void lds_wait(KqSlot<2> &x)
     asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(x.k), "+v"(x.q[0]), "+v"(x.q[1]) : "n"(N));
 }
 
-__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a)
+template <int QG>
+__global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs a, int fold)
 {
-    constexpr int QG = 4, KS = kFwdWaves / QG, kBq = 32 * QG, kBk = 64, JB = kBk / 32;
+    constexpr int KS = kFwdWaves / QG, kBq = 32 * QG, kBk = 64, JB = kBk / 32;
     constexpr int kTile = kBk * 256;            // bytes of one K or V tile
     constexpr int kStage = 2 * kTile, kGroup = 2 * kStage, kRing = KS * kGroup;
-    constexpr int kMerge = 8 * 32 * 8;             // (maximum, sum) of every row of every wave
-    static_assert(kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
+    constexpr int kMerge = KS > 1 ? 8 * 32 * 8 : 0;             // (maximum, sum) of every row of every wave
+    static_assert(KS == 1 || kRing == 8 * 16384, "the merge lays eight accumulator sets over the ring");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kRing + kMerge];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;   // [key group][buf][K|V] tiles
 
@@ -82,7 +85,9 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const LaneAddr la = make_lane_addr(lane);
     const int wq = wave % QG, grp = wave / QG;  // query group, key group
     const int64_t nqt = (a.S + kBq - 1) / kBq;
-    const PairId t = decode_block(a, blockIdx.x, nqt, kLongestFirst, true);
+    const int order = tile_order(kBq, fold);
+    const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
+    if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
@@ -93,10 +98,17 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const uint32_t (&row_addr)[8] = ad.row;
     const uint32_t (&tr_addr)[4][2] = ad.tr;
 
-    const int64_t row0 = t.first * kBq, i0w = row0 + 32 * wq, i = i0w + l32;
+    // the heavy tile of the pair sweeps the keys upwards from row 0, the light one downwards to row 0
+    // (online softmax takes the key tiles in any order)
+    for (int pass = 0; pass < (QG == 8 ? 2 : 1); ++pass) {
+    const int64_t tile = pass == 0 ? (t.second >= 0 ? t.second : t.first) : (t.second >= 0 ? t.first : -1);
+    if (tile < 0) break;
+    const int64_t row0 = tile * kBq, i0w = row0 + 32 * wq, i = i0w + l32;
     const int64_t last_row = min(row0 + kBq, a.S) - 1;
     const int ntiles = (int)(last_row / kBk) + 1, nsteps = (ntiles + KS - 1) / KS;
-    // step n of a key group works tile KS * n + grp
+    // step n of a key group works tile KS * n + grp (KS = 1: also from the other end)
+    const int jfirst = pass ? ntiles - 1 : grp, jstep = pass ? -KS : KS;
+    if (pass) __syncthreads();    // every wave has left the first tile's last LDS buffer
     const TileOffsets<QG, kBk> toff = make_tile_offsets<QG, SwzA, kBk>(a.ss, wq, lane);
     auto fill_k = [&](int off, int jt) {
         toff.fill(lds + grp * kGroup + off, k, a.ss, (int64_t)jt * kBk, a.S, wq);
@@ -106,19 +118,29 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     };
     // Key groups that need the same Q rows bring them in once, as whole rows, in the place of the buffers that the second tiles take: to each
     // wave's registers straight from memory, 32 bytes of a row at a time, they cost a unit 5000 cycles.
+    constexpr bool kStaged = KS > 1;
     constexpr int kBlocks = kStage / (32 * 256);      // 32-row blocks in one such buffer
-    static_assert(KS * kBlocks >= QG, "room for the Q rows");
+    static_assert(!kStaged || KS * kBlocks >= QG, "room for the Q rows");
     auto staged = [&](int block) { return lds + block / kBlocks * kGroup + kStage + block % kBlocks * 32 * 256; };
-    const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzA, 32>(a.ss, wave, lane);
+    if constexpr (kStaged) {
+        const TileOffsets<8, 32> qoff = make_tile_offsets<8, SwzA, 32>(a.ss, wave, lane);
 #pragma unroll
-    for (int blk = 0; blk < QG; ++blk) qoff.fill(staged(blk), q, a.ss, row0 + 32 * blk, a.S, wave);
-    if (grp < ntiles) {
-        fill_k(0, grp);
-        fill_v(0, grp);
+        for (int blk = 0; blk < QG; ++blk) qoff.fill(staged(blk), q, a.ss, row0 + 32 * blk, a.S, wave);
+    }
+    if (jfirst < ntiles) {
+        fill_k(0, jfirst);
+        fill_v(0, jfirst);
     }
 
     // Q^T as B operand: lane = query row i, 8 head-dim values per 16-wide chunk
     bf16x8 qB[8];
+    if constexpr (!kStaged) {
+        const int64_t iq = i < a.S ? i : a.S - 1;     // rows past S are computed and never stored
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc)
+            qB[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(q + iq * a.ss + 16 * kc + 8 * half));
+    }
+
     f32x16 accO[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
@@ -128,12 +150,14 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     const int wave_first_tile_masked = min((int)((i0w + 31) / kBk) + 1, ntiles);   // tiles >= this are fully masked
     const int wave_first_diag = (int)(i0w / kBk);                     // tiles >= this need the mask
 
-    wait_fills();
-    __syncthreads();              // the Q rows are complete; the first step's barrier is what their place waits for
-    static_for<0, 8>([&](auto n) {
-        lds_issue_b128<0>(qB[decltype(n)::value], (uint32_t)(uintptr_t)staged(wq) + (uint32_t)(la.row_op[0] ^ (decltype(n)::value << 5)));
-    });
-    static_for<0, 8>([&](auto n) { lds_wait<0>(qB[decltype(n)::value]); });
+    if constexpr (kStaged) {
+        wait_fills();
+        __syncthreads();          // the Q rows are complete; the first step's barrier is what their place waits for
+        static_for<0, 8>([&](auto n) {
+            lds_issue_b128<0>(qB[decltype(n)::value], (uint32_t)(uintptr_t)staged(wq) + (uint32_t)(la.row_op[0] ^ (decltype(n)::value << 5)));
+        });
+        static_for<0, 8>([&](auto n) { lds_wait<0>(qB[decltype(n)::value]); });
+    }
 
     // One key/value tile.  BUF is a compile-time buffer index, so every LDS address below is
     // a per-lane register plus an immediate offset.
@@ -141,10 +165,10 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
         constexpr int BUF = decltype(bufc)::value;
         constexpr int kOff = BUF * kStage, vOff = kOff + kTile;
         constexpr int nOff = (BUF ^ 1) * kStage;
-        const int jn = jt + KS;
+        const int jn = jt + jstep;
         wait_fills();
         __syncthreads();          // tile jt is complete; nobody still reads the other buffer
-        if (jn < ntiles) {
+        if (jn >= 0 && jn < ntiles) {
             fill_k(nOff, jn);
             fill_v(nOff, jn);
         }
@@ -239,53 +263,61 @@ __global__ __launch_bounds__(64 * kFwdWaves) void attn_fwd_bf16_kernel(AttnArgs 
     };
 
     for (int n = 0; n < nsteps; n += 2) {
-        tile_step(IntC<0>{}, grp + KS * n);
-        if (n + 1 < nsteps) tile_step(IntC<1>{}, grp + KS * (n + 1));
+        tile_step(IntC<0>{}, jfirst + jstep * n);
+        if (n + 1 < nsteps) tile_step(IntC<1>{}, jfirst + jstep * (n + 1));
     }
 
     const float ltot = add_across_halves(lsum);
     __bf16 *o = static_cast<__bf16 *>(a.o_out) + base + i * a.ss;
     float *lse = a.lse + ((int64_t)t.b * a.H + t.h) * a.S + i;
-    // The key groups of a row meet in LDS: every wave leaves its accumulators, (c m) and row sums; each
-    // then combines 16/KS of the sixteen 4-value pieces of its rows over the groups.  A group that had
-    // no tile has m = -inf and weighs exactly zero.
-    LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
-    LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kRing);
-    __syncthreads();          // every wave has left the last LDS buffer
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-        pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
-                                                    accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
-    if (half == 0) stats[wave * 32 + l32] = f32x2{mc, ltot};
-    __syncthreads();
-    float top = -INFINITY, total = 0.f, weight[KS];
-    f32x2 st[KS];
-#pragma unroll
-    for (int g = 0; g < KS; ++g) {
-        st[g] = stats[(g * QG + wq) * 32 + l32];
-        top = fmaxf(top, st[g][0]);
-    }
-#pragma unroll
-    for (int g = 0; g < KS; ++g) {
-        weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
-        total += weight[g] * st[g][1];
-    }
-    if (i < a.S) {
-        const float inv = 1.f / total;
-#pragma unroll
-        for (int n = 0; n < 16 / KS; ++n) {
-            const int e = grp * (16 / KS) + n;
-            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int g = 0; g < KS; ++g) {
-                const f32x4 x = pieces[((g * QG + wq) * 16 + e) * 64 + lane];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
-            }
-            store4(o + 8 * e + 4 * half, sum, inv);
+    if constexpr (KS == 1) {
+        if (i < a.S) {
+            store_acc_T(o, accO, 1.f / ltot, half);
+            if (half == 0) *lse = (mc + __builtin_amdgcn_logf(ltot)) * kLn2;
         }
-        if (grp == 0 && half == 0) *lse = (top + __builtin_amdgcn_logf(total)) * kLn2;
+    } else {
+        // The key groups of a row meet in LDS: every wave leaves its accumulators, (c m) and row sums; each
+        // then combines 16/KS of the sixteen 4-value pieces of its rows over the groups.  A group that had
+        // no tile has m = -inf and weighs exactly zero.
+        LDS_AS f32x4 *pieces = (LDS_AS f32x4 *)lds;
+        LDS_AS f32x2 *stats = (LDS_AS f32x2 *)(lds + kRing);
+        __syncthreads();          // every wave has left the last LDS buffer
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            pieces[(wave * 16 + e) * 64 + lane] = f32x4{accO[e >> 2][4 * (e & 3)], accO[e >> 2][4 * (e & 3) + 1],
+                                                        accO[e >> 2][4 * (e & 3) + 2], accO[e >> 2][4 * (e & 3) + 3]};
+        if (half == 0) stats[wave * 32 + l32] = f32x2{mc, ltot};
+        __syncthreads();
+        float top = -INFINITY, total = 0.f, weight[KS];
+        f32x2 st[KS];
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            st[g] = stats[(g * QG + wq) * 32 + l32];
+            top = fmaxf(top, st[g][0]);
+        }
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            weight[g] = __builtin_amdgcn_exp2f(st[g][0] - top);
+            total += weight[g] * st[g][1];
+        }
+        if (i < a.S) {
+            const float inv = 1.f / total;
+#pragma unroll
+            for (int n = 0; n < 16 / KS; ++n) {
+                const int e = grp * (16 / KS) + n;
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int g = 0; g < KS; ++g) {
+                    const f32x4 x = pieces[((g * QG + wq) * 16 + e) * 64 + lane];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sum[r] += weight[g] * x[r];
+                }
+                store4(o + 8 * e + 4 * half, sum, inv);
+            }
+            if (grp == 0 && half == 0) *lse = (top + __builtin_amdgcn_logf(total)) * kLn2;
+        }
     }
+    }   // pass
 }
 
 // The end of the kernels whose eight waves share out the keys of 32 rows: every wave has left its accumulators as sixteen
@@ -666,7 +698,7 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
 {
     const int64_t heads = (int64_t)a.H * a.B;
     const TileChoice &c = fwd_plan(a.S, heads);
-    const int order = tile_order(c.rows, c.order);    // as in the kernel
+    const int order = tile_order(c.rows, c.order);
     const int64_t blocks = order_grid((a.S + c.rows - 1) / c.rows, heads, order);
     if (blocks > kMaxBlocks)
         return launch_fewer_heads(a, sizeof(__bf16), blocks, kMaxBlocks, [&](const AttnArgs &part) { return launch_attn_fwd_bf16(part, st); });
@@ -678,8 +710,8 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st)
                                                                               : launch(attn_fwd_bf16_short_kernel<1>);
     }
     case 64: return launch_blocks(attn_fwd_bf16_own_kernel, blocks, st, a, Divisor(heads), Divisor(a.H));
-    case 128: return launch_blocks(attn_fwd_bf16_kernel, blocks, st, a);
-    default: return launch_attn_fwd_bf16_long(a, order, blocks, st);
+    case 128: return launch_blocks(attn_fwd_bf16_kernel<4>, blocks, st, a, order);
+    default: return c.waves == 4 ? launch_attn_fwd_bf16_long(a, order, blocks, st) : launch_blocks(attn_fwd_bf16_kernel<8>, blocks, st, a, order);
     }
 }
 

@@ -113,8 +113,8 @@ inline bool f32_bwd_shares_rows(int64_t tiles) { return tiles <= 320; }
 
 // One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
 // 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
-// and after its sweep.
-struct TileChoice { int rows, order; double us_per_mpair, us_per_item; };
+// and after its sweep.  `waves` of a workgroup, and the sequences it is for: more than `over` rows and up to `upto`.
+struct TileChoice { int rows, order; double us_per_mpair, us_per_item; int waves = 8; int64_t over = 0, upto = INT64_MAX; };
 
 // Estimated time of a launch, us.  Folded: rounds of 256 equal pairs of tiles.  Longest first: the n
 // tiles an XCD gets have lengths n, n-1, .. 1 (in units of ntiles / n tiles); the first 32 start
@@ -131,7 +131,8 @@ inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads, doub
     const double n = (double)(ntiles * heads) / kXcds, P = kChunk, j = std::floor(n / (2 * P));
     double makespan = 2 * n * j - 2 * P * j * j + j + n - 2 * P * j;
     if (n < 1) makespan = 1;                                              // fewer tiles than XCDs
-    const double busy = n < P ? n / P : 1.0;                              // a partly idle chip clocks higher
+    // a partly idle chip clocks higher; the four-wave launches, which power bounds most, also where the second of two rounds ends before the first one's longest
+    const double busy = n < P ? n / P : n < 2 * P && c.waves == 4 ? n / (2 * P) : 1.0;
     return makespan * (ntiles / (n < 1 ? 1 : n)) * mpairs * c.us_per_mpair * (0.8 + 0.2 * busy) * (1.0 + crowded * crowding(S, heads)) +
            std::ceil(n / P) * c.us_per_item;
 }
@@ -139,11 +140,12 @@ inline double tile_choice_us(const TileChoice &c, int64_t S, int64_t heads, doub
 template <int N>
 inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t heads)
 {
-    int best = 0;
-    double best_us = tile_choice_us(choices[0], S, heads);
-    for (int i = 1; i < N; ++i) {
+    int best = -1;
+    double best_us = 0.0;
+    for (int i = 0; i < N; ++i) {
+        if (S <= choices[i].over || S > choices[i].upto) continue;
         const double us = tile_choice_us(choices[i], S, heads);
-        if (us < best_us) {
+        if (best < 0 || us < best_us) {
             best = i;
             best_us = us;
         }
@@ -172,13 +174,17 @@ constexpr int tile_order(int rows, int order) { return rows == 256 ? order : kLo
 // (B, H, S) the estimate's choice was within 1.1 % of the fastest variant on average, 21 % at worst; over 36 sizes of 2048 to
 // 400000 rows and 2 to 256 heads 0.3 % and, at S = 40000 with 5 heads (128 rows for 256), 4.6 %.  The worst are sizes
 // of less than a round of workgroups and a few heads (S = 3000, 16 heads: 64 rows for 128, 19 %).
-// The costs of 256 rows were then lowered for the four-wave kernel, which takes 106 and 108, only as far as the estimate of 128 rows
-// (up to 13 % too high in launches of little more than a round) allows: us, 128 rows : 256, S = 20000 H = 10 995 : 864,
-// 40000 H = 4 1486 : 1374, 40000 H = 5 2030 : 1700, 50000 H = 4 2280 : 2095, 90000 H = 2 3845 : 3440 now go to 256, 6000 H = 16 158 : 175,
-// 12000 H = 8 292 : 325, 25000 H = 4 611 : 656, 50000 H = 2 1214 : 1286 stay.
+// 256 rows in four waves of 64 (attn_fwd_long_bf16.hip) take less per pair, but start and end a sweep 3 to 4 us later than in eight of 32, so they are for
+// the longer sequences.  us, eight waves : four, folded S = 482 H = 227 39.7 : 49.5, 1468 H = 161 124 : 134, 2498 H = 116 265 : 276, 3249 H = 33 106.8 : 108.7,
+// 3410 H = 67 231.7 : 227.0, 4397 H = 145 827 : 784; longest first S = 719 H = 177 54.6 : 64.1, 1468 H = 161 126.5 : 134.4, 1977 H = 50 69.2 : 70.7,
+// 2554 H = 81 151 : 156, 2655 H = 91 216 : 204, 2734 H = 70 158 : 160, 2881 H = 145 380 : 362, 3596 H = 96 366 : 343, 4369 H = 82 460 : 426.
+// From 3329 rows on their costs are fitted to 304 sizes of up to 120000 rows and 1 to 256 heads, timed by 64 and 128 rows and by both orders of 256: the choice
+// is 0.4 to 0.9 % slower than the best on average, 21 % at worst (S = 3373 H = 14, 64 rows for 128).  us, 128 rows : 256, longest first, just beyond a round:
+// S = 6000 H = 16 155 : 145, 8422 H = 12 218 : 202, 12715 H = 8 317 : 297, 20000 H = 10 980 : 871, 2667 H = 33 92 : 77, 40000 H = 5 1985 : 1702.
 inline constexpr TileChoice kFwdChoices[] = {
-    {256, kFolded, 113.0, 4.0}, {256, kLongestFirst, 114.0, 8.0}, {128, kLongestFirst, 125.0, 8.0},
-    {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
+    {256, kFolded, 115.5, 4.0, 8, 0, 3328}, {256, kFolded, 108.0, 4.0, 4, 3328},
+    {256, kLongestFirst, 117.0, 8.0, 8, 0, 2560}, {256, kLongestFirst, 117.0, 8.0, 4, 2560, 3328}, {256, kLongestFirst, 109.0, 8.0, 4, 3328},
+    {128, kLongestFirst, 125.0, 8.0}, {64, kLongestFirst, 140.0, 6.0}, {32, kLongestFirst, 185.0, 4.5},
 };
 
 inline const TileChoice &fwd_plan(int64_t S, int64_t heads) { return kFwdChoices[cheapest_tiles(kFwdChoices, S, heads)]; }

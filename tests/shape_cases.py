@@ -31,10 +31,13 @@ LINEAR_SHAPES = {(65, 128, 128, 0): (64, 64), (257, 384, 384, 1): (64, 64), (700
                  (17003, 256, 384, 3): (256, 128), (32879, 128, 384, 0): (256, 128),
                  (40001, 384, 640, 130): (256, 256)}
 
-# four-wave kernels of 256 rows: the last tile of one row, of one 64-row wave and its neighbours, of two waves and a ragged third, whole;
-# (S, heads) -> order of the forward, (S, heads) -> orders of dK/dV and of dQ
+# workgroups of 256 rows: the last tile of one row, of one 64-row wave and its neighbours, of two waves and a ragged third, whole;
+# (S, heads) -> order of the forward: in eight waves of 32 rows, and in four of 64
 FWD_LONG_EDGES = {(513, 128): FOLDED, (575, 160): LONGEST_FIRST, (576, 128): FOLDED, (577, 160): LONGEST_FIRST, (705, 100): FOLDED, (769, 128): FOLDED,
                   (1024, 160): LONGEST_FIRST, (1025, 80): FOLDED}
+FWD_FOUR_WAVE_EDGES = {(3329, 48): LONGEST_FIRST, (3391, 48): LONGEST_FIRST, (3521, 48): LONGEST_FIRST, (3584, 60): LONGEST_FIRST,
+                       (3329, 72): FOLDED, (3391, 68): FOLDED, (3392, 68): FOLDED, (3393, 68): FOLDED, (3585, 64): FOLDED}
+# (S, heads) -> orders of dK/dV and of dQ, in four waves
 BWD_LONG_EDGES = {(3841, 160): (FOLDED, FOLDED), (3903, 128): (FOLDED, FOLDED), (3904, 128): (FOLDED, FOLDED), (3905, 128): (FOLDED, FOLDED),
                   (4351, 96): (LONGEST_FIRST, LONGEST_FIRST), (4352, 96): (LONGEST_FIRST, LONGEST_FIRST), (5121, 160): (LONGEST_FIRST, FOLDED)}
 

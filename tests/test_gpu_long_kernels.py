@@ -1,4 +1,4 @@
-"""The four-wave kernels of 256-row workgroups (csrc/attn_fwd_long_bf16.hip, csrc/attn_bwd_long_bf16.hip) where they can go wrong: waves without
+"""The four-wave kernels of 256-row workgroups (csrc/attn_fwd_long_bf16.hip, csrc/attn_bwd_long_bf16.hip), and the eight-wave forward of shorter sequences, where they can go wrong: waves without
 rows, of one row and of 63, one tile and several, both sweeps of a pair; a running maximum that is brought up to date in every tile, in
 either block of keys and either direction; rows apart, batches; infinities and NaN."""
 import math
@@ -38,7 +38,7 @@ def _check_forward(oracle, q, k, v, o, lse, heads):
         assert np.abs(to_f64(lse[:, h:h + 1]) - rlse).max() <= bar
 
 
-@pytest.mark.parametrize("S,heads", list(shapes.FWD_LONG_EDGES))
+@pytest.mark.parametrize("S,heads", list(shapes.FWD_LONG_EDGES) + list(shapes.FWD_FOUR_WAVE_EDGES))
 def test_forward_edges(oracle, S, heads):
     print(f"[case] long forward S={S} H={heads}", flush=True)
     q, k, v, _ = _inputs(S, heads, S)
@@ -89,7 +89,7 @@ def test_rows_far_apart():
 
 
 @pytest.mark.parametrize("log2_per_tile", [12.0, 500.0, -500.0])
-@pytest.mark.parametrize("S,heads", [(1025, 80), (1024, 160)])
+@pytest.mark.parametrize("S,heads", [(1025, 80), (1024, 160), (3521, 48), (3393, 68)])
 def test_forward_with_scores_climbing_along_the_keys(oracle, S, heads, log2_per_tile):
     # every score moves with the key index by so many binary orders of magnitude per 64 keys (the first channel alone carries it)
     print(f"[case] long forward climbing {log2_per_tile} S={S} H={heads}", flush=True)
@@ -136,9 +136,9 @@ def test_rows_that_depend_on_what_is_not_finite():
     assert torch.equal(clean[0][0, :first, h], got[0][0, :first, h]) and torch.equal(clean[2][0, :first, h], got[2][0, :first, h])
 
 
-def test_masked_scores_of_minus_infinity(oracle):
+@pytest.mark.parametrize("S,heads", [(1025, 80), (3521, 48), (3393, 68)])
+def test_masked_scores_of_minus_infinity(oracle, S, heads):
     # keys whose scores are all -inf weigh nothing, also where they are a wave's first tile
-    S, heads = 1025, 80
     print(f"[case] long forward, -inf S={S} H={heads}", flush=True)
     q, k, v, _ = _inputs(S, heads, 11)
     q[..., 0] = q[..., 0].abs() + 0.5

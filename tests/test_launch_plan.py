@@ -119,10 +119,24 @@ def test_gpu_tests_get_the_shapes_they_are_written_for(plans):
 
 
 def test_the_edges_of_the_long_kernels_get_them(plans):
-    for (S, heads), order in (shapes.FWD_LONG_EDGES | shapes.FWD_LONG_SUMS).items():
-        assert plans([("fwd", S, heads)]) == [(256, order)]
+    for table, waves in ((shapes.FWD_LONG_EDGES, 8), (shapes.FWD_FOUR_WAVE_EDGES, 4), (shapes.FWD_LONG_SUMS, 4)):
+        for (S, heads), order in table.items():
+            assert plans([("fwd", S, heads), ("waves", S, heads)]) == [(256, order), (waves,)]
     for (S, heads), orders in shapes.BWD_LONG_EDGES.items():
         assert plans([("bwd", S, heads)]) == [(256, 0) + orders]
     for (B, S, heads), orders in shapes.LONG_LAYOUTS.items():
-        assert plans([("bwd", S, B * heads)]) == [(256, 0) + orders] and plans([("fwd", S, B * heads)])[0][0] == 256
-    assert plans([("fwd", 3905, 128)])[0][0] == 256
+        assert plans([("bwd", S, B * heads)]) == [(256, 0) + orders] and plans([("waves", S, B * heads)]) == [(4,)]
+    assert plans([("waves", 3905, 128)]) == [(4,)]
+
+
+# a sweep in four waves starts and ends later: where it was measured slower than one in eight
+@pytest.mark.parametrize("S,heads", [(301, 193), (473, 163), (482, 227), (666, 122), (719, 177), (850, 92), (917, 256), (1074, 78), (1468, 161), (1600, 56),
+                                     (1977, 50), (2444, 99), (2543, 99)])
+def test_short_forward_sweeps_do_not_take_four_waves(plans, S, heads):
+    assert plans([("waves", S, heads)]) == [(8,)]
+
+
+# and faster, longest first for 128 rows, in launches of little more than a round
+@pytest.mark.parametrize("S,heads", [(6000, 16), (8422, 12), (10116, 10), (12715, 8), (20000, 10), (25000, 4), (40000, 5), (50000, 2)])
+def test_long_forward_sweeps_just_beyond_a_round_take_four_waves(plans, S, heads):
+    assert plans([("fwd", S, heads), ("waves", S, heads)]) == [(256, LONGEST_FIRST), (4,)]
