@@ -329,10 +329,9 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
 
     // The tile walks the query tiles downwards from the last one to its diagonal: the workgroups of an XCD then read the same
     // Q/dO rows at about the same time.
-    const int dir = -1;
     const int64_t col0 = t.first * kBwdBk, j0w = col0 + 32 * wk;
     const int it0 = (int)(col0 / kBq);                // the tile's first query tile (its diagonal)
-    // the sweep's query tiles it_first, it_first + dir, ...: query group grp takes the positions grp, grp + QS, ...
+    // the sweep's query tiles it_first, it_first - 1, ...: query group grp takes the positions grp, grp + QS, ...
     const int it_first = nit - 1, npos = nit - it0, nsteps = (npos + QS - 1) / QS;
     {   // resident K and V rows (rows past S repeat row S-1, never stored): 32-row pieces, 8 waves x 4 rows
         const __bf16 *kp = static_cast<const __bf16 *>(a.k) + base;
@@ -349,8 +348,8 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
         fill_tile_at<SwzB>(dst, toff, src, a.ss, r0, a.S, wk, lane);
     };
     if (grp < npos) {
-        fill_tile(ring_base, q, (int64_t)(it_first + dir * grp) * kBq);
-        fill_tile(ring_base + kBq * 256, g, (int64_t)(it_first + dir * grp) * kBq);
+        fill_tile(ring_base, q, (int64_t)(it_first - grp) * kBq);
+        fill_tile(ring_base + kBq * 256, g, (int64_t)(it_first - grp) * kBq);
     }
 
     f32x4 accV[8][2], accK[8][2];                     // dV^T, dK^T: [head-dim block][key block]; lane = key
@@ -388,7 +387,7 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
             nd[qt] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.d[qt], -1.f, kZero4, 0, 0, 0);
         }
     };
-    RawStats raw = load_stats(it_first + dir * min(grp, npos - 1));
+    RawStats raw = load_stats(it_first - min(grp, npos - 1));
 
     uint32_t kv_row[4];                               // this wave's K rows; its V rows are 8192 bytes further
 #pragma unroll
@@ -402,7 +401,7 @@ __device__ __forceinline__ void dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
         constexpr int nOff = (BUF ^ 1) * kStageBytes;
         wait_fills();
         __syncthreads();          // tile `it` is complete; the other stage is free
-        const int it = it_first + dir * pos, itn = it + dir * QS;
+        const int it = it_first - pos, itn = it - QS;
         const bool more = pos + QS < npos;
         const int64_t rn = (int64_t)itn * kBq;        // first query of the group's next tile (if there is one)
         const int64_t i0 = (int64_t)it * kBq;         // first query of the tile
@@ -965,8 +964,9 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 // D_i preprocess, then dK, dV and dQ: in one launch of 32-, 64-, 128- or 256-row workgroups, or, where whole rounds
 // of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch
 // fills the chip where neither kernel does alone (S = 2000, 6 heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups,
-// 207 as two launches of 256-row pairs) and lets the dQ tiles run in the tail of the dK/dV ones (S = 16461, H = 4:
-// 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us); two folded launches win from S = 32K at whole rounds (S = 128K, H = 4: 25.0 + 17.8 against 47.3 ms).
+// 207 as two launches of 256-row pairs in eight waves) and lets the dQ tiles run in the tail of the dK/dV ones (in eight waves throughout,
+// S = 16461, H = 4: 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us).  Two launches go out in four waves (attn_bwd_long_bf16.hip) and win
+// from S = 32K at whole rounds (S = 128K, H = 4: 25.0 + 17.8 against 47.3 ms); where they win otherwise the plan does not know yet (bwd_plan).
 // A joint launch goes out in two parts, with the same bits, where dQ takes the place of Q or dO, which all key-stationary
 // workgroups read, and where an event between the stages is asked for.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)

@@ -191,7 +191,8 @@ inline const TileChoice &fwd_plan(int64_t S, int64_t heads) { return kFwdChoices
 
 // ---- bf16 backward
 // Costs of the workgroup shapes alone (see tile_choice_us), fitted as the forward's.  64-row workgroups pay
-// 5 to 20 % more per pair than 256-row ones for their four times larger fill traffic.
+// 5 to 20 % more per pair than 256-row ones for their four times larger fill traffic.  The 256-row figures are those of eight waves, which joint
+// launches run; launches of one gradient run four, which take about 196 and 139 (S = 128K, H = 4).
 inline constexpr TileChoice kDkdvChoices[] = {
     {256, kFolded, 216.0, 4.0}, {256, kLongestFirst, 218.0, 8.0}, {128, kLongestFirst, 222.0, 8.0}, {64, kLongestFirst, 232.0, 6.5},
 };
@@ -214,9 +215,11 @@ inline double own_us(int64_t S, int64_t heads)
 // Workgroups of `rows` rows: dK/dV and dQ in one joint launch, or the one after the other in the orders k_order and q_order.
 struct BwdPlan { int rows; bool joint; int k_order, q_order; };
 
-// The estimate's choice over 80 sizes of 1024 to 262144 rows and 1 to 256 heads with at least 2^16.8 rows in all: 0.1 % slower
-// than the fastest of the variants on average, 1.4 % at worst; against a pair of folded launches 0.5 % at worst (15 %
-// without `crowding`).
+// With eight waves in all 256-row launches the estimate's choice was 0.1 % slower than the fastest of the variants on average and 1.4 % at worst, over 80 sizes
+// of 1024 to 262144 rows and 1 to 256 heads with at least 2^16.8 rows in all.  Launches of one gradient are priced as that still, so that a joint
+// launch is often taken where two of four waves are faster by now: over 88 sizes of 2500 to 140000 rows and 1 to 130 heads the choice of 256 rows is 1.6 % slower than
+// the fastest on average, 10.6 % at worst (us, taken : two launches, S = 12820 H = 18 2300 : 2079, 25000 H = 5 2252 : 2052, 40000 H = 3 3410 : 3148, 70000 H = 4
+// 13974 : 13235, 90000 H = 4 22948 : 21429).  Against eight waves throughout two launches gain 3 to 7 % (40 sizes of 5279 to 96976 rows).
 inline BwdPlan bwd_plan(int64_t S, int64_t heads)
 {
     BwdPlan best = {256, false, kFolded, kFolded};
