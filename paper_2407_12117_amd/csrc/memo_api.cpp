@@ -192,7 +192,7 @@ memo_status memo_swap_out(const void *dev_act, int64_t S, int64_t row_bytes, dou
         return MEMO_ERR_DEVICE;
     // the swapped tokens are the first k rows, which are one contiguous block
     if (plan.bytes_swapped > 0 &&
-        memo::copy_swapped(host_pinned, dev_act, (size_t)plan.bytes_swapped, hipMemcpyDeviceToHost, cs) !=
+        memo::copy_swapped(host_pinned, dev_act, plan.k_swapped, (size_t)row_bytes, hipMemcpyDeviceToHost, cs) !=
             hipSuccess)
         return MEMO_ERR_DEVICE;
     if (done_event && hipEventRecord(static_cast<hipEvent_t>(done_event), cs) != hipSuccess)
@@ -212,7 +212,7 @@ memo_status memo_swap_in(void *dev_act, int64_t S, int64_t row_bytes, double alp
         hipStreamWaitEvent(cs, static_cast<hipEvent_t>(wait_event), 0) != hipSuccess)
         return MEMO_ERR_DEVICE;
     if (plan.bytes_swapped > 0 &&
-        memo::copy_swapped(dev_act, host_pinned, (size_t)plan.bytes_swapped, hipMemcpyHostToDevice, cs) !=
+        memo::copy_swapped(dev_act, host_pinned, plan.k_swapped, (size_t)row_bytes, hipMemcpyHostToDevice, cs) !=
             hipSuccess)
         return MEMO_ERR_DEVICE;
     if (done_event && hipEventRecord(static_cast<hipEvent_t>(done_event), cs) != hipSuccess)

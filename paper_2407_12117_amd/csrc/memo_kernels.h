@@ -26,31 +26,32 @@ struct AttnArgs {
     hipEvent_t *stage_events;   // backward only, nullable: 4 events recorded between the stages
 };
 
-// One copy of swapped rows between device and pinned host memory, one contiguous block.  Asked for as a linear copy, a large block goes to a copy engine that
+// One copy of `rows` swapped rows between device and pinned host memory, one contiguous block.  Asked for as a linear copy, a large block goes to a copy engine that
 // is free at the time of the call, and the stream keeps it: with some copies already queued on other streams these are engines that move 16 GB/s for the
 // 57 of the link (a layer's step of 32K tokens with 192 MiB each way, passes rotating over three pairs of streams: 11.4 to 15 ms for 7.2).
-// Asked for as rows of 4 KiB it takes the engine of its direction, from any stream, at the link's rate.  Both forms take as long by themselves: 64 KiB 10.5 us,
+// Asked for as rows it takes the engine of its direction, from any stream, at the link's rate.  Both forms take as long by themselves: 64 KiB 10.5 us,
 // 1 MiB 27 us, 192 MiB 3.53 ms, 5 GiB 93.9 ms, for rows of 1 KiB to 16 MiB; rows of 256 bytes take 4.6 ms for 192 MiB, and a block of 4 KiB takes 9 us for 5.
-// Blocks below 256 KiB, the bytes behind the last row, and blocks off 16 bytes therefore stay linear, and so do host memory that is not pinned (128 MiB out
-// 7.5 ms, as rows 235) and what the runtime does not take as rows.  Any other failure is the call's.
-inline hipError_t copy_swapped(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t st)
+// The engine of the way out is also the one with which the driver clears freed device memory: for 28 ms per GiB after a hipFree a copy shares it (16 MiB
+// 0.5 ms for 0.3, 1 GiB 51 GB/s for 57), which a linear copy does not.
+// The whole block has to go as rows: a few bytes left to a linear copy are moved by a kernel, which beside a launch that fills the chip waits for one of its workgroups
+// to end (four copies of 64 MiB and 1 KiB beside dK/dV of 256K tokens: 41 ms for 4.7).  So the rows are the token rows where these are of 1 to 64 KiB and a multiple of 16, else
+// of 4 KiB where that divides the block.  Other blocks, those below 256 KiB or off 16 bytes, host memory that is not pinned (128 MiB out 7.5 ms, as rows 235) and
+// what the runtime does not take as rows stay linear.  Any other failure is the call's.
+inline hipError_t copy_swapped(void *dst, const void *src, int64_t rows, size_t row_bytes, hipMemcpyKind kind, hipStream_t st)
 {
-    constexpr size_t kRow = 4096, kLeast = 256 * 1024;
+    const size_t bytes = (size_t)rows * row_bytes, width = row_bytes >= 1024 && row_bytes <= 65536 && row_bytes % 16 == 0 ? row_bytes : 4096;
     const bool aligned = ((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15u) == 0;
-    size_t done = 0;
-    if (aligned && bytes >= kLeast) {
+    if (aligned && bytes % width == 0 && bytes >= 256 * 1024) {
         const hipError_t before = hipPeekAtLastError();
         hipPointerAttribute_t host{};
         hipError_t e = hipPointerGetAttributes(&host, kind == hipMemcpyDeviceToHost ? dst : src);
         if (e == hipSuccess && host.type == hipMemoryTypeHost) {
-            e = hipMemcpy2DAsync(dst, kRow, src, kRow, kRow, bytes / kRow, kind, st);
-            if (e == hipSuccess) done = bytes / kRow * kRow;
-            else if (e != hipErrorInvalidValue && e != hipErrorInvalidPitchValue && e != hipErrorNotSupported) return e;
+            e = hipMemcpy2DAsync(dst, width, src, width, width, bytes / width, kind, st);
+            if (e != hipErrorInvalidValue && e != hipErrorInvalidPitchValue && e != hipErrorNotSupported) return e;
         }
         if (e != hipSuccess && before == hipSuccess) (void)hipGetLastError();    // the refusal's own; an error that the caller has not read yet stays one
     }
-    if (done == bytes) return hipSuccess;
-    return hipMemcpyAsync(static_cast<char *>(dst) + done, static_cast<const char *>(src) + done, bytes - done, kind, st);
+    return hipMemcpyAsync(dst, src, bytes, kind, st);
 }
 
 inline hipError_t record_stage(const AttnArgs &a, int idx, hipStream_t st)

@@ -165,7 +165,7 @@ memo_status memo_sched_forward_end(memo_sched *s, int32_t layer)
         char *slot = s->host + static_cast<size_t>(layer) * s->host_bytes;
         for (const memo_tensor_slot &t : s->slots) {
             if (t.bytes_swapped == 0) continue;
-            if (memo::copy_swapped(slot + t.host_offset, buf + t.dev_offset, t.bytes_swapped,
+            if (memo::copy_swapped(slot + t.host_offset, buf + t.dev_offset, t.k_swapped, t.bytes_swapped / t.k_swapped,
                                    hipMemcpyDeviceToHost, s->offload) != hipSuccess)
                 return fail(s);
         }
@@ -200,7 +200,7 @@ memo_status memo_sched_backward_end(memo_sched *s, int32_t layer)
         const char *slot = s->host + static_cast<size_t>(j) * s->host_bytes;
         for (const memo_tensor_slot &t : s->slots) {
             if (t.bytes_swapped == 0) continue;
-            if (memo::copy_swapped(buf + t.dev_offset, slot + t.host_offset, t.bytes_swapped,
+            if (memo::copy_swapped(buf + t.dev_offset, slot + t.host_offset, t.k_swapped, t.bytes_swapped / t.k_swapped,
                                    hipMemcpyHostToDevice, s->prefetch) != hipSuccess)
                 return fail(s);
         }

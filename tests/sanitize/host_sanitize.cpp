@@ -220,21 +220,27 @@ static void swap_both_sides()
     CHECK(memo_solve_alpha(1, 1, 0, 1, 1.0, 32, 1.0, &a) == MEMO_ERR_INVALID_ARG);
 }
 
-// Blocks that are asked for as rows: what they leave to a linear copy, and what happens where they fail.
+// Blocks that are asked for as rows, which ones are, each in one piece, and what happens where they fail.
 static void swap_as_rows()
 {
-    const int64_t rb = 1001;
-    for (int64_t S : {261, 262, 1000})               // 256 KiB are 261.9 rows
+    const struct { int64_t S, rb; bool rows; } blocks[] = {
+        {252, 1040, false}, {253, 1040, true}, {1001, 1040, true},      // token rows, around 256 KiB
+        {5, 65536, true}, {5, 65552, false},                            // of 64 KiB, and more
+        {262, 1001, false}, {1000, 1032, false},                        // off 16 bytes
+        {4096, 128, true}, {4100, 128, false},                          // shorter ones: by 4 KiB, if that divides them
+    };
+    for (const auto &block : blocks)
         for (int shift : {0, 16, 1}) {
+            const int64_t S = block.S, rb = block.rb;
             const size_t n = (size_t)(S * rb);
             std::vector<unsigned char> act(n + shift), host(n + shift), back(n + shift);
             for (size_t i = 0; i < n; ++i) act[shift + i] = (unsigned char)(i * 131 + 7);
-            const bool rows = n >= 256 * 1024 && shift != 1;
+            const bool rows = block.rows && shift != 1;
             auto out = [&] { return memo_swap_out(act.data() + shift, S, rb, 1.0, host.data() + shift, n, nullptr, nullptr, nullptr); };
             auto in = [&] { return memo_swap_in(back.data() + shift, S, rb, 1.0, host.data() + shift, n, nullptr, nullptr, nullptr); };
             fake::copies = fake::row_copies = 0;
             CHECK(out() == MEMO_OK && in() == MEMO_OK && back == act);
-            CHECK(fake::row_copies == (rows ? 2 : 0) && fake::copies == 2);
+            CHECK(fake::row_copies == (rows ? 2 : 0) && fake::copies == (rows ? 0 : 2));
             if (!rows) continue;
             // refused as rows: copied as one block, and no error of that is left behind
             for (hipError_t refusal : {hipErrorInvalidValue, hipErrorNotSupported}) {

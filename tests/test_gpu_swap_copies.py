@@ -1,5 +1,5 @@
-"""The two forms of a swap copy (copy_swapped, csrc/memo_kernels.h) on both sides of the limits between them: blocks around 256 KiB, bytes
-behind the last row of 4 KiB, blocks off 16 bytes; several pairs of streams at once; graph capture.  Bytes come back as they were."""
+"""The two forms of a swap copy (copy_swapped, csrc/memo_kernels.h) on both sides of the limits between them: blocks around 256 KiB, token rows of
+1 to 64 KiB and others, blocks off 16 bytes; host memory that is not pinned; several pairs of streams at once; graph capture.  Bytes come back as they were."""
 import pytest
 import torch
 
@@ -19,8 +19,9 @@ def _act(rows, row_bytes, shift, seed):
 
 @pytest.mark.parametrize("rows,row_bytes,shift", [
     (63, 4 * KIB, 0), (64, 4 * KIB, 0), (64, 4 * KIB, 16), (64, 4 * KIB, 8), (65, 4 * KIB, 4),   # around the least size and the alignment
-    (255, KIB, 0), (257, KIB, 0), (341, 3080, 0), (1000, 1001, 0), (1000, 1001, 1),              # bytes behind the last row of 4 KiB
-    (12345, 2560, 0),
+    (255, KIB, 0), (257, KIB, 0), (341, 3080, 0), (1000, 1001, 0), (1000, 1001, 1),              # token rows, and off 16 bytes
+    (12345, 2560, 0), (1001, 1040, 16), (5, 64 * KIB, 0), (5, 64 * KIB + 16, 0),
+    (4096, 128, 0), (4100, 128, 0), (33, 8 * KIB + 16, 0),                                       # rows of 4 KiB instead, or none
 ])
 def test_bytes_come_back(rows, row_bytes, shift):
     print(f"[case] swap copy {rows} x {row_bytes} shift {shift}", flush=True)
