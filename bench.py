@@ -591,7 +591,10 @@ def schedule_bench(torch, mb, synth, args):
         t_fwd = (time.perf_counter() - t0) / n
         t_bwd = t_res / n - t_fwd
         res.close(); del res
+        freed = torch.cuda.memory_reserved()
         torch.cuda.empty_cache()
+        # the driver clears freed memory, 28 ms per GiB, with the engine that copies to the host
+        time.sleep(0.04 * (freed - torch.cuda.memory_reserved()) / GIB)
         # copy rates on this machine, both directions, on one layer's worth of bytes
         _, _, layer_host = mb.memo_buffer_plan_make(S, ls.layer_tensors(H, d, 1.0))
         host = torch.empty(max(n - 2, 1) * layer_host, dtype=torch.uint8, pin_memory=True)
