@@ -50,7 +50,7 @@ __device__ __forceinline__ f32x4 sum_pieces(const LDS_AS f32x4 *pieces, int m, i
 }
 
 // ============================================================================ backward: dQ
-// Launches of dQ alone take 256 rows in four waves (attn_bwd_long_bf16.hip); this is for joint launches.
+// 256 rows of longer sequences go out in four waves (attn_bwd_long_bf16.hip); this is for shorter ones and smaller workgroups.
 // Workgroup: 8 waves, 32 query rows per wave (two blocks of 16); keys/values streamed in tiles
 // of 64 through a double-buffered LDS ring filled asynchronously (one barrier per tile).
 //   S^T = K Q^T, dP^T = V dO^T - D   (A = K / V rows from LDS, B = Q^T / dO^T from registers)
@@ -261,8 +261,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, LDS_AS unsigned char 
 }
 
 // ============================================================================ backward: dK, dV
-// Launches of dK and dV alone take 256 keys in four waves (attn_bwd_long_bf16.hip); this is for joint ones, which share their workgroups'
-// shape with dQ.
+// 256 keys of longer sequences go out in four waves (attn_bwd_long_bf16.hip); this is for shorter ones and smaller workgroups.
 // Workgroup (KG = 8): 8 waves, 256 key rows whose K and V stay in LDS for the workgroup's lifetime (128 KB);
 // queries streamed in tiles of 32 through a double-buffered ring (Q and dO rows, 16 KB per stage,
 // one barrier per tile): LDS is full to the byte (160 KB).  The bytes streamed per (query, key) pair
@@ -955,7 +954,9 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
         }
     case 64: return launch(attn_bwd_both_bf16_kernel<2, 2, 32>);
     case 128: return launch(attn_bwd_both_bf16_kernel<4, 4, 64>);
-    default: return launch_blocks(attn_bwd_both_long_bf16_kernel, (dkdv + dq) * tiles * heads, st, a, dkdv ? (uint32_t)nk : 0u);
+    default:
+        if (p.waves == 4) return launch_attn_bwd_both_bf16_long(a, dkdv ? nk : 0, (dkdv + dq) * tiles * heads, st);
+        return launch_blocks(attn_bwd_both_long_bf16_kernel, (dkdv + dq) * tiles * heads, st, a, dkdv ? (uint32_t)nk : 0u);
     }
 }
 
@@ -964,9 +965,9 @@ hipError_t launch_main(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st)
 // D_i preprocess, then dK, dV and dQ: in one launch of 32-, 64-, 128- or 256-row workgroups, or, where whole rounds
 // of folded pairs are cheaper, the key-stationary kernel and then the query-stationary one.  The single launch
 // fills the chip where neither kernel does alone (S = 2000, 6 heads: 32.4 + 27.6 -> 33.0 us with 64-row workgroups,
-// 207 as two launches of 256-row pairs in eight waves) and lets the dQ tiles run in the tail of the dK/dV ones (in eight waves throughout,
-// S = 16461, H = 4: 838 + 588 -> 787 us; S = 40000: 3942 + 2714 -> 4447 us).  Two launches go out in four waves (attn_bwd_long_bf16.hip) and win
-// from S = 32K at whole rounds (S = 128K, H = 4: 25.0 + 17.8 against 47.3 ms); where they win otherwise the plan does not know yet (bwd_plan).
+// 207 as two launches of 256-row pairs in eight waves) and lets the dQ tiles run in the tail of the dK/dV ones (S = 25000 H = 4 1943 -> 1739 us,
+// 70000 H = 4 13004 -> 12669).  256 rows go out in four waves (attn_bwd_long_bf16.hip), in joint launches of up to 3072 rows in eight; two launches win at
+// whole rounds from S = 32K on (S = 32768 H = 4 2741 joint, 2694 as two; 50000 H = 5 8434, 8377).
 // A joint launch goes out in two parts, with the same bits, where dQ takes the place of Q or dO, which all key-stationary
 // workgroups read, and where an event between the stages is asked for.
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st)

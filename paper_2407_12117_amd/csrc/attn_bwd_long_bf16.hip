@@ -85,15 +85,11 @@ __device__ __forceinline__ void settle(f32x4 (&x)[2][4])
     asm volatile("s_nop 15" : "+v"(x[0][0]), "+v"(x[0][1]), "+v"(x[0][2]), "+v"(x[0][3]), "+v"(x[1][0]), "+v"(x[1][1]), "+v"(x[1][2]), "+v"(x[1][3]));
 }
 
-__global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dkdv_bf16_long_kernel(AttnArgs a, int order)
+// lds: [stage][Q|dO], [wave][K|V]; t: key tile p (long) and key tile nkt-1-p (short)
+__device__ __forceinline__ void dkdv_long_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const PairId t)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[kDkdvLds];   // [stage][Q|dO], [wave][K|V]
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t nkt = (a.S + kLongKeys - 1) / kLongKeys;
-    const PairId t = decode_block(a, blockIdx.x, nkt, order, false);      // key tile p (long) and key tile nkt-1-p (short)
-    if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
     const __bf16 *g = static_cast<const __bf16 *>(a.d_o) + base;
@@ -430,16 +426,13 @@ __device__ __forceinline__ void mfma_on_a(f32x4 &d, const bf16x8 &x, const bf16x
     if constexpr (N >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(x), "a"(y), "n"(N));
     else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(x), "a"(y));
 }
-__global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dq_bf16_long_kernel(AttnArgs a, int order)
+
+// lds: K tile t at t % 3, V tile t behind them likewise
+__device__ __forceinline__ void dq_long_rows(const AttnArgs &a, LDS_AS unsigned char *lds, const PairId t)
 {
     constexpr int kRows = 64 * kLongWaves;
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kDqRing];    // K tile t at t % 3, V tile t behind them likewise
-    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t nqt = (a.S + kRows - 1) / kRows;
-    const PairId t = decode_block(a, blockIdx.x, nqt, order, true);
-    if (t.first < 0) return;
     const int64_t base = (int64_t)t.b * a.sb + (int64_t)t.h * a.sh;
     const __bf16 *q = static_cast<const __bf16 *>(a.q) + base;
     const __bf16 *k = static_cast<const __bf16 *>(a.k) + base;
@@ -681,7 +674,42 @@ __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu
     }   // pass
 }
 
+// ============================================================================ launches
+#define LONG_KERNEL __global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu(1, 1))) void
+
+__device__ __forceinline__ int64_t long_tiles(const AttnArgs &a) { return (a.S + kLongKeys - 1) / kLongKeys; }
+
+LONG_KERNEL attn_bwd_dkdv_bf16_long_kernel(AttnArgs a, int order)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kDkdvLds];
+    const PairId t = decode_block(a, blockIdx.x, long_tiles(a), order, false);
+    if (t.first >= 0) dkdv_long_rows(a, (LDS_AS unsigned char *)smem, t);
+}
+
+LONG_KERNEL attn_bwd_dq_bf16_long_kernel(AttnArgs a, int order)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kDqRing];
+    const PairId t = decode_block(a, blockIdx.x, long_tiles(a), order, true);
+    if (t.first >= 0) dq_long_rows(a, (LDS_AS unsigned char *)smem, t);
+}
+
+// both gradients in one launch, single tiles, longest first: all key tiles and then all query tiles.  Against the same launch in eight waves
+// (attn_bwd_bf16.hip), us: S = 14528 H = 8 1226 -> 1127, 25000 H = 4 1899 -> 1739, 40000 H = 5 6141 -> 5597, 90000 H = 4 22911 -> 21012; where four waves lose is
+// beside kJointChoices (launch_plan.h).
+LONG_KERNEL attn_bwd_both_bf16_long_kernel(AttnArgs a, uint32_t dkdv_blocks)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kDkdvLds];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    if (blockIdx.x < dkdv_blocks) dkdv_long_rows(a, lds, decode_block(a, blockIdx.x, long_tiles(a), kLongestFirst, false));
+    else dq_long_rows(a, lds, decode_block(a, blockIdx.x - dkdv_blocks, long_tiles(a), kLongestFirst, true));
+}
+
 }  // namespace
+
+hipError_t launch_attn_bwd_both_bf16_long(const AttnArgs &a, int64_t dkdv_blocks, int64_t blocks, hipStream_t st)
+{
+    return launch_blocks<64 * kLongWaves>(attn_bwd_both_bf16_long_kernel, blocks, st, a, (uint32_t)dkdv_blocks);
+}
 
 hipError_t launch_attn_bwd_dkdv_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st)
 {

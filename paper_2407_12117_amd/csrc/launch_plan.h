@@ -153,16 +153,20 @@ inline int cheapest_tiles(const TileChoice (&choices)[N], int64_t S, int64_t hea
     return best;
 }
 
-// Estimated time of one launch that works the key tiles k and then the query tiles q, each longest first: all
-// work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
+// One way to work key tiles (dK/dV) and then query tiles (dQ) of `rows` rows in one launch, each longest first, and what it costs: as in TileChoice, with
+// `longest` of the longest key tile's estimated time (shorter by what the units that end early leave of the power, longer by its start and end),
+// what `crowding` costs and the time around everything.
+struct JointChoice { int rows, waves; double key_us_per_mpair, query_us_per_mpair, longest, crowded, us; int64_t over = 0, upto = INT64_MAX; };
+
+// Its estimated time: all work there is, spread over the chip, but no shorter than the longest key tile; the last dQ tiles leave a
 // tenth of the longest one uneven.
-inline double both_us(const TileChoice &k, const TileChoice &q, int64_t S, int64_t heads)
+inline double both_us(const JointChoice &c, int64_t S, int64_t heads)
 {
     const double per_row = (double)S / (1 << 20);                         // mpairs per owned row of the longest tile
-    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk) * (1.0 + kCrowdedJoint * crowding(S, heads));
-    const double longest = 0.87 * k.rows * per_row * k.us_per_mpair;
-    const double spread = mean * (k.us_per_mpair + q.us_per_mpair) + 0.1 * q.rows * per_row * q.us_per_mpair;
-    return std::max(longest, spread) + 10.0;
+    const double mean = 0.5 * per_row * (double)(S * heads) / (kXcds * kChunk) * (1.0 + c.crowded * crowding(S, heads));
+    const double longest = c.longest * c.rows * per_row * c.key_us_per_mpair;
+    const double spread = mean * (c.key_us_per_mpair + c.query_us_per_mpair) + 0.1 * c.rows * per_row * c.query_us_per_mpair;
+    return std::max(longest, spread) + c.us;
 }
 
 // The order a workgroup shape can work.  The downward sweep over the second tile of a pair starts every key group at the last
@@ -190,14 +194,16 @@ inline constexpr TileChoice kFwdChoices[] = {
 inline const TileChoice &fwd_plan(int64_t S, int64_t heads) { return kFwdChoices[cheapest_tiles(kFwdChoices, S, heads)]; }
 
 // ---- bf16 backward
-// Costs of the workgroup shapes alone (see tile_choice_us), fitted as the forward's.  64-row workgroups pay
-// 5 to 20 % more per pair than 256-row ones for their four times larger fill traffic.  The 256-row figures are those of eight waves, which joint
-// launches run; launches of one gradient run four, which take about 196 and 139 (S = 128K, H = 4).
-inline constexpr TileChoice kDkdvChoices[] = {
-    {256, kFolded, 216.0, 4.0}, {256, kLongestFirst, 218.0, 8.0}, {128, kLongestFirst, 222.0, 8.0}, {64, kLongestFirst, 232.0, 6.5},
-};
-inline constexpr TileChoice kDqChoices[] = {
-    {256, kFolded, 146.0, 4.0}, {256, kLongestFirst, 149.0, 8.0}, {128, kLongestFirst, 156.0, 8.0}, {64, kLongestFirst, 181.0, 6.5},
+// Costs of launches of one gradient (see tile_choice_us): 256 rows in four waves, and 128, which pay for their larger fill traffic.
+inline constexpr TileChoice kDkdvChoices[] = {{256, kFolded, 196.5, 7.1, 4}, {256, kLongestFirst, 200.6, 8.5, 4}, {128, kLongestFirst, 222.0, 8.0}};
+inline constexpr TileChoice kDqChoices[] = {{256, kFolded, 141.4, 7.1, 4}, {256, kLongestFirst, 146.0, 8.5, 4}, {128, kLongestFirst, 156.0, 8.0}};
+
+// Joint launches.  256 rows go out in four waves of 64 from 3073 rows on, in eight of 32 below: four take less per pair and start and end a sweep later, as in
+// the forward.  us, eight waves : four, S = 961 H = 128 150 : 163, 1442 H = 128 291 : 309, 2115 H = 100 447 : 464, 2538 H = 100 584 : 610, 3868 H = 64 796 : 790,
+// 8577 H = 20 1168 : 1116, 14528 H = 8 1226 : 1127, 22690 H = 5 1948 : 1804, 42591 H = 4 5452 : 4810, 85099 H = 4 20465 : 18772.
+inline constexpr JointChoice kJointChoices[] = {
+    {256, 4, 191.2, 154.8, 0.985, 0.086, 12.8, 3072}, {256, 8, 218.0, 149.0, 0.87, kCrowdedJoint, 10.0, 0, 3072},
+    {128, 8, 222.0, 156.0, 0.87, kCrowdedJoint, 10.0}, {64, 8, 232.0, 181.0, 0.87, kCrowdedJoint, 10.0},
 };
 
 // A launch of 32-row workgroups: no shorter than its longest key tile, nor than all work spread over the chip with the start and
@@ -212,32 +218,32 @@ inline double own_us(int64_t S, int64_t heads)
     return std::max(0.87 * 32 * per_row * 232.0, mean * 450.0 + 4.5 * items / (kXcds * kChunk)) + 10.0;
 }
 
-// Workgroups of `rows` rows: dK/dV and dQ in one joint launch, or the one after the other in the orders k_order and q_order.
-struct BwdPlan { int rows; bool joint; int k_order, q_order; };
+// Workgroups of `rows` rows and `waves` waves: dK/dV and dQ in one joint launch, or the one after the other in the orders k_order and q_order.
+struct BwdPlan { int rows; bool joint; int k_order, q_order, waves; };
 
-// With eight waves in all 256-row launches the estimate's choice was 0.1 % slower than the fastest of the variants on average and 1.4 % at worst, over 80 sizes
-// of 1024 to 262144 rows and 1 to 256 heads with at least 2^16.8 rows in all.  Launches of one gradient are priced as that still, so that a joint
-// launch is often taken where two of four waves are faster by now: over 88 sizes of 2500 to 140000 rows and 1 to 130 heads the choice of 256 rows is 1.6 % slower than
-// the fastest on average, 10.6 % at worst (us, taken : two launches, S = 12820 H = 18 2300 : 2079, 25000 H = 5 2252 : 2052, 40000 H = 3 3410 : 3148, 70000 H = 4
-// 13974 : 13235, 90000 H = 4 22948 : 21429).  Against eight waves throughout two launches gain 3 to 7 % (40 sizes of 5279 to 96976 rows).
+// Fitted to 130 sizes of 961 to 113292 rows and 1 to 128 heads, timed as joint launches of 64, 128 and 256 rows and as two launches in each order: the choice
+// is 0.4 % slower than the fastest of them on average and 6.5 % at worst (S = 2905 H = 10, 64 rows for 128); with joint launches in eight waves throughout
+// and two launches priced as eight waves it was 4 % (us, then : now, S = 25000 H = 4 1930 : 1739, 40000 H = 5 6038 : 5597, 70000 H = 4 13780 : 12669,
+// 90000 H = 4 22735 : 21012).
 inline BwdPlan bwd_plan(int64_t S, int64_t heads)
 {
-    BwdPlan best = {256, false, kFolded, kFolded};
+    BwdPlan best = {256, false, kFolded, kFolded, 4};
     double best_us = 0;
     for (auto [choices, order] : {std::make_pair(kDkdvChoices, &best.k_order), std::make_pair(kDqChoices, &best.q_order)}) {
         const double folded = tile_choice_us(choices[0], S, heads), longest_first = tile_choice_us(choices[1], S, heads);
         *order = longest_first < folded ? kLongestFirst : kFolded;
         best_us += std::min(folded, longest_first);
     }
-    auto offer = [&](int rows, bool joint, double us) {
+    auto offer = [&](int rows, bool joint, int waves, double us) {
         if (us >= best_us) return;
-        best = {rows, joint, kLongestFirst, kLongestFirst};
+        best = {rows, joint, kLongestFirst, kLongestFirst, waves};
         best_us = us;
     };
     // apart: S = 32768, 2 heads 1508 us against 1565 joint (two long sweeps per unit either way); nowhere else
-    offer(128, false, tile_choice_us(kDkdvChoices[2], S, heads, kCrowdedJoint) + tile_choice_us(kDqChoices[2], S, heads, kCrowdedJoint));
-    for (int n = 1; n < 4; ++n) offer(kDkdvChoices[n].rows, true, both_us(kDkdvChoices[n], kDqChoices[n], S, heads));
-    offer(32, true, own_us(S, heads));
+    offer(128, false, 8, tile_choice_us(kDkdvChoices[2], S, heads, kCrowdedJoint) + tile_choice_us(kDqChoices[2], S, heads, kCrowdedJoint));
+    for (const JointChoice &c : kJointChoices)
+        if (S > c.over && S <= c.upto) offer(c.rows, true, c.waves, both_us(c, S, heads));
+    offer(32, true, 8, own_us(S, heads));
     return best;
 }
 

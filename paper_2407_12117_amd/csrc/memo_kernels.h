@@ -102,6 +102,7 @@ hipError_t launch_attn_fwd_bf16_long(const AttnArgs &a, int order, int64_t block
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, hipStream_t st);
 hipError_t launch_attn_bwd_dkdv_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st); // dK, dV by 256-key workgroups
 hipError_t launch_attn_bwd_dq_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st);   // dQ by 256-row workgroups
+hipError_t launch_attn_bwd_both_bf16_long(const AttnArgs &a, int64_t dkdv_blocks, int64_t blocks, hipStream_t st);   // single tiles of both kinds, dK and dV's first
 
 // D_i = sum_c dO_ic * O_ic for either dtype (is_bf16 selects the element type)
 hipError_t launch_attn_delta(const AttnArgs &a, bool is_bf16, hipStream_t st);

@@ -2,6 +2,7 @@
 //   fwd S heads      -> rows order              order: 0 folded pairs, 1 longest first
 //   waves S heads    -> waves of a workgroup of the forward
 //   bwd S heads      -> rows, 1 if dK/dV and dQ go out in one launch, order of dK/dV, order of dQ
+//   bwdwaves S heads -> waves of a workgroup of the backward
 //   lin rows K N     -> tokens and features of a tile
 //   window begin end tile tile_rows live -> first row and number of rows of a tile's buffer
 //   joint keys queries heads -> for each position of a joint launch the rank of its key tile, or -1 - rank of its query tile
@@ -24,6 +25,8 @@ int main()
             std::printf("%d %d\n", t.rows, t.order);
         } else if (!std::strcmp(what, "waves")) {
             std::printf("%d\n", memo::fwd_plan(a, b).waves);
+        } else if (!std::strcmp(what, "bwdwaves")) {
+            std::printf("%d\n", memo::bwd_plan(a, b).waves);
         } else if (!std::strcmp(what, "bwd")) {
             const memo::BwdPlan p = memo::bwd_plan(a, b);
             std::printf("%d %d %d %d\n", p.rows, p.joint, p.k_order, p.q_order);

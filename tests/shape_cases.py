@@ -41,6 +41,9 @@ FWD_FOUR_WAVE_EDGES = {(3329, 48): LONGEST_FIRST, (3391, 48): LONGEST_FIRST, (35
 BWD_LONG_EDGES = {(3841, 160): (FOLDED, FOLDED), (3903, 128): (FOLDED, FOLDED), (3904, 128): (FOLDED, FOLDED), (3905, 128): (FOLDED, FOLDED),
                   (4351, 96): (LONGEST_FIRST, LONGEST_FIRST), (4352, 96): (LONGEST_FIRST, LONGEST_FIRST), (5121, 160): (LONGEST_FIRST, FOLDED)}
 
+# (S, heads): both gradients in one launch of four waves, the last tile of one row, of one wave and its neighbours, whole
+BWD_JOINT_EDGES = [(3073, 24), (3329, 20), (3391, 20), (3392, 20), (3393, 20), (3584, 20), (3585, 24)]
+
 # row sums of a long sweep: (S, heads) -> order of the forward
 FWD_LONG_SUMS = {(16384, 16): FOLDED}
 

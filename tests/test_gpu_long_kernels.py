@@ -46,7 +46,7 @@ def test_forward_edges(oracle, S, heads):
     _check_forward(oracle, q, k, v, o, lse, (0, heads // 2, heads - 1))
 
 
-@pytest.mark.parametrize("S,heads", list(shapes.BWD_LONG_EDGES))
+@pytest.mark.parametrize("S,heads", list(shapes.BWD_LONG_EDGES) + shapes.BWD_JOINT_EDGES)
 def test_backward_edges(oracle, S, heads):
     print(f"[case] long backward S={S} H={heads}", flush=True)
     q, k, v, g = _inputs(S, heads, S)

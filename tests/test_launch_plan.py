@@ -124,6 +124,8 @@ def test_the_edges_of_the_long_kernels_get_them(plans):
             assert plans([("fwd", S, heads), ("waves", S, heads)]) == [(256, order), (waves,)]
     for (S, heads), orders in shapes.BWD_LONG_EDGES.items():
         assert plans([("bwd", S, heads)]) == [(256, 0) + orders]
+    assert plans([("bwd", S, h) for S, h in shapes.BWD_JOINT_EDGES]) == [(256, 1, LONGEST_FIRST, LONGEST_FIRST)] * len(shapes.BWD_JOINT_EDGES)
+    assert plans([("bwdwaves", S, h) for S, h in shapes.BWD_JOINT_EDGES]) == [(4,)] * len(shapes.BWD_JOINT_EDGES)
     for (B, S, heads), orders in shapes.LONG_LAYOUTS.items():
         assert plans([("bwd", S, B * heads)]) == [(256, 0) + orders] and plans([("waves", S, B * heads)]) == [(4,)]
     assert plans([("waves", 3905, 128)]) == [(4,)]
@@ -140,3 +142,10 @@ def test_short_forward_sweeps_do_not_take_four_waves(plans, S, heads):
 @pytest.mark.parametrize("S,heads", [(6000, 16), (8422, 12), (10116, 10), (12715, 8), (20000, 10), (25000, 4), (40000, 5), (50000, 2)])
 def test_long_forward_sweeps_just_beyond_a_round_take_four_waves(plans, S, heads):
     assert plans([("fwd", S, heads), ("waves", S, heads)]) == [(256, LONGEST_FIRST), (4,)]
+
+
+# joint launches of 256 rows: the sizes where four waves were measured slower than eight, and where they and not two launches were fastest
+@pytest.mark.parametrize("S,heads,waves", [(961, 128, 8), (1442, 128, 8), (2115, 100, 8), (8577, 20, 4), (14528, 8, 4), (22690, 5, 4), (42591, 4, 4), (70000, 4, 4),
+                                           (85099, 4, 4)])
+def test_joint_backward_takes_the_faster_number_of_waves(plans, S, heads, waves):
+    assert plans([("bwd", S, heads), ("bwdwaves", S, heads)]) == [(256, 1, LONGEST_FIRST, LONGEST_FIRST), (waves,)]
