@@ -18,6 +18,7 @@ SOURCES = {
     "memo_sched.cpp": [],
     "memo_dsa.cpp": [],
     "attn_f32.hip": [],
+    "attn_f32_split.hip": [],
     "attn_bf16.hip": [],
     "attn_fwd_long_bf16.hip": [],
     "attn_bwd_bf16.hip": [],

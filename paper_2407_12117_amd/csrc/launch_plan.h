@@ -111,6 +111,22 @@ inline int column_parts(int64_t blocks)
 inline bool f32_fwd_shares_rows(int64_t tiles, int64_t heads) { return tiles * heads > kXcds * kChunk && tiles <= 256; }
 inline bool f32_bwd_shares_rows(int64_t tiles) { return tiles <= 320; }
 
+// fp32: from so many rows on a launch goes to the fp16 matrix instructions (attn_f32_split.hip).  Its workgroups of 32 rows start and end 3 to 5 us later than
+// those of 16 rows on fp32 instructions, which also share out a tile's columns where units are idle, and take half the time per pair: it wins where a launch fills
+// the chip.  One line for forward and backward, since a backward has to form its scores as the forward did whose logsumexp it is given; it lies where the two meet
+// forward, over 270 sizes of 1 to 40 heads (us, fp32 instructions : fp16; d = 64 S = 3601 H = 1 37.1 : 38.2, 4501 H = 1 48.2 : 46.6, 1306 H = 4 18.2 : 18.4, 1567 H = 4
+// 22.1 : 20.8, 811 H = 20 22.3 : 25.4, 1151 H = 20 37.8 : 34.2; d = 128 1945 H = 1 31.0 : 34.0, 2201 H = 1 40.2 : 37.4, 1179 H = 4 24.4 : 24.9, 1262 H = 4 25.6 : 25.4,
+// 318 H = 40 23.7 : 20.4), which is later than backward (d = 64 2500 H = 1 71.0 : 47.8, 1100 H = 4 37.6 : 27.1; d = 128 1560 H = 1 59.3 : 51.8, 840 H = 4 36.5 : 34.4).
+// d = 128, where each XCD's L2 brings in three heads or more: later (S = 1678 H = 3 32.3 : 33.8, 1333 H = 5 27.9 : 29.0, 1130 H = 6 25.2 : 23.9).
+// Nor is the output of head dim 64 as exact in shorter sums (S = 504 H = 4 1.45e-7 : 1.44e-7 of fp32 instructions, 750 1.50e-7 : 1.52e-7).
+inline bool f32_splits(int64_t S, int64_t heads, int d)
+{
+    const double h = (double)heads;
+    const bool many = heads / std::gcd(heads, (int64_t)kXcds) >= 3;
+    const double line = d == 64 ? std::max(1050.0, 4300.0 / std::pow(h, 0.75)) : std::max(2200.0 / std::pow(h, 0.45), many ? std::min(1750.0, 7000.0 / h) : 0.0);
+    return (double)S >= line;
+}
+
 // One way to cut a launch into workgroups, and what it costs: `rows` owned rows per workgroup, the time of
 // 2^20 (row, key) pairs on one compute unit with the whole chip busy, and the time a workgroup spends before
 // and after its sweep.  `waves` of a workgroup, and the sequences it is for: more than `over` rows and up to `upto`.

@@ -96,6 +96,11 @@ hipError_t launch_fewer_heads(const AttnArgs &a, size_t element_bytes, int64_t b
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, hipStream_t st);
 hipError_t launch_attn_bwd_f32(const AttnArgs &a, hipStream_t st);
 
+// the same on fp16 matrix instructions, every fp32 operand as the sum of two fp16 ones; rows less than kSplitStride floats apart, S below kSplitRows
+inline constexpr int64_t kSplitStride = (int64_t)1 << 25, kSplitRows = (int64_t)1 << 28;
+hipError_t launch_attn_fwd_f32_split(const AttnArgs &a, hipStream_t st);
+hipError_t launch_attn_bwd_f32_split(const AttnArgs &a, bool dkdv, bool dq, hipStream_t st);     // which of the gradients
+
 // bf16 path (bf16 MFMA contractions, fp32 accumulation and softmax), d = 128
 hipError_t launch_attn_fwd_bf16(const AttnArgs &a, hipStream_t st);
 hipError_t launch_attn_fwd_bf16_long(const AttnArgs &a, int order, int64_t blocks, hipStream_t st);      // 256-row workgroups

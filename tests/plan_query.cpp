@@ -7,6 +7,7 @@
 //   window begin end tile tile_rows live -> first row and number of rows of a tile's buffer
 //   joint keys queries heads -> for each position of a joint launch the rank of its key tile, or -1 - rank of its query tile
 //   f32rows S heads -> head dim 64 in one part: 1 if the forward, and if the backward, brings a workgroup's own rows in once for all waves
+//   f32split S heads d -> 1 if the forward, and if the backward, goes to the fp16 matrix instructions
 //   divide x d       -> quotient and remainder
 //   order rows order -> the order that a shape of that many rows works when asked for `order`
 #include "../paper_2407_12117_amd/csrc/launch_plan.h"
@@ -34,6 +35,8 @@ int main()
             std::printf("%d\n", memo::tile_order((int)a, (int)b));
         } else if (!std::strcmp(what, "f32rows")) {
             std::printf("%d %d\n", memo::f32_fwd_shares_rows((a + 15) / 16, b), memo::f32_bwd_shares_rows((a + 15) / 16));
+        } else if (!std::strcmp(what, "f32split") && std::scanf("%lld", &c) == 1) {
+            std::printf("%d\n", memo::f32_splits(a, b, (int)c));
         } else if (!std::strcmp(what, "divide")) {
             const memo::Division r = memo::Divisor(b)((uint32_t)a);
             std::printf("%u %u\n", r.quot, r.rem);

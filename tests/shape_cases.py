@@ -49,3 +49,7 @@ FWD_LONG_SUMS = {(16384, 16): FOLDED}
 
 # batches in one packed buffer: (B, S, heads) -> orders of dK/dV and of dQ; the forward works 256 rows too
 LONG_LAYOUTS = {(2, 3905, 64): (FOLDED, FOLDED), (3, 4351, 32): (LONGEST_FIRST, LONGEST_FIRST)}
+
+# fp32 on fp16 matrix instructions, forward and backward: (S, heads, d); a last tile of one row, of all but one, whole, and of 17; sweeps of several steps a wave
+F32_SPLIT_EDGES = [(1057, 8, 64), (1055, 8, 64), (1056, 8, 64), (1073, 8, 64), (865, 8, 128), (895, 8, 128), (896, 8, 128), (881, 8, 128), (2049, 3, 64), (2047, 3, 128)]
+F32_SPLIT_ONE = [(1300, 4, 128), (1600, 4, 64)]

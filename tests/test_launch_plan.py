@@ -149,3 +149,12 @@ def test_long_forward_sweeps_just_beyond_a_round_take_four_waves(plans, S, heads
                                            (85099, 4, 4)])
 def test_joint_backward_takes_the_faster_number_of_waves(plans, S, heads, waves):
     assert plans([("bwd", S, heads), ("bwdwaves", S, heads)]) == [(256, 1, LONGEST_FIRST, LONGEST_FIRST), (waves,)]
+
+
+def test_fp32_launches_that_fill_the_chip_go_to_the_fp16_instructions(plans):
+    cases = shapes.F32_SPLIT_EDGES + shapes.F32_SPLIT_ONE
+    assert plans([("f32split", *c) for c in cases]) == [(1,)] * len(cases)
+    # measured slower there forward, and faster
+    slower = ((1990, 1, 64), (950, 4, 64), (527, 8, 64), (751, 40, 64), (1, 8454015, 64), (1945, 1, 128), (1436, 3, 128), (939, 4, 128), (1227, 5, 128), (135, 12, 128))
+    faster = ((4501, 1, 64), (2969, 2, 64), (1959, 4, 64), (1251, 20, 64), (2355, 1, 128), (1262, 4, 128), (1228, 6, 128), (864, 8, 128), (899, 12, 128), (448, 40, 128))
+    assert plans([("f32split", *c) for c in slower + faster]) == [(0,)] * len(slower) + [(1,)] * len(faster)
