@@ -6,9 +6,9 @@
 // instead of four: relative error of a sum of 128 products of N(0,1) numbers 1.39e-7 in one accumulator and 1.1e-7 in two, as the scores are formed here, against
 // 2.05e-7 of one and 1.5e-7 of two on fp32 instructions; of 4096 products 7.1e-7 against 1.15e-6.  fp16's range is kept by powers of two:
 //  * a workgroup's own 32 rows: one per row, from the row's largest magnitude;
-//  * streamed tensors: one per workgroup, from the largest magnitude of that tensor's rows at the workgroup's place; also where they lie in fp16's range by themselves
+//  * streamed tensors: one per workgroup, from the largest magnitude of that tensor's rows at the workgroup's place (kRowTop); also where they lie in fp16's range by themselves
 //    (N(0,1) numbers without a scale are 3 to 5 % faster, but l has no bits below 2^-24, and columns much smaller than the others, alone in a product because the other
-//    tensor is zero there, lose theirs; so, output of S = 1300 H = 4, every other column times 2^8: 1.4 to 1.8e-7, 2^12: 1.6 to 2.1e-7);
+//    tensor is zero there, lose theirs; output of S = 1300 H = 4 with every other column of K smaller, by 1: 1.39e-7, 2^8 1.51e-7, 2^10 1.64e-7, 2^12 4.1e-7);
 //  * probabilities: against the running maximum (forward), times 2^15 (backward); dS: one per output row, brought down when the row's largest dS asks for it.
 // Whether a streamed row fits its scale is checked: its largest magnitude, scaled, must be at least 1/2 (l is then exact to 2^-24 of it), or the row zero; one that
 // overflows makes NaN.  A workgroup that met a row that does not fit, or whose result is not finite, writes nothing and works its rows with the fp32 instructions.
@@ -39,6 +39,9 @@ constexpr f32x16 kZero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.
 // maximum, which is brought up to date before they pass kMostP; the backward's, at most 1: times kProbUp.  By a multiplication, which is exact: in the exponent, five more
 // make its rounding that of a larger number (error of the output 6 % and of the logsumexp 25 % up).
 constexpr float kWeightUp = 32.f, kMostP = 1024.f, kProbUp = 32768.f;
+// Streamed rows are brought to 2^8 by the workgroup's own rows of the tensor, which leaves 2^7 and more for larger rows and 2^8 for smaller ones (us of S = 3000 H = 4 d = 128 with one row of dO
+// a hundred times the others: backward 169, brought to 2^10 316 and on fp32 instructions 298; one row of V: forward 56, 159, 99; tensors whose rows no scale fits: 120 and 355 for 101 and 292).
+constexpr int kRowTop = 8, kOwnTop = 12;
 
 __device__ __forceinline__ float as_float(uint32_t u) { return __builtin_bit_cast(float, u); }
 __device__ __forceinline__ uint32_t as_bits(float x) { return __builtin_bit_cast(uint32_t, x); }
@@ -189,12 +192,13 @@ __device__ __forceinline__ float max_dpp(float x)
     return fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), Ctrl, 0xf, 0xf, true)));
 }
 
-// The power of two that brings a magnitude to 2^10 .. 2^11; one for zero, for what is not finite any.
+// The power of two that brings a magnitude to 2^TO .. 2^(TO + 1); one for zero, for what is not finite any.
+template <int TO>
 __device__ __forceinline__ float scale_for(float top)
 {
     if (top == 0.f) return 1.f;
     const int e = (int)(as_bits(top) >> 23) & 255;
-    const int to = 127 + 127 + 10 - e;
+    const int to = 127 + 127 + TO - e;
     return as_float((uint32_t)(to < 1 ? 1 : to > 254 ? 254 : to) << 23);
 }
 __device__ __forceinline__ float inverse(float power_of_two) { return as_float((254u << 23) - as_bits(power_of_two)); }
@@ -230,7 +234,7 @@ struct Planes {
     {
         const int tid = threadIdx.x, r = tid / kLanes, c = tid % kLanes;
         if (r >= kRows) return;
-        const float scale = scale_for(row_top(own));
+        const float scale = scale_for<kOwnTop>(row_top(own));
         SplitJob job;
         take(job, own.x[0], own.x[1]);
         const Split s = job.at_once<true>(scale);
@@ -274,7 +278,7 @@ struct RowItems {
     Split a, y;
     SplitJob job;
     float scale[K];               // of the streamed tensors
-    uint64_t bad = 0;             // lanes that met a row whose largest magnitude, scaled, is below 1/2 and not zero: its l is not exact enough
+    uint64_t bad = 0;             // lanes that met a row whose largest magnitude, scaled, is below 1/2 and not zero: its l is not exact enough; or out of fp16's range
 
     // rows of operand n (kAll and kAll + 1: the next step's first two)
     template <int N>
@@ -286,7 +290,7 @@ struct RowItems {
     __device__ __forceinline__ void check(float top)
     {
         const float t = max_across_halves(top);
-        bad |= __builtin_amdgcn_ballot_w64(t < 0.5f && t != 0.f);
+        bad |= __builtin_amdgcn_ballot_w64(!(t >= 0.5f && t < 65504.f) && t != 0.f);
     }
     __device__ __forceinline__ void first(const St &st, uint32_t plane_at)
     {
@@ -466,7 +470,7 @@ __device__ __forceinline__ float of_quad(uint32_t u)
 }
 
 // The scales of the two streamed tensors, from the largest magnitudes of the workgroup's own rows of them, which put_tops leaves in LDS.  Rows
-// of down to 2^-11 and up to 2^5 times that can then be split.
+// of down to 2^-9 and up to 2^7 times that can then be split.
 __device__ __forceinline__ void put_tops(LDS_AS float *tops, float a, float b, int wave, int lane)
 {
     if (lane == 0) {
@@ -482,11 +486,11 @@ __device__ __forceinline__ void streamed_scales(const LDS_AS float *tops, float 
         ta = fmaxf(ta, tops[2 * w]);
         tb = fmaxf(tb, tops[2 * w + 1]);
     }
-    a = as_float(__builtin_amdgcn_readfirstlane(as_bits(scale_for(ta))));
-    b = as_float(__builtin_amdgcn_readfirstlane(as_bits(scale_for(tb))));
+    a = as_float(__builtin_amdgcn_readfirstlane(as_bits(scale_for<kRowTop>(ta))));
+    b = as_float(__builtin_amdgcn_readfirstlane(as_bits(scale_for<kRowTop>(tb))));
 }
 // Scales whose products stay far inside fp32, whatever they meet
-__device__ __forceinline__ bool far_scale(float s) { return !(s >= 0x1p-40f && s <= 0x1p40f); }
+__device__ __forceinline__ bool far_scale(float s) { return !(s >= 0x1p-42f && s <= 0x1p42f); }
 
 constexpr int64_t kNone = (int64_t)1 << 40;           // a step past the end of any sequence
 
@@ -667,7 +671,7 @@ __device__ __forceinline__ void scale_ds(f32x16 &ds, float &factor, f32x16 (&acc
     for (int e = 0; e < 16; e += 2) top = fmaxf(fmaxf(fabsf(ds[e]), fabsf(ds[e + 1])), top);
     top = max_across_halves(top);
     if (__builtin_amdgcn_ballot_w64(top * factor > 32768.f) != 0) {
-        const float to = top * factor > 32768.f ? scale_for(top) : factor, corr = to / factor;
+        const float to = top * factor > 32768.f ? scale_for<10>(top) : factor, corr = to / factor;
         factor = to;
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[b] *= corr;
