@@ -26,8 +26,8 @@
 // What bounds it: vector issue.  A step of the forward (d = 128) has 48 MFMAs (1536 cycles) and 580 vector instructions (3180 cycles of issue: v_fma_mix, which
 // makes l, and exponentials take 8 and 16), two waves share a SIMD, and a wave waits a third of its time.  Without the splits 14 % less, without fills 10, without the
 // other loads 8, without operand reads 4.  v_dot2c (x - h in one instruction) runs on the matrix core.
-// us, fp32 instructions -> this, d = 128: S = 3000 H = 4 forward 96 -> 55, backward 311 -> 169; S = 5000 H = 4 B = 2 486 -> 254 and 1676 -> 830; d = 64 S = 3000 H = 4 49 -> 36 and
-// 156 -> 97.
+// us, fp32 instructions -> this, d = 128: S = 3000 H = 4 forward 97 -> 53, backward 309 -> 166; S = 5000 H = 4 B = 2 486 -> 244 and 1628 -> 799; d = 64 S = 3000 H = 4 49 -> 34 and
+// 156 -> 94.
 #include "attn_f32_rows.h"
 
 namespace memo {
@@ -492,6 +492,13 @@ __device__ __forceinline__ void streamed_scales(const LDS_AS float *tops, float 
 // Scales whose products stay far inside fp32, whatever they meet
 __device__ __forceinline__ bool far_scale(float s) { return !(s >= 0x1p-42f && s <= 0x1p42f); }
 
+// Of the two waves of a SIMD the older one is served first and would end its steps ahead; from here on the younger one is, so that they end together and neither works alone
+// (us without : with, forward S = 5000 H = 4 B = 2 d = 128 250 : 244, S = 12000 H = 2 d = 64 222 : 214, backward 812 : 799 and 624 : 610; served first from the start on, 250, 221, 816, 622).
+__device__ __forceinline__ void even_out(int wave, int step, int steps)
+{
+    if (wave >= kWaves / 2 && step >= steps * 7 / 16) __builtin_amdgcn_s_setprio(1);
+}
+
 constexpr int64_t kNone = (int64_t)1 << 40;           // a step past the end of any sequence
 
 // false: some value or row cannot be split (see RowItems::bad, far_scale), nothing has been written
@@ -561,6 +568,7 @@ __device__ __forceinline__ bool fwd_rows(const AttnArgs &a, LDS_AS unsigned char
         };
 #pragma clang loop unroll(disable)
         for (int step = wave; step < steps && !rows.bad; step += kWaves) {
+            even_out(wave, step, steps);
             const __amdgpu_buffer_rsrc_t kn = st.buffer(k, step + kWaves < steps ? step + kWaves : kNone, a.S), vb = st.buffer(v, step, a.S);
             Tr tr[2];
             st.template load<0>(tr[0], vb);
@@ -725,6 +733,7 @@ __device__ __forceinline__ bool dq_rows(const AttnArgs &a, LDS_AS unsigned char 
         rows.first(st, plane_at);
 #pragma clang loop unroll(disable)
         for (int step = wave; step < steps && !rows.bad; step += kWaves) {
+            even_out(wave, step, steps);
             const __amdgpu_buffer_rsrc_t kn = st.buffer(k, step + kWaves < steps ? step + kWaves : kNone, a.S), vb = st.buffer(v, step, a.S);
             Tr tr[2];
             f32x16 s, s1, small, dp;
@@ -847,6 +856,7 @@ __device__ __forceinline__ bool dkdv_rows(const AttnArgs &a, LDS_AS unsigned cha
         rows.first(st, plane_at);
 #pragma clang loop unroll(disable)
         for (int step = first + wave; step < steps && !rows.bad; step += kWaves) {
+            even_out(wave, step - first, steps - first);
             const __amdgpu_buffer_rsrc_t qn = st.buffer(q, step + kWaves < steps ? step + kWaves : kNone, a.S), gb = st.buffer(g, step, a.S);
             f32x16 s, s1, small, dp;
             uint32_t ul[4], ud[4];                    // of query 8 x + 4 half + lane % 4
