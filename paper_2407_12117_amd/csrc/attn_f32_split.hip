@@ -493,10 +493,11 @@ __device__ __forceinline__ void streamed_scales(const LDS_AS float *tops, float 
 __device__ __forceinline__ bool far_scale(float s) { return !(s >= 0x1p-42f && s <= 0x1p42f); }
 
 // Of the two waves of a SIMD the older one is served first and would end its steps ahead; from here on the younger one is, so that they end together and neither works alone
-// (us without : with, forward S = 5000 H = 4 B = 2 d = 128 250 : 244, S = 12000 H = 2 d = 64 222 : 214, backward 812 : 799 and 624 : 610; served first from the start on, 250, 221, 816, 622).
+// (us without : with, forward S = 5000 H = 4 B = 2 d = 128 250 : 244, S = 12000 H = 2 d = 64 222 : 214, backward 812 : 799 and 624 : 610; served first from the start on, 250, 221, 816, 622;
+// from 1/4 of the sweep to 1/2 within 1 %, forward S = 3000 H = 4 d = 128 51.7 at 1/4, 51.3 at 3/8, 52.9 at 7/16, 54.2 at 1/2).
 __device__ __forceinline__ void even_out(int wave, int step, int steps)
 {
-    if (wave >= kWaves / 2 && step >= steps * 7 / 16) __builtin_amdgcn_s_setprio(1);
+    if (wave >= kWaves / 2 && step >= steps * 3 / 8) __builtin_amdgcn_s_setprio(1);
 }
 
 constexpr int64_t kNone = (int64_t)1 << 40;           // a step past the end of any sequence
